@@ -729,26 +729,29 @@ def read_traffic(kernel_key):
     return None
 
 
-FUSED_MAX_GROUPS = 300000       # groups of 512 elements one launch of the fused update covers at most
+FUSED_GROUP = 256                # elements of a group of the fused update
+FUSED_MAX_GROUPS = 600000       # groups one launch of it covers at most
 
 
 def fused_launch_count(w):
-    """Launches one hzp_adamw_shard call over all buckets makes: a launch takes whole runs (a bucket's
-    shard, cut at FUSED_MAX_GROUPS groups) while they fit FUSED_MAX_GROUPS groups and the kernel's
-    segment table (34 segments, 408 pointers of R + 4 per segment)."""
-    cap = min(34, 408 // (w.R + 4))
-    runs = []
-    for b in w.buckets:
-        groups = -(-b.s1 // 512)
-        while groups > 0:
-            runs.append(min(groups, FUSED_MAX_GROUPS))
-            groups -= runs[-1]
-    launches, cnt, blocks = 0, 0, 0
-    for g in runs:
-        if cnt == cap or (cnt > 0 and blocks + g > FUSED_MAX_GROUPS):
-            launches, cnt, blocks = launches + 1, 0, 0
-        cnt, blocks = cnt + 1, blocks + g
-    return launches + (1 if cnt else 0)
+    """Launches one hzp_adamw_shard call over all buckets makes: slices that follow each other in every stream (those
+    of the arena do) are one run, a launch takes runs while they fit FUSED_MAX_GROUPS groups, about the same number in
+    each launch, and a run is cut where a launch is full.  With separate buffers every bucket is a run, and a launch
+    takes as many as its table holds (480 words, R + 6 each)."""
+    runs = [b.s1 for b in w.buckets]
+    if w.layout != "separate":
+        runs = [sum(runs)]
+    groups = [-(-n // FUSED_GROUP) for n in runs]
+    launches = -(-sum(groups) // FUSED_MAX_GROUPS)
+    most, cap = -(-sum(groups) // launches), 480 // (w.R + 6)
+    count, cnt, total = 0, 0, 0
+    for g in groups:
+        while g > 0:
+            if cnt == cap or total == most:
+                count, cnt, total = count + 1, 0, 0
+            part = min(g, most - total)
+            cnt, total, g = cnt + 1, total + part, g - part
+    return count + (1 if cnt else 0)
 
 
 def roofline_entry(np, kernel, algo_bytes, ms, launches, key, step_kernel_ms=None, per_step=None):

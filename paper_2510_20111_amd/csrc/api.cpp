@@ -106,8 +106,8 @@ static hzp_status_t adamw_shard(const char *who, const hzp_plan_t *plan, uint32_
         f.v = v[idx];
         f.out = param_out ? param_out[idx] : nullptr;
         f.n = b->S1;
-        f.first_slot = b->first_slot;
-        f.n_tensors = b->n_tensors;
+        f.first_run = b->first_run;
+        f.n_runs = b->n_runs;
         f.shard_begin = shard_index * b->S1;
         if (f.n >= (1ull << 30))
             return fail(HZP_ERR_UNSUPPORTED, "%s: layer %u: shard of 2^30 elements or more", who, layer);
@@ -126,9 +126,10 @@ static hzp_status_t adamw_shard(const char *who, const hzp_plan_t *plan, uint32_
         segs.push_back(f);
     }
     if (segs.empty()) return HZP_OK;
-    if (hy) return launch_fused(plan, g32, o32, per_layer, segs.data(), segs.size(), derive_scalars(*hy), stream);
-    return launch_fused_dev(plan, g32, o32, per_layer, segs.data(), segs.size(),
-                            reinterpret_cast<const AdamScalars *>(scalars_dev), stream);
+    AdamScalars h;
+    if (hy) h = derive_scalars(*hy);
+    return launch_fused(plan, g32, o32, per_layer, segs.data(), segs.size(), hy ? &h : nullptr,
+                        reinterpret_cast<const AdamScalars *>(scalars_dev), stream);
 }
 
 extern "C" hzp_status_t hzp_adamw_shard(const hzp_plan_t *plan, uint32_t layer_begin, uint32_t layer_end,

@@ -37,7 +37,7 @@ struct Piece {
 struct BucketRec {
     uint32_t layer;
     uint32_t cls;
-    uint32_t first_slot;    // first entry of this bucket in the per-bucket-ordered tables
+    uint32_t first_run, n_runs;     // the bucket's rows in the decay tables
     uint32_t n_tensors;
     uint64_t payload_end, P, S3, S2, S1, base;
     std::vector<uint32_t> tensor_ids;
@@ -49,8 +49,8 @@ struct BucketRec {
 // Lookup tables of one plan on one device.
 struct DeviceTables {
     int device = -1;
-    uint64_t *tensor_off = nullptr;     // [n_tensors] bucket-relative offsets, bucket after bucket
-    float *tensor_wd = nullptr;         // [n_tensors] weight-decay multipliers, same order
+    uint64_t *run_off = nullptr;        // the plan's decay tables
+    float *run_wd = nullptr;
     Piece *pieces = nullptr;            // all buckets' pieces, bucket after bucket
     uint32_t *piece_chunk = nullptr;    // chunk_begin of the same pieces, densely packed
 };
@@ -67,12 +67,13 @@ struct hzp_plan {
     uint32_t K;                                 // Z1/Z3, or 0 when Z3 does not divide Z1
     uint32_t world;                             // lcm(Z1, Z2, Z3): ranks are 0 .. world-1
     uint64_t total_padded;
-    bool uniform_wd;                            // every multiplier is 1: no table lookups
     std::vector<hzp::TensorRec> tensors;        // by tensor id
     std::vector<hzp::BucketRec> buckets;        // by (layer, class)
     std::vector<int32_t> bucket_of;             // [layer*2 + cls] -> bucket index or -1
-    std::vector<uint64_t> slot_off;             // per-bucket-ordered copies for the device
-    std::vector<float> slot_wd;
+    // Bucket after bucket: the bucket positions where the decay multiplier changes (the first at 0), and the
+    // multiplier from there on (the gap behind a tensor counts as the tensor's).
+    std::vector<uint64_t> run_off;
+    std::vector<float> run_wd;
     mutable std::mutex mu;
     mutable std::vector<hzp::DeviceTables> dev; // one entry per device that has used the plan
 };
@@ -88,7 +89,7 @@ struct FusedSegment {
     float *master, *m, *v;
     void *out;                  // nullable
     uint64_t n;                 // elements, a multiple of 8
-    uint32_t first_slot, n_tensors;     // the bucket's rows in the weight-decay tables
+    uint32_t first_run, n_runs; // the bucket's rows in the decay tables
     uint64_t shard_begin;       // bucket position of element 0
 };
 
@@ -102,11 +103,10 @@ static_assert(sizeof(AdamScalars) <= sizeof(hzp_adamw_scalars_t), "the public bl
 // Launchers; their arguments have been validated by the entry points.
 hzp_status_t launch_reduce(bool g32, const void *const *slices, uint32_t R, uint64_t n, float scale,
                            int accumulate, float *out, hipStream_t stream);
-hzp_status_t launch_fused(const hzp_plan_t *plan, bool g32, bool o32, uint32_t R, const FusedSegment *segs,
-                          size_t nseg, const AdamScalars &h, hipStream_t stream);
-// The same with the step's scalars read from device memory at run time (as packed by pack_scalars).
-hzp_status_t launch_fused_dev(const hzp_plan_t *plan, bool g32, bool o32, uint32_t R, const FusedSegment *segs,
-                              size_t nseg, const AdamScalars *scalars_dev, hipStream_t stream);
+// The step's scalars come from `scalars` (copied into the launches) or, where that is null, from device memory
+// at run time (as packed by hzp_adamw_scalars).
+hzp_status_t launch_fused(const hzp_plan_t *plan, bool g32, bool o32, uint32_t R, const FusedSegment *segs, size_t nseg,
+                          const AdamScalars *scalars, const AdamScalars *scalars_dev, hipStream_t stream);
 hzp_status_t launch_concat(const void *const *srcs, uint32_t n_shards, uint64_t bytes_per_shard, void *dst,
                            hipStream_t stream);
 // Concatenates `per_layer` equal pieces for each of n_layers layers; srcs[l*per_layer + k], dsts[l].

@@ -3,23 +3,27 @@
 // Every kernel here streams: each byte is read once and written once, there is no reuse and
 // no contraction, so the bound is HBM bandwidth (26+2R bytes per element for the fused update
 // with bf16 gradients, against about 30 fp32 operations).  The design therefore is
-//   - every load/store instruction of a wavefront covers one contiguous run of memory, and a
-//     lane requests all of its (R+3) x 2 input vectors before it uses the first one;
-//   - single-wavefront workgroups, dispatched in address order, and for the many-stream fused
-//     update only about 5 of them resident per CU: a small, coherent front of in-flight
-//     groups serves the memory controllers better than full occupancy;
+//   - every load/store instruction of a wavefront covers one contiguous run of memory;
+//   - single-wavefront workgroups, dispatched in address order, with a few loads in flight each and a
+//     cap on how many are resident: a small, coherent front of requests serves the memory
+//     controllers better than as many requests as the chip can hold;
+//   - everything a wavefront needs to ask for its data (pointers, lengths, scalars) arrives in one
+//     round of scalar loads;
 //   - non-temporal loads, and stores that are written through to memory with the streaming
 //     hint: nothing is touched twice, so no line should be kept;
 //   - many layers per launch: shards of one layer are only a few MB, so the per-layer
 //     pointers travel in the kernel-argument block and one grid covers all of them;
-//   - consecutive workgroups take consecutive tiles.  The hardware deals workgroups to the
-//     8 XCDs round-robin; with no reuse there is nothing for an XCD-local L2 to keep, the
-//     tiles of any window of workgroups still spread over all memory channels, and a remap
-//     that gives each XCD its own contiguous eighth measured 5 % slower.
+//   - consecutive workgroups take consecutive tiles (neighbouring ones in pairs in the fused update).
+//     The hardware deals workgroups to the 8 XCDs round-robin; with no reuse there is nothing for an
+//     XCD-local L2 to keep, the tiles of any window of workgroups still spread over all memory
+//     channels, and a remap that gives each XCD its own contiguous eighth measured 5 % slower.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstring>
+#include <utility>
 #include <vector>
 
 #include "hzp_internal.hpp"
@@ -39,17 +43,14 @@ __device__ __forceinline__ T ld_stream(const T *p)
     return __builtin_nontemporal_load(p);
 }
 
-// Element (vector) `idx` of a stream whose base is uniform: base + 32-bit byte offset, so that the
-// access uses a scalar base register and one VGPR offset.  Callers keep streams below 4 GiB.
+// Vector `idx` of a stream whose base address is uniform: base + 32-bit byte offset in global memory, so
+// that the access uses a scalar base register and one VGPR offset.  Callers keep streams below 4 GiB.
 template <class T>
-__device__ __forceinline__ const T *at(const void *base, uint32_t idx)
+__device__ __forceinline__ T ld_stream(uint64_t base, uint32_t idx)
 {
-    return reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + idx * (uint32_t)sizeof(T));
-}
-template <class T>
-__device__ __forceinline__ T *at(void *base, uint32_t idx)
-{
-    return reinterpret_cast<T *>(reinterpret_cast<char *>(base) + idx * (uint32_t)sizeof(T));
+    typedef const __attribute__((address_space(1))) char *bytes;
+    typedef const __attribute__((address_space(1))) T *vectors;
+    return __builtin_nontemporal_load((vectors)((bytes)base + idx * (uint32_t)sizeof(T)));
 }
 
 // Streaming store with write-through to memory: system scope plus the non-temporal hint.  Measured
@@ -60,7 +61,7 @@ __device__ __forceinline__ T *at(void *base, uint32_t idx)
 // than 8 bytes and an overwrite of its data registers (the compiler cannot see inside the asm to
 // add them; with one wait state the first dword of some lanes was stored from the next value
 // when the store pipeline was under pressure).
-__device__ __forceinline__ void st_writethrough(void *base, uint32_t byte_off, f32x4 v)
+__device__ __forceinline__ void st_writethrough(uint64_t base, uint32_t byte_off, f32x4 v)
 {
     asm volatile("global_store_dwordx4 %0, %1, %2 sc0 sc1 nt\n\ts_nop 1" ::"v"(byte_off), "v"(v), "s"(base) : "memory");
 }
@@ -70,7 +71,7 @@ __device__ __forceinline__ void st_writethrough(u32x4 *dst, u32x4 v)
 {
     asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1 nt\n\ts_nop 1" ::"v"(dst), "v"(v) : "memory");
 }
-__device__ __forceinline__ void st_writethrough(void *base, uint32_t byte_off, u32x2 v)
+__device__ __forceinline__ void st_writethrough(uint64_t base, uint32_t byte_off, u32x2 v)
 {
     asm volatile("global_store_dwordx2 %0, %1, %2 sc0 sc1 nt" ::"v"(byte_off), "v"(v), "s"(base) : "memory");
 }
@@ -92,18 +93,30 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
 // ---------------------------------------------------------------------------------------
 // Work decomposition of the element-wise kernels.
 //
-// A workgroup is ONE wavefront and owns one group of 512 consecutive elements.  Lane l works on
-// two quads of 4 elements: [4l, 4l+4) and [256+4l, 256+4l+4) of the group.  With that mapping
-// every load/store instruction of the wavefront covers one contiguous run (1 KiB of an fp32
-// stream, 512 B of a bf16 stream), and the fp32 and bf16 streams give each lane the same
-// elements.  Measured on MI355X, single-wavefront workgroups with whole-instruction contiguity
-// stream the 15-19 concurrent address streams of the fused update about 10 % faster than
-// 256-thread workgroups whose lanes read 32 contiguous bytes of the fp32 streams.
-// Shards are multiples of 8 elements, so a quad is never split; only the last group of a
-// segment can be partly filled, and its lanes are predicated per quad.
+// A workgroup is ONE wavefront and owns one group of 256 consecutive elements, a quad of 4 to a
+// lane, so every load or store of the wavefront covers one contiguous run (1 KiB of an fp32 stream,
+// 512 B of a bf16 stream).  The contributions are requested a few at a time (a chunk) and added as
+// they come, and unused LDS caps the resident wavefronts: with 15-19 concurrent streams what decides
+// is how many bytes are in flight per CU, and at what spread of addresses, not how many loads one
+// wavefront can have outstanding.  About 32-50 KiB in flight per CU serve the memory best; below
+// that latency shows, above it the requests queue in an order the memory controllers serve badly.
+// Measured on MI355X, 100 M elements, all R + 3 loads of a 512-element group up front against
+// chunks on 256-element groups: R = 8 bf16 6.68 -> 6.78 TB/s, R = 16 6.24 -> 6.72, fp32 R = 8
+// 6.37 -> 6.73, R = 1 fp32 6.67 -> 6.79.
+// Shards are multiples of 8 elements, so a quad is never split; lanes past the end of a segment
+// read its last quad again and store nothing.
 // ---------------------------------------------------------------------------------------
 constexpr int kWave = 64;
-constexpr uint32_t kGroupQuads = 128;       // quads per group (512 elements)
+constexpr uint32_t kGroupQuads = 64;        // quads per group (256 elements)
+
+// Dynamic LDS that leaves room for `waves` single-wavefront workgroups per CU (160 KiB).
+constexpr unsigned lds_for(unsigned waves) { return waves ? 163840u / waves / 512u * 512u : 0u; }
+
+// Contributions one wavefront has in flight.  Measured at 100 M elements: bf16 R = 8 with chunks of 2 / 3 / 4 / 6 / 8
+// 6.76 / 6.78 / 6.78 / 6.76 / 6.78 TB/s, R = 16 6.73 / 6.68 / 6.72 / 6.74 / 6.71; fp32 R = 8 with 2 / 3 / 4 / 8
+// 6.73 / 6.77 / 6.73 / 6.72, R = 16 6.57 / 6.57 / 6.47 / 6.45.
+constexpr uint32_t fused_chunk(bool g32) { return g32 ? 3u : 4u; }
+constexpr uint32_t kReduceChunk = 4;
 
 // Four gradient elements of one contribution, widened to fp32 on access.
 template <bool G32>
@@ -111,7 +124,7 @@ struct GradQuad;
 template <>
 struct GradQuad<false> {
     u32x2 w;
-    __device__ __forceinline__ void load(const void *base, uint32_t quad) { w = ld_stream(at<u32x2>(base, quad)); }
+    __device__ __forceinline__ void load(uint64_t base, uint32_t quad) { w = ld_stream<u32x2>(base, quad); }
     __device__ __forceinline__ float get(int e) const
     {
         const uint32_t word = w[e >> 1];
@@ -121,78 +134,63 @@ struct GradQuad<false> {
 template <>
 struct GradQuad<true> {
     f32x4 a;
-    __device__ __forceinline__ void load(const void *base, uint32_t quad) { a = ld_stream(at<f32x4>(base, quad)); }
+    __device__ __forceinline__ void load(uint64_t base, uint32_t quad) { a = ld_stream<f32x4>(base, quad); }
     __device__ __forceinline__ float get(int e) const { return a[e]; }
 };
 
-// Issue the loads of R_T contributions for the lane's two quads (valid[h]: quad h exists).
-template <int R_T, bool G32, bool FULL>
-__device__ __forceinline__ void load_contributions(GradQuad<G32> (&g)[R_T][2], const void *const *slices,
-                                                   const uint32_t quad[2], const bool valid[2])
+// Contributions per chunk: R spread evenly over the fewest chunks of at most `most`.
+constexpr uint32_t chunk_of(uint32_t R, uint32_t most)
 {
-#pragma unroll
-    for (int r = 0; r < R_T; ++r)
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-            if (FULL || valid[h]) g[r][h].load(slices[r], quad[h]);
+    const uint32_t chunks = (R + most - 1) / most;
+    return (R + chunks - 1) / chunks;
 }
 
-// Left-to-right fp32 sum of loaded contributions: ((g0 + g1) + g2) + ...
-template <int R_T, bool G32>
-__device__ __forceinline__ void sum_loaded(const GradQuad<G32> (&g)[R_T][2], float s[2][4])
+// Pins uniform values: they are read (from the arguments) no later than here, and not where they are used, with
+// nothing to hide the read behind.
+template <class T>
+__device__ __forceinline__ void pin(T &x)
 {
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) s[h][e] = g[0][h].get(e);
-#pragma unroll
-    for (int r = 1; r < R_T; ++r)
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) s[h][e] = s[h][e] + g[r][h].get(e);
+    asm volatile("" : "+s"(x));
+}
+template <class T, class... Rest>
+__device__ __forceinline__ void pin(T &x, Rest &...rest)
+{
+    pin(x);
+    pin(rest...);
 }
 
-// The same sum for a run-time R: two contributions in flight, still added in order.
-template <bool G32, bool FULL>
-__device__ __forceinline__ void sum_contributions_loop(const void *const *slices, uint32_t R, const uint32_t quad[2],
-                                                       const bool valid[2], float s[2][4])
+// Left-to-right fp32 sum of R contributions, ((g0 + g1) + g2) + ..., at most `MOST` of them in flight, for
+// Q quads; slice[r] + shift is contribution r, and `at` holds the first chunk's pointers.
+template <uint32_t R, uint32_t MOST, bool G32, int Q>
+__device__ __forceinline__ void sum_contributions(uint64_t (&at)[MOST], const uint64_t *slice, int64_t shift,
+                                                  const uint32_t (&quad)[Q], float (&s)[Q][4])
 {
-    GradQuad<G32> g0[2];
+    constexpr uint32_t C = chunk_of(R, MOST);
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-        if (FULL || valid[h]) g0[h].load(slices[0], quad[h]);
+    for (uint32_t base = 0; base < R; base += C) {
+        GradQuad<G32> g[C][Q];
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+        for (uint32_t c = 0; c < C; ++c)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) s[h][e] = g0[h].get(e);
-    uint32_t r = 1;
-    for (; r + 1 < R; r += 2) {
-        GradQuad<G32> ga[2], gb[2];
+            for (int q = 0; q < Q; ++q)
+                if (base + c < R) g[c][q].load(at[c] + shift, quad[q]);
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
-            if (FULL || valid[h]) {
-                ga[h].load(slices[r], quad[h]);
-                gb[h].load(slices[r + 1], quad[h]);
-            }
+        for (uint32_t c = 0; c < C; ++c)
+            if (base + C + c < R) at[c] = slice[base + C + c];
+        __builtin_amdgcn_sched_barrier(0);      // the whole chunk is requested (and the next one's pointers) before its first add,
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (uint32_t c = 0; c < C; ++c)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) s[h][e] = s[h][e] + ga[h].get(e);
+            for (int q = 0; q < Q; ++q)
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+                for (int e = 0; e < 4; ++e)
+                    if (base + c < R) s[q][e] = base + c ? s[q][e] + g[c][q].get(e) : g[c][q].get(e);
+        // and the next chunk only behind its last: the sum is pinned here, or the adds sink to the sum's use
 #pragma unroll
-            for (int e = 0; e < 4; ++e) s[h][e] = s[h][e] + gb[h].get(e);
-    }
-    if (r < R) {
-        GradQuad<G32> ga[2];
+        for (int q = 0; q < Q; ++q)
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
-            if (FULL || valid[h]) ga[h].load(slices[r], quad[h]);
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) s[h][e] = s[h][e] + ga[h].get(e);
+            for (int e = 0; e < 4; ++e) asm volatile("" : "+v"(s[q][e]));
+        __builtin_amdgcn_sched_barrier(0);
     }
 }
 
@@ -200,233 +198,244 @@ __device__ __forceinline__ void sum_contributions_loop(const void *const *slices
 // Standalone reduction (bit-exact with the scalar definition: fixed order, no contraction).
 // ---------------------------------------------------------------------------------------
 struct ReduceArgs {
-    const void *g[HZP_MAX_REPLICAS];
+    uint64_t g[HZP_MAX_REPLICAS];
     float *out;
-    uint32_t R;
     uint32_t nquad;     // 4-element quads in the slice
     float scale;
-    int accumulate;
 };
 
-template <bool G32, int R_T, bool FULL>
-__device__ __forceinline__ void reduce_group(const ReduceArgs &a, const uint32_t quad[2], const bool valid[2])
-{
-#pragma clang fp contract(off)
-    float s[2][4];
-    f32x4 prev[2];
-    if (a.accumulate) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-            if (FULL || valid[h]) prev[h] = ld_stream(at<f32x4>((const void *)a.out, quad[h]));
-    }
-    if constexpr (R_T != 0) {
-        GradQuad<G32> g[R_T][2];
-        load_contributions<R_T, G32, FULL>(g, a.g, quad, valid);
-        __builtin_amdgcn_sched_barrier(0);      // every load is issued before the first add
-        sum_loaded<R_T, G32>(g, s);
-    } else {
-        sum_contributions_loop<G32, FULL>(a.g, a.R, quad, valid, s);
-    }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        f32x4 t;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) t[e] = a.scale * s[h][e];
-        if (a.accumulate) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) t[e] = prev[h][e] + t[e];
-        }
-        if (FULL || valid[h]) st_writethrough((void *)a.out, quad[h] * 16u, t);
-    }
-}
+// Quads per lane: with a single bf16 contribution one quad is 512 B of reads to a wavefront, too little even at full
+// occupancy (25 M elements: 5.89 TB/s; with two quads 6.22).
+constexpr int reduce_quads(uint32_t R, bool g32) { return R == 1 && !g32 ? 2 : 1; }
 
-template <bool G32, int R_T>
+template <uint32_t R, bool G32, bool ACC>
 __global__ __launch_bounds__(kWave) void reduce_kernel(const ReduceArgs a)
 {
-    const uint32_t q0 = blockIdx.x * kGroupQuads + threadIdx.x;
-    const uint32_t quad[2] = {q0, q0 + kWave};
-    const bool valid[2] = {quad[0] < a.nquad, quad[1] < a.nquad};
-    if ((uint64_t)(blockIdx.x + 1) * kGroupQuads <= a.nquad)
-        reduce_group<G32, R_T, true>(a, quad, valid);
-    else
-        reduce_group<G32, R_T, false>(a, quad, valid);
+#pragma clang fp contract(off)
+    constexpr int Q = reduce_quads(R, G32);
+    uint64_t out = reinterpret_cast<uint64_t>(a.out), at[kReduceChunk];
+#pragma unroll
+    for (uint32_t c = 0; c < kReduceChunk; ++c) at[c] = c < R ? a.g[c] : 0;
+    uint32_t nquad = a.nquad;
+    float scale = a.scale;
+    pin(out, at[0], at[1], at[2], at[3], nquad, scale);
+    uint32_t q0[Q], quad[Q];
+    f32x4 t[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        q0[q] = (blockIdx.x * Q + q) * kGroupQuads + threadIdx.x;
+        quad[q] = q0[q] < nquad ? q0[q] : nquad - 1;
+        if (ACC) t[q] = ld_stream<f32x4>(out, quad[q]);
+    }
+    float s[Q][4];
+    sum_contributions<R, kReduceChunk, G32>(at, a.g, 0, quad, s);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float x = scale * s[q][e];
+            t[q][e] = ACC ? t[q][e] + x : x;
+        }
+        if (q0[q] < nquad) st_writethrough(out, quad[q] * 16u, t[q]);
+    }
 }
 
 // ---------------------------------------------------------------------------------------
-// Fused reduce + scale + AdamW + cast over many shard segments (one per layer bucket).
+// Fused reduce + scale + AdamW + cast over many shard segments.
 // ---------------------------------------------------------------------------------------
-// Where a launch finds the step's scalars: in its argument block, or in device memory (a captured
-// launch then takes each replay's values from there).
-struct ScalarsInMemory {
-    const AdamScalars *p;
+// What one launch covers travels in the argument block: `segments` runs of elements, each with its R + 4
+// pointers (master, m, v, parameter output or null, R contributions) followed by a record.  A call of many
+// small segments that lie at the same distances from each other in all streams (the layers of an arena)
+// can share one set of pointers; a record then gives the segment's distance from the first.
+//   word 0: groups up to and including the segment (2-D grid: the segment's own), number of quads
+//   word 1: decay multiplier; where the launch looks decay up: first entry and number of entries
+//   word 2 (launches that look decay up): bucket position of the segment's first element
+//   last word (launches with one set of pointers): distance in quads, and the output's own
+constexpr uint32_t kPlainRecord = 2;        // words of a record with pointers of its own and no look-up
+constexpr uint32_t kTableWords = 480;       // 3840 bytes: 34 segments at R = 8 with pointers of their own
+struct FusedArgs {
+    uint32_t segments;
+    uint32_t stride, ptr_stride;            // words from a segment's record / pointers to the next one's (0: shared)
+    uint32_t dist;                          // where the distance stands in a record (0: no distance)
+    uint32_t grid2d;                        // 1: grid is (groups, segments)
+    uint32_t lookup;                        // 1: decay multipliers come from the tables
+    const uint64_t *run_off;                // device: bucket positions where the decay multiplier changes
+    const float *run_wd;                    // device: the multiplier from there on
+    const AdamScalars *scalars_dev;         // device, or null: `scalars` are the step's
+    AdamScalars scalars;
+    uint64_t word[kTableWords];
 };
-__device__ __forceinline__ const AdamScalars &scalars_of(const AdamScalars &h) { return h; }
-__device__ __forceinline__ AdamScalars scalars_of(const ScalarsInMemory &h) { return *h.p; }
+static_assert(sizeof(FusedArgs) <= 4096, "kernel arguments");
 
-// Segment table in the kernel-argument block.  Segment s owns workgroups
-// [blk_end[s-1], blk_end[s]) and the pointers ptr[s*(R+4) ...]: R gradient slices, master,
-// momentum, variance, parameter output (may be null).
-template <int MAXSEG, int PTRCAP>
-struct SegTable {
-    static constexpr int kMaxSeg = MAXSEG;
-    static constexpr int kPtrCap = PTRCAP;
-    uint32_t nseg;
-    uint32_t R;
-    uint32_t grid2d;            // 1: grid is (groups, segments) and blk_end[s] is segment s's group count
-    uint32_t pad_;
-    uint32_t blk_end[MAXSEG];   // flat grid: running total of groups up to and including segment s
-    uint32_t nquad[MAXSEG];
-    const void *ptr[PTRCAP];
-};
-typedef SegTable<34, 408> SegTableWide;      // 3552 bytes: 34 layer buckets at R = 8 in one launch
-typedef SegTable<20, 280> SegTableNarrow;    // leaves room for the weight-decay lookup arguments
-
-struct WdLookup {
-    const uint64_t *tensor_off;     // device: bucket-relative tensor offsets, bucket after bucket
-    const float *tensor_wd;         // device: multipliers, same order
-    uint32_t first_slot[SegTableNarrow::kMaxSeg];
-    uint32_t n_tensors[SegTableNarrow::kMaxSeg];
-    uint64_t shard_begin[SegTableNarrow::kMaxSeg];
-};
-struct NoLookup {};
-
-template <int R_T, bool G32, bool O32, bool FULL, class Wd>
-__device__ __forceinline__ void fused_group(const void *const *sp, uint32_t R, const AdamScalars &h, const Wd &w,
-                                            uint32_t seg, const uint32_t quad[2], const bool valid[2])
-{
-    void *const P = const_cast<void *>(sp[R]);
-    void *const M = const_cast<void *>(sp[R + 1]);
-    void *const V = const_cast<void *>(sp[R + 2]);
-    void *const OUT = const_cast<void *>(sp[R + 3]);
-
-    // Request the R gradient streams (used first), then the state streams; a scheduling barrier
-    // keeps all of the lane's (R+3) x 2 loads above the first use, otherwise the scheduler sinks
-    // the loads that are needed last and the wavefront pays two memory round trips.
-    f32x4 p[2], m[2], v[2];
-    float g[2][4];
-    auto load_state = [&]() {
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh)
-            if (FULL || valid[hh]) {
-                p[hh] = ld_stream(at<f32x4>((const void *)P, quad[hh]));
-                m[hh] = ld_stream(at<f32x4>((const void *)M, quad[hh]));
-                v[hh] = ld_stream(at<f32x4>((const void *)V, quad[hh]));
-            }
-    };
-    if constexpr (R_T != 0) {
-        GradQuad<G32> gq[R_T][2];
-        load_contributions<R_T, G32, FULL>(gq, sp, quad, valid);
-        load_state();
-        __builtin_amdgcn_sched_barrier(0);
-        sum_loaded<R_T, G32>(gq, g);
-    } else {
-        load_state();
-        sum_contributions_loop<G32, FULL>(sp, R, quad, valid, g);
+// The decay runs that a group meets, found while the streams arrive: begin() narrows the search to 64
+// runs and requests their starts (lane by lane), find() requests the next ones and the first multiplier,
+// get() picks the lane's own.  Runs are whole numbers of 8 elements, so a group meets at most 33.
+struct DecayRuns {
+    const uint64_t *off;
+    const float *wd;
+    uint32_t lo, end;           // find(): the run that holds the group's first element; the slice's last + 1
+    uint64_t start, next;       // lane l: the starts of runs lo + l; lo + 1 + l
+    float mult;                 // run lo's multiplier
+    __device__ __forceinline__ void begin(uint32_t first, uint32_t n, uint64_t pos)
+    {
+        const uint32_t lane = threadIdx.x;
+        lo = first;
+        end = first + n;
+        uint32_t left = n;
+        while (left > kWave) {                  // 64 pivots a round
+            const uint32_t stride = (left + kWave - 1) / kWave;
+            const uint32_t mine = lane * stride;
+            const bool le = mine < left && off[lo + mine] <= pos;
+            const uint32_t step = ((uint32_t)__popcll(__ballot(le)) - 1u) * stride;
+            left = left - step < stride ? left - step : stride;
+            lo += step;
+        }
+        start = ~0ull;
+        if (lane < left) start = off[lo + lane];
     }
+    __device__ __forceinline__ void find(uint64_t pos)
+    {
+        const uint32_t lane = threadIdx.x;
+        lo = __builtin_amdgcn_readfirstlane(lo + (uint32_t)__popcll(__ballot(start <= pos)) - 1u);
+        next = ~0ull;
+        if (lo + 1 + lane < end) next = off[lo + 1 + lane];
+        mult = wd[lo];
+    }
+    __device__ __forceinline__ float get(uint64_t pos) const
+    {
+        const uint32_t inside = (uint32_t)__popcll(__ballot(next < pos + 4 * kGroupQuads));
+        if (inside == 0) return mult;
+        const uint64_t mine = pos + 4 * threadIdx.x;
+        uint32_t r = lo;
+        for (uint32_t k = 1; k <= inside; ++k)
+            if (off[lo + k] <= mine) r = lo + k;
+        return wd[r];
+    }
+};
 
-    float wd[2] = {h.weight_decay, h.weight_decay};
-    if constexpr (!std::is_same<Wd, NoLookup>::value) {
-        // Every tensor starts on a multiple of A >= 8 elements, so the 4 elements of a quad
-        // belong to one tensor: the last one whose offset is <= the quad's bucket position.
-        const uint64_t *off = w.tensor_off + w.first_slot[seg];
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-            const uint64_t pos = w.shard_begin[seg] + 4ull * quad[hh];
-            uint32_t tl = 0, th = w.n_tensors[seg] - 1;
-            while (tl < th) {
-                const uint32_t mid = (tl + th + 1) >> 1;
-                if (off[mid] <= pos)
-                    tl = mid;
+// PAIRS: each XCD takes two neighbouring groups (workgroups are dealt to the 8 XCDs round-robin, so of every
+// 16 consecutive groups workgroups x and x + 8 take groups 2x and 2x + 1).  A bf16 access of a group covers
+// 512 B; as pairs an XCD's accesses to a bf16 stream cover 1 KiB, like those to an fp32 stream.  Measured
+// with bf16 contributions (R = 4 / 8 / 16, 100 M elements): 6.74 / 6.68 / 6.58 -> 6.77 / 6.78 / 6.72 TB/s;
+// quadruples lose again (6.66 / 6.73 / 6.66), and where all streams are fp32 pairs lose 1 % (6.79 -> 6.73).
+//
+// PLAIN: a 2-D grid over segments with pointers of their own and one multiplier each (a whole arena of equal decay is
+// one such segment).  Everything a wavefront needs then lies at an address that blockIdx gives and arrives in one
+// round of scalar loads.  Otherwise a uniform binary search finds the segment, three more rounds, which the few
+// resident wavefronts hide badly (105 M elements, R = 8, one segment: 6.65 TB/s at the best number of wavefronts, 6.73
+// with the one round).
+template <uint32_t R, bool G32, bool O32, bool PLAIN>
+__global__ __launch_bounds__(kWave) void fused_adamw_kernel(const FusedArgs a)
+{
+    constexpr bool PAIRS = !G32;
+    // Which segment and which group of it?
+    uint32_t grp = blockIdx.x, before = 0;      // workgroups of the segments ahead of it
+    const uint64_t *ptr, *rec;
+    int64_t shift = 0, out_shift = 0;           // of the segment against the pointers, in quads
+    bool lookup = false;
+    if constexpr (PLAIN) {
+        ptr = a.word + blockIdx.y * (R + 4 + kPlainRecord);
+        rec = ptr + R + 4;
+    } else {
+        uint32_t segments = a.segments, stride = a.stride, ptr_stride = a.ptr_stride, dist = a.dist, grid2d = a.grid2d, look = a.lookup;
+        pin(segments, stride, ptr_stride, dist, grid2d, look);
+        lookup = look;
+        const uint64_t *const records = a.word + R + 4;
+        uint32_t seg = blockIdx.y;
+        if (!grid2d) {
+            uint32_t lo = 0, hi = segments - 1;
+            while (lo < hi) {
+                const uint32_t mid = (lo + hi) >> 1;
+                if (blockIdx.x < (uint32_t)records[mid * stride])
+                    hi = mid;
                 else
-                    th = mid - 1;
+                    lo = mid + 1;
             }
-            wd[hh] *= w.tensor_wd[w.first_slot[seg] + tl];
+            seg = lo;
+            before = seg ? (uint32_t)records[(seg - 1) * stride] : 0u;
+        }
+        rec = records + seg * stride;
+        ptr = a.word + seg * ptr_stride;
+        grp -= before;
+        if (dist) {
+            const uint64_t d = rec[dist];
+            shift = (int32_t)(uint32_t)d;
+            out_shift = (int32_t)(uint32_t)(d >> 32);
         }
     }
+    constexpr uint32_t CHUNK = fused_chunk(G32);
+    uint64_t P = ptr[0], M = ptr[1], V = ptr[2], OUT = ptr[3], extent = rec[0], decay = rec[1];
+    uint64_t at[CHUNK];
+#pragma unroll
+    for (uint32_t c = 0; c < CHUNK; ++c) at[c] = c < R ? ptr[4 + c] : 0;
+    AdamScalars h = a.scalars;
+    uint64_t scalars_dev = reinterpret_cast<uint64_t>(a.scalars_dev);
+    pin(P, M, V, OUT, extent, decay, at[0], at[1], at[2], at[CHUNK - 1], scalars_dev);
+    pin(h.lr, h.beta1, h.beta2, h.one_minus_beta1, h.one_minus_beta2, h.eps, h.weight_decay, h.grad_scale, h.inv_bc1, h.inv_bc2);
+    const uint32_t groups = (uint32_t)extent - before, nquad = (uint32_t)(extent >> 32);
+    if (grp >= groups) return;                  // of a longer segment of a 2-D grid
+    if (PAIRS && grp < (groups & ~15u)) grp = (grp & ~15u) | ((grp & 7u) << 1) | ((grp >> 3) & 1u);
+    const bool has_out = OUT != 0;
+    P += shift * 16;
+    M += shift * 16;
+    V += shift * 16;
+    OUT += out_shift * (O32 ? 16 : 8);
 
-    // The arithmetic is not hidden behind other wavefronts (few are resident by design), so it is
+    const uint32_t q0 = grp * kGroupQuads + threadIdx.x;
+    const uint32_t quad = q0 < nquad ? q0 : nquad - 1;
+    const uint32_t quads[1] = {quad};
+    DecayRuns runs{a.run_off, a.run_wd};
+    uint64_t pos = 0;                           // of the group's first element in its bucket
+    if (!PLAIN && lookup) {
+        pos = rec[2] + 4ull * kGroupQuads * grp;
+        runs.begin((uint32_t)decay, (uint32_t)(decay >> 32), pos);
+    }
+    // The states are requested ahead of the contributions: they are needed last and then have the
+    // contributions' time to arrive.
+    f32x4 p = ld_stream<f32x4>(P, quad);
+    f32x4 m = ld_stream<f32x4>(M, quad);
+    f32x4 v = ld_stream<f32x4>(V, quad);
+    __builtin_amdgcn_sched_barrier(0);
+    if (!PLAIN && lookup) runs.find(pos);
+    if (scalars_dev) {
+        typedef const __attribute__((address_space(4))) float const_float;      // scalar loads
+        const_float *c = reinterpret_cast<const_float *>(scalars_dev);
+        h = {c[0], c[1], c[2], c[3], c[4], c[5], c[6], c[7], c[8], c[9]};
+    }
+    float g[1][4];
+    sum_contributions<R, CHUNK, G32>(at, ptr + 4, shift * (G32 ? 16 : 8), quads, g);
+
+    const float wd = h.weight_decay * (!PLAIN && lookup ? runs.get(pos) : __uint_as_float((uint32_t)decay));
+
+    // The arithmetic is hardly hidden behind other wavefronts (few are resident by design), so it is
     // kept short: hardware square root and reciprocal (1 ulp each) instead of the correctly
     // rounded expansions.  Their error enters p only through lr*u, far below the tolerance.
 #pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float ge = h.grad_scale * g[hh][e];
-            const float mn = h.beta1 * m[hh][e] + h.one_minus_beta1 * ge;
-            const float vn = h.beta2 * v[hh][e] + (h.one_minus_beta2 * ge) * ge;
-            const float denom = __builtin_amdgcn_sqrtf(vn * h.inv_bc2) + h.eps;
-            const float u = (mn * h.inv_bc1) * __builtin_amdgcn_rcpf(denom);
-            const float pe = p[hh][e];
-            m[hh][e] = mn;
-            v[hh][e] = vn;
-            p[hh][e] = pe - h.lr * (u + wd[hh] * pe);
+    for (int e = 0; e < 4; ++e) {
+        const float ge = h.grad_scale * g[0][e];
+        const float mn = h.beta1 * m[e] + h.one_minus_beta1 * ge;
+        const float vn = h.beta2 * v[e] + (h.one_minus_beta2 * ge) * ge;
+        const float denom = __builtin_amdgcn_sqrtf(vn * h.inv_bc2) + h.eps;
+        const float u = (mn * h.inv_bc1) * __builtin_amdgcn_rcpf(denom);
+        const float pe = p[e];
+        m[e] = mn;
+        v[e] = vn;
+        p[e] = pe - h.lr * (u + wd * pe);
+    }
+    if (q0 >= nquad) return;
+    st_writethrough(P, quad * 16u, p);
+    st_writethrough(M, quad * 16u, m);
+    st_writethrough(V, quad * 16u, v);
+    if (has_out) {
+        if constexpr (O32) {
+            st_writethrough(OUT, quad * 16u, p);
+        } else {
+            u32x2 o;
+            o[0] = pack_bf16(p[0], p[1]);
+            o[1] = pack_bf16(p[2], p[3]);
+            st_writethrough(OUT, quad * 8u, o);
         }
     }
-#pragma unroll
-    for (int hh = 0; hh < 2; ++hh)
-        if (FULL || valid[hh]) {
-            st_writethrough(P, quad[hh] * 16u, p[hh]);
-            st_writethrough(M, quad[hh] * 16u, m[hh]);
-            st_writethrough(V, quad[hh] * 16u, v[hh]);
-        }
-    if (OUT) {
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh)
-            if (FULL || valid[hh]) {
-                if constexpr (O32) {
-                    st_writethrough(OUT, quad[hh] * 16u, p[hh]);
-                } else {
-                    u32x2 o;
-                    o[0] = pack_bf16(p[hh][0], p[hh][1]);
-                    o[1] = pack_bf16(p[hh][2], p[hh][3]);
-                    st_writethrough(OUT, quad[hh] * 8u, o);
-                }
-            }
-    }
-}
-
-// Unused LDS requested at launch so that at most 5 single-wavefront workgroups are resident per
-// CU.  With 15-19 address streams, a smaller, more coherent front of in-flight groups serves the
-// memory controllers better than full occupancy; each wavefront already keeps (R+3) x 2 loads
-// in flight.  Measured optimum on MI355X: 4-6 wavefronts per CU.
-constexpr unsigned kFusedLdsBytes = 32768;
-
-template <int R_T, bool G32, bool O32, class Seg, class H, class Wd>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 2))) void fused_adamw_kernel(const Seg a, const H h, const Wd w)
-{
-    // Which segment and which group of it?  When the segments are of similar length the grid is
-    // two-dimensional (y = segment, x = group; surplus workgroups of shorter segments leave at
-    // once) and nothing is looked up; otherwise the grid is flat and a uniform binary search over
-    // the table in the argument block finds the segment.  With few wavefronts resident, the
-    // search's chain of dependent scalar loads would delay every wavefront's first memory request.
-    uint32_t seg, grp;
-    if (a.grid2d) {
-        seg = blockIdx.y;
-        grp = blockIdx.x;
-        if (grp >= a.blk_end[seg]) return;      // holds the segment's own group count in this mode
-    } else {
-        const uint32_t blk = blockIdx.x;
-        uint32_t lo = 0, hi = a.nseg - 1;
-        while (lo < hi) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (blk < a.blk_end[mid])
-                hi = mid;
-            else
-                lo = mid + 1;
-        }
-        seg = lo;
-        grp = blk - (seg ? a.blk_end[seg - 1] : 0u);
-    }
-    const uint32_t R = R_T ? (uint32_t)R_T : a.R;
-    const void *const *sp = a.ptr + (size_t)seg * (R + 4);
-    const uint32_t nquad = a.nquad[seg];
-    const uint32_t q0 = grp * kGroupQuads + threadIdx.x;
-    const uint32_t quad[2] = {q0, q0 + kWave};
-    const bool valid[2] = {quad[0] < nquad, quad[1] < nquad};
-    if ((uint64_t)(grp + 1) * kGroupQuads <= nquad)
-        fused_group<R_T, G32, O32, true>(sp, R, scalars_of(h), w, seg, quad, valid);
-    else
-        fused_group<R_T, G32, O32, false>(sp, R, scalars_of(h), w, seg, quad, valid);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -582,76 +591,53 @@ static hzp_status_t check_launch(const char *what)
     return HZP_OK;
 }
 
+// One kernel per number of contributions: the loads of a chunk are then straight-line code (a run-time R
+// puts a wait between any two of them), and all of a launch's pointers arrive in one round of scalar loads.
+template <bool G32, bool ACC, size_t... I>
+static constexpr std::array<void (*)(ReduceArgs), sizeof...(I)> reduce_kernels(std::index_sequence<I...>)
+{
+    return {reduce_kernel<I + 1, G32, ACC>...};
+}
+template <bool G32, bool O32, bool PLAIN, size_t... I>
+static constexpr std::array<void (*)(FusedArgs), sizeof...(I)> fused_kernels(std::index_sequence<I...>)
+{
+    return {fused_adamw_kernel<I + 1, G32, O32, PLAIN>...};
+}
+
+// Wavefronts per CU for the reduction: what keeps about 48 KiB in flight per CU where the contributions fit one chunk,
+// 34 (bf16) or 38 (fp32) KiB where several chunks follow each other, and half as much again in a short launch (below
+// about 30 us), where filling and draining the chip weighs more than the order of the requests.  Measured at 25 M / 6.3 M
+// elements, TB/s with 28 wavefronts -> by this rule: bf16 R = 4 6.57 / 5.81 -> 6.64 / 5.80, R = 8 6.33 / 6.04 -> 6.59 / 6.05,
+// R = 16 6.31 / 6.10 -> 6.60 / 6.30; fp32 R = 4 (accumulating) 6.22 / 5.89 -> 6.30 / 5.89, R = 8 6.00 / 5.86 -> 6.49 / 6.09,
+// R = 16 5.77 / 5.87 -> 6.39 / 6.43.
+static unsigned reduce_waves(bool g32, uint32_t R, uint64_t n, int accumulate)
+{
+    const uint32_t chunk = chunk_of(R, kReduceChunk), es = g32 ? 4u : 2u;
+    const unsigned budget = (chunk == R ? 48u : g32 ? 38u : 34u) * 1024u;
+    const unsigned wave = chunk * es * 256u * reduce_quads(R, g32) + (accumulate ? 512u : 0u);
+    const bool brief = n * (R * es + 4u) < (g32 ? 256u << 20 : 160u << 20);
+    if (n <= 256u * 32u * 4u * kGroupQuads) return 0;                           // all resident at once
+    return std::min(28u, (brief ? budget * 3 / 2 : budget) / wave);
+}
+
 hzp_status_t launch_reduce(bool g32, const void *const *slices, uint32_t R, uint64_t n, float scale,
                            int accumulate, float *out, hipStream_t stream)
 {
     if (n == 0) return HZP_OK;
     ReduceArgs a{};
-    for (uint32_t r = 0; r < R; ++r) a.g[r] = slices[r];
+    for (uint32_t r = 0; r < R; ++r) a.g[r] = reinterpret_cast<uint64_t>(slices[r]);
     a.out = out;
-    a.R = R;
     a.nquad = (uint32_t)(n / 4);
     a.scale = scale;
-    a.accumulate = accumulate;
-    const dim3 grid((a.nquad + kGroupQuads - 1) / kGroupQuads), block(kWave);
-    // Unused LDS per workgroup caps the resident wavefronts, as in the fused update.  For the
-    // reduction it pays only with many bf16 streams (measured on MI355X: R = 8, 8 wavefronts per CU:
-    // 6.23 -> 6.37 TB/s; R = 16, 6 per CU: 6.03 -> 6.18; nothing at R = 4 or with fp32 inputs).
-#define HZP_REDUCE_CASE(G, RT, LDS) hipLaunchKernelGGL((reduce_kernel<G, RT>), grid, block, LDS, stream, a)
-    if (!g32) {
-        switch (R) {
-        case 4: HZP_REDUCE_CASE(false, 4, 0); break;
-        case 8: HZP_REDUCE_CASE(false, 8, 20480); break;
-        case 16: HZP_REDUCE_CASE(false, 16, 27136); break;
-        default: HZP_REDUCE_CASE(false, 0, 0); break;
-        }
-    } else {
-        switch (R) {
-        case 4: HZP_REDUCE_CASE(true, 4, 0); break;
-        case 8: HZP_REDUCE_CASE(true, 8, 0); break;
-        default: HZP_REDUCE_CASE(true, 0, 0); break;
-        }
-    }
-#undef HZP_REDUCE_CASE
+    const uint32_t group = kGroupQuads * reduce_quads(R, g32);
+    const dim3 grid((a.nquad + group - 1) / group), block(kWave);
+    const unsigned lds = lds_for(reduce_waves(g32, R, n, accumulate));
+    constexpr std::make_index_sequence<HZP_MAX_REPLICAS> all;
+    static constexpr std::array<void (*)(ReduceArgs), HZP_MAX_REPLICAS> kernels[2][2] = {
+        {reduce_kernels<false, false>(all), reduce_kernels<false, true>(all)},
+        {reduce_kernels<true, false>(all), reduce_kernels<true, true>(all)}};
+    hipLaunchKernelGGL(kernels[g32][accumulate != 0][R - 1], grid, block, lds, stream, a);
     return check_launch("hzp_reduce_shard");
-}
-
-template <class Seg, class H, class Wd>
-static void launch_fused_variant(bool g32, bool o32, uint32_t R, const Seg &a, const H &h,
-                                 const Wd &w, dim3 grid, hipStream_t stream)
-{
-    const dim3 block(kWave);
-    // The occupancy cap pays off only where every load is issued up front (compile-time R);
-    // the run-time-R loop keeps two contributions in flight and needs the resident wavefronts.
-    const unsigned lds = kFusedLdsBytes;
-#define HZP_FUSED_CASE(RT, G, O) \
-    hipLaunchKernelGGL((fused_adamw_kernel<RT, G, O, Seg, H, Wd>), grid, block, (RT) ? lds : 0u, stream, a, h, w)
-    if (!g32 && !o32) {
-        switch (R) {
-        case 1: HZP_FUSED_CASE(1, false, false); break;
-        case 2: HZP_FUSED_CASE(2, false, false); break;
-        case 4: HZP_FUSED_CASE(4, false, false); break;
-        case 8: HZP_FUSED_CASE(8, false, false); break;
-        case 16: HZP_FUSED_CASE(16, false, false); break;
-        default: HZP_FUSED_CASE(0, false, false); break;
-        }
-    } else if (g32 && o32) {
-        switch (R) {
-        case 4: HZP_FUSED_CASE(4, true, true); break;
-        case 8: HZP_FUSED_CASE(8, true, true); break;
-        case 16: HZP_FUSED_CASE(16, true, true); break;
-        default: HZP_FUSED_CASE(0, true, true); break;
-        }
-    } else if (g32 && !o32) {
-        if (R == 1) {
-            HZP_FUSED_CASE(1, true, false);     // the pre-reduced form
-        } else {
-            HZP_FUSED_CASE(0, true, false);
-        }
-    } else {
-        HZP_FUSED_CASE(0, false, true);
-    }
-#undef HZP_FUSED_CASE
 }
 
 // Most groups one launch of the fused update covers (about 150 M elements, 0.6-1.3 ms of work).
@@ -659,114 +645,212 @@ static void launch_fused_variant(bool g32, bool o32, uint32_t R, const Seg &a, c
 // launch; the XCDs do not run at exactly the same speed, and over a long launch they drift apart
 // (measured on MI355X: by 5-10 % of the grid after 3 ms), which spreads the addresses in flight and
 // leaves the slowest XCD to finish alone.  A launch boundary lines them up again for a few
-// microseconds: at R = 16 on 72 M-element shards, launches of 140-280 k groups stream 2-6 % faster
-// than one launch over everything, and shorter ones lose to the gaps between launches.
-constexpr uint32_t kMaxGroupsPerLaunch = 300000;
+// microseconds.  Shorter launches lose to the gaps between them: R = 16, 571 M elements, launches of at most 100 / 200 / 300 /
+// 400 / 600 / 800 / 1200 k groups and one launch for all 6.35 / 6.42 / 6.44 / 6.45 / 6.46 / 6.46 / 6.45 / 6.42 TB/s.
+constexpr uint32_t kMaxGroupsPerLaunch = 600000;
 
-// A run of one segment handled by one launch: elements [first, first + n) of segment `seg`.
+// Segments share one set of pointers where that saves launches and a launch of segments with their own would hold fewer
+// groups than this (8 M elements, about 50 us): a wavefront then has to read a record before it can ask for data, which
+// costs 2-3 % of the launch, against 2.7 us for one more launch.
+constexpr uint64_t kShareGroups = 32768;
+
+// Elements [first, first + n) of segment `seg`, with the decay multiplier they share, or (runs != 0)
+// with the table entries that hold theirs.
 struct SegRun {
     uint32_t seg;
     uint64_t first, n;
+    float wd;
+    uint32_t run0, runs;
 };
 
-template <class Seg, class H>
-static hzp_status_t launch_fused_table(const hzp_plan_t *plan, bool use_wd, bool g32, bool o32, uint32_t R,
-                                       const FusedSegment *segs, size_t nseg, const H &h,
-                                       hipStream_t stream)
+static inline char *out_at(const FusedSegment &f, uint64_t elem, uint32_t osz)
 {
-    const DeviceTables *tab = nullptr;
-    if (use_wd) {
-        hzp_status_t st = device_tables(plan, &tab);
-        if (st != HZP_OK) return st;
+    return f.out ? static_cast<char *>(f.out) + elem * osz : nullptr;
+}
+
+// Do the elements of run b follow run a's in every stream (so that one segment can cover both)?
+static bool follows(const FusedSegment *segs, const SegRun &a, const SegRun &b, uint32_t R, uint32_t gsz, uint32_t osz)
+{
+    const FusedSegment &f = segs[a.seg], &g = segs[b.seg];
+    const uint64_t end = a.first + a.n;
+    if (f.master + end != g.master + b.first || f.m + end != g.m + b.first || f.v + end != g.v + b.first) return false;
+    if (!f.out != !g.out || out_at(f, end, osz) != out_at(g, b.first, osz)) return false;
+    for (uint32_t r = 0; r < R; ++r)
+        if (static_cast<const char *>(f.grads[r]) + end * gsz != static_cast<const char *>(g.grads[r]) + b.first * gsz) return false;
+    return true;
+}
+
+// Distance of run b from run a in quads where it is the same in every stream (the output has its own).
+static bool distance(const FusedSegment *segs, const SegRun &a, const SegRun &b, uint32_t R, uint32_t gsz, uint32_t osz,
+                     int32_t *quads, int32_t *out_quads)
+{
+    const FusedSegment &f = segs[a.seg], &g = segs[b.seg];
+    auto bytes = [](const void *x, uint64_t xo, const void *y, uint64_t yo) {
+        return (int64_t)((reinterpret_cast<uint64_t>(y) + yo) - (reinterpret_cast<uint64_t>(x) + xo));
+    };
+    const int64_t d = bytes(f.master, a.first * 4, g.master, b.first * 4);     // a multiple of 16
+    if (bytes(f.m, a.first * 4, g.m, b.first * 4) != d || bytes(f.v, a.first * 4, g.v, b.first * 4) != d) return false;
+    for (uint32_t r = 0; r < R; ++r)
+        if (bytes(f.grads[r], a.first * gsz, g.grads[r], b.first * gsz) != d / 4 * (int64_t)gsz) return false;
+    int64_t o = 0;
+    if (f.out) o = bytes(f.out, a.first * osz, g.out, b.first * osz) / (4 * (int64_t)osz);   // both multiples of 16 bytes
+    const int64_t q = d / 16;
+    if (q != (int32_t)q || o != (int32_t)o) return false;
+    *quads = (int32_t)q;
+    *out_quads = (int32_t)o;
+    return true;
+}
+
+// The call as runs: a bucket's slice has one multiplier (most do) or needs the tables, and slices that follow
+// each other in every stream and share the multiplier become one run.
+static void list_runs(const hzp_plan_t *plan, const FusedSegment *segs, size_t nseg, uint32_t R, uint32_t gsz, uint32_t osz,
+                      std::vector<SegRun> &runs)
+{
+    for (size_t s = 0; s < nseg; ++s) {
+        const FusedSegment &f = segs[s];
+        const uint64_t *off = plan->run_off.data() + f.first_run;
+        const uint32_t lo = (uint32_t)(std::upper_bound(off, off + f.n_runs, f.shard_begin) - off) - 1;
+        const uint32_t hi = (uint32_t)(std::upper_bound(off + lo, off + f.n_runs, f.shard_begin + f.n - 1) - off);
+        SegRun r{(uint32_t)s, 0, f.n, plan->run_wd[f.first_run + lo], f.first_run + lo, hi - lo > 1 ? hi - lo : 0};
+        if (!runs.empty() && !r.runs && !runs.back().runs && std::memcmp(&runs.back().wd, &r.wd, sizeof r.wd) == 0 &&
+            follows(segs, runs.back(), r, R, gsz, osz))
+            runs.back().n += r.n;
+        else
+            runs.push_back(r);
     }
+}
+
+template <bool PLAIN>
+static void start_kernel(bool g32, bool o32, uint32_t R, const FusedArgs &a, dim3 grid, hipStream_t stream)
+{
+    static constexpr auto kernels16 = fused_kernels<false, false, PLAIN>(std::make_index_sequence<HZP_MAX_REPLICAS>());
+    static constexpr auto kernels32 = fused_kernels<true, true, PLAIN>(std::make_index_sequence<HZP_MAX_REPLICAS>());
+    void (*const kernel)(FusedArgs) = !g32 ? kernels16[R - 1] : o32 ? kernels32[R - 1] : fused_adamw_kernel<1, true, false, PLAIN>;
+    // 10 wavefronts per CU with bf16 contributions (R = 8, 105 M elements: 8 / 9 / 10 / 11 / 12 / 14 / 16 6.67 / 6.73 / 6.73 /
+    // 6.72 / 6.70 / 6.61 / 6.56 TB/s), 8 with fp32 ones, whose chunks hold half as much again (R = 1, 107 M: 7 / 8 / 9 / 10 / 12
+    // 6.56 / 6.74 / 6.64 / 6.63 / 6.55).  Where the segment is searched for or decay looked up a wavefront lives longer:
+    // R = 8 with looked-up decay 10 / 11 / 12 / 13 / 14 6.31 / 6.50 / 6.54 / 6.48 / 6.37.
+    hipLaunchKernelGGL(kernel, grid, dim3(kWave), lds_for(g32 ? (PLAIN ? 8 : 10) : (PLAIN ? 10 : 12)), stream, a);
+}
+
+hzp_status_t launch_fused(const hzp_plan_t *plan, bool g32, bool o32, uint32_t R, const FusedSegment *segs, size_t nseg,
+                          const AdamScalars *scalars, const AdamScalars *scalars_dev, hipStream_t stream)
+{
     const uint32_t per_seg = R + 4;
-    const size_t cap = std::min<size_t>(Seg::kMaxSeg, Seg::kPtrCap / per_seg);
     const uint32_t gsz = g32 ? 4u : 2u, osz = o32 ? 4u : 2u;
     constexpr uint64_t kGroupElems = 4ull * kGroupQuads;
-    // Cut the segments into runs of at most kMaxGroupsPerLaunch groups (a shard longer than that is
-    // covered by several launches), then fill launches with whole runs.
     std::vector<SegRun> runs;
     try {
-        for (size_t s = 0; s < nseg; ++s)
-            for (uint64_t first = 0; first < segs[s].n; first += kMaxGroupsPerLaunch * kGroupElems)
-                runs.push_back(SegRun{(uint32_t)s, first, std::min<uint64_t>(segs[s].n - first, kMaxGroupsPerLaunch * kGroupElems)});
+        list_runs(plan, segs, nseg, R, gsz, osz, runs);
     } catch (const std::bad_alloc &) {
         return fail(HZP_ERR_NOMEM, "hzp_adamw_shard: out of host memory");
     }
-    size_t r0 = 0;
-    while (r0 < runs.size()) {
-        Seg a{};
-        WdLookup w{};
-        uint32_t blocks = 0;
+    bool lookup = false;
+    uint64_t groups = 0;
+    for (const SegRun &r : runs) {
+        lookup = lookup || r.runs;
+        groups += (r.n + kGroupElems - 1) / kGroupElems;
+    }
+    FusedArgs a{};
+    if (lookup) {
+        const DeviceTables *tab = nullptr;
+        hzp_status_t st = device_tables(plan, &tab);
+        if (st != HZP_OK) return st;
+        a.run_off = tab->run_off;
+        a.run_wd = tab->run_wd;
+    }
+    a.lookup = lookup;
+    if (scalars) a.scalars = *scalars;
+    a.scalars_dev = scalars_dev;
+    // Launches of about equal length; a run is cut where a launch is full.
+    const uint64_t launches = (groups + kMaxGroupsPerLaunch - 1) / kMaxGroupsPerLaunch;
+    const uint64_t most = (groups + launches - 1) / launches;
+    size_t next = 0;            // first run not yet launched, and how much of it is done
+    uint64_t done = 0;
+    const uint32_t rec_own = kPlainRecord + a.lookup, rec_shared = rec_own + 1;
+    const size_t cap_own = kTableWords / (per_seg + rec_own), cap_shared = (kTableWords - per_seg) / rec_shared;
+    const bool may_share = runs.size() > cap_own && groups * cap_own / runs.size() < kShareGroups;
+    SegRun part[kTableWords / 3];
+    int32_t dist[kTableWords / 3], out_dist[kTableWords / 3];
+    while (next < runs.size()) {
         uint32_t cnt = 0;
-        for (; r0 + cnt < runs.size() && cnt < cap; ++cnt) {
-            const SegRun &run = runs[r0 + cnt];
-            const FusedSegment &f = segs[run.seg];
-            const uint32_t nquad = (uint32_t)(run.n / 4);
-            const uint32_t nb = (nquad + kGroupQuads - 1) / kGroupQuads;
-            if (cnt > 0 && blocks + nb > kMaxGroupsPerLaunch) break;    // start another launch
-            blocks += nb;
-            a.blk_end[cnt] = blocks;
-            a.nquad[cnt] = nquad;
-            const void **sp = a.ptr + (size_t)cnt * per_seg;
-            for (uint32_t r = 0; r < R; ++r) sp[r] = static_cast<const char *>(f.grads[r]) + run.first * gsz;
-            sp[R] = f.master + run.first;
-            sp[R + 1] = f.m + run.first;
-            sp[R + 2] = f.v + run.first;
-            sp[R + 3] = f.out ? static_cast<char *>(f.out) + run.first * osz : nullptr;
-            if constexpr (std::is_same<Seg, SegTableNarrow>::value) {
-                w.first_slot[cnt] = f.first_slot;
-                w.n_tensors[cnt] = f.n_tensors;
-                w.shard_begin[cnt] = f.shard_begin + run.first;
+        uint64_t total = 0;
+        bool same = may_share;
+        size_t at = next;
+        uint64_t at_done = done;
+        while (at < runs.size() && total < most && cnt < (same ? cap_shared : cap_own)) {
+            SegRun r = runs[at];
+            r.first += at_done;
+            r.n = std::min(r.n - at_done, (most - total) * kGroupElems);
+            part[cnt] = r;
+            if (same && !distance(segs, part[0], r, R, gsz, osz, &dist[cnt], &out_dist[cnt])) {
+                if (cnt >= cap_own) break;      // the ones before it share their pointers: launch those
+                same = false;
+            }
+            ++cnt;
+            total += (r.n + kGroupElems - 1) / kGroupElems;
+            at_done += r.n;
+            if (at_done == runs[at].n) {
+                ++at;
+                at_done = 0;
             }
         }
-        a.nseg = cnt;
-        a.R = R;
+        const bool shared = same && cnt > cap_own;
+        a.segments = cnt;
+        a.stride = shared ? rec_shared : per_seg + rec_own;
+        a.ptr_stride = shared ? 0 : a.stride;
+        a.dist = shared ? rec_shared - 1 : 0;
+        uint32_t blocks = 0, longest = 0;
+        for (uint32_t c = 0; c < cnt; ++c) {
+            const SegRun &r = part[c];
+            const FusedSegment &f = segs[r.seg];
+            if (c == 0 || !shared) {
+                uint64_t *w = a.word + (size_t)c * a.ptr_stride;
+                w[0] = reinterpret_cast<uint64_t>(f.master + r.first);
+                w[1] = reinterpret_cast<uint64_t>(f.m + r.first);
+                w[2] = reinterpret_cast<uint64_t>(f.v + r.first);
+                w[3] = reinterpret_cast<uint64_t>(out_at(f, r.first, osz));
+                for (uint32_t i = 0; i < R; ++i) w[4 + i] = reinterpret_cast<uint64_t>(f.grads[i]) + r.first * gsz;
+            }
+            const uint32_t nb = (uint32_t)((r.n + kGroupElems - 1) / kGroupElems);
+            blocks += nb;
+            longest = std::max(longest, nb);
+            uint64_t *w = a.word + per_seg + (size_t)c * a.stride;
+            w[0] = blocks | (r.n / 4) << 32;
+            if (a.lookup) {
+                w[1] = r.run0 | (uint64_t)std::max(r.runs, 1u) << 32;
+                w[2] = f.shard_begin + r.first;
+            } else {
+                uint32_t bits;
+                std::memcpy(&bits, &r.wd, sizeof bits);
+                w[1] = bits;
+            }
+            if (shared) w[a.dist] = (uint32_t)dist[c] | (uint64_t)(uint32_t)out_dist[c] << 32;
+        }
         // Two-dimensional grid unless the segments differ so much in length that more than an
         // eighth of its workgroups would be surplus.
-        uint32_t max_groups = 0;
-        for (uint32_t c = 0; c < cnt; ++c) {
-            const uint32_t groups = a.blk_end[c] - (c ? a.blk_end[c - 1] : 0u);
-            max_groups = std::max(max_groups, groups);
-        }
+        a.grid2d = (uint64_t)longest * cnt - blocks <= blocks / 8;
         dim3 grid(blocks);
-        const bool two_d = (uint64_t)max_groups * cnt - blocks <= blocks / 8 && cnt <= 65535;
-        if (two_d) {
-            for (uint32_t c = cnt; c-- > 0;) a.blk_end[c] -= c ? a.blk_end[c - 1] : 0u;
-            a.grid2d = 1;
-            grid = dim3(max_groups, cnt);
+        if (a.grid2d) {
+            uint64_t *w = a.word + per_seg;
+            for (uint32_t c = cnt; c-- > 1;) w[(size_t)c * a.stride] -= (uint32_t)w[(size_t)(c - 1) * a.stride];
+            grid = dim3(longest, cnt);
         }
-        if (blocks > 0) {
-            if constexpr (std::is_same<Seg, SegTableNarrow>::value) {
-                w.tensor_off = tab->tensor_off;
-                w.tensor_wd = tab->tensor_wd;
-                launch_fused_variant(g32, o32, R, a, h, w, grid, stream);
-            } else {
-                launch_fused_variant(g32, o32, R, a, h, NoLookup{}, grid, stream);
+        if (a.grid2d && !shared && !a.lookup)
+            start_kernel<true>(g32, o32, R, a, grid, stream);
+        else
+            start_kernel<false>(g32, o32, R, a, grid, stream);
+        hzp_status_t st = check_launch("hzp_adamw_shard");
+        if (st != HZP_OK) return st;
+        for (uint32_t c = 0; c < cnt; ++c) {
+            done += part[c].n;
+            if (done == runs[next].n) {
+                ++next;
+                done = 0;
             }
-            hzp_status_t st = check_launch("hzp_adamw_shard");
-            if (st != HZP_OK) return st;
         }
-        r0 += cnt;
     }
     return HZP_OK;
-}
-
-hzp_status_t launch_fused(const hzp_plan_t *plan, bool g32, bool o32, uint32_t R, const FusedSegment *segs,
-                          size_t nseg, const AdamScalars &h, hipStream_t stream)
-{
-    if (plan->uniform_wd)
-        return launch_fused_table<SegTableWide>(plan, false, g32, o32, R, segs, nseg, h, stream);
-    return launch_fused_table<SegTableNarrow>(plan, true, g32, o32, R, segs, nseg, h, stream);
-}
-
-hzp_status_t launch_fused_dev(const hzp_plan_t *plan, bool g32, bool o32, uint32_t R, const FusedSegment *segs,
-                              size_t nseg, const AdamScalars *scalars_dev, hipStream_t stream)
-{
-    const ScalarsInMemory h{scalars_dev};
-    if (plan->uniform_wd)
-        return launch_fused_table<SegTableWide>(plan, false, g32, o32, R, segs, nseg, h, stream);
-    return launch_fused_table<SegTableNarrow>(plan, true, g32, o32, R, segs, nseg, h, stream);
 }
 
 hzp_status_t launch_concat(const void *const *srcs, uint32_t n_shards, uint64_t bytes_per_shard, void *dst,
@@ -1015,22 +1099,22 @@ hzp_status_t device_tables(const hzp_plan_t *plan, const DeviceTables **out)
     t.device = dev;
     std::vector<Piece> all;
     for (const BucketRec &b : plan->buckets) all.insert(all.end(), b.pieces.begin(), b.pieces.end());
-    const size_t nt = plan->slot_off.size();
+    const size_t nr = plan->run_off.size();
     auto upload = [&](void **dptr, const void *src, size_t bytes) -> hipError_t {
         hipError_t err = hipMalloc(dptr, bytes ? bytes : 16);
         if (err != hipSuccess) return err;
         return bytes ? hipMemcpy(*dptr, src, bytes, hipMemcpyHostToDevice) : hipSuccess;
     };
-    e = upload((void **)&t.tensor_off, plan->slot_off.data(), nt * sizeof(uint64_t));
-    if (e == hipSuccess) e = upload((void **)&t.tensor_wd, plan->slot_wd.data(), nt * sizeof(float));
+    e = upload((void **)&t.run_off, plan->run_off.data(), nr * sizeof(uint64_t));
+    if (e == hipSuccess) e = upload((void **)&t.run_wd, plan->run_wd.data(), nr * sizeof(float));
     if (e == hipSuccess) e = upload((void **)&t.pieces, all.data(), all.size() * sizeof(Piece));
     std::vector<uint32_t> chunk_begin(all.size());
     for (size_t i = 0; i < all.size(); ++i) chunk_begin[i] = all[i].chunk_begin;
     if (e == hipSuccess) e = upload((void **)&t.piece_chunk, chunk_begin.data(), chunk_begin.size() * sizeof(uint32_t));
     if (e != hipSuccess) {
         (void)hipFree(t.piece_chunk);
-        (void)hipFree(t.tensor_off);
-        (void)hipFree(t.tensor_wd);
+        (void)hipFree(t.run_off);
+        (void)hipFree(t.run_wd);
         (void)hipFree(t.pieces);
         return fail(e == hipErrorOutOfMemory ? HZP_ERR_NOMEM : HZP_ERR_HIP, "device tables: %s",
                     hipGetErrorString(e));
@@ -1067,8 +1151,8 @@ void free_device_tables(hzp_plan_t *plan)
     for (DeviceTables &t : plan->dev) {
         int cur = -1;
         if (hipGetDevice(&cur) == hipSuccess && cur != t.device) (void)hipSetDevice(t.device);
-        (void)hipFree(t.tensor_off);
-        (void)hipFree(t.tensor_wd);
+        (void)hipFree(t.run_off);
+        (void)hipFree(t.run_wd);
         (void)hipFree(t.pieces);
         (void)hipFree(t.piece_chunk);
         if (cur >= 0 && cur != t.device) (void)hipSetDevice(cur);

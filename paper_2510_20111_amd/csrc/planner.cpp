@@ -10,6 +10,7 @@
 // (Figure 1, Section 3.1).
 #include <cstdarg>
 #include <cstdio>
+#include <cstring>
 #include <new>
 
 #include "hzp_internal.hpp"
@@ -140,19 +141,17 @@ extern "C" hzp_status_t hzp_plan(const hzp_plan_desc_t *d, hzp_plan_t **out)
         p->z1 = d->z1;
         p->K = d->z1 % d->z3 == 0 ? d->z1 / d->z3 : 0;
         p->world = (uint32_t)world;
-        p->uniform_wd = true;
         p->tensors.resize(n_tensors);
         p->bucket_of.assign((size_t)d->n_layers * 2, -1);
         const uint64_t quantum = (uint64_t)A * world;     // every level's shard is a multiple of A
         uint64_t base = 0;
-        uint32_t tid0 = 0, slot = 0, piece_slot = 0;
+        uint32_t tid0 = 0, piece_slot = 0;
         for (uint32_t l = 0; l < d->n_layers; ++l) {
             const uint32_t cnt = d->tensors_per_layer[l];
             for (uint32_t cls = 0; cls < 2; ++cls) {
                 BucketRec b{};
                 b.layer = l;
                 b.cls = cls;
-                b.first_slot = slot;
                 uint64_t off = 0, payload_end = 0;
                 for (uint32_t t = tid0; t < tid0 + cnt; ++t) {
                     const uint32_t c = d->tensor_class ? d->tensor_class[t] : 0u;
@@ -165,7 +164,6 @@ extern "C" hzp_status_t hzp_plan(const hzp_plan_desc_t *d, hzp_plan_t **out)
                     r.offset = off;
                     r.numel = d->tensor_numel[t];
                     r.wd_mult = d->tensor_wd_mult ? d->tensor_wd_mult[t] : 1.0f;
-                    if (r.wd_mult != 1.0f) p->uniform_wd = false;
                     if (__builtin_add_overflow(off, r.numel, &payload_end) ||
                         !round_up(payload_end, A, &off)) {
                         delete p;
@@ -190,11 +188,15 @@ extern "C" hzp_status_t hzp_plan(const hzp_plan_desc_t *d, hzp_plan_t **out)
                     return fail(HZP_ERR_UNSUPPORTED, "hzp_plan: layer %u is too large to unpack", l);
                 }
                 piece_slot += (uint32_t)b.pieces.size();
+                b.first_run = (uint32_t)p->run_off.size();
                 for (uint32_t t : b.tensor_ids) {
-                    p->slot_off.push_back(p->tensors[t].offset);
-                    p->slot_wd.push_back(p->tensors[t].wd_mult);
+                    const TensorRec &r = p->tensors[t];
+                    if (p->run_off.size() > b.first_run && std::memcmp(&p->run_wd.back(), &r.wd_mult, sizeof r.wd_mult) == 0)
+                        continue;
+                    p->run_off.push_back(r.offset);
+                    p->run_wd.push_back(r.wd_mult);
                 }
-                slot += b.n_tensors;
+                b.n_runs = (uint32_t)p->run_off.size() - b.first_run;
                 p->bucket_of[(size_t)l * 2 + cls] = (int32_t)p->buckets.size();
                 p->buckets.push_back(std::move(b));
             }

@@ -1,0 +1,134 @@
+"""The forms one update or reduction can be launched in, against the CPU oracle: segments merged, listed with pointers
+of their own or sharing one set, found by a 2-D grid or by search, decay constant or looked up; every number of
+contributions; sizes at the edges of a group of 256 elements and of a block of 16 groups."""
+import numpy as np
+import pytest
+import torch
+
+import hzp_inputs
+import paper_2510_20111_amd as hzp
+from oracle import numeric as on
+from oracle import planner as op
+
+from gpu_util import DEV, assert_cast_of, assert_close_f32, oracle_plan, to_dev, to_host, wd_mult_array
+
+pytestmark = pytest.mark.gpu
+
+HP = hzp_inputs.ADAMW
+EDGES = [8, 248, 256, 264, 15 * 256 + 8, 16 * 256, 16 * 256 + 8, 33 * 256 - 8]
+
+
+def carve(sizes, dtype, place):
+    """Buffers of the given lengths: each alone ("own"), back to back in one allocation ("packed"), or at equal
+    distances in one allocation, in ascending ("spread") or descending ("down") order of address."""
+    if place == "own":
+        return [torch.zeros(n, dtype=dtype, device=DEV) for n in sizes]
+    if place == "packed":
+        return list(torch.split(torch.zeros(sum(sizes), dtype=dtype, device=DEV), sizes))
+    step = max(sizes) + 264
+    whole = torch.zeros(step * len(sizes), dtype=dtype, device=DEV)
+    at = [k * step for k in range(len(sizes))]
+    return [whole[a:a + n] for a, n in zip(at if place == "spread" else at[::-1], sizes)]
+
+
+def update_against_oracle(desc, align, z1, R, rank, cls, place, out_place=None, split=False, seed=3):
+    """One update of class `cls` over all layers (or call by call) from random states, compared with the oracle."""
+    oplan = oracle_plan(desc, align, 1, z1)
+    plan = hzp.hzp_plan(desc["tensors_per_layer"], desc["tensor_numel"], align, 1, z1,
+                        tensor_class=desc.get("tensor_class"), tensor_wd_mult=desc.get("tensor_wd_mult"))
+    buckets = [b for b in oplan["buckets"] if b["cls"] == cls]
+    sizes = [b["S1"] for b in buckets]
+    rng = np.random.default_rng(seed)
+    g16 = cls == 0
+    grads = [[rng.standard_normal(n, dtype=np.float32) * np.float32(1e-3) for _ in range(R)] for n in sizes]
+    if g16:
+        grads = [[hzp_inputs.to_bf16_bits(g) for g in per] for per in grads]
+    p, m = ([rng.standard_normal(n, dtype=np.float32) * np.float32(s) for n in sizes] for s in (0.02, 1e-4))
+    v = [np.square(rng.standard_normal(n, dtype=np.float32)) * np.float32(1e-7) for n in sizes]
+    dev_g = [carve(sizes, torch.int16 if g16 else torch.float32, place) for _ in range(R)]
+    dev = [carve(sizes, torch.float32, place) for _ in range(3)]
+    out = carve(sizes, torch.int16 if g16 else torch.float32, out_place or place)
+    for i in range(len(sizes)):
+        for r in range(R):
+            dev_g[r][i].copy_(to_dev(grads[i][r]))
+        for d, h in zip(dev, (p, m, v)):
+            d[i].copy_(to_dev(h[i]))
+    hy = hzp.adamw_hyper(HP["lr"], HP["beta1"], HP["beta2"], HP["eps"], HP["weight_decay"], 1.0 / R, 3)
+    at = {b["layer"]: i for i, b in enumerate(buckets)}
+    flat = lambda lists, lo, hi: [lists[at[layer]] if layer in at else 0 for layer in range(lo, hi)]  # noqa: E731
+    spans = [(0, oplan["n_layers"])] if not split else [(k, k + 1) for k in sorted(at)]
+    for lo, hi in spans:
+        gl = [dev_g[r][at[layer]] if layer in at else 0 for layer in range(lo, hi) for r in range(R)]
+        hzp.hzp_adamw_shard(plan, lo, hi, cls, rank, hy, gl, R, *(flat(d, lo, hi) for d in dev), flat(out, lo, hi))
+    torch.cuda.synchronize()
+    got = [[to_host(d[i], np.float32) for i in range(len(sizes))] for d in dev]
+    for i, b in enumerate(buckets):
+        beg, n = op.shard_range(oplan, b, 1, rank)
+        wd = wd_mult_array(oplan, b, beg, n) if desc.get("tensor_wd_mult") else None
+        on.adamw(on.reduce(grads[i], scale=1.0 / R), p[i], m[i], v[i], step=3, wd_mult=wd, out_bf16=g16, **HP)
+        tag = "%s R=%d layer %d n=%d" % (place, R, b["layer"], n)
+        for key, have, want in zip("pmv", got, (p[i], m[i], v[i])):
+            assert_close_f32(have[i], want, tag + " " + key, key)
+        if g16:
+            assert_cast_of(to_host(out[i], np.uint16), got[0][i], tag + " out")
+        else:
+            assert np.array_equal(to_host(out[i], np.uint32), got[0][i].view(np.uint32)), tag + " out"
+    return got
+
+
+@pytest.mark.parametrize("R", range(1, 33))
+@pytest.mark.parametrize("cls", [0, 1])
+def test_every_number_of_contributions_at_group_edges(R, cls):
+    """Segments of unlike length in one call (found by search) and call by call (one segment each): the same bits."""
+    print("R=%d class %d" % (R, cls), flush=True)
+    desc = dict(tensors_per_layer=[1] * len(EDGES), tensor_numel=EDGES, tensor_class=[cls] * len(EDGES))
+    a = update_against_oracle(desc, 8, 1, R, 0, cls, "own")
+    b = update_against_oracle(desc, 8, 1, R, 0, cls, "own", split=True)
+    for x, y in zip(a, b):
+        assert all(np.array_equal(s.view(np.uint32), t.view(np.uint32)) for s, t in zip(x, y))
+
+
+@pytest.mark.parametrize("place,out_place", [("packed", None), ("spread", None), ("down", None), ("packed", "spread"),
+                                             ("spread", "down"), ("own", None), ("spread", "own"), ("own", "packed")])
+@pytest.mark.parametrize("R,layers,ragged", [(8, 50, False), (8, 50, True), (32, 30, True), (3, 200, True)])
+def test_many_segments_in_every_placement(place, out_place, R, layers, ragged):
+    """More buckets than one launch lists with pointers of their own (34 at R = 8, 12 at R = 32, 53 at R = 3)."""
+    print(place, out_place, R, layers, ragged, flush=True)
+    rng = np.random.default_rng(layers)
+    numel = [int(x) for x in rng.integers(1, 3000, layers)] if ragged else [1000] * layers
+    wd = [float(k % 5 == 4) for k in range(layers)] if ragged else None        # equal inside a bucket
+    desc = dict(tensors_per_layer=[1] * layers, tensor_numel=numel, tensor_wd_mult=wd)
+    update_against_oracle(desc, 8, 1, R, 0, 0, place, out_place)
+
+
+@pytest.mark.parametrize("z1,rank", [(1, 0), (3, 1)])
+@pytest.mark.parametrize("place", ["packed", "own", "spread"])
+def test_decay_looked_up_in_long_and_short_tables(z1, rank, place):
+    """Up to 400 changes of the multiplier in a bucket, several inside one group, beside buckets without any."""
+    rng = np.random.default_rng(8)
+    layers = [[8] * 400, [3000], [int(x) for x in rng.integers(1, 30, 300)], [5000, 64, 5000], [70000, 8, 8, 70000],
+              [int(x) for x in rng.integers(200, 600, 70)]] * 8
+    numel = [n for layer in layers for n in layer]
+    wd = [float(w) for w in rng.choice([0.0, 1.0, 0.5], len(numel))]
+    desc = dict(tensors_per_layer=[len(x) for x in layers], tensor_numel=numel, tensor_wd_mult=wd)
+    update_against_oracle(desc, 8, z1, 8, rank, 0, place)
+
+
+@pytest.mark.parametrize("R", range(1, 33))
+@pytest.mark.parametrize("g32", [False, True])
+def test_reduction_of_every_number_of_contributions_at_group_edges(R, g32):
+    print("reduce R=%d %s" % (R, "fp32" if g32 else "bf16"), flush=True)
+    plan = hzp.hzp_plan([1] * len(EDGES), EDGES, align=8, z3=1, z1=1)
+    rng = np.random.default_rng(R)
+    for layer, n in enumerate(EDGES):
+        g = [rng.standard_normal(n, dtype=np.float32) for _ in range(R)]
+        if not g32:
+            g = [hzp_inputs.to_bf16_bits(x) for x in g]
+        for acc in (False, True):
+            want = on.reduce(g, scale=0.3, accumulate=acc, out=np.full(n, 0.5, np.float32) if acc else None)
+            whole = torch.full((n + 64,), 0.5, device=DEV)
+            hzp.hzp_reduce_shard(plan, layer, 0, 1, 0, [to_dev(x) for x in g], 0.3, acc, whole[:n],
+                                 grad_dtype=hzp.HZP_GRAD_F32 if g32 else hzp.HZP_GRAD_BF16)
+            torch.cuda.synchronize()
+            assert np.array_equal(to_host(whole[:n], np.uint32), want.view(np.uint32)), (n, acc)
+            assert bool((whole[n:] == 0.5).all())
