@@ -23,6 +23,7 @@
 #include <array>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 #include <utility>
 #include <vector>
 
@@ -266,6 +267,14 @@ struct FusedArgs {
     uint64_t word[kTableWords];
 };
 static_assert(sizeof(FusedArgs) <= 4096, "kernel arguments");
+// The same for one segment with pointers of its own and one multiplier: a tenth of the block, and launching costs
+// 2.4-2.8 us with the smallest blocks and 2.7-4.0 us with the largest (the host writes it to device memory).
+struct FusedOneArgs {
+    const AdamScalars *scalars_dev;
+    AdamScalars scalars;
+    uint64_t word[HZP_MAX_REPLICAS + 4 + kPlainRecord];
+};
+enum FusedForm { kSearched, kPlain, kOne };
 
 // The decay runs that a group meets, found while the streams arrive: begin() narrows the search to 64
 // runs and requests their starts (lane by lane), find() requests the next ones and the first multiplier,
@@ -319,13 +328,13 @@ struct DecayRuns {
 // with bf16 contributions (R = 4 / 8 / 16, 100 M elements): 6.74 / 6.68 / 6.58 -> 6.77 / 6.78 / 6.72 TB/s;
 // quadruples lose again (6.66 / 6.73 / 6.66), and where all streams are fp32 pairs lose 1 % (6.79 -> 6.73).
 //
-// PLAIN: a 2-D grid over segments with pointers of their own and one multiplier each (a whole arena of equal decay is
-// one such segment).  Everything a wavefront needs then lies at an address that blockIdx gives and arrives in one
-// round of scalar loads.  Otherwise a uniform binary search finds the segment, three more rounds, which the few
-// resident wavefronts hide badly (105 M elements, R = 8, one segment: 6.65 TB/s at the best number of wavefronts, 6.73
-// with the one round).
-template <uint32_t R, bool G32, bool O32, bool PLAIN>
-__global__ __launch_bounds__(kWave) void fused_adamw_kernel(const FusedArgs a)
+// kPlain: a 2-D grid over segments with pointers of their own and one multiplier each; kOne: a single such segment
+// (a whole arena of equal decay is one).  Everything a wavefront needs then lies at an address that blockIdx gives and
+// arrives in one round of scalar loads.  kSearched: a uniform binary search may have to find the segment, three more
+// rounds, which the few resident wavefronts hide badly (105 M elements, R = 8, one segment: 6.65 TB/s at the best
+// number of wavefronts, 6.73 with the one round).
+template <uint32_t R, bool G32, bool O32, FusedForm FORM>
+__global__ __launch_bounds__(kWave) void fused_adamw_kernel(const std::conditional_t<FORM == kOne, FusedOneArgs, FusedArgs> a)
 {
     constexpr bool PAIRS = !G32;
     // Which segment and which group of it?
@@ -333,8 +342,10 @@ __global__ __launch_bounds__(kWave) void fused_adamw_kernel(const FusedArgs a)
     const uint64_t *ptr, *rec;
     int64_t shift = 0, out_shift = 0;           // of the segment against the pointers, in quads
     bool lookup = false;
-    if constexpr (PLAIN) {
-        ptr = a.word + blockIdx.y * (R + 4 + kPlainRecord);
+    DecayRuns runs;
+    uint64_t pos = 0;                           // of the group's first element in its bucket
+    if constexpr (FORM != kSearched) {
+        ptr = a.word + (FORM == kOne ? 0 : blockIdx.y * (R + 4 + kPlainRecord));
         rec = ptr + R + 4;
     } else {
         uint32_t segments = a.segments, stride = a.stride, ptr_stride = a.ptr_stride, dist = a.dist, grid2d = a.grid2d, look = a.lookup;
@@ -384,11 +395,13 @@ __global__ __launch_bounds__(kWave) void fused_adamw_kernel(const FusedArgs a)
     const uint32_t q0 = grp * kGroupQuads + threadIdx.x;
     const uint32_t quad = q0 < nquad ? q0 : nquad - 1;
     const uint32_t quads[1] = {quad};
-    DecayRuns runs{a.run_off, a.run_wd};
-    uint64_t pos = 0;                           // of the group's first element in its bucket
-    if (!PLAIN && lookup) {
-        pos = rec[2] + 4ull * kGroupQuads * grp;
-        runs.begin((uint32_t)decay, (uint32_t)(decay >> 32), pos);
+    if constexpr (FORM == kSearched) {
+        if (lookup) {
+            runs.off = a.run_off;
+            runs.wd = a.run_wd;
+            pos = rec[2] + 4ull * kGroupQuads * grp;
+            runs.begin((uint32_t)decay, (uint32_t)(decay >> 32), pos);
+        }
     }
     // The states are requested ahead of the contributions: they are needed last and then have the
     // contributions' time to arrive.
@@ -396,7 +409,7 @@ __global__ __launch_bounds__(kWave) void fused_adamw_kernel(const FusedArgs a)
     f32x4 m = ld_stream<f32x4>(M, quad);
     f32x4 v = ld_stream<f32x4>(V, quad);
     __builtin_amdgcn_sched_barrier(0);
-    if (!PLAIN && lookup) runs.find(pos);
+    if (FORM == kSearched && lookup) runs.find(pos);
     if (scalars_dev) {
         typedef const __attribute__((address_space(4))) float const_float;      // scalar loads
         const_float *c = reinterpret_cast<const_float *>(scalars_dev);
@@ -405,7 +418,7 @@ __global__ __launch_bounds__(kWave) void fused_adamw_kernel(const FusedArgs a)
     float g[1][4];
     sum_contributions<R, CHUNK, G32>(at, ptr + 4, shift * (G32 ? 16 : 8), quads, g);
 
-    const float wd = h.weight_decay * (!PLAIN && lookup ? runs.get(pos) : __uint_as_float((uint32_t)decay));
+    const float wd = h.weight_decay * (FORM == kSearched && lookup ? runs.get(pos) : __uint_as_float((uint32_t)decay));
 
     // The arithmetic is hardly hidden behind other wavefronts (few are resident by design), so it is
     // kept short: hardware square root and reciprocal (1 ulp each) instead of the correctly
@@ -439,71 +452,94 @@ __global__ __launch_bounds__(kWave) void fused_adamw_kernel(const FusedArgs a)
 }
 
 // ---------------------------------------------------------------------------------------
-// Gather: concatenation of equal shards (16-byte vectors; everything is aligned).
-// grid = (wavefront tiles per shard, number of shards).
+// Gather: copies of whole pieces (16-byte vectors; everything is aligned).
+//
+// One wavefront per workgroup, one 16-byte vector per lane: of the shapes measured (1-8 vectors per lane, 64- and
+// 256-thread workgroups, with and without an occupancy cap, neighbouring tiles paired per XCD or not) this one copies
+// fastest on MI355X (6.8 TB/s on the 8 x 51 MB -> 405 MB layer gather); a plain copy keeps few bytes in flight per
+// wavefront and wants every wave slot filled.  A wavefront's piece is given by blockIdx and everything about it
+// arrives in one round of scalar loads.
 // ---------------------------------------------------------------------------------------
-struct ConcatArgs {
-    const void *src[HZP_MAX_GROUP];     // the pieces that are copied (one that already lies in place is left out)
-    uint8_t slot[HZP_MAX_GROUP];        // position of each of them in the output
-    u32x4 *dst;
-    uint32_t vec_per_shard;
-};
-// One wavefront per workgroup, one 16-byte vector per lane: of the shapes measured (1-8 vectors
-// per lane, 64- and 256-thread workgroups, with and without an occupancy cap) this one copies
-// fastest on MI355X (6.8 TB/s on the 8 x 51 MB -> 405 MB layer gather); a plain copy keeps few
-// bytes in flight per wavefront and wants every wave slot filled.
-__global__ __launch_bounds__(kWave) void concat_kernel(const ConcatArgs a)
+__device__ __forceinline__ void copy_tile(uint32_t tile, uint64_t src, uint64_t dst, uint32_t nvec)
 {
-    const uint32_t s = blockIdx.y;
-    const uint32_t vec = blockIdx.x * kWave + threadIdx.x;
-    if (vec >= a.vec_per_shard) return;
-    const u32x4 val = ld_stream(reinterpret_cast<const u32x4 *>(a.src[s]) + vec);
-    u32x4 *dst = a.dst + (size_t)a.slot[s] * a.vec_per_shard + vec;
-    st_writethrough(dst, val);
+    typedef const __attribute__((address_space(1))) u32x4 *vectors;
+    const uint32_t vec = tile * kWave + threadIdx.x;
+    if (vec >= nvec) return;
+    const u32x4 val = __builtin_nontemporal_load((vectors)src + vec);
+    st_writethrough(reinterpret_cast<u32x4 *>(dst) + vec, val);
 }
 
-// The same copy for the buckets of many layers in one launch (the post-step gather runs for all
-// layers at once; 34 launches of 16 us each leave the memory system idle between them).
-// grid = (tiles of the longest piece, pieces to copy of all layers); a piece that already lies in
-// place is left out of the list.  Everything a workgroup needs is indexed by its piece alone (one
-// round of scalar loads before the first vector load).
-constexpr int kLayersPieceCap = 192;
-struct ConcatLayersArgs {
-    const void *src[kLayersPieceCap];
-    u32x4 *dst[kLayersPieceCap];            // where the piece goes
-    uint32_t nvec[kLayersPieceCap];         // its length in 16-byte vectors
+// A list of pieces, of one bucket or of many layers (the post-step gather runs for all layers at once; 34 launches of
+// 16 us each leave the memory system idle between them).  grid = (tiles of the longest piece, pieces); a piece that
+// already lies in place is left out of the list.
+template <int PIECES>
+struct CopyListArgs {
+    static constexpr int kPieces = PIECES;
+    uint64_t src[PIECES], dst[PIECES];
+    uint32_t nvec[PIECES];                  // length in 16-byte vectors
 };
-static_assert(sizeof(ConcatLayersArgs) <= 4096, "kernel arguments");
-__global__ __launch_bounds__(kWave) void concat_layers_kernel(const ConcatLayersArgs a)
+typedef CopyListArgs<8> CopyFewArgs;
+typedef CopyListArgs<192> CopyManyArgs;
+static_assert(sizeof(CopyManyArgs) <= 4096, "kernel arguments");
+template <class Args>
+__global__ __launch_bounds__(kWave) void copy_list_kernel(const Args a)
 {
-    const uint32_t s = blockIdx.y;
-    const uint32_t vec = blockIdx.x * kWave + threadIdx.x;
-    if (vec >= a.nvec[s]) return;
-    const u32x4 val = ld_stream(reinterpret_cast<const u32x4 *>(a.src[s]) + vec);
-    st_writethrough(a.dst[s] + vec, val);
+    uint64_t src = a.src[blockIdx.y], dst = a.dst[blockIdx.y];
+    uint32_t nvec = a.nvec[blockIdx.y];
+    pin(src, dst, nvec);
+    copy_tile(blockIdx.x, src, dst, nvec);
+}
+
+// Many layers whose pieces lie at the same distances from the first layer's in every source (the layers of an arena, or
+// of one buffer per source): one pointer per source and a record per layer, so that a launch covers 204 layers of up to 64
+// pieces instead of 192 pieces.  grid = (tiles of the longest piece, sources, layers).
+constexpr int kSharedLayers = 204;
+struct CopySharedArgs {
+    uint64_t src[HZP_MAX_GROUP];            // the first layer's piece in each source
+    uint32_t slot[HZP_MAX_GROUP];           // its position in the layer's output
+    struct Layer {
+        uint64_t dst;
+        int32_t dist;                       // of its pieces from the first layer's, in 16-byte vectors
+        uint32_t nvec;
+    } layer[kSharedLayers];
+};
+static_assert(sizeof(CopySharedArgs) <= 4096, "kernel arguments");
+__global__ __launch_bounds__(kWave) void copy_shared_kernel(const CopySharedArgs a)
+{
+    uint64_t src = a.src[blockIdx.y], dst = a.layer[blockIdx.z].dst;
+    uint32_t slot = a.slot[blockIdx.y], nvec = a.layer[blockIdx.z].nvec;
+    int32_t dist = a.layer[blockIdx.z].dist;
+    pin(src, dst, slot, nvec, dist);
+    copy_tile(blockIdx.x, src + (int64_t)dist * 16, dst + (uint64_t)slot * nvec * 16, nvec);
 }
 
 // The same copy for pieces of different lengths (a ZeRO-3 shard rebuilt from whole and partial
 // ZeRO-1 shards when the group sizes do not nest).  One-dimensional grid over the 64-vector tiles
-// of all pieces; a workgroup finds its piece by scanning the tile prefix (at most HZP_MAX_GROUP
-// uniform compares), so no workgroup is launched for nothing.
+// of all pieces, so no workgroup is launched for nothing; a workgroup counts the pieces that end at or before
+// its tile, eight to a scalar load (unused entries are never reached).
 struct ConcatRangesArgs {
+    uint32_t tile_end[HZP_MAX_GROUP];       // running count of tiles up to and including the piece
     const void *src[HZP_MAX_GROUP];         // first vector to read of each piece
     uint32_t dst_vec[HZP_MAX_GROUP];        // where it goes, in 16-byte vectors from dst
     uint32_t nvec[HZP_MAX_GROUP];
-    uint32_t tile_end[HZP_MAX_GROUP];       // running count of tiles up to and including the piece
     u32x4 *dst;
     uint32_t n;
 };
 __global__ __launch_bounds__(kWave) void concat_ranges_kernel(const ConcatRangesArgs a)
 {
-    uint32_t s = 0;
-    while (s + 1 < a.n && blockIdx.x >= a.tile_end[s]) ++s;
-    const uint32_t tile = blockIdx.x - (s ? a.tile_end[s - 1] : 0u);
-    const uint32_t vec = tile * kWave + threadIdx.x;
-    if (vec >= a.nvec[s]) return;
-    const u32x4 val = ld_stream(reinterpret_cast<const u32x4 *>(a.src[s]) + vec);
-    st_writethrough(a.dst + (size_t)a.dst_vec[s] + vec, val);
+    uint32_t s = 0, first = 0;              // the workgroup's piece and its first tile
+    for (uint32_t i = 0; i < a.n; i += 8) {
+#pragma unroll
+        for (uint32_t k = 0; k < 8; ++k)
+            if (blockIdx.x >= a.tile_end[i + k]) {
+                s = i + k + 1;
+                first = a.tile_end[i + k];
+            }
+    }
+    uint64_t src = reinterpret_cast<uint64_t>(a.src[s]), dst = reinterpret_cast<uint64_t>(a.dst);
+    uint32_t nvec = a.nvec[s], dst_vec = a.dst_vec[s];
+    pin(src, dst, nvec, dst_vec);
+    copy_tile(blockIdx.x - first, src, dst + (uint64_t)dst_vec * 16, nvec);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -517,18 +553,25 @@ __global__ __launch_bounds__(kWave) void concat_ranges_kernel(const ConcatRanges
 // then read unaligned), single elements.
 // ---------------------------------------------------------------------------------------
 constexpr int kUnpackTensorCap = 400;
+// (the argument block in three sizes: launching with the smallest is 0.3-1 us cheaper than with the largest)
+template <int SHARDS, int TENSORS>
 struct UnpackArgs {
-    const void *shard[HZP_MAX_GROUP];
-    void *tensor[kUnpackTensorCap];     // tensor[t - tensor0]
+    static constexpr int kShards = SHARDS, kTensors = TENSORS;
     const Piece *pieces;                // device table of the bucket, pieces [0, n_pieces)
     const uint32_t *piece_chunk;        // device: chunk_begin of the same pieces, densely packed
     uint32_t n_pieces;
     uint32_t chunk0, chunk_end;         // chunks handled by this launch
     uint32_t tensor0;
+    const void *shard[SHARDS];
+    void *tensor[TENSORS];              // tensor[t - tensor0]
 };
+typedef UnpackArgs<8, 4> UnpackFewArgs;
+typedef UnpackArgs<16, 64> UnpackSomeArgs;
+typedef UnpackArgs<HZP_MAX_GROUP, kUnpackTensorCap> UnpackManyArgs;
+static_assert(sizeof(UnpackManyArgs) <= 4096, "kernel arguments");
 
-template <int ES>   // element size in bytes: 2 or 4
-__global__ __launch_bounds__(kWave) void unpack_kernel(const UnpackArgs a)
+template <int ES, class Args>   // element size in bytes: 2 or 4
+__global__ __launch_bounds__(kWave) void unpack_kernel(const Args a)
 {
     constexpr uint32_t VE = 16 / ES;    // elements per vector
     typedef typename std::conditional<ES == 2, uint16_t, uint32_t>::type elem_t;
@@ -598,10 +641,10 @@ static constexpr std::array<void (*)(ReduceArgs), sizeof...(I)> reduce_kernels(s
 {
     return {reduce_kernel<I + 1, G32, ACC>...};
 }
-template <bool G32, bool O32, bool PLAIN, size_t... I>
-static constexpr std::array<void (*)(FusedArgs), sizeof...(I)> fused_kernels(std::index_sequence<I...>)
+template <bool G32, bool O32, FusedForm FORM, class Args, size_t... I>
+static constexpr std::array<void (*)(Args), sizeof...(I)> fused_kernels(std::index_sequence<I...>)
 {
-    return {fused_adamw_kernel<I + 1, G32, O32, PLAIN>...};
+    return {fused_adamw_kernel<I + 1, G32, O32, FORM>...};
 }
 
 // Wavefronts per CU for the reduction: what keeps about 48 KiB in flight per CU where the contributions fit one chunk,
@@ -720,17 +763,17 @@ static void list_runs(const hzp_plan_t *plan, const FusedSegment *segs, size_t n
     }
 }
 
-template <bool PLAIN>
-static void start_kernel(bool g32, bool o32, uint32_t R, const FusedArgs &a, dim3 grid, hipStream_t stream)
+template <FusedForm FORM, class Args>
+static void start_kernel(bool g32, bool o32, uint32_t R, const Args &a, dim3 grid, hipStream_t stream)
 {
-    static constexpr auto kernels16 = fused_kernels<false, false, PLAIN>(std::make_index_sequence<HZP_MAX_REPLICAS>());
-    static constexpr auto kernels32 = fused_kernels<true, true, PLAIN>(std::make_index_sequence<HZP_MAX_REPLICAS>());
-    void (*const kernel)(FusedArgs) = !g32 ? kernels16[R - 1] : o32 ? kernels32[R - 1] : fused_adamw_kernel<1, true, false, PLAIN>;
+    static constexpr auto kernels16 = fused_kernels<false, false, FORM, Args>(std::make_index_sequence<HZP_MAX_REPLICAS>());
+    static constexpr auto kernels32 = fused_kernels<true, true, FORM, Args>(std::make_index_sequence<HZP_MAX_REPLICAS>());
+    void (*const kernel)(Args) = !g32 ? kernels16[R - 1] : o32 ? kernels32[R - 1] : fused_adamw_kernel<1, true, false, FORM>;
     // 10 wavefronts per CU with bf16 contributions (R = 8, 105 M elements: 8 / 9 / 10 / 11 / 12 / 14 / 16 6.67 / 6.73 / 6.73 /
     // 6.72 / 6.70 / 6.61 / 6.56 TB/s), 8 with fp32 ones, whose chunks hold half as much again (R = 1, 107 M: 7 / 8 / 9 / 10 / 12
     // 6.56 / 6.74 / 6.64 / 6.63 / 6.55).  Where the segment is searched for or decay looked up a wavefront lives longer:
     // R = 8 with looked-up decay 10 / 11 / 12 / 13 / 14 6.31 / 6.50 / 6.54 / 6.48 / 6.37.
-    hipLaunchKernelGGL(kernel, grid, dim3(kWave), lds_for(g32 ? (PLAIN ? 8 : 10) : (PLAIN ? 10 : 12)), stream, a);
+    hipLaunchKernelGGL(kernel, grid, dim3(kWave), lds_for(FORM == kSearched ? (g32 ? 10 : 12) : (g32 ? 8 : 10)), stream, a);
 }
 
 hzp_status_t launch_fused(const hzp_plan_t *plan, bool g32, bool o32, uint32_t R, const FusedSegment *segs, size_t nseg,
@@ -751,7 +794,7 @@ hzp_status_t launch_fused(const hzp_plan_t *plan, bool g32, bool o32, uint32_t R
         lookup = lookup || r.runs;
         groups += (r.n + kGroupElems - 1) / kGroupElems;
     }
-    FusedArgs a{};
+    FusedArgs a;                // the words a launch uses are all written below
     if (lookup) {
         const DeviceTables *tab = nullptr;
         hzp_status_t st = device_tables(plan, &tab);
@@ -760,7 +803,7 @@ hzp_status_t launch_fused(const hzp_plan_t *plan, bool g32, bool o32, uint32_t R
         a.run_wd = tab->run_wd;
     }
     a.lookup = lookup;
-    if (scalars) a.scalars = *scalars;
+    a.scalars = scalars ? *scalars : AdamScalars{};
     a.scalars_dev = scalars_dev;
     // Launches of about equal length; a run is cut where a launch is full.
     const uint64_t launches = (groups + kMaxGroupsPerLaunch - 1) / kMaxGroupsPerLaunch;
@@ -836,10 +879,17 @@ hzp_status_t launch_fused(const hzp_plan_t *plan, bool g32, bool o32, uint32_t R
             for (uint32_t c = cnt; c-- > 1;) w[(size_t)c * a.stride] -= (uint32_t)w[(size_t)(c - 1) * a.stride];
             grid = dim3(longest, cnt);
         }
-        if (a.grid2d && !shared && !a.lookup)
-            start_kernel<true>(g32, o32, R, a, grid, stream);
-        else
-            start_kernel<false>(g32, o32, R, a, grid, stream);
+        if (cnt == 1 && !a.lookup) {
+            FusedOneArgs one;
+            one.scalars_dev = a.scalars_dev;
+            one.scalars = a.scalars;
+            std::memcpy(one.word, a.word, (per_seg + kPlainRecord) * sizeof one.word[0]);
+            start_kernel<kOne>(g32, o32, R, one, grid, stream);
+        } else if (a.grid2d && !shared && !a.lookup) {
+            start_kernel<kPlain>(g32, o32, R, a, grid, stream);
+        } else {
+            start_kernel<kSearched>(g32, o32, R, a, grid, stream);
+        }
         hzp_status_t st = check_launch("hzp_adamw_shard");
         if (st != HZP_OK) return st;
         for (uint32_t c = 0; c < cnt; ++c) {
@@ -853,79 +903,159 @@ hzp_status_t launch_fused(const hzp_plan_t *plan, bool g32, bool o32, uint32_t R
     return HZP_OK;
 }
 
+// A piece that has to move.
+struct Move {
+    uint64_t src, dst, nvec;
+};
+
+template <class Args>
+static hzp_status_t copy_list(const Move *moves, size_t n, hipStream_t stream, const char *who)
+{
+    Args a;
+    uint64_t longest = 0;
+    for (size_t s = 0; s < n; ++s) {
+        a.src[s] = moves[s].src;
+        a.dst[s] = moves[s].dst;
+        a.nvec[s] = (uint32_t)moves[s].nvec;
+        longest = std::max(longest, moves[s].nvec);
+    }
+    const dim3 grid((uint32_t)((longest + kWave - 1) / kWave), (uint32_t)n), block(kWave);
+    hipLaunchKernelGGL(copy_list_kernel<Args>, grid, block, 0, stream, a);
+    return check_launch(who);
+}
+
+// Most tiles of 64 vectors in one launch of a copy (600 MB, about 180 us).  Over a longer launch the XCDs drift apart, as in the
+// update; shorter ones lose to the gaps.  Post-step gather of 2.95 GB, launches of 100 / 200 / 400 / 600 / 800 / 1200 k tiles and
+// one for all: 6.59 / 6.71 / 6.77 / 6.77 / 6.76 / 6.71 / 6.70 TB/s.
+constexpr uint64_t kMaxTilesPerLaunch = 600000;
+
+static uint64_t tiles_of(uint64_t nvec) { return (nvec + kWave - 1) / kWave; }
+
+// (a grid holds fewer than 2^32 threads per dimension: one thread per vector, rounded up to whole wavefronts)
+constexpr uint64_t kMostVectors = 0xFFFFFFFFull - kWave;
+
+// Launches over a list of pieces: whole pieces, kMaxTilesPerLaunch tiles at most (or one piece).
+static hzp_status_t copy_moves(const Move *moves, size_t n, hipStream_t stream, const char *who)
+{
+    for (size_t at = 0; at < n;) {
+        size_t cnt = 0;
+        uint64_t tiles = 0;
+        while (at + cnt < n && cnt < (size_t)CopyManyArgs::kPieces) {
+            tiles += tiles_of(moves[at + cnt].nvec);
+            if (cnt > 0 && tiles > kMaxTilesPerLaunch) break;
+            ++cnt;
+        }
+        const hzp_status_t st = cnt <= (size_t)CopyFewArgs::kPieces ? copy_list<CopyFewArgs>(moves + at, cnt, stream, who)
+                                                                    : copy_list<CopyManyArgs>(moves + at, cnt, stream, who);
+        if (st != HZP_OK) return st;
+        at += cnt;
+    }
+    return HZP_OK;
+}
+
 hzp_status_t launch_concat(const void *const *srcs, uint32_t n_shards, uint64_t bytes_per_shard, void *dst,
                            hipStream_t stream)
 {
     if (bytes_per_shard == 0) return HZP_OK;
     const uint64_t nvec = bytes_per_shard / 16;
-    // (a grid holds fewer than 2^32 threads per dimension: one thread per vector, rounded up to whole wavefronts)
-    if (nvec > 0xFFFFFFFFull - kWave) return fail(HZP_ERR_UNSUPPORTED, "hzp_gather_layer: shard of 64 GiB or more");
-    ConcatArgs a{};
-    uint32_t listed = 0;
+    if (nvec > kMostVectors) return fail(HZP_ERR_UNSUPPORTED, "hzp_gather_layer: shard of 64 GiB or more");
+    Move moves[HZP_MAX_GROUP];
+    size_t n = 0;
     for (uint32_t s = 0; s < n_shards; ++s) {
-        if (srcs[s] == static_cast<const char *>(dst) + (size_t)s * bytes_per_shard) continue;     // in place
-        a.src[listed] = srcs[s];
-        a.slot[listed++] = (uint8_t)s;
+        const uint64_t from = reinterpret_cast<uint64_t>(srcs[s]), to = reinterpret_cast<uint64_t>(dst) + s * bytes_per_shard;
+        if (from != to) moves[n++] = {from, to, nvec};          // else it lies in place
     }
-    if (listed == 0) return HZP_OK;
-    a.dst = reinterpret_cast<u32x4 *>(dst);
-    a.vec_per_shard = (uint32_t)nvec;
-    const dim3 grid((uint32_t)((nvec + kWave - 1) / kWave), listed), block(kWave);
-    hipLaunchKernelGGL(concat_kernel, grid, block, 0, stream, a);
-    return check_launch("hzp_gather_layer");
+    return copy_moves(moves, n, stream, "hzp_gather_layer");
+}
+
+// Layers whose pieces lie at equal distances, in launches of kSharedLayers; *done is false (and nothing launched) where
+// they do not.  Every layer leaves out the same pieces (those that lie in place).
+static hzp_status_t copy_shared(const void *const *srcs, uint32_t per_layer, const uint64_t *bytes_per_piece,
+                                void *const *dsts, uint32_t n_layers, hipStream_t stream, bool *done)
+{
+    *done = false;
+    uint32_t first = 0;
+    while (first < n_layers && bytes_per_piece[first] == 0) ++first;
+    if (first == n_layers) return HZP_OK;
+    auto piece = [&](uint32_t l, uint32_t k) { return reinterpret_cast<uint64_t>(srcs[(size_t)l * per_layer + k]); };
+    auto place = [&](uint32_t l, uint32_t k) { return reinterpret_cast<uint64_t>(dsts[l]) + k * bytes_per_piece[l]; };
+    CopySharedArgs a;
+    uint32_t n_src = 0;
+    for (uint32_t k = 0; k < per_layer; ++k)
+        if (piece(first, k) != place(first, k)) {
+            a.src[n_src] = piece(first, k);
+            a.slot[n_src++] = k;
+        }
+    if (n_src == 0) return HZP_OK;
+    for (uint32_t l = first; l < n_layers; ++l) {
+        if (bytes_per_piece[l] == 0) continue;
+        const int64_t d = (int64_t)(piece(l, a.slot[0]) - a.src[0]);
+        if (d / 16 != (int32_t)(d / 16)) return HZP_OK;
+        for (uint32_t k = 0, i = 0; k < per_layer; ++k) {
+            const bool listed = i < n_src && a.slot[i] == k;
+            if (listed == (piece(l, k) == place(l, k))) return HZP_OK;
+            if (listed && (int64_t)(piece(l, k) - a.src[i++]) != d) return HZP_OK;
+        }
+    }
+    *done = true;
+    uint32_t n = 0;
+    uint64_t longest = 0, tiles = 0;
+    auto launch = [&] {
+        const dim3 grid((uint32_t)tiles_of(longest), n_src, n), block(kWave);
+        hipLaunchKernelGGL(copy_shared_kernel, grid, block, 0, stream, a);
+        n = 0;
+        longest = tiles = 0;
+        return check_launch("hzp_gather_layers");
+    };
+    for (uint32_t l = first; l < n_layers; ++l) {
+        if (bytes_per_piece[l] == 0) continue;
+        const uint64_t nvec = bytes_per_piece[l] / 16, more = tiles_of(nvec) * n_src;
+        if (n == kSharedLayers || (n > 0 && tiles + more > kMaxTilesPerLaunch)) {
+            const hzp_status_t st = launch();
+            if (st != HZP_OK) return st;
+        }
+        const int64_t d = (int64_t)(piece(l, a.slot[0]) - a.src[0]);
+        a.layer[n++] = {reinterpret_cast<uint64_t>(dsts[l]), (int32_t)(d / 16), (uint32_t)nvec};
+        longest = std::max(longest, nvec);
+        tiles += more;
+    }
+    return launch();
 }
 
 hzp_status_t launch_concat_layers(const void *const *srcs, uint32_t per_layer, const uint64_t *bytes_per_piece,
                                   void *const *dsts, uint32_t n_layers, hipStream_t stream)
 {
+    for (uint32_t l = 0; l < n_layers; ++l)
+        if (bytes_per_piece[l] / 16 > kMostVectors) return fail(HZP_ERR_UNSUPPORTED, "hzp_gather_layers: shard of 64 GiB or more");
+    if ((size_t)n_layers * per_layer > (size_t)CopyManyArgs::kPieces) {         // where one list would not do
+        bool done = false;
+        const hzp_status_t st = copy_shared(srcs, per_layer, bytes_per_piece, dsts, n_layers, stream, &done);
+        if (st != HZP_OK || done) return st;
+    }
     // the pieces that have to move, layer after layer
-    struct Item {
-        const void *src;
-        char *dst;
-        uint64_t nvec;
-    };
-    std::vector<Item> items;
+    std::vector<Move> moves;
     try {
-        items.reserve((size_t)n_layers * per_layer);
+        moves.reserve((size_t)n_layers * per_layer);
     } catch (const std::bad_alloc &) {
         return fail(HZP_ERR_NOMEM, "hzp_gather_layers: out of host memory");
     }
     for (uint32_t l = 0; l < n_layers; ++l) {
         const uint64_t bytes = bytes_per_piece[l];
-        if (bytes / 16 > 0xFFFFFFFFull - kWave) return fail(HZP_ERR_UNSUPPORTED, "hzp_gather_layers: shard of 64 GiB or more");
         if (bytes == 0) continue;
         for (uint32_t k = 0; k < per_layer; ++k) {
-            const void *src = srcs[(size_t)l * per_layer + k];
-            char *dst = static_cast<char *>(dsts[l]) + (size_t)k * bytes;
-            if (src != dst) items.push_back({src, dst, bytes / 16});      // else the piece lies in place
+            const uint64_t src = reinterpret_cast<uint64_t>(srcs[(size_t)l * per_layer + k]);
+            const uint64_t dst = reinterpret_cast<uint64_t>(dsts[l]) + k * bytes;
+            if (src != dst) moves.push_back({src, dst, bytes / 16});        // else the piece lies in place
         }
     }
-    // launches of equal numbers of pieces
-    const size_t launches = (items.size() + kLayersPieceCap - 1) / kLayersPieceCap;
-    for (size_t i = 0, done = 0; i < launches; ++i) {
-        const size_t cnt = (items.size() - done + (launches - i) - 1) / (launches - i);
-        ConcatLayersArgs a{};
-        uint64_t longest = 0;
-        for (size_t s = 0; s < cnt; ++s) {
-            const Item &it = items[done + s];
-            a.src[s] = it.src;
-            a.dst[s] = reinterpret_cast<u32x4 *>(it.dst);
-            a.nvec[s] = (uint32_t)it.nvec;
-            longest = std::max(longest, it.nvec);
-        }
-        done += cnt;
-        const dim3 grid((uint32_t)((longest + kWave - 1) / kWave), (uint32_t)cnt), block(kWave);
-        hipLaunchKernelGGL(concat_layers_kernel, grid, block, 0, stream, a);
-        hzp_status_t st = check_launch("hzp_gather_layers");
-        if (st != HZP_OK) return st;
-    }
-    return HZP_OK;
+    return copy_moves(moves.data(), moves.size(), stream, "hzp_gather_layers");
 }
 
 hzp_status_t launch_concat_ranges(const void *const *srcs, const uint64_t *dst_off, const uint64_t *bytes,
                                   uint32_t n, void *dst, hipStream_t stream)
 {
-    ConcatRangesArgs a{};
+    ConcatRangesArgs a;
+    std::fill(std::begin(a.tile_end), std::end(a.tile_end), 0xFFFFFFFFu);
     uint64_t tiles = 0, total = 0;
     bool uniform = true;
     for (uint32_t s = 0; s < n; ++s) {
@@ -949,34 +1079,57 @@ hzp_status_t launch_concat_ranges(const void *const *srcs, const uint64_t *dst_o
     return check_launch("hzp_gather_shard");
 }
 
-// Launches of the unpack kernel for tensors [t_begin, t_end) of a bucket; `pieces` and `piece_chunk`
-// are device tables that hold the bucket's pieces from entry 0.
-static hzp_status_t launch_unpack_with(const Piece *pieces, const uint32_t *piece_chunk, const BucketRec &b,
-                                       const void *const *shards, uint32_t n_shards, void *const *tensors,
-                                       uint32_t t_begin, uint32_t t_end, hipStream_t stream, const char *who)
+// What the launches of one unpacking call share.
+struct UnpackCall {
+    const Piece *pieces;                // device tables that hold the bucket's pieces from entry 0
+    const uint32_t *piece_chunk;
+    const BucketRec &b;
+    const void *const *shards;
+    uint32_t n_shards;
+    hipStream_t stream;
+};
+
+// One launch: tensors [t0, t1), whose pieces are [p0, p1).
+template <class Args>
+static void start_unpack(const UnpackCall &u, void *const *tensors, uint32_t t0, uint32_t t1, size_t p0, size_t p1)
+{
+    Args a;
+    a.pieces = u.pieces;
+    a.piece_chunk = u.piece_chunk;
+    a.n_pieces = (uint32_t)u.b.pieces.size();
+    a.chunk0 = u.b.pieces[p0].chunk_begin;
+    a.chunk_end = p1 < u.b.pieces.size() ? u.b.pieces[p1].chunk_begin : u.b.n_chunks;
+    a.tensor0 = t0;
+    for (uint32_t s = 0; s < u.n_shards; ++s) a.shard[s] = u.shards[s];
+    for (uint32_t t = t0; t < t1; ++t) a.tensor[t - t0] = tensors[t - t0];
+    const dim3 grid(a.chunk_end - a.chunk0), block(kWave);
+    if (u.b.cls == HZP_CLASS_F32)
+        hipLaunchKernelGGL((unpack_kernel<4, Args>), grid, block, 0, u.stream, a);
+    else
+        hipLaunchKernelGGL((unpack_kernel<2, Args>), grid, block, 0, u.stream, a);
+}
+
+// Launches of the unpack kernel for tensors [t_begin, t_end) of a bucket.
+static hzp_status_t launch_unpack_with(const UnpackCall &u, void *const *tensors, uint32_t t_begin, uint32_t t_end,
+                                       const char *who)
 {
     // Tensors travel in the argument block, kUnpackTensorCap at a time; pieces are sorted by tensor.
-    size_t p0 = 0;
-    while (p0 < b.pieces.size() && b.pieces[p0].tensor < t_begin) ++p0;
+    const std::vector<Piece> &pieces = u.b.pieces;
+    auto first_of = [&](size_t from, uint32_t t) {
+        return (size_t)(std::lower_bound(pieces.begin() + from, pieces.end(), t,
+                                         [](const Piece &p, uint32_t x) { return p.tensor < x; }) - pieces.begin());
+    };
+    size_t p0 = first_of(0, t_begin);
     for (uint32_t t0 = t_begin; t0 < t_end; t0 += kUnpackTensorCap) {
-        const uint32_t t1 = std::min<uint32_t>(t_end, t0 + kUnpackTensorCap);
-        size_t p1 = p0;
-        while (p1 < b.pieces.size() && b.pieces[p1].tensor < t1) ++p1;
-        UnpackArgs a{};
-        for (uint32_t s = 0; s < n_shards; ++s) a.shard[s] = shards[s];
-        for (uint32_t t = t0; t < t1; ++t) a.tensor[t - t0] = tensors[t - t_begin];
-        a.pieces = pieces;
-        a.piece_chunk = piece_chunk;
-        a.n_pieces = (uint32_t)b.pieces.size();
-        a.chunk0 = b.pieces[p0].chunk_begin;
-        a.chunk_end = p1 < b.pieces.size() ? b.pieces[p1].chunk_begin : b.n_chunks;
-        a.tensor0 = t0;
-        const uint32_t chunks = a.chunk_end - a.chunk0;
-        const dim3 grid(chunks), block(kWave);
-        if (b.cls == HZP_CLASS_F32)
-            hipLaunchKernelGGL(unpack_kernel<4>, grid, block, 0, stream, a);
+        const uint32_t t1 = std::min<uint32_t>(t_end, t0 + kUnpackTensorCap), n = t1 - t0;
+        const size_t p1 = first_of(p0, t1);
+        void *const *at = tensors + (t0 - t_begin);
+        if (n <= (uint32_t)UnpackFewArgs::kTensors && u.n_shards <= (uint32_t)UnpackFewArgs::kShards)
+            start_unpack<UnpackFewArgs>(u, at, t0, t1, p0, p1);
+        else if (n <= (uint32_t)UnpackSomeArgs::kTensors && u.n_shards <= (uint32_t)UnpackSomeArgs::kShards)
+            start_unpack<UnpackSomeArgs>(u, at, t0, t1, p0, p1);
         else
-            hipLaunchKernelGGL(unpack_kernel<2>, grid, block, 0, stream, a);
+            start_unpack<UnpackManyArgs>(u, at, t0, t1, p0, p1);
         hzp_status_t st = check_launch(who);
         if (st != HZP_OK) return st;
         p0 = p1;
@@ -991,8 +1144,8 @@ hzp_status_t launch_unpack(const hzp_plan_t *plan, const BucketRec &b, const voi
     const DeviceTables *tab = nullptr;
     hzp_status_t st = device_tables(plan, &tab);
     if (st != HZP_OK) return st;
-    return launch_unpack_with(tab->pieces + b.piece_slot, tab->piece_chunk + b.piece_slot, b, shards, n_shards,
-                              tensors, t_begin, t_end, stream, "hzp_gather_layer");
+    const UnpackCall u{tab->pieces + b.piece_slot, tab->piece_chunk + b.piece_slot, b, shards, n_shards, stream};
+    return launch_unpack_with(u, tensors, t_begin, t_end, "hzp_gather_layer");
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1077,8 +1230,8 @@ hzp_status_t launch_unpack_static(const BucketRec &b, const void *const *shards,
     st = fill_table(tab->pieces, b.pieces.data(), b.pieces.size() * sizeof(Piece), stream);
     if (st == HZP_OK) st = fill_table(tab->piece_chunk, chunk_begin, b.pieces.size() * sizeof(uint32_t), stream);
     if (st != HZP_OK) return st;
-    return launch_unpack_with(tab->pieces, tab->piece_chunk, b, shards, n_shards, tensors, 0, b.n_tensors, stream,
-                              "hzp_gather_layer_static");
+    const UnpackCall u{tab->pieces, tab->piece_chunk, b, shards, n_shards, stream};
+    return launch_unpack_with(u, tensors, 0, b.n_tensors, "hzp_gather_layer_static");
 }
 
 // ---------------------------------------------------------------------------------------

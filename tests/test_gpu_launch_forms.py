@@ -1,6 +1,6 @@
-"""The forms one update or reduction can be launched in, against the CPU oracle: segments merged, listed with pointers
-of their own or sharing one set, found by a 2-D grid or by search, decay constant or looked up; every number of
-contributions; sizes at the edges of a group of 256 elements and of a block of 16 groups."""
+"""The forms one update, reduction or post-step gather can be launched in, against the CPU oracle: segments merged, listed
+with pointers of their own or sharing one set, found by a 2-D grid or by search, decay constant or looked up; every
+number of contributions; sizes at the edges of a group of 256 elements and of a block of 16 groups."""
 import numpy as np
 import pytest
 import torch
@@ -132,3 +132,30 @@ def test_reduction_of_every_number_of_contributions_at_group_edges(R, g32):
             torch.cuda.synchronize()
             assert np.array_equal(to_host(whole[:n], np.uint32), want.view(np.uint32)), (n, acc)
             assert bool((whole[n:] == 0.5).all())
+
+
+@pytest.mark.parametrize("place", ["own", "packed", "spread", "down"])
+@pytest.mark.parametrize("layers,K,own,ragged", [(30, 8, None, True), (30, 8, 3, True), (210, 4, 0, True), (250, 1, None, False),
+                                                 (5, 64, 63, False), (3, 2, 1, True)])
+def test_post_step_gather_of_many_layers_in_every_placement(place, layers, K, own, ragged):
+    """More pieces than one list holds (192) and fewer; layers at equal distances in every source or not; one piece of
+    each layer already in place or none."""
+    print(place, layers, K, own, flush=True)
+    rng = np.random.default_rng(layers + K)
+    numel = [int(x) for x in rng.integers(1, 40000, layers)] if ragged else [2500] * layers
+    plan = hzp.hzp_plan([1] * layers, numel, align=8, z3=1, z1=K)
+    sizes = [plan.bucket(layer).s1 for layer in range(layers)]
+    whole = [torch.full((n * K,), -1, dtype=torch.int16, device=DEV) for n in sizes]
+    sources = [carve(sizes, torch.int16, place) for _ in range(K)]
+    want = []
+    for i, n in enumerate(sizes):
+        host = rng.integers(-30000, 30000, (K, n)).astype(np.int16)
+        want.append(host.reshape(-1))
+        for k in range(K):
+            if k == own:
+                sources[k][i] = whole[i][k * n:(k + 1) * n]
+            sources[k][i].copy_(torch.from_numpy(host[k]))
+    hzp.hzp_gather_layers(plan, 0, layers, 0, 1, [sources[k][i] for i in range(layers) for k in range(K)], K, whole)
+    torch.cuda.synchronize()
+    for i in range(layers):
+        assert np.array_equal(whole[i].cpu().numpy(), want[i]), i
