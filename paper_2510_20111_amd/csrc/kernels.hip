@@ -118,6 +118,11 @@ constexpr unsigned lds_for(unsigned waves) { return waves ? 163840u / waves / 51
 // 6.73 / 6.77 / 6.73 / 6.72, R = 16 6.57 / 6.57 / 6.47 / 6.45.
 constexpr uint32_t fused_chunk(bool g32) { return g32 ? 3u : 4u; }
 constexpr uint32_t kReduceChunk = 4;
+// A launch of so few groups that all wavefronts are resident at once lasts as long as one wavefront, whose chunks follow
+// each other: there, more than 8 contributions are requested up to 16 at a time (64 k elements, R = 32: reduction 5.5 -> 3.7 us,
+// update 6.2 -> 4.3; 512 k: 7.7 -> 7.4, 11.7 -> 10.4; with R <= 8 no difference).
+constexpr uint32_t kFewGroups = 2048;
+constexpr uint32_t few_chunk(uint32_t R, uint32_t chunk) { return R > 8 ? 16u : chunk; }
 
 // Four gradient elements of one contribution, widened to fp32 on access.
 template <bool G32>
@@ -209,14 +214,14 @@ struct ReduceArgs {
 // occupancy (25 M elements: 5.89 TB/s; with two quads 6.22).
 constexpr int reduce_quads(uint32_t R, bool g32) { return R == 1 && !g32 ? 2 : 1; }
 
-template <uint32_t R, bool G32, bool ACC>
+template <uint32_t R, bool G32, bool ACC, uint32_t CHUNK>
 __global__ __launch_bounds__(kWave) void reduce_kernel(const ReduceArgs a)
 {
 #pragma clang fp contract(off)
     constexpr int Q = reduce_quads(R, G32);
-    uint64_t out = reinterpret_cast<uint64_t>(a.out), at[kReduceChunk];
+    uint64_t out = reinterpret_cast<uint64_t>(a.out), at[CHUNK];
 #pragma unroll
-    for (uint32_t c = 0; c < kReduceChunk; ++c) at[c] = c < R ? a.g[c] : 0;
+    for (uint32_t c = 0; c < CHUNK; ++c) at[c] = c < R ? a.g[c] : 0;
     uint32_t nquad = a.nquad;
     float scale = a.scale;
     pin(out, at[0], at[1], at[2], at[3], nquad, scale);
@@ -229,7 +234,7 @@ __global__ __launch_bounds__(kWave) void reduce_kernel(const ReduceArgs a)
         if (ACC) t[q] = ld_stream<f32x4>(out, quad[q]);
     }
     float s[Q][4];
-    sum_contributions<R, kReduceChunk, G32>(at, a.g, 0, quad, s);
+    sum_contributions<R, CHUNK, G32>(at, a.g, 0, quad, s);
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
 #pragma unroll
@@ -333,7 +338,7 @@ struct DecayRuns {
 // arrives in one round of scalar loads.  kSearched: a uniform binary search may have to find the segment, three more
 // rounds, which the few resident wavefronts hide badly (105 M elements, R = 8, one segment: 6.65 TB/s at the best
 // number of wavefronts, 6.73 with the one round).
-template <uint32_t R, bool G32, bool O32, FusedForm FORM>
+template <uint32_t R, bool G32, bool O32, FusedForm FORM, uint32_t CHUNK>
 __global__ __launch_bounds__(kWave) void fused_adamw_kernel(const std::conditional_t<FORM == kOne, FusedOneArgs, FusedArgs> a)
 {
     constexpr bool PAIRS = !G32;
@@ -374,14 +379,13 @@ __global__ __launch_bounds__(kWave) void fused_adamw_kernel(const std::condition
             out_shift = (int32_t)(uint32_t)(d >> 32);
         }
     }
-    constexpr uint32_t CHUNK = fused_chunk(G32);
     uint64_t P = ptr[0], M = ptr[1], V = ptr[2], OUT = ptr[3], extent = rec[0], decay = rec[1];
     uint64_t at[CHUNK];
 #pragma unroll
     for (uint32_t c = 0; c < CHUNK; ++c) at[c] = c < R ? ptr[4 + c] : 0;
     AdamScalars h = a.scalars;
     uint64_t scalars_dev = reinterpret_cast<uint64_t>(a.scalars_dev);
-    pin(P, M, V, OUT, extent, decay, at[0], at[1], at[2], at[CHUNK - 1], scalars_dev);
+    pin(P, M, V, OUT, extent, decay, at[0], at[1], at[2], at[CHUNK > 3 ? 3 : 2], scalars_dev);
     pin(h.lr, h.beta1, h.beta2, h.one_minus_beta1, h.one_minus_beta2, h.eps, h.weight_decay, h.grad_scale, h.inv_bc1, h.inv_bc2);
     const uint32_t groups = (uint32_t)extent - before, nquad = (uint32_t)(extent >> 32);
     if (grp >= groups) return;                  // of a longer segment of a 2-D grid
@@ -636,15 +640,15 @@ static hzp_status_t check_launch(const char *what)
 
 // One kernel per number of contributions: the loads of a chunk are then straight-line code (a run-time R
 // puts a wait between any two of them), and all of a launch's pointers arrive in one round of scalar loads.
-template <bool G32, bool ACC, size_t... I>
+template <bool G32, bool ACC, bool FEW, size_t... I>
 static constexpr std::array<void (*)(ReduceArgs), sizeof...(I)> reduce_kernels(std::index_sequence<I...>)
 {
-    return {reduce_kernel<I + 1, G32, ACC>...};
+    return {reduce_kernel<I + 1, G32, ACC, FEW ? few_chunk(I + 1, kReduceChunk) : kReduceChunk>...};
 }
-template <bool G32, bool O32, FusedForm FORM, class Args, size_t... I>
+template <bool G32, bool O32, FusedForm FORM, bool FEW, class Args, size_t... I>
 static constexpr std::array<void (*)(Args), sizeof...(I)> fused_kernels(std::index_sequence<I...>)
 {
-    return {fused_adamw_kernel<I + 1, G32, O32, FORM>...};
+    return {fused_adamw_kernel<I + 1, G32, O32, FORM, FEW ? few_chunk(I + 1, fused_chunk(G32)) : fused_chunk(G32)>...};
 }
 
 // Wavefronts per CU for the reduction: what keeps about 48 KiB in flight per CU where the contributions fit one chunk,
@@ -676,10 +680,12 @@ hzp_status_t launch_reduce(bool g32, const void *const *slices, uint32_t R, uint
     const dim3 grid((a.nquad + group - 1) / group), block(kWave);
     const unsigned lds = lds_for(reduce_waves(g32, R, n, accumulate));
     constexpr std::make_index_sequence<HZP_MAX_REPLICAS> all;
-    static constexpr std::array<void (*)(ReduceArgs), HZP_MAX_REPLICAS> kernels[2][2] = {
-        {reduce_kernels<false, false>(all), reduce_kernels<false, true>(all)},
-        {reduce_kernels<true, false>(all), reduce_kernels<true, true>(all)}};
-    hipLaunchKernelGGL(kernels[g32][accumulate != 0][R - 1], grid, block, lds, stream, a);
+    static constexpr std::array<void (*)(ReduceArgs), HZP_MAX_REPLICAS> kernels[2][2][2] = {
+        {{reduce_kernels<false, false, false>(all), reduce_kernels<false, false, true>(all)},
+         {reduce_kernels<false, true, false>(all), reduce_kernels<false, true, true>(all)}},
+        {{reduce_kernels<true, false, false>(all), reduce_kernels<true, false, true>(all)},
+         {reduce_kernels<true, true, false>(all), reduce_kernels<true, true, true>(all)}}};
+    hipLaunchKernelGGL(kernels[g32][accumulate != 0][grid.x <= kFewGroups][R - 1], grid, block, lds, stream, a);
     return check_launch("hzp_reduce_shard");
 }
 
@@ -763,17 +769,22 @@ static void list_runs(const hzp_plan_t *plan, const FusedSegment *segs, size_t n
     }
 }
 
-template <FusedForm FORM, class Args>
-static void start_kernel(bool g32, bool o32, uint32_t R, const Args &a, dim3 grid, hipStream_t stream)
+template <FusedForm FORM, bool FEW, class Args>
+static void start_kernel(bool g32, bool o32, uint32_t R, const Args &a, dim3 grid, uint32_t groups, hipStream_t stream)
 {
-    static constexpr auto kernels16 = fused_kernels<false, false, FORM, Args>(std::make_index_sequence<HZP_MAX_REPLICAS>());
-    static constexpr auto kernels32 = fused_kernels<true, true, FORM, Args>(std::make_index_sequence<HZP_MAX_REPLICAS>());
-    void (*const kernel)(Args) = !g32 ? kernels16[R - 1] : o32 ? kernels32[R - 1] : fused_adamw_kernel<1, true, false, FORM>;
-    // 10 wavefronts per CU with bf16 contributions (R = 8, 105 M elements: 8 / 9 / 10 / 11 / 12 / 14 / 16 6.67 / 6.73 / 6.73 /
-    // 6.72 / 6.70 / 6.61 / 6.56 TB/s), 8 with fp32 ones, whose chunks hold half as much again (R = 1, 107 M: 7 / 8 / 9 / 10 / 12
-    // 6.56 / 6.74 / 6.64 / 6.63 / 6.55).  Where the segment is searched for or decay looked up a wavefront lives longer:
-    // R = 8 with looked-up decay 10 / 11 / 12 / 13 / 14 6.31 / 6.50 / 6.54 / 6.48 / 6.37.
-    hipLaunchKernelGGL(kernel, grid, dim3(kWave), lds_for(FORM == kSearched ? (g32 ? 10 : 12) : (g32 ? 8 : 10)), stream, a);
+    constexpr std::make_index_sequence<HZP_MAX_REPLICAS> all;
+    static constexpr auto kernels16 = fused_kernels<false, false, FORM, FEW, Args>(all);
+    static constexpr auto kernels32 = fused_kernels<true, true, FORM, FEW, Args>(all);
+    void (*const kernel)(Args) = !g32 ? kernels16[R - 1] : o32 ? kernels32[R - 1] : fused_adamw_kernel<1, true, false, FORM, fused_chunk(true)>;
+    // Wavefronts per CU.  bf16 contributions: 10 (R = 8, 105 M elements: 8 / 9 / 10 / 11 / 12 / 14 / 16 6.67 / 6.73 / 6.73 / 6.72 /
+    // 6.70 / 6.61 / 6.56 TB/s), more in shorter launches, where filling and draining the chip counts (R = 8, 33 M: 10 / 12 / 14
+    // 6.42 / 6.51 / 6.45; R = 16, 4 M: 10 / 12 / 14 / 16 5.58 / 5.79 / 5.82 / 5.77).  fp32: 8, whose chunks hold half as much again
+    // (R = 1, 107 M: 7 / 8 / 9 / 10 / 12 6.56 / 6.74 / 6.64 / 6.63 / 6.55; R = 8, 17 M: 8 / 10 / 12 6.57 / 6.45 / 6.25).  Where the
+    // segment is searched for or decay looked up a wavefront lives longer: R = 8 with looked-up decay 10 / 11 / 12 / 13 / 14 6.31 /
+    // 6.50 / 6.54 / 6.48 / 6.37.
+    const unsigned waves16 = groups > 200000u ? (FORM == kSearched ? 12u : 10u) : groups > 32768u ? 12u : 14u;
+    const unsigned waves32 = FORM == kSearched ? 10u : 8u;
+    hipLaunchKernelGGL(kernel, grid, dim3(kWave), FEW ? 0u : lds_for(g32 ? waves32 : waves16), stream, a);
 }
 
 hzp_status_t launch_fused(const hzp_plan_t *plan, bool g32, bool o32, uint32_t R, const FusedSegment *segs, size_t nseg,
@@ -884,11 +895,14 @@ hzp_status_t launch_fused(const hzp_plan_t *plan, bool g32, bool o32, uint32_t R
             one.scalars_dev = a.scalars_dev;
             one.scalars = a.scalars;
             std::memcpy(one.word, a.word, (per_seg + kPlainRecord) * sizeof one.word[0]);
-            start_kernel<kOne>(g32, o32, R, one, grid, stream);
+            if (blocks <= kFewGroups)
+                start_kernel<kOne, true>(g32, o32, R, one, grid, blocks, stream);
+            else
+                start_kernel<kOne, false>(g32, o32, R, one, grid, blocks, stream);
         } else if (a.grid2d && !shared && !a.lookup) {
-            start_kernel<kPlain>(g32, o32, R, a, grid, stream);
+            start_kernel<kPlain, false>(g32, o32, R, a, grid, blocks, stream);
         } else {
-            start_kernel<kSearched>(g32, o32, R, a, grid, stream);
+            start_kernel<kSearched, false>(g32, o32, R, a, grid, blocks, stream);
         }
         hzp_status_t st = check_launch("hzp_adamw_shard");
         if (st != HZP_OK) return st;
