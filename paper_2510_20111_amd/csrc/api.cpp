@@ -197,13 +197,9 @@ extern "C" hzp_status_t hzp_gather_layer(const hzp_plan_t *plan, uint32_t layer,
             if (reinterpret_cast<uintptr_t>(tensor_out[t]) % es)
                 return fail(HZP_ERR_ALIGN, "hzp_gather_layer: tensor_out[%u] is not element-aligned", t);
         }
-    const uint64_t len = level == 1 ? b->S1 : b->S3;
-    if (bucket_out) {
-        hzp_status_t st = launch_concat(shard_ptrs, n_shards, len * es, bucket_out, stream);
-        if (st != HZP_OK) return st;
-    }
+    if (bucket_out && tensor_out) return launch_unpack_both(plan, *b, shard_ptrs, n_shards, bucket_out, tensor_out, stream);
     if (tensor_out) return launch_unpack(plan, *b, shard_ptrs, n_shards, tensor_out, 0, b->n_tensors, stream);
-    return HZP_OK;
+    return launch_concat(shard_ptrs, n_shards, (level == 1 ? b->S1 : b->S3) * es, bucket_out, stream);
 }
 
 extern "C" hzp_status_t hzp_gather_layer_static(const hzp_plan_t *plan, uint32_t layer, uint32_t cls,

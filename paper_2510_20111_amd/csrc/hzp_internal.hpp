@@ -67,6 +67,7 @@ struct hzp_plan {
     uint32_t K;                                 // Z1/Z3, or 0 when Z3 does not divide Z1
     uint32_t world;                             // lcm(Z1, Z2, Z3): ranks are 0 .. world-1
     uint64_t total_padded;
+    bool uniform_wd;                            // every multiplier is 1: no update needs the decay tables
     std::vector<hzp::TensorRec> tensors;        // by tensor id
     std::vector<hzp::BucketRec> buckets;        // by (layer, class)
     std::vector<int32_t> bucket_of;             // [layer*2 + cls] -> bucket index or -1
@@ -120,11 +121,16 @@ hzp_status_t launch_concat_ranges(const void *const *srcs, const uint64_t *dst_o
 hzp_status_t launch_unpack(const hzp_plan_t *plan, const BucketRec &b, const void *const *shards,
                            uint32_t n_shards, void *const *tensors, uint32_t t_begin, uint32_t t_end,
                            hipStream_t stream);
-// The same for all tensors of the bucket with the piece table in the library's fixed device array
+// The whole bucket (16-byte aligned) and all its tensors.
+hzp_status_t launch_unpack_both(const hzp_plan_t *plan, const BucketRec &b, const void *const *shards, uint32_t n_shards,
+                                void *bucket, void *const *tensors, hipStream_t stream);
+// The tensors of the bucket with the piece table in the library's fixed device array
 // (no allocation, no copy call); refuses buckets with more than HZP_STATIC_MAX_PIECES pieces.
 hzp_status_t launch_unpack_static(const BucketRec &b, const void *const *shards, uint32_t n_shards,
                                   void *const *tensors, hipStream_t stream);
-// Tables for the current device (creates them on first use).  Defined with the launchers.
+// Tables for the current device (creates them on first use).  Defined with the launchers.  Every unpacking call asks for
+// them, and every update of a plan with multipliers other than 1, whether this one reads them or not: after one such call
+// outside a graph capture, or hzp_plan_prepare, none on the plan allocates.
 hzp_status_t device_tables(const hzp_plan_t *plan, const DeviceTables **out);
 void free_device_tables(hzp_plan_t *plan);
 }  // namespace hzp

@@ -548,34 +548,111 @@ __global__ __launch_bounds__(kWave) void concat_ranges_kernel(const ConcatRanges
 
 // ---------------------------------------------------------------------------------------
 // Gather + unpack: ZeRO-3 shards -> separate, unpadded tensor buffers.
-// One single-wavefront workgroup per chunk of at most kUnpackChunk elements of one piece (a run of
-// one tensor inside one shard).  1024-element chunks measured fastest on MI355X (6.5-6.6 TB/s on
-// dense and MoE layers; 4096: 6.0, 16384: 5.4, 512: 5.3-6.0): like the plain copy, this kernel
-// wants little work per wavefront and every wave slot filled.  Sources are 16-byte aligned; a
-// destination is only element-aligned, so a chunk is written as: up to 15 bytes of single
-// elements to reach a 16-byte boundary of the destination, whole 16-byte vectors (whose source is
-// then read unaligned), single elements.
+//
+// A part is a run of elements that moves from one shard to one tensor.  Sources are 16-byte aligned where a part
+// begins; a tensor is only element-aligned, so a part is written as up to 15 bytes of single elements to reach a
+// 16-byte boundary of the destination, whole 16-byte vectors (whose source is then read unaligned), single elements.
+// The kernel is the plain copy's: one vector per lane, pointers and lengths in the argument block.
+//   - Parts of about equal length (the host cuts a few long ones to that end): grid = (tiles of the longest part, parts),
+//     one round of scalar loads before a wavefront asks for data.
+//   - FLAT, parts of very different lengths: a grid without surplus workgroups over the tiles of all parts; a workgroup
+//     counts the parts that end at or before its tile, 64 to a load.
+// (Finding the piece of a chunk in device tables took four rounds, and even at full occupancy those bound the rate. MoE
+// layer of 199 tensors 6.57 -> 6.75 TB/s, dense layer 6.48 -> 6.75, odd sizes 5.91 -> 6.35, 25 MB layers 4.31 -> 5.28.)
+//
+// BOTH: the part is also copied to its place in the layer bucket, aligned as the shard is, together with the padding
+// behind it in the same shard (`n_bucket` >= n elements, whole vectors).  A part may be padding alone (n = 0).
+// Dense layer into bucket and tensors: two kernels 981 us, one 749.
 // ---------------------------------------------------------------------------------------
+template <int PARTS, bool BOTH, bool FLAT>
+struct UnpackListArgs {
+    static constexpr int kParts = PARTS;
+    static constexpr bool kBoth = BOTH, kFlat = FLAT;
+    uint64_t src[PARTS], dst[PARTS];
+    uint64_t bucket[BOTH ? PARTS : 1];
+    uint32_t n[PARTS];                  // elements
+    uint32_t n_bucket[BOTH ? PARTS : 1];
+    uint32_t tile_end[FLAT ? (PARTS + kWave - 1) / kWave * kWave : 1];      // running count of tiles; behind the last part ~0
+};
+typedef UnpackListArgs<8, false, false> UnpackList8;
+typedef UnpackListArgs<72, false, false> UnpackList72;
+typedef UnpackListArgs<200, false, false> UnpackList200;
+typedef UnpackListArgs<64, false, true> UnpackFlat64;
+typedef UnpackListArgs<160, false, true> UnpackFlat160;
+typedef UnpackListArgs<124, true, false> UnpackBoth124;
+typedef UnpackListArgs<64, true, true> UnpackBothFlat64;
+typedef UnpackListArgs<108, true, true> UnpackBothFlat108;
+static_assert(sizeof(UnpackList200) <= 4096 && sizeof(UnpackFlat160) <= 4096 && sizeof(UnpackBoth124) <= 4096 &&
+              sizeof(UnpackBothFlat108) <= 4096, "kernel arguments");
+
+template <int ES, class Args>   // element size in bytes: 2 or 4
+__global__ __launch_bounds__(kWave) void unpack_list_kernel(const Args a)
+{
+    constexpr uint32_t VE = 16 / ES;    // elements per vector
+    typedef typename std::conditional<ES == 2, uint16_t, uint32_t>::type elem_t;
+    typedef typename std::conditional<ES == 2, u32x4_a2, u32x4_a4>::type vec_unaligned_t;
+    typedef const __attribute__((address_space(1))) vec_unaligned_t *vectors;
+    typedef const __attribute__((address_space(1))) elem_t *elements;
+    typedef __attribute__((address_space(1))) elem_t *elements_out;
+    const uint32_t lane = threadIdx.x;
+    uint32_t part = blockIdx.y, tile = blockIdx.x;
+    if constexpr (Args::kFlat) {
+        part = 0;
+#pragma unroll
+        for (int k = 0; k < Args::kParts; k += kWave) part += (uint32_t)__popcll(__ballot(a.tile_end[k + lane] <= blockIdx.x));
+        part = __builtin_amdgcn_readfirstlane(part);
+        tile -= part ? a.tile_end[part - 1] : 0u;
+    }
+    uint64_t src = a.src[part], dst = a.dst[part], bucket = 0;
+    uint32_t n = a.n[part], n_bucket = 0;
+    if constexpr (Args::kBoth) {
+        bucket = a.bucket[part];
+        n_bucket = a.n_bucket[part];
+    }
+    pin(src, dst, bucket, n, n_bucket);
+    const uint32_t q = tile * kWave + lane;
+    if constexpr (Args::kBoth) {        // source, bucket and tensor are aligned alike
+        if (q >= n_bucket / VE) return;
+        const u32x4 val = __builtin_nontemporal_load((vectors)src + q);
+        st_writethrough(reinterpret_cast<u32x4 *>(bucket) + q, val);
+        if (q < n / VE) {
+            st_writethrough(reinterpret_cast<u32x4 *>(dst) + q, val);
+        } else if (q == n / VE) {       // the tensor's last elements
+#pragma unroll
+            for (uint32_t e = 0; e < VE - 1; ++e)
+                if (e < n % VE) ((elements_out)dst)[q * VE + e] = (elem_t)(ES == 4 ? val[e] : val[e / 2] >> (e % 2 * 16));
+        }
+    } else {
+        uint32_t head = ((16u - (uint32_t)(dst & 15u)) & 15u) / ES;
+        if (head > n) head = n;
+        const uint32_t nbody = (n - head) / VE, tail0 = head + nbody * VE;
+        if (tile == 0) {
+            if (lane < head) ((elements_out)dst)[lane] = ((elements)src)[lane];
+            if (lane < n - tail0) ((elements_out)dst)[tail0 + lane] = ((elements)src)[tail0 + lane];
+        }
+        if (q >= nbody) return;
+        const u32x4 val = __builtin_nontemporal_load((vectors)(src + head * (uint32_t)ES) + q);
+        st_writethrough(reinterpret_cast<u32x4 *>(dst + head * (uint32_t)ES) + q, val);
+    }
+}
+
+// The same for buckets of very many small tensors: one single-wavefront workgroup per chunk of at most kUnpackChunk
+// elements of one piece (a run of one tensor inside one shard), found in the plan's device tables, so that a launch
+// covers 400 tensors whatever their sizes.
 constexpr int kUnpackTensorCap = 400;
-// (the argument block in three sizes: launching with the smallest is 0.3-1 us cheaper than with the largest)
-template <int SHARDS, int TENSORS>
 struct UnpackArgs {
-    static constexpr int kShards = SHARDS, kTensors = TENSORS;
     const Piece *pieces;                // device table of the bucket, pieces [0, n_pieces)
     const uint32_t *piece_chunk;        // device: chunk_begin of the same pieces, densely packed
     uint32_t n_pieces;
     uint32_t chunk0, chunk_end;         // chunks handled by this launch
     uint32_t tensor0;
-    const void *shard[SHARDS];
-    void *tensor[TENSORS];              // tensor[t - tensor0]
+    const void *shard[HZP_MAX_GROUP];
+    void *tensor[kUnpackTensorCap];     // tensor[t - tensor0]
 };
-typedef UnpackArgs<8, 4> UnpackFewArgs;
-typedef UnpackArgs<16, 64> UnpackSomeArgs;
-typedef UnpackArgs<HZP_MAX_GROUP, kUnpackTensorCap> UnpackManyArgs;
-static_assert(sizeof(UnpackManyArgs) <= 4096, "kernel arguments");
+static_assert(sizeof(UnpackArgs) <= 4096, "kernel arguments");
 
-template <int ES, class Args>   // element size in bytes: 2 or 4
-__global__ __launch_bounds__(kWave) void unpack_kernel(const Args a)
+template <int ES>   // element size in bytes: 2 or 4
+__global__ __launch_bounds__(kWave) void unpack_kernel(const UnpackArgs a)
 {
     constexpr uint32_t VE = 16 / ES;    // elements per vector
     typedef typename std::conditional<ES == 2, uint16_t, uint32_t>::type elem_t;
@@ -806,7 +883,7 @@ hzp_status_t launch_fused(const hzp_plan_t *plan, bool g32, bool o32, uint32_t R
         groups += (r.n + kGroupElems - 1) / kGroupElems;
     }
     FusedArgs a;                // the words a launch uses are all written below
-    if (lookup) {
+    if (!plan->uniform_wd) {
         const DeviceTables *tab = nullptr;
         hzp_status_t st = device_tables(plan, &tab);
         if (st != HZP_OK) return st;
@@ -1093,6 +1170,102 @@ hzp_status_t launch_concat_ranges(const void *const *srcs, const uint64_t *dst_o
     return check_launch("hzp_gather_shard");
 }
 
+// A run of elements to move; with a bucket beside the tensors, its place there and its length with the padding behind it.
+struct Part {
+    uint64_t src, dst, n, bucket, n_bucket;
+    uint64_t length() const { return std::max(n, n_bucket); }
+};
+constexpr uint64_t kMostInPart = 1ull << 30;        // (a part's length has 32 bits)
+
+// One launch over parts, cut into runs of at most `cut` elements.
+template <class Args, int ES>
+static hzp_status_t unpack_list(const Part *parts, size_t n, uint64_t cut, hipStream_t stream, const char *who)
+{
+    Args a;
+    uint32_t cnt = 0, tiles = 0;
+    uint64_t longest = 0;
+    for (size_t i = 0; i < n; ++i) {
+        const Part &p = parts[i];
+        for (uint64_t at = 0; at < p.length(); at += cut) {
+            const uint64_t len = std::min(p.length() - at, cut);
+            a.src[cnt] = p.src + at * ES;
+            a.dst[cnt] = p.dst + at * ES;
+            a.n[cnt] = (uint32_t)(p.n > at ? std::min(p.n - at, cut) : 0);
+            if constexpr (Args::kBoth) {
+                a.bucket[cnt] = p.bucket + at * ES;
+                a.n_bucket[cnt] = (uint32_t)len;
+            }
+            // (a part with an unaligned destination has fewer whole vectors, never more)
+            if constexpr (Args::kFlat) a.tile_end[cnt] = tiles += (uint32_t)std::max<uint64_t>(1, tiles_of(len * ES / 16));
+            longest = std::max(longest, len);
+            ++cnt;
+        }
+    }
+    dim3 grid((uint32_t)std::max<uint64_t>(1, tiles_of(longest * ES / 16)), cnt);
+    if constexpr (Args::kFlat) {
+        std::fill(a.tile_end + cnt, std::end(a.tile_end), ~0u);
+        grid = dim3(tiles);
+    }
+    hipLaunchKernelGGL((unpack_list_kernel<ES, Args>), grid, dim3(kWave), 0, stream, a);
+    return check_launch(who);
+}
+
+// Launches over a list of parts: each takes parts while they fit its table and hold no more than kMaxTilesPerLaunch tiles.
+template <int ES>
+static hzp_status_t unpack_parts(const Part *parts, size_t n, bool both, hipStream_t stream, const char *who)
+{
+    constexpr uint64_t kTile = kWave * 16 / ES;     // elements of a tile
+    const size_t cap = both ? UnpackBoth124::kParts : UnpackList200::kParts;
+    const size_t cap_flat = both ? UnpackBothFlat108::kParts : UnpackFlat160::kParts;
+    for (size_t at = 0; at < n;) {
+        const Part *const first = parts + at;
+        size_t cnt = 0;
+        uint64_t total = 0, longest = 0;
+        auto take = [&](size_t most) {
+            cnt = 0;
+            total = longest = 0;
+            while (at + cnt < n && cnt < most) {
+                const uint64_t len = first[cnt].length();
+                if (cnt > 0 && (total + len) / kTile > kMaxTilesPerLaunch) break;
+                total += len;
+                longest = std::max(longest, len);
+                ++cnt;
+            }
+        };
+        take(cap);
+        const bool even = longest * cnt <= total + std::max(total / 16, 256 * kTile);
+        uint64_t cut = 0;           // 0: a flat grid
+        if (even) {
+            cut = longest;
+        } else if (cnt <= cap / 9) {                // cut at an eighth more than total / cap, they fill the table
+            cut = (total + (cap - cnt) - 1) / (cap - cnt);
+            cut = std::min(longest, (cut + kTile - 1) / kTile * kTile);
+        } else if (cnt > cap_flat) {
+            take(cap_flat);
+        }
+        hzp_status_t st;
+        if (both)
+            st = cut                   ? unpack_list<UnpackBoth124, ES>(first, cnt, cut, stream, who)
+                 : cnt <= 64           ? unpack_list<UnpackBothFlat64, ES>(first, cnt, longest, stream, who)
+                                       : unpack_list<UnpackBothFlat108, ES>(first, cnt, longest, stream, who);
+        else
+            st = !cut                  ? (cnt <= 64 ? unpack_list<UnpackFlat64, ES>(first, cnt, longest, stream, who)
+                                                    : unpack_list<UnpackFlat160, ES>(first, cnt, longest, stream, who))
+                 : even && cnt <= 8    ? unpack_list<UnpackList8, ES>(first, cnt, cut, stream, who)
+                 : even && cnt <= 72   ? unpack_list<UnpackList72, ES>(first, cnt, cut, stream, who)
+                                       : unpack_list<UnpackList200, ES>(first, cnt, cut, stream, who);
+        if (st != HZP_OK) return st;
+        at += cnt;
+    }
+    return HZP_OK;
+}
+
+static hzp_status_t unpack_parts(const BucketRec &b, const std::vector<Part> &parts, bool both, hipStream_t stream)
+{
+    return b.cls == HZP_CLASS_F32 ? unpack_parts<4>(parts.data(), parts.size(), both, stream, "hzp_gather_layer")
+                                  : unpack_parts<2>(parts.data(), parts.size(), both, stream, "hzp_gather_layer");
+}
+
 // What the launches of one unpacking call share.
 struct UnpackCall {
     const Piece *pieces;                // device tables that hold the bucket's pieces from entry 0
@@ -1104,10 +1277,9 @@ struct UnpackCall {
 };
 
 // One launch: tensors [t0, t1), whose pieces are [p0, p1).
-template <class Args>
 static void start_unpack(const UnpackCall &u, void *const *tensors, uint32_t t0, uint32_t t1, size_t p0, size_t p1)
 {
-    Args a;
+    UnpackArgs a;
     a.pieces = u.pieces;
     a.piece_chunk = u.piece_chunk;
     a.n_pieces = (uint32_t)u.b.pieces.size();
@@ -1118,9 +1290,16 @@ static void start_unpack(const UnpackCall &u, void *const *tensors, uint32_t t0,
     for (uint32_t t = t0; t < t1; ++t) a.tensor[t - t0] = tensors[t - t0];
     const dim3 grid(a.chunk_end - a.chunk0), block(kWave);
     if (u.b.cls == HZP_CLASS_F32)
-        hipLaunchKernelGGL((unpack_kernel<4, Args>), grid, block, 0, u.stream, a);
+        hipLaunchKernelGGL(unpack_kernel<4>, grid, block, 0, u.stream, a);
     else
-        hipLaunchKernelGGL((unpack_kernel<2, Args>), grid, block, 0, u.stream, a);
+        hipLaunchKernelGGL(unpack_kernel<2>, grid, block, 0, u.stream, a);
+}
+
+// First piece at or behind `from` of a tensor or a later one (pieces are sorted by tensor).
+static size_t first_piece(const BucketRec &b, size_t from, uint32_t tensor)
+{
+    return (size_t)(std::lower_bound(b.pieces.begin() + from, b.pieces.end(), tensor,
+                                     [](const Piece &p, uint32_t t) { return p.tensor < t; }) - b.pieces.begin());
 }
 
 // Launches of the unpack kernel for tensors [t_begin, t_end) of a bucket.
@@ -1128,22 +1307,11 @@ static hzp_status_t launch_unpack_with(const UnpackCall &u, void *const *tensors
                                        const char *who)
 {
     // Tensors travel in the argument block, kUnpackTensorCap at a time; pieces are sorted by tensor.
-    const std::vector<Piece> &pieces = u.b.pieces;
-    auto first_of = [&](size_t from, uint32_t t) {
-        return (size_t)(std::lower_bound(pieces.begin() + from, pieces.end(), t,
-                                         [](const Piece &p, uint32_t x) { return p.tensor < x; }) - pieces.begin());
-    };
-    size_t p0 = first_of(0, t_begin);
+    size_t p0 = first_piece(u.b, 0, t_begin);
     for (uint32_t t0 = t_begin; t0 < t_end; t0 += kUnpackTensorCap) {
-        const uint32_t t1 = std::min<uint32_t>(t_end, t0 + kUnpackTensorCap), n = t1 - t0;
-        const size_t p1 = first_of(p0, t1);
-        void *const *at = tensors + (t0 - t_begin);
-        if (n <= (uint32_t)UnpackFewArgs::kTensors && u.n_shards <= (uint32_t)UnpackFewArgs::kShards)
-            start_unpack<UnpackFewArgs>(u, at, t0, t1, p0, p1);
-        else if (n <= (uint32_t)UnpackSomeArgs::kTensors && u.n_shards <= (uint32_t)UnpackSomeArgs::kShards)
-            start_unpack<UnpackSomeArgs>(u, at, t0, t1, p0, p1);
-        else
-            start_unpack<UnpackManyArgs>(u, at, t0, t1, p0, p1);
+        const uint32_t t1 = std::min<uint32_t>(t_end, t0 + kUnpackTensorCap);
+        const size_t p1 = first_piece(u.b, p0, t1);
+        start_unpack(u, tensors + (t0 - t_begin), t0, t1, p0, p1);
         hzp_status_t st = check_launch(who);
         if (st != HZP_OK) return st;
         p0 = p1;
@@ -1155,11 +1323,76 @@ hzp_status_t launch_unpack(const hzp_plan_t *plan, const BucketRec &b, const voi
                            uint32_t n_shards, void *const *tensors, uint32_t t_begin, uint32_t t_end,
                            hipStream_t stream)
 {
+    const size_t p0 = first_piece(b, 0, t_begin), p1 = first_piece(b, p0, t_end), n = p1 - p0;
+    const uint32_t es = b.cls == HZP_CLASS_F32 ? 4 : 2;
+    const DeviceTables *tab = nullptr;
+    const hzp_status_t st = device_tables(plan, &tab);
+    if (st != HZP_OK) return st;
+    uint64_t total = 0;
+    for (size_t i = p0; i < p1; ++i) total += b.pieces[i].len;
+    if (n > (size_t)UnpackList200::kParts && total / n < 4096) {        // 200 parts of so few elements do not fill the chip
+        const UnpackCall u{tab->pieces + b.piece_slot, tab->piece_chunk + b.piece_slot, b, shards, n_shards, stream};
+        return launch_unpack_with(u, tensors, t_begin, t_end, "hzp_gather_layer");
+    }
+    std::vector<Part> parts;
+    try {
+        parts.reserve(n);
+        for (size_t i = p0; i < p1; ++i) {
+            const Piece &p = b.pieces[i];
+            const uint64_t src = reinterpret_cast<uint64_t>(shards[p.shard]) + p.src_off * es;
+            const uint64_t dst = reinterpret_cast<uint64_t>(tensors[p.tensor - t_begin]) + p.dst_off * es;
+            for (uint64_t x = 0; x < p.len; x += kMostInPart)
+                parts.push_back({src + x * es, dst + x * es, std::min(p.len - x, kMostInPart), 0, 0});
+        }
+    } catch (const std::bad_alloc &) {
+        return fail(HZP_ERR_NOMEM, "hzp_gather_layer: out of host memory");
+    }
+    return unpack_parts(b, parts, false, stream);
+}
+
+hzp_status_t launch_unpack_both(const hzp_plan_t *plan, const BucketRec &b, const void *const *shards, uint32_t n_shards,
+                                void *bucket, void *const *tensors, hipStream_t stream)
+{
+    const uint32_t es = b.cls == HZP_CLASS_F32 ? 4 : 2;
+    const uint64_t out = reinterpret_cast<uint64_t>(bucket);
+    // One pass serves both outputs where what is aligned in the shard is aligned in the tensor too and no shard lies in
+    // place; not for so many small tensors that it would take more launches than the two passes.
+    bool one_pass = b.pieces.size() + n_shards <= (size_t)UnpackBothFlat108::kParts || b.P / b.pieces.size() >= (1u << 20);
+    for (uint32_t t = 0; t < b.n_tensors; ++t) one_pass = one_pass && (reinterpret_cast<uint64_t>(tensors[t]) & 15u) == 0;
+    for (uint32_t j = 0; j < n_shards; ++j) one_pass = one_pass && reinterpret_cast<uint64_t>(shards[j]) != out + j * b.S3 * es;
     const DeviceTables *tab = nullptr;
     hzp_status_t st = device_tables(plan, &tab);
     if (st != HZP_OK) return st;
-    const UnpackCall u{tab->pieces + b.piece_slot, tab->piece_chunk + b.piece_slot, b, shards, n_shards, stream};
-    return launch_unpack_with(u, tensors, t_begin, t_end, "hzp_gather_layer");
+    if (!one_pass) {
+        st = launch_concat(shards, n_shards, b.S3 * es, bucket, stream);
+        if (st != HZP_OK) return st;
+        return launch_unpack(plan, b, shards, n_shards, tensors, 0, b.n_tensors, stream);
+    }
+    // The bucket shard by shard: tensor pieces with the padding behind them, and padding that a shard begins with.
+    std::vector<Part> parts;
+    auto add = [&](uint32_t j, uint64_t begin, uint64_t end, uint64_t tensor, uint64_t n) {     // [begin, end) of shard j
+        const uint64_t src = reinterpret_cast<uint64_t>(shards[j]) + begin * es, dst = out + (j * b.S3 + begin) * es;
+        for (uint64_t x = 0; x < end - begin; x += kMostInPart)
+            parts.push_back({src + x * es, tensor + x * es, n > x ? std::min(n - x, kMostInPart) : 0, dst + x * es,
+                             std::min(end - begin - x, kMostInPart)});
+    };
+    try {
+        parts.reserve(b.pieces.size() + n_shards);
+        size_t i = 0;
+        for (uint32_t j = 0; j < n_shards; ++j) {
+            const uint64_t first = i < b.pieces.size() && b.pieces[i].shard == j ? b.pieces[i].src_off : b.S3;
+            if (first > 0) add(j, 0, first, out, 0);
+            for (; i < b.pieces.size() && b.pieces[i].shard == j; ++i) {
+                const Piece &p = b.pieces[i];
+                const bool last = i + 1 == b.pieces.size() || b.pieces[i + 1].shard != j;
+                add(j, p.src_off, last ? b.S3 : b.pieces[i + 1].src_off, reinterpret_cast<uint64_t>(tensors[p.tensor]) + p.dst_off * es,
+                    p.len);
+            }
+        }
+    } catch (const std::bad_alloc &) {
+        return fail(HZP_ERR_NOMEM, "hzp_gather_layer: out of host memory");
+    }
+    return unpack_parts(b, parts, true, stream);
 }
 
 // ---------------------------------------------------------------------------------------

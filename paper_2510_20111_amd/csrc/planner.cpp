@@ -141,6 +141,7 @@ extern "C" hzp_status_t hzp_plan(const hzp_plan_desc_t *d, hzp_plan_t **out)
         p->z1 = d->z1;
         p->K = d->z1 % d->z3 == 0 ? d->z1 / d->z3 : 0;
         p->world = (uint32_t)world;
+        p->uniform_wd = true;
         p->tensors.resize(n_tensors);
         p->bucket_of.assign((size_t)d->n_layers * 2, -1);
         const uint64_t quantum = (uint64_t)A * world;     // every level's shard is a multiple of A
@@ -164,6 +165,7 @@ extern "C" hzp_status_t hzp_plan(const hzp_plan_desc_t *d, hzp_plan_t **out)
                     r.offset = off;
                     r.numel = d->tensor_numel[t];
                     r.wd_mult = d->tensor_wd_mult ? d->tensor_wd_mult[t] : 1.0f;
+                    if (r.wd_mult != 1.0f) p->uniform_wd = false;
                     if (__builtin_add_overflow(off, r.numel, &payload_end) ||
                         !round_up(payload_end, A, &off)) {
                         delete p;

@@ -31,6 +31,11 @@ hzp_status_t launch_unpack(const hzp_plan_t *, const BucketRec &, const void *co
 {
     return no_gpu("launch_unpack");
 }
+hzp_status_t launch_unpack_both(const hzp_plan_t *, const BucketRec &, const void *const *, uint32_t, void *, void *const *,
+                                hipStream_t)
+{
+    return no_gpu("launch_unpack_both");
+}
 hzp_status_t launch_unpack_static(const BucketRec &, const void *const *, uint32_t, void *const *, hipStream_t)
 {
     return no_gpu("launch_unpack_static");

@@ -159,3 +159,43 @@ def test_post_step_gather_of_many_layers_in_every_placement(place, layers, K, ow
     torch.cuda.synchronize()
     for i in range(layers):
         assert np.array_equal(whole[i].cpu().numpy(), want[i]), i
+
+
+@pytest.mark.parametrize("cls", [0, 1])
+@pytest.mark.parametrize("shift", [0, 1, 4])
+@pytest.mark.parametrize("name,numel,z3", [("few", [5000, 64, 5000], 1), ("edges", [1, 7, 8, 9, 511, 512, 513, 4096, 70001], 3),
+                                           ("lopsided", [3000001] + [40] * 60, 4), ("many", [9000] * 260, 2), ("tiny", [3] * 450, 2),
+                                           ("one", [1234567], 8)])
+def test_tensors_and_bucket_in_one_pass_or_two(name, numel, z3, shift, cls):
+    """The unpacking gather alone, with the bucket beside it and for one tensor at a time; tensors that start on a 16-byte
+    boundary (one pass serves both outputs), an element and half a vector behind one."""
+    print(name, z3, shift, cls, flush=True)
+    plan = hzp.hzp_plan([len(numel)], numel, align=8, z3=z3, z1=z3, tensor_class=[cls] * len(numel))
+    info = plan.bucket(0, cls)
+    dt = torch.int32 if cls else torch.int16
+    gen = torch.Generator(device=DEV).manual_seed(len(numel) + shift)
+    bucket = torch.randint(-30000, 30000, (info.padded,), dtype=dt, device=DEV, generator=gen)
+    shards = [bucket[j * info.s3:(j + 1) * info.s3].clone() for j in range(z3)]
+    places, at = [], 16
+    for n in numel:
+        places.append(at + shift)
+        at += -(-(n + 24) // 16) * 16
+    want = torch.full((at,), 77, dtype=dt, device=DEV)
+    for t, (n, place) in enumerate(zip(numel, places)):
+        off = plan.tensor(t).offset
+        want[place:place + n] = bucket[off:off + n]
+
+    def views(flat):
+        return [flat[place:place + n] for n, place in zip(numel, places)]
+    alone, beside, single = (torch.full((at,), 77, dtype=dt, device=DEV) for _ in range(3))
+    whole = torch.full((info.padded + 32,), 77, dtype=dt, device=DEV)
+    hzp.hzp_gather_layer(plan, 0, cls, 3, shards, None, views(alone))
+    hzp.hzp_gather_layer(plan, 0, cls, 3, shards, whole[16:16 + info.padded], views(beside))
+    for t in range(0, len(numel), max(1, len(numel) // 40)):
+        hzp.hzp_gather_tensor(plan, t, shards, views(single)[t])
+        views(want)[t].eq(views(single)[t]).all().item() or pytest.fail("tensor %d" % t)
+    torch.cuda.synchronize()
+    assert torch.equal(alone, want)
+    assert torch.equal(beside, want)
+    assert torch.equal(whole[16:16 + info.padded], bucket)
+    assert bool((whole[:16] == 77).all()) and bool((whole[16 + info.padded:] == 77).all())
