@@ -754,6 +754,23 @@ def fused_launch_count(w):
     return count + (1 if cnt else 0)
 
 
+COPY_MAX_TILES = 600000         # 1 KiB tiles one launch of the layer-range gather covers at most
+
+
+def gather1_launches(w):
+    """(kernel, launches) of the layer-range gather of all layers: whole layers (up to 204) where there are more than 192
+    pieces and they lie at equal distances in every source (the arena's do), otherwise whole pieces (up to 192)."""
+    shared = w.n_layers * w.K > 192 and w.layout != "separate"
+    tiles = [-(-2 * b.s1 // 1024) for b in w.buckets]
+    units = [t * w.K for t in tiles] if shared else [t for t in tiles for _ in range(w.K)]
+    count, cnt, total = 1, 0, 0
+    for t in units:
+        if cnt == (204 if shared else 192) or (cnt > 0 and total + t > COPY_MAX_TILES):
+            count, cnt, total = count + 1, 0, 0
+        cnt, total = cnt + 1, total + t
+    return "copy_shared_kernel" if shared else "copy_list_kernel", count
+
+
 def roofline_entry(np, kernel, algo_bytes, ms, launches, key, step_kernel_ms=None, per_step=None):
     """One kernel's roofline object: `ms` is the average time of its `launches` launches in a step (or
     secondary pass), `algo_bytes` what they move together; `per_step` the same time for each timed step."""
@@ -834,15 +851,15 @@ def time_workload(idx, args, torch, np, hzp, hzp_inputs, steps, warmup, keep=Fal
             "avg_launch_us": round(alone_ms / fused_launches * 1e3, 2), "calls": alone}
     if "gather1" in phases:
         if w.l1_per_layer:
-            rooflines["gather_level1"] = roof("concat_kernel (K=%d x S1 -> S3)" % w.K, g1_bytes, g1_ms,
-                                              w.n_layers, "concat_l1_%s" % cfg["name"], ph[:, 1])
+            rooflines["gather_level1"] = roof("copy_list_kernel (K=%d x S1 -> S3)" % w.K, g1_bytes, g1_ms,
+                                              w.n_layers, "gather_l1_per_layer_%s" % cfg["name"], ph[:, 1])
         else:
-            pieces = w.n_layers * w.K               # one launch of the layer-range gather holds 192 pieces
-            rooflines["gather_level1"] = roof("concat_layers_kernel (all layers, K=%d x S1 -> S3)" % w.K, g1_bytes,
-                                              g1_ms, -(-pieces // 192), "concat_layers_l1_%s" % cfg["name"], ph[:, 1])
+            kernel, launches = gather1_launches(w)
+            rooflines["gather_level1"] = roof("%s (all layers, K=%d x S1 -> S3)" % (kernel, w.K), g1_bytes, g1_ms, launches,
+                                              "gather_l1_%s" % cfg["name"], ph[:, 1])
     if "gather3" in phases:
-        rooflines["gather_level3"] = roof("concat_kernel (Z3=%d x S3 -> P)" % w.z3, g3_bytes, g3_ms,
-                                          w.n_layers, "concat_l3_%s" % cfg["name"], ph[:, 2])
+        rooflines["gather_level3"] = roof("copy_list_kernel (Z3=%d x S3 -> P)" % w.z3, g3_bytes, g3_ms,
+                                          w.n_layers, "gather_l3_%s" % cfg["name"], ph[:, 2])
     # the launch-bound workloads also as one captured step replayed (context; the timed steps are issued call by call)
     graph = None
     if cfg["name"] in ("tiny", "irregular") and phases == {"fused", "gather1", "gather3"} and steps >= 10:
@@ -966,14 +983,14 @@ def main():
                       "f32class": lambda: (28 + 4 * R) * w.s1_total,
                       "perlayer": lambda: fused_bytes, "freegroups": lambda: 4 * w.free_s3_total,
                       "prereduced": lambda: 30 * w.s1_total}[phase]()
-            kname = {"unpack": "unpack_kernel<2>", "reduce": "reduce_kernel<bf16,R=%d>" % R,
+            kname = {"unpack": "unpack_list_kernel<2>", "reduce": "reduce_kernel<bf16,R=%d>" % R,
                      "accumulate": "reduce_kernel<f32,R=%d,accumulate>" % R,
                      "inplace": "fused update writing into the ZeRO-3 shard + level-1 gather of the other %d pieces" % (w.K - 1),
                      "notinplace": "fused update + level-1 gather of all %d pieces" % w.K,
                      "f32class": "fused_adamw_kernel<R=%d, fp32 gradients, fp32 output> (class F32 on the same shapes)" % R,
                      "perlayer": "fused_adamw_kernel<R=%d,bf16>, one call per layer" % R,
                      "prereduced": "fused_adamw_kernel<R=1,f32 gradient> (update from a reduced fp32 shard)",
-                     "freegroups": "concat_ranges_kernel (Z1=%d over Z3=%d: ZeRO-3 shard from partial owners)"
+                     "freegroups": "copy_ranges_kernel (Z1=%d over Z3=%d: ZeRO-3 shard from partial owners)"
                                    % (getattr(w, "free_z1", 0), w.z3)}[phase]
             launches = fused_launches if phase in ("prereduced", "f32class") else 1 if phase in ("inplace", "notinplace") else w.n_layers
             result["secondary"][phase] = roof(kname, nbytes, ms, launches, "%s_%s" % (phase, cfg["name"]))

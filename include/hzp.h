@@ -367,8 +367,9 @@ hzp_status_t hzp_arena_tune(const hzp_plan_t *plan, uint32_t cls, uint32_t rank,
  * address of piece s inside bucket_out (bucket_out + s * shard bytes) -- the case of a rank whose
  * update wrote its parameters straight into its ZeRO-3 shard -- is not copied and costs nothing; this
  * holds for hzp_gather_layers and the scheduler's gathers as well.  Any other overlap of outputs and
- * inputs is not detected and gives undefined contents.  With both outputs the shards are read twice
- * (one copy kernel per output).
+ * inputs is not detected and gives undefined contents.  With both outputs the shards are read once where
+ * every tensor starts on a multiple of 16 bytes, no shard lies in place, and the bucket has at most about 100 pieces or
+ * pieces of a million elements; otherwise once per output.
  * Errors: INVALID_ARG (n_shards mismatch, no output, tensor_out at level 1), RANGE, UNSUPPORTED
  * (more than HZP_MAX_GROUP shards; level 1 on a plan whose z3 does not divide z1 -- use
  * hzp_gather_shard), ALIGN, NOMEM, HIP.
@@ -399,8 +400,8 @@ hzp_status_t hzp_gather_layer_static(const hzp_plan_t *plan, uint32_t layer, uin
                                      void *const *tensor_out, hipStream_t stream);
 
 /* ------------------------------------------------------------------------------------------
- * hzp_gather_layer's bucket output for a range of layers in one call (one kernel launch for up
- * to 40 layers): the post-step gather of Section 4.1.2 runs for every layer at once, and many
+ * hzp_gather_layer's bucket output for a range of layers in one call (a kernel launch holds up to 192
+ * pieces, or 204 layers whose pieces lie at equal distances in every source, and about 600 MB): the post-step gather of Section 4.1.2 runs for every layer at once, and many
  * small launches leave the memory system idle between them.
  *   shard_ptrs : host array [(layer_end-layer_begin) * n_shards]; entry (l*n_shards + s) is shard s
  *                of layer layer_begin+l, as in hzp_gather_layer; entries of layers that have no

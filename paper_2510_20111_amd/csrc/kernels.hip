@@ -520,19 +520,20 @@ __global__ __launch_bounds__(kWave) void copy_shared_kernel(const CopySharedArgs
 // The same copy for pieces of different lengths (a ZeRO-3 shard rebuilt from whole and partial
 // ZeRO-1 shards when the group sizes do not nest).  One-dimensional grid over the 64-vector tiles
 // of all pieces, so no workgroup is launched for nothing; a workgroup counts the pieces that end at or before
-// its tile, eight to a scalar load (unused entries are never reached).
-struct ConcatRangesArgs {
-    uint32_t tile_end[HZP_MAX_GROUP];       // running count of tiles up to and including the piece
-    const void *src[HZP_MAX_GROUP];         // first vector to read of each piece
-    uint32_t dst_vec[HZP_MAX_GROUP];        // where it goes, in 16-byte vectors from dst
-    uint32_t nvec[HZP_MAX_GROUP];
-    u32x4 *dst;
+// its tile, eight to a scalar load.
+template <int PIECES>
+struct CopyRangesArgs {
+    static constexpr int kPieces = PIECES;
+    uint32_t tile_end[PIECES];              // running count of tiles up to and including the piece; ~0 behind the last
+    uint64_t src[PIECES], dst[PIECES];
+    uint32_t nvec[PIECES];
     uint32_t n;
 };
-__global__ __launch_bounds__(kWave) void concat_ranges_kernel(const ConcatRangesArgs a)
+template <class Args>
+__global__ __launch_bounds__(kWave) void copy_ranges_kernel(const Args a)
 {
     uint32_t s = 0, first = 0;              // the workgroup's piece and its first tile
-    for (uint32_t i = 0; i < a.n; i += 8) {
+    for (uint32_t i = 0; i < (Args::kPieces == 8 ? 8u : a.n); i += 8) {
 #pragma unroll
         for (uint32_t k = 0; k < 8; ++k)
             if (blockIdx.x >= a.tile_end[i + k]) {
@@ -540,10 +541,10 @@ __global__ __launch_bounds__(kWave) void concat_ranges_kernel(const ConcatRanges
                 first = a.tile_end[i + k];
             }
     }
-    uint64_t src = reinterpret_cast<uint64_t>(a.src[s]), dst = reinterpret_cast<uint64_t>(a.dst);
-    uint32_t nvec = a.nvec[s], dst_vec = a.dst_vec[s];
-    pin(src, dst, nvec, dst_vec);
-    copy_tile(blockIdx.x - first, src, dst + (uint64_t)dst_vec * 16, nvec);
+    uint64_t src = a.src[s], dst = a.dst[s];
+    uint32_t nvec = a.nvec[s];
+    pin(src, dst, nvec);
+    copy_tile(blockIdx.x - first, src, dst, nvec);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1015,7 +1016,7 @@ static hzp_status_t copy_list(const Move *moves, size_t n, hipStream_t stream, c
     return check_launch(who);
 }
 
-// Most tiles of 64 vectors in one launch of a copy (600 MB, about 180 us).  Over a longer launch the XCDs drift apart, as in the
+// Most tiles of 64 vectors in one launch of a copy of many pieces (600 MB, about 180 us).  Over a longer launch the XCDs drift apart, as in the
 // update; shorter ones lose to the gaps.  Post-step gather of 2.95 GB, launches of 100 / 200 / 400 / 600 / 800 / 1200 k tiles and
 // one for all: 6.59 / 6.71 / 6.77 / 6.77 / 6.76 / 6.71 / 6.70 TB/s.
 constexpr uint64_t kMaxTilesPerLaunch = 600000;
@@ -1025,7 +1026,7 @@ static uint64_t tiles_of(uint64_t nvec) { return (nvec + kWave - 1) / kWave; }
 // (a grid holds fewer than 2^32 threads per dimension: one thread per vector, rounded up to whole wavefronts)
 constexpr uint64_t kMostVectors = 0xFFFFFFFFull - kWave;
 
-// Launches over a list of pieces: whole pieces, kMaxTilesPerLaunch tiles at most (or one piece).
+// Launches over the pieces of many layers: whole pieces, kMaxTilesPerLaunch tiles at most (or one piece).
 static hzp_status_t copy_moves(const Move *moves, size_t n, hipStream_t stream, const char *who)
 {
     for (size_t at = 0; at < n;) {
@@ -1056,7 +1057,10 @@ hzp_status_t launch_concat(const void *const *srcs, uint32_t n_shards, uint64_t 
         const uint64_t from = reinterpret_cast<uint64_t>(srcs[s]), to = reinterpret_cast<uint64_t>(dst) + s * bytes_per_shard;
         if (from != to) moves[n++] = {from, to, nvec};          // else it lies in place
     }
-    return copy_moves(moves, n, stream, "hzp_gather_layer");
+    // (one bucket's pieces stay one launch: cut into launches, 1.7-2.3 GB buckets copy no faster)
+    if (n == 0) return HZP_OK;
+    if (n <= (size_t)CopyFewArgs::kPieces) return copy_list<CopyFewArgs>(moves, n, stream, "hzp_gather_layer");
+    return copy_list<CopyManyArgs>(moves, n, stream, "hzp_gather_layer");
 }
 
 // Layers whose pieces lie at equal distances, in launches of kSharedLayers; *done is false (and nothing launched) where
@@ -1142,32 +1146,42 @@ hzp_status_t launch_concat_layers(const void *const *srcs, uint32_t per_layer, c
     return copy_moves(moves.data(), moves.size(), stream, "hzp_gather_layers");
 }
 
+template <class Args>
+static hzp_status_t copy_ranges(const Move *moves, uint32_t n, uint32_t tiles, hipStream_t stream)
+{
+    Args a;
+    std::fill(std::begin(a.tile_end), std::end(a.tile_end), ~0u);
+    a.n = n;
+    uint32_t end = 0;
+    for (uint32_t s = 0; s < n; ++s) {
+        a.src[s] = moves[s].src;
+        a.dst[s] = moves[s].dst;
+        a.nvec[s] = (uint32_t)moves[s].nvec;
+        a.tile_end[s] = end += (uint32_t)tiles_of(moves[s].nvec);
+    }
+    hipLaunchKernelGGL(copy_ranges_kernel<Args>, dim3(tiles), dim3(kWave), 0, stream, a);
+    return check_launch("hzp_gather_shard");
+}
+
 hzp_status_t launch_concat_ranges(const void *const *srcs, const uint64_t *dst_off, const uint64_t *bytes,
                                   uint32_t n, void *dst, hipStream_t stream)
 {
-    ConcatRangesArgs a;
-    std::fill(std::begin(a.tile_end), std::end(a.tile_end), 0xFFFFFFFFu);
+    Move moves[HZP_MAX_GROUP];
     uint64_t tiles = 0, total = 0;
     bool uniform = true;
     for (uint32_t s = 0; s < n; ++s) {
-        if (bytes[s] / 16 > 0xFFFFFFFFull - kWave || dst_off[s] / 16 > 0xFFFFFFFFull)
+        if (bytes[s] / 16 > kMostVectors || dst_off[s] / 16 > 0xFFFFFFFFull)
             return fail(HZP_ERR_UNSUPPORTED, "hzp_gather_shard: shard larger than 64 GiB");
-        a.src[s] = srcs[s];
-        a.dst_vec[s] = (uint32_t)(dst_off[s] / 16);
-        a.nvec[s] = (uint32_t)(bytes[s] / 16);
-        tiles += (bytes[s] / 16 + kWave - 1) / kWave;
-        a.tile_end[s] = (uint32_t)tiles;           // checked below
+        moves[s] = {reinterpret_cast<uint64_t>(srcs[s]), reinterpret_cast<uint64_t>(dst) + dst_off[s], bytes[s] / 16};
+        tiles += tiles_of(moves[s].nvec);
         uniform = uniform && bytes[s] == bytes[0] && dst_off[s] == s * bytes[0];
         total += bytes[s];
     }
     if (total == 0) return HZP_OK;
     if (uniform) return launch_concat(srcs, n, bytes[0], dst, stream);     // equal whole pieces
     if (tiles > 0x7FFFFFFFull) return fail(HZP_ERR_UNSUPPORTED, "hzp_gather_shard: shard too large for one launch");
-    a.dst = reinterpret_cast<u32x4 *>(dst);
-    a.n = n;
-    const dim3 grid((uint32_t)tiles), block(kWave);
-    hipLaunchKernelGGL(concat_ranges_kernel, grid, block, 0, stream, a);
-    return check_launch("hzp_gather_shard");
+    if (n <= 8) return copy_ranges<CopyRangesArgs<8>>(moves, n, (uint32_t)tiles, stream);
+    return copy_ranges<CopyRangesArgs<HZP_MAX_GROUP>>(moves, n, (uint32_t)tiles, stream);
 }
 
 // A run of elements to move; with a bucket beside the tensors, its place there and its length with the padding behind it.
