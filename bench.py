@@ -758,17 +758,25 @@ COPY_MAX_TILES = 600000         # 1 KiB tiles one launch of the layer-range gath
 
 
 def gather1_launches(w):
-    """(kernel, launches) of the layer-range gather of all layers: whole layers (up to 204) where there are more than 192
-    pieces and they lie at equal distances in every source (the arena's do), otherwise whole pieces (up to 192)."""
+    """(kernel, launches) of the layer-range gather of all layers, longest first: whole layers (up to 204) where there are more than
+    192 pieces and they lie at equal distances in every source (the arena's do), otherwise whole pieces (up to 192)."""
     shared = w.n_layers * w.K > 192 and w.layout != "separate"
-    tiles = [-(-2 * b.s1 // 1024) for b in w.buckets]
-    units = [t * w.K for t in tiles] if shared else [t for t in tiles for _ in range(w.K)]
-    count, cnt, total = 1, 0, 0
-    for t in units:
-        if cnt == (204 if shared else 192) or (cnt > 0 and total + t > COPY_MAX_TILES):
-            count, cnt, total = count + 1, 0, 0
-        cnt, total = cnt + 1, total + t
-    return "copy_shared_kernel" if shared else "copy_list_kernel", count
+    rows, most = (w.K, 204) if shared else (1, 192)
+    left = sorted((-(-2 * b.s1 // 1024) * rows for b in w.buckets for _ in range(1 if shared else w.K)), reverse=True)
+    launches = 0
+    while left:
+        # all that fit, unless too many workgroups have nothing to do; then those of about equal length
+        for each, last in ((float("inf"), 24576), (8192, 8192)):
+            cnt = tiles = 0
+            while cnt < min(len(left), most):
+                total = tiles + left[cnt]
+                if cnt and (total > COPY_MAX_TILES or left[0] * (cnt + 1) - total > total // 8 + each):
+                    break
+                cnt, tiles = cnt + 1, total
+            if left[0] * cnt - tiles <= tiles // 8 + last:
+                break
+        left, launches = left[cnt:], launches + 1
+    return "copy_shared_kernel" if shared else "copy_list_kernel", launches
 
 
 def roofline_entry(np, kernel, algo_bytes, ms, launches, key, step_kernel_ms=None, per_step=None):

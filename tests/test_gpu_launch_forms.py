@@ -134,6 +134,30 @@ def test_reduction_of_every_number_of_contributions_at_group_edges(R, g32):
             assert bool((whole[n:] == 0.5).all())
 
 
+@pytest.mark.parametrize("place", ["own", "packed"])
+@pytest.mark.parametrize("layers,K", [(24, 16), (40, 4)])
+def test_post_step_gather_of_uneven_layers(place, layers, K):
+    """Two layers a thousand times the others: more launches than one, longest pieces first, in one list or with shared distances."""
+    print(place, layers, K, flush=True)
+    rng = np.random.default_rng(K)
+    numel = [2_000_000 if layer in (3, layers - 1) else int(rng.integers(1, 4000)) for layer in range(layers)]
+    plan = hzp.hzp_plan([1] * layers, numel, align=8, z3=1, z1=K)
+    sizes = [plan.bucket(layer).s1 for layer in range(layers)]
+    whole = [torch.full((n * K + 8,), -1, dtype=torch.int16, device=DEV) for n in sizes]
+    sources = [carve(sizes, torch.int16, place) for _ in range(K)]
+    want = [rng.integers(-30000, 30000, (K, n)).astype(np.int16) for n in sizes]
+    for i in range(layers):
+        for k in range(K):
+            sources[k][i].copy_(torch.from_numpy(want[i][k]))
+    hzp.hzp_gather_layers(plan, 0, layers, 0, 1, [sources[k][i] for i in range(layers) for k in range(K)], K,
+                          [w[:-8] for w in whole])
+    torch.cuda.synchronize()
+    for i in range(layers):
+        got = whole[i].cpu().numpy()
+        assert np.array_equal(got[:-8], want[i].reshape(-1)), i
+        assert (got[-8:] == -1).all()
+
+
 @pytest.mark.parametrize("place", ["own", "packed", "spread", "down"])
 @pytest.mark.parametrize("layers,K,own,ragged", [(30, 8, None, True), (30, 8, 3, True), (210, 4, 0, True), (250, 1, None, False),
                                                  (5, 64, 63, False), (3, 2, 1, True)])
