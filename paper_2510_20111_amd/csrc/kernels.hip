@@ -729,42 +729,65 @@ static constexpr std::array<void (*)(Args), sizeof...(I)> fused_kernels(std::ind
     return {fused_adamw_kernel<I + 1, G32, O32, FORM, FEW ? few_chunk(I + 1, fused_chunk(G32)) : fused_chunk(G32)>...};
 }
 
-// Wavefronts per CU for the reduction: what keeps about 48 KiB in flight per CU where the contributions fit one chunk,
-// 34 (bf16) or 38 (fp32) KiB where several chunks follow each other, and half as much again in a short launch (below
-// about 30 us), where filling and draining the chip weighs more than the order of the requests.  Measured at 25 M / 6.3 M
-// elements, TB/s with 28 wavefronts -> by this rule: bf16 R = 4 6.57 / 5.81 -> 6.64 / 5.80, R = 8 6.33 / 6.04 -> 6.59 / 6.05,
-// R = 16 6.31 / 6.10 -> 6.60 / 6.30; fp32 R = 4 (accumulating) 6.22 / 5.89 -> 6.30 / 5.89, R = 8 6.00 / 5.86 -> 6.49 / 6.09,
-// R = 16 5.77 / 5.87 -> 6.39 / 6.43.
+// Wavefronts per CU for the reduction: what keeps so many KiB in flight per CU.  Where the contributions fit one chunk 48; where
+// several chunks follow each other about 30, from what a wavefront asks for on average; in a short launch (below about
+// 30 us) half as much again, because there filling and draining the chip weighs more than the order of the requests.
+// Measured at 100 M elements, TB/s with 7 / 8 / 9 / 12 wavefronts: fp32 R = 8 6.83 / 7.00 / 6.84 / 6.61, R = 16 6.92 / 6.79 / 6.61 / 6.49,
+// accumulating 6.93 / 6.95 / 6.78 / 6.65 and 6.90 / 6.74 / 6.61 / 6.51; bf16 with 12 / 14 / 16 / 18 / 22: R = 6 5.54 / 6.35 / 6.74 /
+// 6.85 / 6.72, R = 8 accumulating (12 / 13 / 14 / 16 / 18) 6.70 / 6.80 / 6.73 / 6.54 / 6.45, R = 12 6.37 / 6.71 / 6.60 / 6.56 / 6.41,
+// R = 16 6.28 / 6.55 / 6.52 / 6.43 / 6.30, R = 32 6.07 / 6.32 / 6.40 / 6.29 / 6.11.
+// At 25 M / 6.3 M elements with 28 -> by this rule: bf16 R = 4 6.57 / 5.81 -> 6.64 / 5.80, R = 8 6.33 / 6.04 -> 6.59 / 6.05, R = 16
+// 6.31 / 6.10 -> 6.60 / 6.30; fp32 R = 4 (accumulating) 6.22 / 5.89 -> 6.30 / 5.89, R = 8 6.00 / 5.86 -> 6.49 / 6.09.
 static unsigned reduce_waves(bool g32, uint32_t R, uint64_t n, int accumulate)
 {
-    const uint32_t chunk = chunk_of(R, kReduceChunk), es = g32 ? 4u : 2u;
-    const unsigned budget = (chunk == R ? 48u : g32 ? 38u : 34u) * 1024u;
-    const unsigned wave = chunk * es * 256u * reduce_quads(R, g32) + (accumulate ? 512u : 0u);
-    const bool brief = n * (R * es + 4u) < (g32 ? 256u << 20 : 160u << 20);
     if (n <= 256u * 32u * 4u * kGroupQuads) return 0;                           // all resident at once
-    return std::min(28u, (brief ? budget * 3 / 2 : budget) / wave);
+    const uint32_t chunk = chunk_of(R, kReduceChunk), chunks = (R + chunk - 1) / chunk, es = g32 ? 4u : 2u;
+    const uint64_t bytes = n * (R * es + 4u);
+    const bool brief = bytes < (g32 ? 256u << 20 : 160u << 20);
+    const unsigned asked = (brief ? chunk * es * 256u : R * es * 256u / chunks) * reduce_quads(R, g32) + (accumulate ? 512u : 0u);
+    unsigned half_kib;
+    if (chunks == 1)
+        half_kib = brief ? 144 : 96;
+    else if (g32)
+        half_kib = brief ? 114 : R > 8 ? (accumulate ? 67 : 62) : accumulate ? 72 : 64;
+    else
+        half_kib = brief ? 102 : R <= 16 && bytes >= 1000000000u ? (accumulate ? 65 : 60) : 68;
+    return std::min(28u, half_kib * 512u / asked);
 }
+
+// Most bytes one launch of the reduction moves (0.45 / 0.9 ms); with more streams a drift of the XCDs (below) costs more.  285 M elements
+// in 1 / 2 / 4 / 8 launches: bf16 R = 16 (10.3 GB) 6.53 / 6.57 / 6.59 / 6.58 TB/s, fp32 R = 16 accumulating (20.6 GB) 6.72 / 6.78 /
+// 6.84 / 6.85, bf16 R = 8 (5.7 GB) 6.89 / 6.88 / 6.82 / 6.70, R = 4 (3.4 GB) 6.84 / 6.82 / 6.80 / 6.68.
+constexpr uint64_t most_reduce_bytes(uint32_t R) { return R > 8 ? 3000000000ull : 6000000000ull; }
 
 hzp_status_t launch_reduce(bool g32, const void *const *slices, uint32_t R, uint64_t n, float scale,
                            int accumulate, float *out, hipStream_t stream)
 {
     if (n == 0) return HZP_OK;
-    ReduceArgs a{};
-    for (uint32_t r = 0; r < R; ++r) a.g[r] = reinterpret_cast<uint64_t>(slices[r]);
-    a.out = out;
-    a.nquad = (uint32_t)(n / 4);
-    a.scale = scale;
-    const uint32_t group = kGroupQuads * reduce_quads(R, g32);
-    const dim3 grid((a.nquad + group - 1) / group), block(kWave);
-    const unsigned lds = lds_for(reduce_waves(g32, R, n, accumulate));
+    const uint32_t es = g32 ? 4u : 2u, group = kGroupQuads * reduce_quads(R, g32);
     constexpr std::make_index_sequence<HZP_MAX_REPLICAS> all;
     static constexpr std::array<void (*)(ReduceArgs), HZP_MAX_REPLICAS> kernels[2][2][2] = {
         {{reduce_kernels<false, false, false>(all), reduce_kernels<false, false, true>(all)},
          {reduce_kernels<false, true, false>(all), reduce_kernels<false, true, true>(all)}},
         {{reduce_kernels<true, false, false>(all), reduce_kernels<true, false, true>(all)},
          {reduce_kernels<true, true, false>(all), reduce_kernels<true, true, true>(all)}}};
-    hipLaunchKernelGGL(kernels[g32][accumulate != 0][grid.x <= kFewGroups][R - 1], grid, block, lds, stream, a);
-    return check_launch("hzp_reduce_shard");
+    // Launches of about equal length; over a longer one the XCDs drift apart, as in the update below.
+    const uint64_t launches = (n * (R * es + (accumulate ? 8u : 4u)) + most_reduce_bytes(R) - 1) / most_reduce_bytes(R);
+    const uint64_t most = ((n + launches - 1) / launches + 4 * group - 1) / (4 * group) * (4 * group);
+    for (uint64_t first = 0; first < n; first += most) {
+        const uint64_t here = std::min(n - first, most);
+        ReduceArgs a{};
+        for (uint32_t r = 0; r < R; ++r) a.g[r] = reinterpret_cast<uint64_t>(slices[r]) + first * es;
+        a.out = out + first;
+        a.nquad = (uint32_t)(here / 4);
+        a.scale = scale;
+        const dim3 grid((a.nquad + group - 1) / group), block(kWave);
+        const unsigned lds = lds_for(reduce_waves(g32, R, here, accumulate));
+        hipLaunchKernelGGL(kernels[g32][accumulate != 0][grid.x <= kFewGroups][R - 1], grid, block, lds, stream, a);
+        const hzp_status_t st = check_launch("hzp_reduce_shard");
+        if (st != HZP_OK) return st;
+    }
+    return HZP_OK;
 }
 
 // Most groups one launch of the fused update covers (about 150 M elements, 0.6-1.3 ms of work).

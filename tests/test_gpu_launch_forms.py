@@ -134,6 +134,27 @@ def test_reduction_of_every_number_of_contributions_at_group_edges(R, g32):
             assert bool((whole[n:] == 0.5).all())
 
 
+@pytest.mark.parametrize("g32", [False, True])
+def test_reduction_cut_into_launches(g32):
+    """A slice of more than 3 GB of nine contributions and the sum: two launches, the second one shorter."""
+    R, es = 9, 4 if g32 else 2
+    n = 3_100_000_000 // (R * es + 8) // 8 * 8 + 8
+    print(n, R, g32, flush=True)
+    plan = hzp.hzp_plan([1], [n], align=8, z3=1, z1=1)
+    torch.manual_seed(1)
+    g = [torch.empty(n, dtype=torch.float32 if g32 else torch.bfloat16, device=DEV).normal_() for _ in range(R)]
+    out = torch.full((n + 64,), 0.5, device=DEV)
+    want = g[0].to(torch.float32, copy=True)
+    for x in g[1:]:
+        want += x
+    want *= 0.3
+    want += 0.5
+    hzp.hzp_reduce_shard(plan, 0, 0, 1, 0, g, 0.3, True, out[:n], grad_dtype=hzp.HZP_GRAD_F32 if g32 else hzp.HZP_GRAD_BF16)
+    torch.cuda.synchronize()
+    assert torch.equal(out[:n], want)
+    assert bool((out[n:] == 0.5).all())
+
+
 @pytest.mark.parametrize("place", ["own", "packed"])
 @pytest.mark.parametrize("layers,K", [(24, 16), (40, 4)])
 def test_post_step_gather_of_uneven_layers(place, layers, K):
