@@ -401,7 +401,8 @@ hzp_status_t hzp_gather_layer_static(const hzp_plan_t *plan, uint32_t layer, uin
 
 /* ------------------------------------------------------------------------------------------
  * hzp_gather_layer's bucket output for a range of layers in one call (a kernel launch holds up to 192
- * pieces, or 204 layers whose pieces lie at equal distances in every source, and about 600 MB): the post-step gather of Section 4.1.2 runs for every layer at once, and many
+ * pieces, or 204 layers whose pieces lie at equal distances in every source, about 600 MB, and pieces that do not differ
+ * too much in length): the post-step gather of Section 4.1.2 runs for every layer at once, and many
  * small launches leave the memory system idle between them.
  *   shard_ptrs : host array [(layer_end-layer_begin) * n_shards]; entry (l*n_shards + s) is shard s
  *                of layer layer_begin+l, as in hzp_gather_layer; entries of layers that have no
