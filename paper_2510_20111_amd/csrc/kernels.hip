@@ -740,7 +740,9 @@ static constexpr std::array<void (*)(Args), sizeof...(I)> fused_kernels(std::ind
 // 6.31 / 6.10 -> 6.60 / 6.30; fp32 R = 4 (accumulating) 6.22 / 5.89 -> 6.30 / 5.89, R = 8 6.00 / 5.86 -> 6.49 / 6.09.
 static unsigned reduce_waves(bool g32, uint32_t R, uint64_t n, int accumulate)
 {
-    if (n <= 256u * 32u * 4u * kGroupQuads) return 0;                           // all resident at once
+    // All resident at once; with many bf16 contributions also a little beyond (2.2 M elements, R = 24 / 32: 21.2 -> 19.7 / 27.2 -> 25.3 us).
+    const uint64_t slots = 256u * 32u * 4u * kGroupQuads;
+    if (n <= (!g32 && R > 16 && !accumulate ? slots / 4 * 5 : slots)) return 0;
     const uint32_t chunk = chunk_of(R, kReduceChunk), chunks = (R + chunk - 1) / chunk, es = g32 ? 4u : 2u;
     const uint64_t bytes = n * (R * es + 4u);
     const bool brief = bytes < (g32 ? 256u << 20 : 160u << 20);
@@ -783,7 +785,10 @@ hzp_status_t launch_reduce(bool g32, const void *const *slices, uint32_t R, uint
         a.scale = scale;
         const dim3 grid((a.nquad + group - 1) / group), block(kWave);
         const unsigned lds = lds_for(reduce_waves(g32, R, here, accumulate));
-        hipLaunchKernelGGL(kernels[g32][accumulate != 0][grid.x <= kFewGroups][R - 1], grid, block, lds, stream, a);
+        // Many bf16 contributions in a launch that just fits the chip: the wavefronts run in step, and long chunks make fewer steps
+        // (1.5 M elements, R = 24 / 32: 14.6 -> 13.9 / 18.9 -> 18.1 us; 1.0 M 10.1 -> 10.1 / 12.3 -> 13.1).
+        const bool few = grid.x <= kFewGroups || (!g32 && R > 16 && grid.x > 5120 && grid.x <= 8192);
+        hipLaunchKernelGGL(kernels[g32][accumulate != 0][few][R - 1], grid, block, lds, stream, a);
         const hzp_status_t st = check_launch("hzp_reduce_shard");
         if (st != HZP_OK) return st;
     }

@@ -155,6 +155,26 @@ def test_reduction_cut_into_launches(g32):
     assert bool((out[n:] == 0.5).all())
 
 
+@pytest.mark.parametrize("R", [17, 32])
+@pytest.mark.parametrize("groups", [5120, 5121, 8192, 8193, 10240, 10241])
+def test_reduction_that_just_fits_the_chip(R, groups):
+    n = groups * 256 - 8
+    print(n, R, flush=True)
+    plan = hzp.hzp_plan([1], [n], align=8, z3=1, z1=1)
+    torch.manual_seed(groups)
+    g = [torch.empty(n, dtype=torch.bfloat16, device=DEV).normal_() for _ in range(R)]
+    want = g[0].to(torch.float32, copy=True)
+    for x in g[1:]:
+        want += x
+    want *= 0.3
+    for acc in (False, True):
+        out = torch.full((n + 64,), 0.5, device=DEV)
+        hzp.hzp_reduce_shard(plan, 0, 0, 1, 0, g, 0.3, acc, out[:n], grad_dtype=hzp.HZP_GRAD_BF16)
+        torch.cuda.synchronize()
+        assert torch.equal(out[:n], want + 0.5 if acc else want), acc
+        assert bool((out[n:] == 0.5).all())
+
+
 @pytest.mark.parametrize("place", ["own", "packed"])
 @pytest.mark.parametrize("layers,K", [(24, 16), (40, 4)])
 def test_post_step_gather_of_uneven_layers(place, layers, K):
