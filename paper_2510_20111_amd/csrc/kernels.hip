@@ -637,9 +637,9 @@ __global__ __launch_bounds__(kWave) void unpack_list_kernel(const Args a)
     }
 }
 
-// The same for buckets of very many small tensors: one single-wavefront workgroup per chunk of at most kUnpackChunk
-// elements of one piece (a run of one tensor inside one shard), found in the plan's device tables, so that a launch
-// covers 400 tensors whatever their sizes.
+// The same for short copies and for buckets of very many tensors: one single-wavefront workgroup per chunk of at most
+// kUnpackChunk elements of one piece (a run of one tensor inside one shard), found in the plan's device tables, so that a
+// launch covers 400 tensors whatever their sizes.
 constexpr int kUnpackTensorCap = 400;
 struct UnpackArgs {
     const Piece *pieces;                // device table of the bucket, pieces [0, n_pieces)
@@ -1235,6 +1235,29 @@ struct Part {
 };
 constexpr uint64_t kMostInPart = 1ull << 30;        // (a part's length has 32 bits)
 
+// Are parts of about equal length, so that a grid with the longest part's tiles for each has few workgroups with nothing to do?
+// `tile` elements make a tile.
+static bool even_parts(size_t n, uint64_t total, uint64_t longest, uint64_t tile)
+{
+    return longest * n <= total + std::max(total / 16, 256 * tile);
+}
+
+// Lists of parts in the argument block, or pieces found in the device tables?  The lists copy 5-20 % faster, but 200 even or 160
+// uneven parts fill a launch and cost the host 1 us more than the tables' launch, which covers 400 tensors.  So lists where
+// the copies are long enough to show it: 4 MB where one launch does (tables / lists, us: 48 parts of 3.1 MB 4.8 / 4.9, of 6.3 MB 5.8 /
+// 5.0; 103 parts of 1.6 MB 3.7 / 4.1, of 6.6 MB 5.4 / 4.2), 16 MB a launch where even parts take several (243 parts of 31 MB
+// 13.7 / 14.1, of 63 MB 23.3 / 22.4; 800 of 52 MB 23.9 / 25.6, of 105 MB 40.3 / 39.1), 128 MB where uneven ones do (243 parts of
+// 126 MB 46.7 / 47.2, of 252 MB 88.8 / 88.8; 800 of 26 MB 16.9 / 28.7, of 210 MB 79.3 / 85.6, of 839 MB 296 / 296).
+// Up to 8 even parts go in the smallest block whatever their length (4.3 / 4.0).
+static bool lists_pay(size_t n, uint64_t total, uint64_t longest, uint32_t es)
+{
+    constexpr uint64_t kMega = 1000000;
+    const bool even = even_parts(n, total, longest, kWave * 16 / es);
+    const uint64_t most = even ? UnpackList200::kParts : UnpackFlat160::kParts, launches = (n + most - 1) / most;
+    if (even && n <= (size_t)UnpackList8::kParts) return true;
+    return total * es >= (launches == 1 ? 4 : even ? 16 * launches : 128 * launches) * kMega;
+}
+
 // One launch over parts, cut into runs of at most `cut` elements.
 template <class Args, int ES>
 static hzp_status_t unpack_list(const Part *parts, size_t n, uint64_t cut, hipStream_t stream, const char *who)
@@ -1291,7 +1314,7 @@ static hzp_status_t unpack_parts(const Part *parts, size_t n, bool both, hipStre
             }
         };
         take(cap);
-        const bool even = longest * cnt <= total + std::max(total / 16, 256 * kTile);
+        const bool even = even_parts(cnt, total, longest, kTile);
         uint64_t cut = 0;           // 0: a flat grid
         if (even) {
             cut = longest;
@@ -1386,9 +1409,12 @@ hzp_status_t launch_unpack(const hzp_plan_t *plan, const BucketRec &b, const voi
     const DeviceTables *tab = nullptr;
     const hzp_status_t st = device_tables(plan, &tab);
     if (st != HZP_OK) return st;
-    uint64_t total = 0;
-    for (size_t i = p0; i < p1; ++i) total += b.pieces[i].len;
-    if (n > (size_t)UnpackList200::kParts && total / n < 4096) {        // 200 parts of so few elements do not fill the chip
+    uint64_t total = 0, longest = 0;
+    for (size_t i = p0; i < p1; ++i) {
+        total += b.pieces[i].len;
+        longest = std::max(longest, b.pieces[i].len);
+    }
+    if (!lists_pay(n, total, longest, es)) {
         const UnpackCall u{tab->pieces + b.piece_slot, tab->piece_chunk + b.piece_slot, b, shards, n_shards, stream};
         return launch_unpack_with(u, tensors, t_begin, t_end, "hzp_gather_layer");
     }

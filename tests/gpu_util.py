@@ -1,10 +1,12 @@
 """Helpers of the GPU parity tests: host<->device moves, tolerances, oracle drivers."""
+import ctypes
 import math
 
 import numpy as np
 import torch
 
 import hzp_inputs
+import paper_2510_20111_amd as hzp
 from oracle import numeric as on
 from oracle import planner as op
 
@@ -12,6 +14,30 @@ DEV = "cuda:0"
 REL_TOL = 2e-6          # fp32 master / momentum / variance against the fp64 evaluation
 POISON16 = 0x7FC1       # a NaN pattern used for guard bands (positive as int16)
 POISON32 = 0x7FC12345
+
+
+class _KernelNode(ctypes.Structure):
+    _fields_ = [("block", ctypes.c_uint32 * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", ctypes.c_uint32 * 3),
+                ("params", ctypes.c_void_p), ("lds", ctypes.c_uint32)]
+
+
+def launches_of(call):
+    """The kernels that `call` enqueues on the current stream, in order, as (grid, dynamic LDS bytes): the call is captured into
+    a HIP graph, whose nodes are read; nothing runs.  Plans have to be prepared."""
+    hip = hzp.binding._L            # symbols of the HIP runtime are found through the library that links it
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    raw, count = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(count)) == 0
+    nodes = (ctypes.c_void_p * count.value)()
+    assert hip.hipGraphGetNodes(raw, nodes, ctypes.byref(count)) == 0
+    out = []
+    for node in nodes:
+        info = _KernelNode()
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(info)) == 0
+        out.append((tuple(info.grid), info.lds))
+    return out
 
 
 def to_dev(a):

@@ -10,7 +10,7 @@ import paper_2510_20111_amd as hzp
 from oracle import numeric as on
 from oracle import planner as op
 
-from gpu_util import DEV, assert_cast_of, assert_close_f32, oracle_plan, to_dev, to_host, wd_mult_array
+from gpu_util import DEV, assert_cast_of, assert_close_f32, launches_of, oracle_plan, to_dev, to_host, wd_mult_array
 
 pytestmark = pytest.mark.gpu
 
@@ -230,7 +230,10 @@ def test_post_step_gather_of_many_layers_in_every_placement(place, layers, K, ow
 @pytest.mark.parametrize("shift", [0, 1, 4])
 @pytest.mark.parametrize("name,numel,z3", [("few", [5000, 64, 5000], 1), ("edges", [1, 7, 8, 9, 511, 512, 513, 4096, 70001], 3),
                                            ("lopsided", [3000001] + [40] * 60, 4), ("many", [9000] * 260, 2), ("tiny", [3] * 450, 2),
-                                           ("one", [1234567], 8)])
+                                           ("one", [1234567], 8), ("cut", [1, 7, 8, 9, 511, 512, 513, 4096, 4000001], 3),
+                                           ("uneven", [300007, 5, 70001, 513] * 30, 2), ("even", [30011] * 150, 2),
+                                           ("even launches", [70011] * 260, 2), ("uneven launches", [1300003, 400007] * 160, 2),
+                                           ("tiny and one", [100] * 700 + [3000001] + [100] * 500, 4)])
 def test_tensors_and_bucket_in_one_pass_or_two(name, numel, z3, shift, cls):
     """The unpacking gather alone, with the bucket beside it and for one tensor at a time; tensors that start on a 16-byte
     boundary (one pass serves both outputs), an element and half a vector behind one."""
@@ -264,3 +267,17 @@ def test_tensors_and_bucket_in_one_pass_or_two(name, numel, z3, shift, cls):
     assert torch.equal(beside, want)
     assert torch.equal(whole[16:16 + info.padded], bucket)
     assert bool((whole[:16] == 77).all()) and bool((whole[16 + info.padded:] == 77).all())
+
+
+@pytest.mark.parametrize("numel,most", [([5000] * 199, 1), ([100, 20000] * 80, 1), ([5000, 5000, 20000] * 100, 1), ([16384] * 800, 2),
+                                        ([100] * 5000 + [50000000] + [100] * 5000, 26), ([1000000] * 150, 1)])
+def test_unpacking_takes_no_more_launches_than_the_tensors_need(numel, most):
+    """Short copies of many tensors: a launch for every 400 tensors, whatever their sizes."""
+    print(len(numel), flush=True)
+    plan = hzp.hzp_plan([len(numel)], numel, align=8, z3=2, z1=2)
+    plan.prepare()
+    info = plan.bucket(0)
+    shards = [torch.empty(info.s3, dtype=torch.int16, device=DEV) for _ in range(2)]
+    views = list(torch.split(torch.empty(sum(numel), dtype=torch.int16, device=DEV), numel))
+    got = launches_of(lambda: hzp.hzp_gather_layer(plan, 0, 0, 3, shards, None, views))
+    assert len(got) <= most, len(got)
