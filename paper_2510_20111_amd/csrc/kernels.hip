@@ -483,6 +483,7 @@ struct CopyListArgs {
     uint32_t nvec[PIECES];                  // length in 16-byte vectors
 };
 typedef CopyListArgs<8> CopyFewArgs;
+typedef CopyListArgs<64> CopyGroupArgs;
 typedef CopyListArgs<192> CopyManyArgs;
 static_assert(sizeof(CopyManyArgs) <= 4096, "kernel arguments");
 template <class Args>
@@ -1078,13 +1079,21 @@ static size_t units_of_launch(size_t left, size_t most, uint64_t rows, TilesAt t
     return all ? all : take(8192, 8192);
 }
 
+// One launch, with the smallest block that holds the pieces (buckets of 64 KiB to 1 MiB from 9 to 64 shards, call after call: 4.75 us
+// with the block of 192, 4.55 with the block of 64; up to 8 shards 4.4 with the block of 8).
+static hzp_status_t copy_one(const Move *moves, size_t n, hipStream_t stream, const char *who)
+{
+    if (n <= (size_t)CopyFewArgs::kPieces) return copy_list<CopyFewArgs>(moves, n, stream, who);
+    if (n <= (size_t)CopyGroupArgs::kPieces) return copy_list<CopyGroupArgs>(moves, n, stream, who);
+    return copy_list<CopyManyArgs>(moves, n, stream, who);
+}
+
 // Launches over the pieces of many layers, longest first.
 static hzp_status_t copy_moves(const Move *moves, size_t n, hipStream_t stream, const char *who)
 {
     for (size_t at = 0; at < n;) {
         const size_t cnt = units_of_launch(n - at, CopyManyArgs::kPieces, 1, [&](size_t i) { return tiles_of(moves[at + i].nvec); });
-        const hzp_status_t st = cnt <= (size_t)CopyFewArgs::kPieces ? copy_list<CopyFewArgs>(moves + at, cnt, stream, who)
-                                                                    : copy_list<CopyManyArgs>(moves + at, cnt, stream, who);
+        const hzp_status_t st = copy_one(moves + at, cnt, stream, who);
         if (st != HZP_OK) return st;
         at += cnt;
     }
@@ -1104,9 +1113,7 @@ hzp_status_t launch_concat(const void *const *srcs, uint32_t n_shards, uint64_t 
         if (from != to) moves[n++] = {from, to, nvec};          // else it lies in place
     }
     // (one bucket's pieces stay one launch: cut into launches, 1.7-2.3 GB buckets copy no faster)
-    if (n == 0) return HZP_OK;
-    if (n <= (size_t)CopyFewArgs::kPieces) return copy_list<CopyFewArgs>(moves, n, stream, "hzp_gather_layer");
-    return copy_list<CopyManyArgs>(moves, n, stream, "hzp_gather_layer");
+    return n ? copy_one(moves, n, stream, "hzp_gather_layer") : HZP_OK;
 }
 
 // Layers whose pieces lie at equal distances, in launches of kSharedLayers; *done is false (and nothing launched) where

@@ -22,7 +22,7 @@ class _KernelNode(ctypes.Structure):
 
 
 def launches_of(call):
-    """The kernels that `call` enqueues on the current stream, in order, as (grid, dynamic LDS bytes): the call is captured into
+    """The kernels that `call` enqueues on the current stream, in order, as (grid, dynamic LDS bytes, kernel): the call is captured into
     a HIP graph, whose nodes are read; nothing runs.  Plans have to be prepared."""
     hip = hzp.binding._L            # symbols of the HIP runtime are found through the library that links it
     graph = torch.cuda.CUDAGraph(keep_graph=True)
@@ -36,7 +36,7 @@ def launches_of(call):
     for node in nodes:
         info = _KernelNode()
         assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(info)) == 0
-        out.append((tuple(info.grid), info.lds))
+        out.append((tuple(info.grid), info.lds, info.func))
     return out
 
 

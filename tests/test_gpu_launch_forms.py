@@ -281,3 +281,35 @@ def test_unpacking_takes_no_more_launches_than_the_tensors_need(numel, most):
     views = list(torch.split(torch.empty(sum(numel), dtype=torch.int16, device=DEV), numel))
     got = launches_of(lambda: hzp.hzp_gather_layer(plan, 0, 0, 3, shards, None, views))
     assert len(got) <= most, len(got)
+
+
+def test_a_copy_of_few_pieces_travels_in_a_small_block():
+    """1 to 8, 9 to 64 and more pieces have a kernel with an argument block each."""
+    kernel = {}
+    for k in (1, 8, 9, 16, 64):
+        plan = hzp.hzp_plan([1], [8 * k], align=8, z3=k, z1=k)
+        plan.prepare()
+        shards = [torch.empty(8, dtype=torch.int16, device=DEV) for _ in range(k)]
+        out = torch.empty(8 * k, dtype=torch.int16, device=DEV)
+        got = launches_of(lambda: hzp.hzp_gather_layer(plan, 0, 0, 3, shards, out, None))
+        assert [g[:2] for g in got] == [((1, k, 1), 0)]
+        kernel[k] = got[0][2]
+    plan = hzp.hzp_plan([1] * 10, [80] * 10, align=8, z3=1, z1=10)
+    plan.prepare()
+    own = [torch.empty(8, dtype=torch.int16, device=DEV) for _ in range(100)]
+    out = [torch.empty(80, dtype=torch.int16, device=DEV) for _ in range(10)]
+    got = launches_of(lambda: hzp.hzp_gather_layers(plan, 0, 10, 0, 1, own, 10, out))
+    assert [g[:2] for g in got] == [((1, 100, 1), 0)]
+    assert kernel[1] == kernel[8] and kernel[9] == kernel[16] == kernel[64] and len({kernel[8], kernel[64], got[0][2]}) == 3
+
+
+@pytest.mark.parametrize("k", [9, 16, 64])
+def test_bucket_of_many_shards(k):
+    n = 8 * 64 * 3 + 8
+    plan = hzp.hzp_plan([1], [n * k], align=8, z3=k, z1=k)
+    want = torch.randint(-30000, 30000, (n * k,), dtype=torch.int16, device=DEV)
+    shards = [x.clone() for x in torch.split(want, n)]
+    out = torch.full((n * k + 8,), 77, dtype=torch.int16, device=DEV)
+    hzp.hzp_gather_layer(plan, 0, 0, 3, shards, out[:n * k], None)
+    torch.cuda.synchronize()
+    assert torch.equal(out[:n * k], want) and bool((out[n * k:] == 77).all())
