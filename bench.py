@@ -758,24 +758,33 @@ COPY_MAX_TILES = 600000         # 1 KiB tiles one launch of the layer-range gath
 
 
 def gather1_launches(w):
-    """(kernel, launches) of the layer-range gather of all layers, longest first: whole layers (up to 204) where there are more than
-    192 pieces and they lie at equal distances in every source (the arena's do), otherwise whole pieces (up to 192)."""
-    shared = w.n_layers * w.K > 192 and w.layout != "separate"
-    rows, most = (w.K, 204) if shared else (1, 192)
-    left = sorted((-(-2 * b.s1 // 1024) * rows for b in w.buckets for _ in range(1 if shared else w.K)), reverse=True)
+    """(kernel, launches) of the layer-range gather of all layers: whole layers (up to 204) where that saves launches
+    and they lie at equal distances in every source (the arena's do), otherwise whole pieces (up to 192).  Longest first, unless
+    the launches have next to no workgroups with nothing to do as they come."""
+    shared = -(-len(w.buckets) * w.K // 192) > -(-len(w.buckets) // 204) and w.layout != "separate"
+
+    def take(units, most, each, last):
+        cnt = tiles = longest = 0
+        while cnt < min(len(units), most):
+            total, longer = tiles + units[cnt], max(longest, units[cnt])
+            if cnt and (total > COPY_MAX_TILES or longer * (cnt + 1) - total > total // 8 + each):
+                break
+            cnt, tiles, longest = cnt + 1, total, longer
+        return cnt if longest * cnt - tiles <= tiles // 8 + last else 0
+
+    layers = [-(-2 * b.s1 // 1024) * w.K for b in w.buckets]
+    most = 204 if shared else len(layers)
+    left = list(layers)
+    while left:
+        cnt = take(left, most, float("inf"), 2048)
+        if cnt == 0:
+            layers.sort(reverse=True)
+            break
+        left = left[cnt:]
+    left, most = (layers, 204) if shared else ([n // w.K for n in layers for _ in range(w.K)], 192)
     launches = 0
     while left:
-        # all that fit, unless too many workgroups have nothing to do; then those of about equal length
-        for each, last in ((float("inf"), 24576), (8192, 8192)):
-            cnt = tiles = 0
-            while cnt < min(len(left), most):
-                total = tiles + left[cnt]
-                if cnt and (total > COPY_MAX_TILES or left[0] * (cnt + 1) - total > total // 8 + each):
-                    break
-                cnt, tiles = cnt + 1, total
-            if left[0] * cnt - tiles <= tiles // 8 + last:
-                break
-        left, launches = left[cnt:], launches + 1
+        left, launches = left[take(left, most, float("inf"), 24576) or take(left, most, 8192, 8192):], launches + 1
     return "copy_shared_kernel" if shared else "copy_list_kernel", launches
 
 
