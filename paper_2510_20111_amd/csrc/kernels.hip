@@ -877,6 +877,12 @@ static void list_runs(const hzp_plan_t *plan, const FusedSegment *segs, size_t n
     }
 }
 
+// A launch of so few groups has no cap: at most 20 wavefronts per CU are resident then, and a cap of 14 or 8 would leave a second,
+// nearly empty round.  With / without one, us: fp32 0.66 M elements R = 1 / 4 / 16 5.9 / 7.4 / 13.4 and 5.3 / 6.4 / 11.3, 1.05 M
+// 7.5 / 9.9 / 17.7 and 7.2 / 9.3 / 17.2, 1.3 M 8.8 / 11.5 / 22.2 and 8.7 / 11.4 / 21.6; bf16 R = 8 / 24 / 32 0.98 M 9.7 / 16.2 / 19.5
+// and 9.4 / 14.2 / 16.8, 1.3 M 11.4 / 19.4 / 22.9 and 11.5 / 19.2 / 22.7; beyond, the order of the requests counts (below).
+constexpr uint32_t kUncappedGroups = 5120;
+
 template <FusedForm FORM, bool FEW, class Args>
 static void start_kernel(bool g32, bool o32, uint32_t R, const Args &a, dim3 grid, uint32_t groups, hipStream_t stream)
 {
@@ -892,7 +898,8 @@ static void start_kernel(bool g32, bool o32, uint32_t R, const Args &a, dim3 gri
     // 6.50 / 6.54 / 6.48 / 6.37.
     const unsigned waves16 = groups > 200000u ? (FORM == kSearched ? 12u : 10u) : groups > 32768u ? 12u : 14u;
     const unsigned waves32 = FORM == kSearched ? 10u : 8u;
-    hipLaunchKernelGGL(kernel, grid, dim3(kWave), FEW ? 0u : lds_for(g32 ? waves32 : waves16), stream, a);
+    const bool capped = groups > kUncappedGroups;
+    hipLaunchKernelGGL(kernel, grid, dim3(kWave), capped ? lds_for(g32 ? waves32 : waves16) : 0u, stream, a);
 }
 
 hzp_status_t launch_fused(const hzp_plan_t *plan, bool g32, bool o32, uint32_t R, const FusedSegment *segs, size_t nseg,

@@ -313,3 +313,30 @@ def test_bucket_of_many_shards(k):
     hzp.hzp_gather_layer(plan, 0, 0, 3, shards, out[:n * k], None)
     torch.cuda.synchronize()
     assert torch.equal(out[:n * k], want) and bool((out[n * k:] == 77).all())
+
+
+def update_launches(groups, cls, R, layers=1, split=None):
+    """The launches of one update call over `layers` buckets of separate buffers that hold `groups` groups of 256 elements together;
+    split: a second tensor of so many elements without decay in each bucket."""
+    n = groups * 256 // layers
+    numel = [n] if split is None else [n - split, split]
+    wd = None if split is None else [1.0, 0.0] * layers
+    plan = hzp.hzp_plan([len(numel)] * layers, numel * layers, align=8, z3=1, z1=1, tensor_class=[cls] * (len(numel) * layers),
+                        tensor_wd_mult=wd)
+    plan.prepare()
+    grad, out = (torch.float32, torch.float32) if cls else (torch.bfloat16, torch.bfloat16)
+
+    def buffers(dtype, count=layers):
+        return [torch.empty(n + 64, dtype=dtype, device=DEV) for _ in range(count)]
+    hy = hzp.adamw_hyper(HP["lr"], HP["beta1"], HP["beta2"], HP["eps"], HP["weight_decay"], 1.0 / R, 3)
+    g, p, m, v, o = buffers(grad, layers * R), *(buffers(torch.float32) for _ in range(3)), buffers(out)
+    return launches_of(lambda: hzp.hzp_adamw_shard(plan, 0, layers, cls, 0, hy, g, R, p, m, v, o))
+
+
+@pytest.mark.parametrize("layers,split", [(1, None), (4, None), (4, 128)])
+@pytest.mark.parametrize("cls,R", [(0, 4), (0, 32), (1, 1), (1, 4)])
+def test_short_updates_are_not_capped(cls, R, layers, split):
+    """All wavefronts of a launch of up to 5120 groups are resident; longer ones are capped by unused LDS."""
+    for groups in (2060, 3600, 4096, 5120):
+        assert [lds for _, lds, _ in update_launches(groups, cls, R, layers, split)] == [0], groups
+    assert update_launches(5124, cls, R, layers, split)[0][1] > 0
