@@ -122,6 +122,7 @@ constexpr uint32_t kReduceChunk = 4;
 // A launch of so few groups that all wavefronts are resident at once lasts as long as one wavefront, whose chunks follow
 // each other: there, more than 8 contributions are requested up to 16 at a time (64 k elements, R = 32: reduction 5.5 -> 3.7 us,
 // update 6.2 -> 4.3; 512 k: 7.7 -> 7.4, 11.7 -> 10.4; with R <= 8 no difference).
+// (the update of several segments, 0.15 M elements, R = 16 / 32: 5.8 / 7.3 -> 5.1 / 5.3)
 constexpr uint32_t kFewGroups = 2048;
 constexpr uint32_t few_chunk(uint32_t R, uint32_t chunk) { return R > 8 ? 16u : chunk; }
 
@@ -863,6 +864,7 @@ static bool distance(const FusedSegment *segs, const SegRun &a, const SegRun &b,
 static void list_runs(const hzp_plan_t *plan, const FusedSegment *segs, size_t nseg, uint32_t R, uint32_t gsz, uint32_t osz,
                       std::vector<SegRun> &runs)
 {
+    runs.reserve(nseg);
     for (size_t s = 0; s < nseg; ++s) {
         const FusedSegment &f = segs[s];
         const uint64_t *off = plan->run_off.data() + f.first_run;
@@ -1005,6 +1007,9 @@ hzp_status_t launch_fused(const hzp_plan_t *plan, bool g32, bool o32, uint32_t R
             for (uint32_t c = cnt; c-- > 1;) w[(size_t)c * a.stride] -= (uint32_t)w[(size_t)(c - 1) * a.stride];
             grid = dim3(longest, cnt);
         }
+        // (where wavefronts also read tables, 16 fp32 contributions are too many a little earlier: 32 segments of 0.52 M elements together,
+        // R = 16, 10.1 us without and 10.5 with them; 0.38 M 8.6 and 8.4)
+        const bool few = blocks <= (g32 ? kFewGroups / 4 * 3 : kFewGroups);
         if (cnt == 1 && !a.lookup) {
             FusedOneArgs one;
             one.scalars_dev = a.scalars_dev;
@@ -1015,9 +1020,15 @@ hzp_status_t launch_fused(const hzp_plan_t *plan, bool g32, bool o32, uint32_t R
             else
                 start_kernel<kOne, false>(g32, o32, R, one, grid, blocks, stream);
         } else if (a.grid2d && !shared && !a.lookup) {
-            start_kernel<kPlain, false>(g32, o32, R, a, grid, blocks, stream);
+            if (few)
+                start_kernel<kPlain, true>(g32, o32, R, a, grid, blocks, stream);
+            else
+                start_kernel<kPlain, false>(g32, o32, R, a, grid, blocks, stream);
         } else {
-            start_kernel<kSearched, false>(g32, o32, R, a, grid, blocks, stream);
+            if (few)
+                start_kernel<kSearched, true>(g32, o32, R, a, grid, blocks, stream);
+            else
+                start_kernel<kSearched, false>(g32, o32, R, a, grid, blocks, stream);
         }
         hzp_status_t st = check_launch("hzp_adamw_shard");
         if (st != HZP_OK) return st;

@@ -340,3 +340,11 @@ def test_short_updates_are_not_capped(cls, R, layers, split):
     for groups in (2060, 3600, 4096, 5120):
         assert [lds for _, lds, _ in update_launches(groups, cls, R, layers, split)] == [0], groups
     assert update_launches(5124, cls, R, layers, split)[0][1] > 0
+
+
+@pytest.mark.parametrize("layers,split", [(1, None), (4, None), (4, 128)])
+@pytest.mark.parametrize("cls,R", [(0, 16), (1, 16)])
+def test_many_contributions_of_few_groups_have_a_kernel_of_their_own(cls, R, layers, split):
+    """One segment, several, and several whose decay is looked up."""
+    few, more = (update_launches(groups, cls, R, layers, split) for groups in (600, 3000))
+    assert len(few) == len(more) == 1 and few[0][2] != more[0][2]
