@@ -120,9 +120,9 @@ constexpr unsigned lds_for(unsigned waves) { return waves ? 163840u / waves / 51
 constexpr uint32_t fused_chunk(bool g32) { return g32 ? 3u : 4u; }
 constexpr uint32_t kReduceChunk = 4;
 // A launch of so few groups that all wavefronts are resident at once lasts as long as one wavefront, whose chunks follow
-// each other: there, more than 8 contributions are requested up to 16 at a time (64 k elements, R = 32: reduction 5.5 -> 3.7 us,
-// update 6.2 -> 4.3; 512 k: 7.7 -> 7.4, 11.7 -> 10.4; with R <= 8 no difference).
-// (the update of several segments, 0.15 M elements, R = 16 / 32: 5.8 / 7.3 -> 5.1 / 5.3)
+// each other: there, more than 8 contributions are requested up to 16 at a time (chunks of 4 / 16, us a call: 64 k elements, R = 32:
+// reduction 6.1 / 4.2, update 6.5 / 4.4; 512 k 7.9 / 7.7 and 10.8 / 10.1, fp32 R = 32 at 512 k 12.4 / 12.9 and 14.8 / 15.3; the update of
+// several segments, 0.15 M elements, R = 16 / 32: 5.8 -> 5.1 and 7.3 -> 5.3; with R <= 8 no difference).
 constexpr uint32_t kFewGroups = 2048;
 constexpr uint32_t few_chunk(uint32_t R, uint32_t chunk) { return R > 8 ? 16u : chunk; }
 
@@ -212,31 +212,43 @@ struct ReduceArgs {
     float scale;
 };
 
+// The forms of a launch: contributions in flight (chunk), quads per lane, and whether the sum that is accumulated onto is requested
+// behind the contributions instead of ahead of them.
+enum ReduceForm { kReducePlain, kReduceFew, kReduceNarrow };
+constexpr uint32_t reduce_chunk(uint32_t R, ReduceForm form)
+{
+    return form == kReducePlain ? kReduceChunk : form == kReduceFew ? few_chunk(R, kReduceChunk) : 2u;
+}
 // Quads per lane: with a single bf16 contribution one quad is 512 B of reads to a wavefront, too little even at full
 // occupancy (25 M elements: 5.89 TB/s; with two quads 6.22).
-constexpr int reduce_quads(uint32_t R, bool g32) { return R == 1 && !g32 ? 2 : 1; }
+constexpr int reduce_quads(uint32_t R, bool g32, ReduceForm form) { return form == kReduceNarrow || (R == 1 && !g32) ? 2 : 1; }
 
-template <uint32_t R, bool G32, bool ACC, uint32_t CHUNK>
+template <uint32_t R, bool G32, bool ACC, ReduceForm FORM>
 __global__ __launch_bounds__(kWave) void reduce_kernel(const ReduceArgs a)
 {
 #pragma clang fp contract(off)
-    constexpr int Q = reduce_quads(R, G32);
+    constexpr int Q = reduce_quads(R, G32, FORM);
+    constexpr uint32_t CHUNK = reduce_chunk(R, FORM);
+    constexpr bool LATE = FORM == kReduceNarrow;
     uint64_t out = reinterpret_cast<uint64_t>(a.out), at[CHUNK];
 #pragma unroll
     for (uint32_t c = 0; c < CHUNK; ++c) at[c] = c < R ? a.g[c] : 0;
     uint32_t nquad = a.nquad;
     float scale = a.scale;
-    pin(out, at[0], at[1], at[2], at[3], nquad, scale);
+    pin(out, at[0], at[1], at[CHUNK > 2 ? 2 : 0], at[CHUNK > 2 ? 3 : 0], nquad, scale);
     uint32_t q0[Q], quad[Q];
     f32x4 t[Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
         q0[q] = (blockIdx.x * Q + q) * kGroupQuads + threadIdx.x;
         quad[q] = q0[q] < nquad ? q0[q] : nquad - 1;
-        if (ACC) t[q] = ld_stream<f32x4>(out, quad[q]);
+        if (ACC && !LATE) t[q] = ld_stream<f32x4>(out, quad[q]);
     }
     float s[Q][4];
     sum_contributions<R, CHUNK, G32>(at, a.g, 0, quad, s);
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+        if (ACC && LATE) t[q] = ld_stream<f32x4>(out, quad[q]);
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
 #pragma unroll
@@ -721,10 +733,11 @@ static hzp_status_t check_launch(const char *what)
 
 // One kernel per number of contributions: the loads of a chunk are then straight-line code (a run-time R
 // puts a wait between any two of them), and all of a launch's pointers arrive in one round of scalar loads.
-template <bool G32, bool ACC, bool FEW, size_t... I>
+// (the other forms are for more than 8 contributions)
+template <bool G32, bool ACC, ReduceForm FORM, size_t... I>
 static constexpr std::array<void (*)(ReduceArgs), sizeof...(I)> reduce_kernels(std::index_sequence<I...>)
 {
-    return {reduce_kernel<I + 1, G32, ACC, FEW ? few_chunk(I + 1, kReduceChunk) : kReduceChunk>...};
+    return {reduce_kernel<I + 1, G32, ACC, I < 8 ? kReducePlain : FORM>...};
 }
 template <bool G32, bool O32, FusedForm FORM, bool FEW, class Args, size_t... I>
 static constexpr std::array<void (*)(Args), sizeof...(I)> fused_kernels(std::index_sequence<I...>)
@@ -743,13 +756,11 @@ static constexpr std::array<void (*)(Args), sizeof...(I)> fused_kernels(std::ind
 // 6.31 / 6.10 -> 6.60 / 6.30; fp32 R = 4 (accumulating) 6.22 / 5.89 -> 6.30 / 5.89, R = 8 6.00 / 5.86 -> 6.49 / 6.09.
 static unsigned reduce_waves(bool g32, uint32_t R, uint64_t n, int accumulate)
 {
-    // All resident at once; with many bf16 contributions also a little beyond (2.2 M elements, R = 24 / 32: 21.2 -> 19.7 / 27.2 -> 25.3 us).
-    const uint64_t slots = 256u * 32u * 4u * kGroupQuads;
-    if (n <= (!g32 && R > 16 && !accumulate ? slots / 4 * 5 : slots)) return 0;
+    if (n <= 256u * 32u * 4u * kGroupQuads) return 0;       // all resident at once
     const uint32_t chunk = chunk_of(R, kReduceChunk), chunks = (R + chunk - 1) / chunk, es = g32 ? 4u : 2u;
     const uint64_t bytes = n * (R * es + 4u);
     const bool brief = bytes < (g32 ? 256u << 20 : 160u << 20);
-    const unsigned asked = (brief ? chunk * es * 256u : R * es * 256u / chunks) * reduce_quads(R, g32) + (accumulate ? 512u : 0u);
+    const unsigned asked = (brief ? chunk * es * 256u : R * es * 256u / chunks) * reduce_quads(R, g32, kReducePlain) + (accumulate ? 512u : 0u);
     unsigned half_kib;
     if (chunks == 1)
         half_kib = brief ? 144 : 96;
@@ -758,6 +769,21 @@ static unsigned reduce_waves(bool g32, uint32_t R, uint64_t n, int accumulate)
     else
         half_kib = brief ? 102 : R <= 16 && bytes >= 1000000000u ? (accumulate ? 65 : 60) : 68;
     return std::min(28u, half_kib * 512u / asked);
+}
+
+// The form of a launch of `groups` groups.  Where all wavefronts are resident at once there is no cap, and a CU has groups / 256 x chunk
+// x 512 B (bf16) or 1 KiB (fp32) in flight; as in long launches, what exceeds 40-48 KiB only queues.  So with more than 8
+// contributions: up to 2048 groups 16 at a time (latency counts); up to that limit chunks of 4; above it chunks of 2 on two quads (half as
+// many wavefronts, so that they still all fit), to where a capped launch no longer suffers from its uneven last round.
+// Chunks of 4 / of 2 on two quads, us: bf16 R = 32 1.05 M elements 11.6 / 13.9, 1.47 M 19.6 / 16.8, 1.8 M 24.1 / 20.6, R = 24 2.36 M
+// (capped) 21.5 / 19.9, R = 32 3.1 M (capped) 32.3 / 37.9; fp32 R = 32 0.66 M 14.9 / 14.9, 1.05 M 24.5 / 22.0, 1.8 M 40.4 / 37.2,
+// 2.2 M (capped) 44.8 / 48.9; R = 9 (chunks of 3) 1.05 M 8.0 / 8.5, 1.3 M 9.8 / 9.7.
+static ReduceForm reduce_form(bool g32, uint32_t R, uint64_t groups)
+{
+    if (R <= 8) return kReducePlain;
+    if (groups <= kFewGroups) return kReduceFew;
+    const uint64_t in_flight = groups * chunk_of(R, kReduceChunk) * (g32 ? 4 : 2);      // bytes per CU
+    return in_flight > (g32 ? 48u << 10 : 40u << 10) && groups <= (g32 ? 8192u : 10240u) ? kReduceNarrow : kReducePlain;
 }
 
 // Most bytes one launch of the reduction moves (0.45 / 0.9 ms); with more streams a drift of the XCDs (below) costs more.  285 M elements
@@ -769,16 +795,17 @@ hzp_status_t launch_reduce(bool g32, const void *const *slices, uint32_t R, uint
                            int accumulate, float *out, hipStream_t stream)
 {
     if (n == 0) return HZP_OK;
-    const uint32_t es = g32 ? 4u : 2u, group = kGroupQuads * reduce_quads(R, g32);
+    const uint32_t es = g32 ? 4u : 2u;
     constexpr std::make_index_sequence<HZP_MAX_REPLICAS> all;
-    static constexpr std::array<void (*)(ReduceArgs), HZP_MAX_REPLICAS> kernels[2][2][2] = {
-        {{reduce_kernels<false, false, false>(all), reduce_kernels<false, false, true>(all)},
-         {reduce_kernels<false, true, false>(all), reduce_kernels<false, true, true>(all)}},
-        {{reduce_kernels<true, false, false>(all), reduce_kernels<true, false, true>(all)},
-         {reduce_kernels<true, true, false>(all), reduce_kernels<true, true, true>(all)}}};
+    static constexpr std::array<void (*)(ReduceArgs), HZP_MAX_REPLICAS> kernels[2][2][3] = {
+        {{reduce_kernels<false, false, kReducePlain>(all), reduce_kernels<false, false, kReduceFew>(all), reduce_kernels<false, false, kReduceNarrow>(all)},
+         {reduce_kernels<false, true, kReducePlain>(all), reduce_kernels<false, true, kReduceFew>(all), reduce_kernels<false, true, kReduceNarrow>(all)}},
+        {{reduce_kernels<true, false, kReducePlain>(all), reduce_kernels<true, false, kReduceFew>(all), reduce_kernels<true, false, kReduceNarrow>(all)},
+         {reduce_kernels<true, true, kReducePlain>(all), reduce_kernels<true, true, kReduceFew>(all), reduce_kernels<true, true, kReduceNarrow>(all)}}};
     // Launches of about equal length; over a longer one the XCDs drift apart, as in the update below.
     const uint64_t launches = (n * (R * es + (accumulate ? 8u : 4u)) + most_reduce_bytes(R) - 1) / most_reduce_bytes(R);
-    const uint64_t most = ((n + launches - 1) / launches + 4 * group - 1) / (4 * group) * (4 * group);
+    constexpr uint64_t kTwoGroups = 8 * kGroupQuads;        // what a wavefront with two quads per lane takes
+    const uint64_t most = ((n + launches - 1) / launches + kTwoGroups - 1) / kTwoGroups * kTwoGroups;
     for (uint64_t first = 0; first < n; first += most) {
         const uint64_t here = std::min(n - first, most);
         ReduceArgs a{};
@@ -786,12 +813,10 @@ hzp_status_t launch_reduce(bool g32, const void *const *slices, uint32_t R, uint
         a.out = out + first;
         a.nquad = (uint32_t)(here / 4);
         a.scale = scale;
-        const dim3 grid((a.nquad + group - 1) / group), block(kWave);
-        const unsigned lds = lds_for(reduce_waves(g32, R, here, accumulate));
-        // Many bf16 contributions in a launch that just fits the chip: the wavefronts run in step, and long chunks make fewer steps
-        // (1.5 M elements, R = 24 / 32: 14.6 -> 13.9 / 18.9 -> 18.1 us; 1.0 M 10.1 -> 10.1 / 12.3 -> 13.1).
-        const bool few = grid.x <= kFewGroups || (!g32 && R > 16 && grid.x > 5120 && grid.x <= 8192);
-        hipLaunchKernelGGL(kernels[g32][accumulate != 0][few][R - 1], grid, block, lds, stream, a);
+        const ReduceForm form = reduce_form(g32, R, (a.nquad + kGroupQuads - 1) / kGroupQuads);
+        const uint32_t quads = kGroupQuads * reduce_quads(R, g32, form);        // to a wavefront
+        const unsigned waves = form == kReduceNarrow ? 0 : reduce_waves(g32, R, here, accumulate);
+        hipLaunchKernelGGL(kernels[g32][accumulate != 0][form][R - 1], dim3((a.nquad + quads - 1) / quads), dim3(kWave), lds_for(waves), stream, a);
         const hzp_status_t st = check_launch("hzp_reduce_shard");
         if (st != HZP_OK) return st;
     }

@@ -348,3 +348,40 @@ def test_many_contributions_of_few_groups_have_a_kernel_of_their_own(cls, R, lay
     """One segment, several, and several whose decay is looked up."""
     few, more = (update_launches(groups, cls, R, layers, split) for groups in (600, 3000))
     assert len(few) == len(more) == 1 and few[0][2] != more[0][2]
+
+
+def reduce_plan(n):
+    plan = hzp.hzp_plan([1], [n], align=8, z3=1, z1=1)
+    plan.prepare()
+    return plan
+
+
+# edges of the forms, in groups of 256 elements: many at a time, chunks of 4, chunks of 2 on two quads per lane, capped
+@pytest.mark.parametrize("R,g32,few,fours,twos", [(16, False, 2048, 5120, 10240), (32, False, 2048, 5120, 10240), (9, False, 2048, 6826, 10240),
+                                                  (16, True, 2048, 3072, 8192), (32, True, 2048, 3072, 8192), (9, True, 2048, 4096, 8192)])
+@pytest.mark.parametrize("acc", [False, True])
+def test_reduction_forms_at_their_edges(R, g32, few, fours, twos, acc):
+    """The grid and the LDS say which form a launch has; the results are those of the sum in order, bit for bit."""
+    dt, gd = (torch.float32, hzp.HZP_GRAD_F32) if g32 else (torch.bfloat16, hzp.HZP_GRAD_BF16)
+    torch.manual_seed(R)
+    most = (twos + 3) * 256
+    g = [torch.empty(most, dtype=dt, device=DEV).normal_() for _ in range(R)]
+    want = g[0].to(torch.float32, copy=True)
+    for x in g[1:]:
+        want += x
+    want *= 0.3
+    if acc:
+        want += 0.5
+    for groups, per_lane in ((few, 1), (few + 1, 1), (fours, 1), (fours + 1, 2), (twos, 2), (twos + 1, 1)):
+        for n in (groups * 256, groups * 256 - 248):
+            print(R, g32, acc, n, flush=True)
+            plan, out = reduce_plan(n), torch.full((most + 64,), 0.5, device=DEV)
+            slices = [x[:n] for x in g]
+
+            def call():
+                hzp.hzp_reduce_shard(plan, 0, 0, 1, 0, slices, 0.3, acc, out[:n], grad_dtype=gd)
+            (grid, lds, _), = launches_of(call)
+            assert grid == (-(-groups // per_lane), 1, 1) and (lds > 0) == (groups > twos)
+            call()
+            torch.cuda.synchronize()
+            assert torch.equal(out[:n], want[:n]) and bool((out[n:] == 0.5).all())
