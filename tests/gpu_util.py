@@ -40,6 +40,27 @@ def launches_of(call):
     return out
 
 
+def update_cuts(sizes):
+    """Where the launches of one update call end inside its segments of `sizes` elements (that do not follow each other, or are one):
+    launches of at most 600,000 groups of 256 elements, all of about the same number; per segment the element positions."""
+    groups = [-(-n // 256) for n in sizes]
+    launches = -(-sum(groups) // 600000)
+    most = -(-sum(groups) // launches)
+    cuts, before = [], 0
+    for n in groups:
+        cuts.append([(at - before) * 256 for at in range(most, sum(groups), most) if before < at < before + n])
+        before += n
+    return cuts
+
+
+def reduce_cuts(n, R, es, accumulate):
+    """Where the launches of a reduction of R contributions of `es` bytes an element end: launches of at most 6 GB (3 GB with more than
+    8 contributions), all of about the same length, in multiples of 512 elements."""
+    launches = -(-n * (R * es + (8 if accumulate else 4)) // (3000000000 if R > 8 else 6000000000))
+    most = -(-(-(-n // launches)) // 512) * 512
+    return list(range(most, n, most))
+
+
 def to_dev(a):
     """numpy array (uint16 / float32 / uint32) -> device tensor with the same bits."""
     a = np.ascontiguousarray(a)

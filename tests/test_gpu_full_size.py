@@ -13,7 +13,7 @@ import paper_2510_20111_amd as hzp
 from oracle import numeric as on
 from oracle import planner as op
 
-from gpu_util import (DEV, assert_cast_of, assert_close_f32, oracle_plan, to_dev, to_host)
+from gpu_util import (DEV, assert_cast_of, assert_close_f32, launches_of, oracle_plan, reduce_cuts, to_dev, to_host, update_cuts)
 from test_gpu_parity import Sim, say
 
 pytestmark = pytest.mark.gpu
@@ -23,9 +23,10 @@ def _bits16(t):
     return t.view(torch.int16)
 
 
-def _sample_indices(n, rng, count=4096, edge=1024):
+def _sample_indices(n, rng, count=4096, edge=1024, marks=()):
     edge = min(edge, n // 2)
-    idx = np.concatenate([np.arange(edge), np.arange(n - edge, n), rng.integers(0, n, size=count)])
+    idx = np.concatenate([np.arange(edge), np.arange(n - edge, n), rng.integers(0, n, size=count)] +
+                         [np.arange(max(0, c - 600), min(n, c + 600)) for c in marks])
     return np.unique(idx)
 
 
@@ -39,14 +40,20 @@ def _fused_sampled_parity(cfg_idx, n_layers, steps=2):
     rng = np.random.default_rng(100 + cfg_idx)
     a = cfg["adamw"]
     samples = []
+    # the layers follow each other in the arena: one segment, cut where a launch is full, some layers are sampled around a cut
+    (cuts,) = update_cuts([w.s1_total])
+    begins = np.cumsum([0] + [t[1].numel() for t in w.keep])
     for l, (grads, p, m, v, out, owners, shard3, shards, bucket) in enumerate(w.keep):
-        idx = _sample_indices(p.numel(), rng)
+        idx = _sample_indices(p.numel(), rng, marks=[c - int(begins[l]) for c in cuts if -600 < c - begins[l] < p.numel() + 600])
         ti = torch.from_numpy(idx).to(DEV)
         samples.append(dict(idx=idx, ti=ti,
                             g=[to_host(_bits16(g)[ti], np.uint16) for g in grads],
                             p=to_host(p[ti], np.float32).copy(), m=to_host(m[ti], np.float32).copy(),
                             v=to_host(v[ti], np.float32).copy()))
     torch.cuda.synchronize()
+    w.plan.prepare()
+    grids = [grid for grid, _, _ in launches_of(lambda: bench.run_step(w, hzp, 1, torch.cuda.current_stream(), {"fused"}))]
+    assert grids == [(-(-n // 256), 1, 1) for n in np.diff([0] + cuts + [w.s1_total]).tolist()]
     for step in range(1, steps + 1):
         say("workload %s: step %d over %d buckets, %d shard elements" % (cfg["name"], step, n_layers, w.s1_total))
         bench.run_step(w, hzp, step, stream, {"fused", "gather1", "gather3"})
@@ -83,38 +90,39 @@ def test_dense7b_rank_share_as_benchmarked():
 
 
 def test_dense70b_layer_stream_sampled():
-    """36 of the 80 layers in one call: more than one launch holds (a launch takes at most 300,000
-    groups of 512 elements, 22 of these layers), two steps."""
-    w = _fused_sampled_parity(2, 36)
+    """37 of the 80 layers in one call: more than one launch holds (at most 600,000 groups of 256 elements, 22 of
+    these layers), two steps; the cut falls into the middle of the nineteenth."""
+    w = _fused_sampled_parity(2, 37)
     assert w.buckets[0].s1 == 6684800 and w.buckets[0].padded == 855654400
-    assert 22 * (6684800 // 512) <= 300000 < 23 * (6684800 // 512)
+    assert update_cuts([w.s1_total]) == [[18 * 6684800 + 3342592]]
 
 
 def test_moe_layer_set_sampled_over_many_launches():
-    """21 of the 24 MoE layers at R = 16 in one call, two steps: eleven launches of two layers each."""
+    """21 of the 24 MoE layers at R = 16 in one call, two steps: ten launches of 2.1 layers each."""
     w = _fused_sampled_parity(3, 21)
     assert w.buckets[0].s1 == 71385088 and w.s1_total == 21 * 71385088
+    assert len(update_cuts([w.s1_total])[0]) == 9
 
 
 def test_one_shard_longer_than_a_launch():
-    """A single ZeRO-1 shard of 160 M elements: the update cuts it into runs of at most 300,000 groups
-    of 512 elements, one launch each.  Sampled against the oracle at both ends, on both sides of the
-    cut (element 153,600,000) and at random positions; decay multipliers are looked up per tensor, so
-    the second run must see bucket positions that continue the first."""
-    n_a, n_b = 153_600_000 - 4096, 6_400_000 + 4096 + 24
-    say("one shard of %d elements across two launches" % (n_a + n_b))
+    """A single ZeRO-1 shard of 160 M elements: the update cuts it into two launches of about equal length (at most 600,000
+    groups of 256 elements each).  Sampled against the oracle at both ends, on both sides of the cut (element 80,000,256) and
+    at random positions; decay multipliers are looked up, so the second launch must see bucket positions that
+    continue the first, and the multiplier changes 4096 elements before the cut."""
+    n = 160_000_024
+    (cut,), = update_cuts([n])
+    n_a = cut - 4096
+    say("one shard of %d elements across two launches" % n)
     wd = [1.0, 0.0]
-    plan = hzp.hzp_plan([2], [n_a, n_b], 8, 1, 1, tensor_wd_mult=wd)
+    plan = hzp.hzp_plan([2], [n_a, n - n_a], 8, 1, 1, tensor_wd_mult=wd)
     b = plan.bucket(0, 0)
-    n = int(b.s1)
-    assert n > 300000 * 512 and plan.tensor(1).offset == n_a
+    assert cut == 80_000_256 and b.s1 == n and plan.tensor(1).offset == n_a
     R = 2
     bf16, f32 = torch.bfloat16, torch.float32
     g = [hzp_inputs.device_normal(n, 1e-3, 31 + r, DEV, bf16, None, 0) for r in range(R)]
     p = hzp_inputs.device_normal(n, 0.02, 77, DEV, f32, None, 0)
     m, v = torch.zeros(n, device=DEV), torch.zeros(n, device=DEV)
     out = torch.zeros(n, dtype=bf16, device=DEV)
-    cut = 300000 * 512
     rng = np.random.default_rng(5)
     idx = np.unique(np.concatenate([np.arange(1024), np.arange(n - 1024, n), np.arange(cut - 1024, cut + 1024),
                                     np.arange(n_a - 512, n_a + 512), rng.integers(0, n, size=8192)]))
@@ -123,9 +131,14 @@ def test_one_shard_longer_than_a_launch():
              m=np.zeros(idx.size, np.float32), v=np.zeros(idx.size, np.float32))
     wd_arr = np.where(idx < n_a, 1.0, 0.0).astype(np.float32)
     a = hzp_inputs.ADAMW
+    plan.prepare()
     for step in (1, 2):
         hy = hzp.adamw_hyper(a["lr"], a["beta1"], a["beta2"], a["eps"], a["weight_decay"], 1.0 / R, step)
-        hzp.hzp_adamw_shard(plan, 0, 1, 0, 0, hy, g, R, [p], [m], [v], [out])
+
+        def call():
+            hzp.hzp_adamw_shard(plan, 0, 1, 0, 0, hy, g, R, [p], [m], [v], [out])
+        assert [grid for grid, _, _ in launches_of(call)] == [(cut // 256, 1, 1), (-(-(n - cut) // 256), 1, 1)]
+        call()
         torch.cuda.synchronize()
         on.adamw(on.reduce(s["g"], scale=1.0 / R), s["p"], s["m"], s["v"], step=step, wd_mult=wd_arr, **a)
         for key, t in (("p", p), ("m", m), ("v", v)):
@@ -152,15 +165,19 @@ def test_the_longest_shard_the_entry_points_accept():
     m, v = torch.zeros(n, device=DEV), torch.zeros(n, device=DEV)
     out = torch.zeros(n, dtype=bf16, device=DEV)
     rng = np.random.default_rng(9)
-    marks = [k * 300000 * 512 for k in range(1, 7)] + [1 << 26, 1 << 27, 1 << 28, 1 << 29, 3 << 28]
-    idx = np.unique(np.concatenate([np.arange(1024), np.arange(n - 1024, n), rng.integers(0, n, size=8192)] +
-                                   [np.arange(c - 600, c + 600) for c in marks]))
+    (cuts,), sum_cuts = update_cuts([n]), reduce_cuts(n, 2, 2, False)
+    idx = _sample_indices(n, rng, 8192, marks=cuts + sum_cuts + [1 << 26, 1 << 27, 1 << 28, 1 << 29, 3 << 28])
     ti = torch.from_numpy(idx).to(DEV)
     s = dict(g=to_host(_bits16(g)[ti], np.uint16), p=to_host(p[ti], np.float32).copy(),
              m=np.zeros(idx.size, np.float32), v=np.zeros(idx.size, np.float32))
     a = hzp_inputs.ADAMW
     hy = hzp.adamw_hyper(a["lr"], a["beta1"], a["beta2"], a["eps"], a["weight_decay"], 1.0, 1)
-    hzp.hzp_adamw_shard(plan, 0, 1, 0, 0, hy, [g], 1, [p], [m], [v], [out])
+
+    def update():
+        hzp.hzp_adamw_shard(plan, 0, 1, 0, 0, hy, [g], 1, [p], [m], [v], [out])
+    plan.prepare()
+    assert len(cuts) == 6 and [grid[0] * 256 for grid, _, _ in launches_of(update)][:6] == np.diff([0] + cuts).tolist()
+    update()
     torch.cuda.synchronize()
     on.adamw(on.reduce([s["g"]], scale=1.0), s["p"], s["m"], s["v"], step=1, **a)
     for key, t in (("p", p), ("m", m), ("v", v)):
@@ -170,7 +187,10 @@ def test_the_longest_shard_the_entry_points_accept():
     assert int((m == 0).sum().item()) == int((g == 0).sum().item())
     # stand-alone reduction of two slices of that length into v's buffer, bit for bit on the samples;
     # the whole output against the same sum formed by the library of the tensors' operations
-    hzp.hzp_reduce_shard(plan, 0, 0, 1, 0, [g, out], 0.5, False, v)
+    def reduce():
+        hzp.hzp_reduce_shard(plan, 0, 0, 1, 0, [g, out], 0.5, False, v)
+    assert len(sum_cuts) == 1 and launches_of(reduce)[0][0] == (sum_cuts[0] // 256, 1, 1)
+    reduce()
     torch.cuda.synchronize()
     want = on.reduce([s["g"], to_host(_bits16(out)[ti], np.uint16)], scale=0.5)
     assert np.array_equal(to_host(v[ti], np.uint32), want.view(np.uint32))
@@ -193,8 +213,8 @@ def test_the_longest_shard_the_entry_points_accept():
 @pytest.mark.parametrize("R", [4, 16])
 def test_fp32_class_at_size_over_several_launches(R):
     """Buckets of class F32 (fp32 gradients in, fp32 parameters out) at large shapes: three layers of
-    40, 70 and 170 M elements in one call (the last one longer than a launch), per-tensor decay
-    multipliers, two steps; sampled against the oracle at the ends, around the cuts and at random."""
+    40, 70 and 170 M elements in one call (two launches, cut inside the last one), per-tensor decay
+    multipliers, two steps; sampled against the oracle at the ends, around the cut and at random."""
     sizes = [40_000_000 + 8, 70_000_000 + 24, 170_000_000]
     say("fp32 class at size, R=%d" % R)
     gc.collect()
@@ -203,6 +223,8 @@ def test_fp32_class_at_size_over_several_launches(R):
     f32 = torch.float32
     rng = np.random.default_rng(17 + R)
     a = hzp_inputs.ADAMW
+    cuts = update_cuts(sizes)
+    assert [len(c) for c in cuts] == [0, 0, 1]
     g, p, m, v, out, samples = [], [], [], [], [], []
     for l, n in enumerate(sizes):
         assert plan.bucket(l, 1).s1 == n
@@ -210,16 +232,20 @@ def test_fp32_class_at_size_over_several_launches(R):
         g += gl
         p.append(hzp_inputs.device_normal(n, 0.02, 900 + l, DEV, f32, None, 0))
         m.append(torch.zeros(n, device=DEV)); v.append(torch.zeros(n, device=DEV)); out.append(torch.zeros(n, device=DEV))
-        cuts = [c for c in (300000 * 512,) if c < n]
-        idx = np.unique(np.concatenate([np.arange(1024), np.arange(n - 1024, n), rng.integers(0, n, size=6000)] +
-                                       [np.arange(c - 600, c + 600) for c in cuts]))
+        idx = _sample_indices(n, rng, 6000, marks=cuts[l])
         ti = torch.from_numpy(idx).to(DEV)
         samples.append(dict(ti=ti, g=[to_host(x[ti], np.float32).copy() for x in gl], p=to_host(p[l][ti], np.float32).copy(),
                             m=np.zeros(idx.size, np.float32), v=np.zeros(idx.size, np.float32),
                             wd=np.full(idx.size, [1.0, 0.0, 0.5][l], np.float32)))
+    plan.prepare()
     for step in (1, 2):
         hy = hzp.adamw_hyper(a["lr"], a["beta1"], a["beta2"], a["eps"], a["weight_decay"], 1.0 / R, step)
-        hzp.hzp_adamw_shard(plan, 0, 3, 1, 0, hy, g, R, p, m, v, out)
+
+        def call():
+            hzp.hzp_adamw_shard(plan, 0, 3, 1, 0, hy, g, R, p, m, v, out)
+        got = launches_of(call)             # the first: three segments in a flat grid, ended where the second begins
+        assert len(got) == 2 and got[1][0] == (-(-(sizes[2] - cuts[2][0]) // 256), 1, 1)
+        call()
         torch.cuda.synchronize()
         for l, s in enumerate(samples):
             on.adamw(on.reduce(s["g"], scale=1.0 / R), s["p"], s["m"], s["v"], step=step, wd_mult=s["wd"], out_bf16=False, **a)
@@ -230,8 +256,8 @@ def test_fp32_class_at_size_over_several_launches(R):
 
 def test_accumulation_flow_at_size():
     """fp32 contributions of two micro-batches accumulated into resident fp32 gradient shards of 100 and
-    170 M elements (R = 8 per micro-batch), then the update from those shards (the R == 0 form) over
-    several launches; accumulator sampled bit for bit, update sampled within tolerance."""
+    170 M elements (R = 8 per micro-batch; the longer one in two launches), then the update from those shards (the R == 0
+    form) over two launches; accumulator sampled bit for bit, update sampled within tolerance, both around their cuts."""
     sizes = [100_000_000 + 40, 170_000_000]
     R, M = 8, 2
     say("accumulation flow at size")
@@ -241,15 +267,15 @@ def test_accumulation_flow_at_size():
     f32 = torch.float32
     rng = np.random.default_rng(23)
     a = hzp_inputs.ADAMW
+    cuts = [c + [x for accumulate in (False, True) for x in reduce_cuts(n, R, 4, accumulate)] for n, c in zip(sizes, update_cuts(sizes))]
+    assert [len(c) for c in cuts] == [0, 3]
     acc, p, m, v, out, samples = [], [], [], [], [], []
     for l, n in enumerate(sizes):
         acc.append(torch.full((n,), 3.0, device=DEV))
         p.append(hzp_inputs.device_normal(n, 0.02, 700 + l, DEV, f32, None, 0))
         m.append(torch.zeros(n, device=DEV)); v.append(torch.zeros(n, device=DEV))
         out.append(torch.zeros(n, dtype=torch.int16, device=DEV))
-        cuts = [c for c in (300000 * 512,) if c < n]
-        idx = np.unique(np.concatenate([np.arange(1024), np.arange(n - 1024, n), rng.integers(0, n, size=6000)] +
-                                       [np.arange(c - 600, c + 600) for c in cuts]))
+        idx = _sample_indices(n, rng, 6000, marks=cuts[l])
         samples.append(dict(ti=torch.from_numpy(idx).to(DEV), acc=np.zeros(idx.size, np.float32),
                             p=to_host(p[l][torch.from_numpy(idx).to(DEV)], np.float32).copy(),
                             m=np.zeros(idx.size, np.float32), v=np.zeros(idx.size, np.float32)))
@@ -263,7 +289,13 @@ def test_accumulation_flow_at_size():
             assert np.array_equal(to_host(acc[l][s["ti"]], np.uint32), s["acc"].view(np.uint32)), (mb, l)
             del g
     hy = hzp.adamw_hyper(a["lr"], a["beta1"], a["beta2"], a["eps"], a["weight_decay"], 1.0 / M, 1)
-    hzp.hzp_adamw_shard(plan, 0, 2, 0, 0, hy, acc, 0, p, m, v, out)
+
+    def call():
+        hzp.hzp_adamw_shard(plan, 0, 2, 0, 0, hy, acc, 0, p, m, v, out)
+    plan.prepare()
+    got = launches_of(call)
+    assert len(got) == 2 and got[1][0] == (-(-(sizes[1] - update_cuts(sizes)[1][0]) // 256), 1, 1)
+    call()
     torch.cuda.synchronize()
     for l, s in enumerate(samples):
         on.adamw(on.reduce([s["acc"]], scale=1.0 / M), s["p"], s["m"], s["v"], step=1, **a)
