@@ -495,3 +495,37 @@ def test_single_parameter_gather_at_dense7b_size():
         want = on.unpack_tensor(host_shards, int(rec.offset) + int(start), 80)
         assert np.array_equal(to_host(view[start:start + 80], np.uint16), want), start
     assert not to_host(pool[:5], np.uint16).any() and not to_host(pool[5 + rec.numel:], np.uint16).any()
+
+
+@pytest.mark.parametrize("cls,shift", [(0, 0), (0, 3), (1, 0), (1, 1)])
+def test_unpacking_a_tensor_longer_than_a_part(cls, shift):
+    """A tensor of 2^30 + 12,345 elements in one shard: more than the 32-bit length of a part holds is cut at 2^30 elements.
+    Alone, with the bucket beside it (one pass where every tensor starts on 16 bytes), and by itself; whole outputs on the device."""
+    gc.collect()
+    torch.cuda.empty_cache()
+    numel = [(1 << 30) + 12345, 1001]
+    say("unpacking %d elements, class %d" % (numel[0], cls))
+    plan = hzp.hzp_plan([2], numel, 8, 1, 1, tensor_class=[cls, cls])
+    info, dt = plan.bucket(0, cls), torch.int32 if cls else torch.int16
+    shard = torch.empty(info.padded, dtype=dt, device=DEV)
+    gen = torch.Generator(device=DEV).manual_seed(7)
+    shard.random_(-30000, 30000, generator=gen)
+    places = [shift, -(-(shift + numel[0]) // 16) * 16 + shift]
+    pool = torch.empty(places[1] + numel[1] + 16, dtype=dt, device=DEV)
+    bucket = torch.empty(info.padded + 16, dtype=dt, device=DEV)
+    offs = [plan.tensor(t).offset for t in range(2)]
+    for form in ("tensors", "both", "single"):
+        pool.fill_(77)
+        bucket.fill_(77)
+        views = [pool[p:p + n] for p, n in zip(places, numel)]
+        if form == "single":
+            for t in range(2):
+                hzp.hzp_gather_tensor(plan, t, [shard], views[t])
+        else:
+            hzp.hzp_gather_layer(plan, 0, cls, 3, [shard], bucket[:info.padded] if form == "both" else None, views)
+        torch.cuda.synchronize()
+        for view, off, n in zip(views, offs, numel):
+            assert torch.equal(view, shard[off:off + n]), form
+        gaps = [pool[:places[0]], pool[places[0] + numel[0]:places[1]], pool[places[1] + numel[1]:], bucket[info.padded:]]
+        assert all(bool((gap == 77).all()) for gap in gaps), form
+        assert torch.equal(bucket[:info.padded], shard) == (form == "both"), form
