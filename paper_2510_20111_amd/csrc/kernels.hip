@@ -1327,7 +1327,8 @@ struct Part {
 constexpr uint64_t kMostInPart = 1ull << 30;        // (a part's length has 32 bits)
 
 // Are parts of about equal length, so that a grid with the longest part's tiles for each has few workgroups with nothing to do?
-// `tile` elements make a tile.
+// `tile` elements make a tile.  100 parts of 80 MB, every tenth longer by 5 / 10 / 20 / 40 / 80 %, even / flat grid, us: 27.9 / 29.1, 27.7 /
+// 29.1, 25.2 / 26.4, 27.6 / 29.1, 30.2 / 29.2 (surplus 4 / 9 / 18 / 35 / 67 %): the line is a cautious one.
 static bool even_parts(size_t n, uint64_t total, uint64_t longest, uint64_t tile)
 {
     return longest * n <= total + std::max(total / 16, 256 * tile);
@@ -1335,18 +1336,19 @@ static bool even_parts(size_t n, uint64_t total, uint64_t longest, uint64_t tile
 
 // Lists of parts in the argument block, or pieces found in the device tables?  The lists copy 5-20 % faster, but 200 even or 160
 // uneven parts fill a launch and cost the host 1 us more than the tables' launch, which covers 400 tensors.  So lists where
-// the copies are long enough to show it: 4 MB where one launch does (tables / lists, us: 48 parts of 3.1 MB 4.8 / 4.9, of 6.3 MB 5.8 /
+// the copies are long enough to show it: 3 MB where one launch does (tables / lists, us: 48 parts of 3.1 MB 4.8 / 4.9, of 6.3 MB 5.8 /
 // 5.0; 103 parts of 1.6 MB 3.7 / 4.1, of 6.6 MB 5.4 / 4.2), 16 MB a launch where even parts take several (243 parts of 31 MB
 // 13.7 / 14.1, of 63 MB 23.3 / 22.4; 800 of 52 MB 23.9 / 25.6, of 105 MB 40.3 / 39.1), 128 MB where uneven ones do (243 parts of
-// 126 MB 46.7 / 47.2, of 252 MB 88.8 / 88.8; 800 of 26 MB 16.9 / 28.7, of 210 MB 79.3 / 85.6, of 839 MB 296 / 296).
+// 126 MB 46.7 / 47.2, of 252 MB 88.8 / 88.8; 800 of 26 MB 16.9 / 28.7, of 210 MB 79.3 / 85.6, of 839 MB 296 / 296), 62 MB of those where the
+// longest lies at an odd address (243 parts of 63 MB 27.6 / 27.9, of 126 MB 56.9 / 53.5; 2000 of 1.05 GB 490 / 431).
 // Up to 8 even parts go in the smallest block whatever their length (4.3 / 4.0).
-static bool lists_pay(size_t n, uint64_t total, uint64_t longest, uint32_t es)
+static bool lists_pay(size_t n, uint64_t total, uint64_t longest, bool odd, uint32_t es)
 {
     constexpr uint64_t kMega = 1000000;
     const bool even = even_parts(n, total, longest, kWave * 16 / es);
     const uint64_t most = even ? UnpackList200::kParts : UnpackFlat160::kParts, launches = (n + most - 1) / most;
     if (even && n <= (size_t)UnpackList8::kParts) return true;
-    return total * es >= (launches == 1 ? 4 : even ? 16 * launches : 128 * launches) * kMega;
+    return total * es >= (launches == 1 ? 3 : (even ? 16 : odd ? 62 : 128) * launches) * kMega;
 }
 
 // One launch over parts, cut into runs of at most `cut` elements.
@@ -1383,6 +1385,7 @@ static hzp_status_t unpack_list(const Part *parts, size_t n, uint64_t cut, hipSt
 }
 
 // Launches over a list of parts: each takes parts while they fit its table and hold no more than kMaxTilesPerLaunch tiles.
+// The smaller blocks save the host what they leave out (4 MB in 24 / 48 / 72 even parts, block of 72 / of 200, us: 4.9 / 5.1, 5.1 / 5.4, 5.3 / 5.5).
 template <int ES>
 static hzp_status_t unpack_parts(const Part *parts, size_t n, bool both, hipStream_t stream, const char *who)
 {
@@ -1410,6 +1413,7 @@ static hzp_status_t unpack_parts(const Part *parts, size_t n, bool both, hipStre
         if (even) {
             cut = longest;
         } else if (cnt <= cap / 9) {                // cut at an eighth more than total / cap, they fill the table
+            // (cut / flat, us: 3 to 22 very uneven parts of 20 MB 8.6-9.0 / 8.9-9.3, of 300 MB 94-107 / 97-110; 40 of 300 MB 101 / 105)
             cut = (total + (cap - cnt) - 1) / (cap - cnt);
             cut = std::min(longest, (cut + kTile - 1) / kTile * kTile);
         } else if (cnt > cap_flat) {
@@ -1500,12 +1504,15 @@ hzp_status_t launch_unpack(const hzp_plan_t *plan, const BucketRec &b, const voi
     const DeviceTables *tab = nullptr;
     const hzp_status_t st = device_tables(plan, &tab);
     if (st != HZP_OK) return st;
-    uint64_t total = 0, longest = 0;
+    uint64_t total = 0;
+    size_t longest = p0;
     for (size_t i = p0; i < p1; ++i) {
         total += b.pieces[i].len;
-        longest = std::max(longest, b.pieces[i].len);
+        if (b.pieces[i].len > b.pieces[longest].len) longest = i;
     }
-    if (!lists_pay(n, total, longest, es)) {
+    const Piece &l = b.pieces[longest];
+    const bool odd = (reinterpret_cast<uint64_t>(tensors[l.tensor - t_begin]) + l.dst_off * es) & 15u;
+    if (!lists_pay(n, total, l.len, odd, es)) {
         const UnpackCall u{tab->pieces + b.piece_slot, tab->piece_chunk + b.piece_slot, b, shards, n_shards, stream};
         return launch_unpack_with(u, tensors, t_begin, t_end, "hzp_gather_layer");
     }
@@ -1531,7 +1538,9 @@ hzp_status_t launch_unpack_both(const hzp_plan_t *plan, const BucketRec &b, cons
     const uint32_t es = b.cls == HZP_CLASS_F32 ? 4 : 2;
     const uint64_t out = reinterpret_cast<uint64_t>(bucket);
     // One pass serves both outputs where what is aligned in the shard is aligned in the tensor too and no shard lies in
-    // place; not for so many small tensors that it would take more launches than the two passes.
+    // place; not for so many small tensors that it would take more launches than the two passes.  One pass / two, us: 60 and 100 tensors
+    // of 128 KB 5.9 / 9.2 and 8.5 / 11.9, of 2 MB 58.9 / 75.8 and 98 / 125; several launches: 200 tensors of 32 KB 10.7 / 10.0, of 128 KB
+    // 17.8 / 19.2, of 2 MB 193 / 246: the line at 2 MB (bf16) is a cautious one.
     bool one_pass = b.pieces.size() + n_shards <= (size_t)UnpackBothFlat108::kParts || b.P / b.pieces.size() >= (1u << 20);
     for (uint32_t t = 0; t < b.n_tensors; ++t) one_pass = one_pass && (reinterpret_cast<uint64_t>(tensors[t]) & 15u) == 0;
     for (uint32_t j = 0; j < n_shards; ++j) one_pass = one_pass && reinterpret_cast<uint64_t>(shards[j]) != out + j * b.S3 * es;
