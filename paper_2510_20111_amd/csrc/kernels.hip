@@ -652,7 +652,7 @@ __global__ __launch_bounds__(kWave) void unpack_list_kernel(const Args a)
     }
 }
 
-// The same for short copies and for buckets of very many tensors: one single-wavefront workgroup per chunk of at most
+// The same for buckets of very many tensors in short copies: one single-wavefront workgroup per chunk of at most
 // kUnpackChunk elements of one piece (a run of one tensor inside one shard), found in the plan's device tables, so that a
 // launch covers 400 tensors whatever their sizes.
 constexpr int kUnpackTensorCap = 400;
@@ -1326,6 +1326,30 @@ struct Part {
 };
 constexpr uint64_t kMostInPart = 1ull << 30;        // (a part's length has 32 bits)
 
+// Where the launches find their parts: a list, or the pieces of a bucket and the caller's pointers as they are (short calls
+// show the time of a list made first: 100 / 160 small tensors, 4.6 / 4.8 us a call with one, 4.2 / 4.3 without).
+struct ListedParts {
+    const Part *part;
+    uint64_t length(size_t i) const { return part[i].length(); }
+    const Part &operator[](size_t i) const { return part[i]; }
+    ListedParts from(size_t i) const { return {part + i}; }
+};
+template <int ES>
+struct PieceParts {
+    const Piece *piece;
+    const void *const *shards;
+    void *const *tensors;               // tensors[0] is tensor t_begin's
+    uint32_t t_begin;
+    uint64_t length(size_t i) const { return piece[i].len; }
+    Part operator[](size_t i) const
+    {
+        const Piece &p = piece[i];
+        return {reinterpret_cast<uint64_t>(shards[p.shard]) + p.src_off * ES,
+                reinterpret_cast<uint64_t>(tensors[p.tensor - t_begin]) + p.dst_off * ES, p.len, 0, 0};
+    }
+    PieceParts from(size_t i) const { return {piece + i, shards, tensors, t_begin}; }
+};
+
 // Are parts of about equal length, so that a grid with the longest part's tiles for each has few workgroups with nothing to do?
 // `tile` elements make a tile.  100 parts of 80 MB, every tenth longer by 5 / 10 / 20 / 40 / 80 %, even / flat grid, us: 27.9 / 29.1, 27.7 /
 // 29.1, 25.2 / 26.4, 27.6 / 29.1, 30.2 / 29.2 (surplus 4 / 9 / 18 / 35 / 67 %): the line is a cautious one.
@@ -1334,32 +1358,28 @@ static bool even_parts(size_t n, uint64_t total, uint64_t longest, uint64_t tile
     return longest * n <= total + std::max(total / 16, 256 * tile);
 }
 
-// Lists of parts in the argument block, or pieces found in the device tables?  The lists copy 5-20 % faster, but 200 even or 160
-// uneven parts fill a launch and cost the host 1 us more than the tables' launch, which covers 400 tensors.  So lists where
-// the copies are long enough to show it: 3 MB where one launch does (tables / lists, us: 48 parts of 3.1 MB 4.8 / 4.9, of 6.3 MB 5.8 /
-// 5.0; 103 parts of 1.6 MB 3.7 / 4.1, of 6.6 MB 5.4 / 4.2), 16 MB a launch where even parts take several (243 parts of 31 MB
-// 13.7 / 14.1, of 63 MB 23.3 / 22.4; 800 of 52 MB 23.9 / 25.6, of 105 MB 40.3 / 39.1), 128 MB where uneven ones do (243 parts of
-// 126 MB 46.7 / 47.2, of 252 MB 88.8 / 88.8; 800 of 26 MB 16.9 / 28.7, of 210 MB 79.3 / 85.6, of 839 MB 296 / 296), 62 MB of those where the
+// Lists of parts in the argument block, or pieces found in the device tables?  The lists copy 5-20 % faster (2.0-2.3 us on the device
+// against 2.6-3.0 for up to 100 short parts), but 200 even or 160 uneven parts fill a launch, and the tables' launch covers 400 tensors.
+// So tables where lists take several launches that are not long enough (tables / lists, us): 16 MB a launch of even parts (243 parts of
+// 31 MB 13.7 / 14.1, of 63 MB 23.3 / 22.4; 800 of 52 MB 23.9 / 25.6, of 105 MB 40.3 / 39.1), 128 MB of uneven ones (243 parts of 126 MB
+// 46.7 / 47.2, of 252 MB 88.8 / 88.8; 800 of 26 MB 16.9 / 28.7, of 210 MB 79.3 / 85.6, of 839 MB 296 / 296), 62 MB of those where the
 // longest lies at an odd address (243 parts of 63 MB 27.6 / 27.9, of 126 MB 56.9 / 53.5; 2000 of 1.05 GB 490 / 431).
-// Up to 8 even parts go in the smallest block whatever their length (4.3 / 4.0).
 static bool lists_pay(size_t n, uint64_t total, uint64_t longest, bool odd, uint32_t es)
 {
-    constexpr uint64_t kMega = 1000000;
     const bool even = even_parts(n, total, longest, kWave * 16 / es);
     const uint64_t most = even ? UnpackList200::kParts : UnpackFlat160::kParts, launches = (n + most - 1) / most;
-    if (even && n <= (size_t)UnpackList8::kParts) return true;
-    return total * es >= (launches == 1 ? 3 : (even ? 16 : odd ? 62 : 128) * launches) * kMega;
+    return launches == 1 || total * es >= (even ? 16 : odd ? 62 : 128) * 1000000 * launches;
 }
 
 // One launch over parts, cut into runs of at most `cut` elements.
-template <class Args, int ES>
-static hzp_status_t unpack_list(const Part *parts, size_t n, uint64_t cut, hipStream_t stream, const char *who)
+template <class Args, int ES, class Parts>
+static hzp_status_t unpack_list(const Parts &parts, size_t n, uint64_t cut, hipStream_t stream, const char *who)
 {
     Args a;
     uint32_t cnt = 0, tiles = 0;
     uint64_t longest = 0;
     for (size_t i = 0; i < n; ++i) {
-        const Part &p = parts[i];
+        const Part p = parts[i];
         for (uint64_t at = 0; at < p.length(); at += cut) {
             const uint64_t len = std::min(p.length() - at, cut);
             a.src[cnt] = p.src + at * ES;
@@ -1386,21 +1406,21 @@ static hzp_status_t unpack_list(const Part *parts, size_t n, uint64_t cut, hipSt
 
 // Launches over a list of parts: each takes parts while they fit its table and hold no more than kMaxTilesPerLaunch tiles.
 // The smaller blocks save the host what they leave out (4 MB in 24 / 48 / 72 even parts, block of 72 / of 200, us: 4.9 / 5.1, 5.1 / 5.4, 5.3 / 5.5).
-template <int ES>
-static hzp_status_t unpack_parts(const Part *parts, size_t n, bool both, hipStream_t stream, const char *who)
+template <int ES, bool BOTH, class Parts>
+static hzp_status_t unpack_parts(const Parts &parts, size_t n, hipStream_t stream, const char *who)
 {
     constexpr uint64_t kTile = kWave * 16 / ES;     // elements of a tile
-    const size_t cap = both ? UnpackBoth124::kParts : UnpackList200::kParts;
-    const size_t cap_flat = both ? UnpackBothFlat108::kParts : UnpackFlat160::kParts;
+    constexpr size_t cap = BOTH ? UnpackBoth124::kParts : UnpackList200::kParts;
+    constexpr size_t cap_flat = BOTH ? UnpackBothFlat108::kParts : UnpackFlat160::kParts;
     for (size_t at = 0; at < n;) {
-        const Part *const first = parts + at;
+        const Parts first = parts.from(at);
         size_t cnt = 0;
         uint64_t total = 0, longest = 0;
         auto take = [&](size_t most) {
             cnt = 0;
             total = longest = 0;
             while (at + cnt < n && cnt < most) {
-                const uint64_t len = first[cnt].length();
+                const uint64_t len = first.length(cnt);
                 if (cnt > 0 && (total + len) / kTile > kMaxTilesPerLaunch) break;
                 total += len;
                 longest = std::max(longest, len);
@@ -1411,35 +1431,31 @@ static hzp_status_t unpack_parts(const Part *parts, size_t n, bool both, hipStre
         const bool even = even_parts(cnt, total, longest, kTile);
         uint64_t cut = 0;           // 0: a flat grid
         if (even) {
-            cut = longest;
-        } else if (cnt <= cap / 9) {                // cut at an eighth more than total / cap, they fill the table
-            // (cut / flat, us: 3 to 22 very uneven parts of 20 MB 8.6-9.0 / 8.9-9.3, of 300 MB 94-107 / 97-110; 40 of 300 MB 101 / 105)
+            cut = std::min(longest, kMostInPart);       // (a part beyond that is alone: a launch has fewer tiles)
+        } else if (cnt <= cap / 9 && total * ES >= 1000000) {       // cut at an eighth more than total / cap, they fill the table
+            // (cut / flat, us: 3 to 22 very uneven parts of 20 MB 8.6-9.0 / 8.9-9.3, of 300 MB 94-107 / 97-110; 40 of 300 MB 101 / 105; call
+            // after call and on the device alone, 12 of 0.4 MB 4.8 / 4.5 and 2.55 / 2.52, 0.8 MB 4.8 / 4.5 and 2.84 / 2.74, 1.5 MB 4.8 / 4.6
+            // and 3.1 / 3.3, 4 MB 4.7 / 4.9 and 4.1 / 4.3)
             cut = (total + (cap - cnt) - 1) / (cap - cnt);
             cut = std::min(longest, (cut + kTile - 1) / kTile * kTile);
         } else if (cnt > cap_flat) {
             take(cap_flat);
         }
         hzp_status_t st;
-        if (both)
+        if constexpr (BOTH)
             st = cut                   ? unpack_list<UnpackBoth124, ES>(first, cnt, cut, stream, who)
                  : cnt <= 64           ? unpack_list<UnpackBothFlat64, ES>(first, cnt, longest, stream, who)
                                        : unpack_list<UnpackBothFlat108, ES>(first, cnt, longest, stream, who);
         else
             st = !cut                  ? (cnt <= 64 ? unpack_list<UnpackFlat64, ES>(first, cnt, longest, stream, who)
                                                     : unpack_list<UnpackFlat160, ES>(first, cnt, longest, stream, who))
-                 : even && cnt <= 8    ? unpack_list<UnpackList8, ES>(first, cnt, cut, stream, who)
-                 : even && cnt <= 72   ? unpack_list<UnpackList72, ES>(first, cnt, cut, stream, who)
-                                       : unpack_list<UnpackList200, ES>(first, cnt, cut, stream, who);
+                 : cut < longest || cnt > 72 ? unpack_list<UnpackList200, ES>(first, cnt, cut, stream, who)
+                 : cnt <= 8            ? unpack_list<UnpackList8, ES>(first, cnt, cut, stream, who)
+                                       : unpack_list<UnpackList72, ES>(first, cnt, cut, stream, who);
         if (st != HZP_OK) return st;
         at += cnt;
     }
     return HZP_OK;
-}
-
-static hzp_status_t unpack_parts(const BucketRec &b, const std::vector<Part> &parts, bool both, hipStream_t stream)
-{
-    return b.cls == HZP_CLASS_F32 ? unpack_parts<4>(parts.data(), parts.size(), both, stream, "hzp_gather_layer")
-                                  : unpack_parts<2>(parts.data(), parts.size(), both, stream, "hzp_gather_layer");
 }
 
 // What the launches of one unpacking call share.
@@ -1504,32 +1520,23 @@ hzp_status_t launch_unpack(const hzp_plan_t *plan, const BucketRec &b, const voi
     const DeviceTables *tab = nullptr;
     const hzp_status_t st = device_tables(plan, &tab);
     if (st != HZP_OK) return st;
-    uint64_t total = 0;
-    size_t longest = p0;
-    for (size_t i = p0; i < p1; ++i) {
-        total += b.pieces[i].len;
-        if (b.pieces[i].len > b.pieces[longest].len) longest = i;
-    }
-    const Piece &l = b.pieces[longest];
-    const bool odd = (reinterpret_cast<uint64_t>(tensors[l.tensor - t_begin]) + l.dst_off * es) & 15u;
-    if (!lists_pay(n, total, l.len, odd, es)) {
-        const UnpackCall u{tab->pieces + b.piece_slot, tab->piece_chunk + b.piece_slot, b, shards, n_shards, stream};
-        return launch_unpack_with(u, tensors, t_begin, t_end, "hzp_gather_layer");
-    }
-    std::vector<Part> parts;
-    try {
-        parts.reserve(n);
+    if (n > (size_t)UnpackFlat160::kParts) {            // (fewer are one launch)
+        uint64_t total = 0;
+        size_t longest = p0;
         for (size_t i = p0; i < p1; ++i) {
-            const Piece &p = b.pieces[i];
-            const uint64_t src = reinterpret_cast<uint64_t>(shards[p.shard]) + p.src_off * es;
-            const uint64_t dst = reinterpret_cast<uint64_t>(tensors[p.tensor - t_begin]) + p.dst_off * es;
-            for (uint64_t x = 0; x < p.len; x += kMostInPart)
-                parts.push_back({src + x * es, dst + x * es, std::min(p.len - x, kMostInPart), 0, 0});
+            total += b.pieces[i].len;
+            if (b.pieces[i].len > b.pieces[longest].len) longest = i;
         }
-    } catch (const std::bad_alloc &) {
-        return fail(HZP_ERR_NOMEM, "hzp_gather_layer: out of host memory");
+        const Piece &l = b.pieces[longest];
+        const bool odd = (reinterpret_cast<uint64_t>(tensors[l.tensor - t_begin]) + l.dst_off * es) & 15u;
+        if (!lists_pay(n, total, l.len, odd, es)) {
+            const UnpackCall u{tab->pieces + b.piece_slot, tab->piece_chunk + b.piece_slot, b, shards, n_shards, stream};
+            return launch_unpack_with(u, tensors, t_begin, t_end, "hzp_gather_layer");
+        }
     }
-    return unpack_parts(b, parts, false, stream);
+    const Piece *const piece = b.pieces.data() + p0;
+    return es == 4 ? unpack_parts<4, false>(PieceParts<4>{piece, shards, tensors, t_begin}, n, stream, "hzp_gather_layer")
+                   : unpack_parts<2, false>(PieceParts<2>{piece, shards, tensors, t_begin}, n, stream, "hzp_gather_layer");
 }
 
 hzp_status_t launch_unpack_both(const hzp_plan_t *plan, const BucketRec &b, const void *const *shards, uint32_t n_shards,
@@ -1576,7 +1583,9 @@ hzp_status_t launch_unpack_both(const hzp_plan_t *plan, const BucketRec &b, cons
     } catch (const std::bad_alloc &) {
         return fail(HZP_ERR_NOMEM, "hzp_gather_layer: out of host memory");
     }
-    return unpack_parts(b, parts, true, stream);
+    const ListedParts listed{parts.data()};
+    return es == 4 ? unpack_parts<4, true>(listed, parts.size(), stream, "hzp_gather_layer")
+                   : unpack_parts<2, true>(listed, parts.size(), stream, "hzp_gather_layer");
 }
 
 // ---------------------------------------------------------------------------------------
