@@ -724,10 +724,19 @@ __global__ __launch_bounds__(kWave) void unpack_kernel(const UnpackArgs a)
 // ---------------------------------------------------------------------------------------
 // Launchers (host).  Arguments were validated by the callers in api.cpp.
 // ---------------------------------------------------------------------------------------
-static hzp_status_t check_launch(const char *what)
+template <class T>
+struct AsIs {
+    typedef T type;
+};
+// Launches `kernel`.  (The <<<>>> form first pushes the launch shape for a stub that pops it again: 0.1 us more a launch.)
+template <class... P>
+static hzp_status_t start(const char *who, void (*kernel)(P...), dim3 grid, dim3 block, unsigned lds, hipStream_t stream,
+                          const typename AsIs<P>::type &...args)
 {
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return fail(HZP_ERR_HIP, "%s: launch failed: %s", what, hipGetErrorString(e));
+    void *ptrs[] = {const_cast<void *>(static_cast<const void *>(&args))...};
+    (void)hipLaunchKernel(reinterpret_cast<const void *>(kernel), grid, block, ptrs, lds, stream);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return fail(HZP_ERR_HIP, "%s: launch failed: %s", who, hipGetErrorString(e));
     return HZP_OK;
 }
 
@@ -816,8 +825,8 @@ hzp_status_t launch_reduce(bool g32, const void *const *slices, uint32_t R, uint
         const ReduceForm form = reduce_form(g32, R, (a.nquad + kGroupQuads - 1) / kGroupQuads);
         const uint32_t quads = kGroupQuads * reduce_quads(R, g32, form);        // to a wavefront
         const unsigned waves = form == kReduceNarrow ? 0 : reduce_waves(g32, R, here, accumulate);
-        hipLaunchKernelGGL(kernels[g32][accumulate != 0][form][R - 1], dim3((a.nquad + quads - 1) / quads), dim3(kWave), lds_for(waves), stream, a);
-        const hzp_status_t st = check_launch("hzp_reduce_shard");
+        const hzp_status_t st = start("hzp_reduce_shard", kernels[g32][accumulate != 0][form][R - 1], dim3((a.nquad + quads - 1) / quads), dim3(kWave),
+                                      lds_for(waves), stream, a);
         if (st != HZP_OK) return st;
     }
     return HZP_OK;
@@ -911,7 +920,7 @@ static void list_runs(const hzp_plan_t *plan, const FusedSegment *segs, size_t n
 constexpr uint32_t kUncappedGroups = 5120;
 
 template <FusedForm FORM, bool FEW, class Args>
-static void start_kernel(bool g32, bool o32, uint32_t R, const Args &a, dim3 grid, uint32_t groups, hipStream_t stream)
+static hzp_status_t start_fused(bool g32, bool o32, uint32_t R, const Args &a, dim3 grid, uint32_t groups, hipStream_t stream)
 {
     constexpr std::make_index_sequence<HZP_MAX_REPLICAS> all;
     static constexpr auto kernels16 = fused_kernels<false, false, FORM, FEW, Args>(all);
@@ -926,7 +935,7 @@ static void start_kernel(bool g32, bool o32, uint32_t R, const Args &a, dim3 gri
     const unsigned waves16 = groups > 200000u ? (FORM == kSearched ? 12u : 10u) : groups > 32768u ? 12u : 14u;
     const unsigned waves32 = FORM == kSearched ? 10u : 8u;
     const bool capped = groups > kUncappedGroups;
-    hipLaunchKernelGGL(kernel, grid, dim3(kWave), capped ? lds_for(g32 ? waves32 : waves16) : 0u, stream, a);
+    return start("hzp_adamw_shard", kernel, grid, dim3(kWave), capped ? lds_for(g32 ? waves32 : waves16) : 0u, stream, a);
 }
 
 hzp_status_t launch_fused(const hzp_plan_t *plan, bool g32, bool o32, uint32_t R, const FusedSegment *segs, size_t nseg,
@@ -1035,27 +1044,27 @@ hzp_status_t launch_fused(const hzp_plan_t *plan, bool g32, bool o32, uint32_t R
         // (where wavefronts also read tables, 16 fp32 contributions are too many a little earlier: 32 segments of 0.52 M elements together,
         // R = 16, 10.1 us without and 10.5 with them; 0.38 M 8.6 and 8.4)
         const bool few = blocks <= (g32 ? kFewGroups / 4 * 3 : kFewGroups);
+        hzp_status_t st;
         if (cnt == 1 && !a.lookup) {
             FusedOneArgs one;
             one.scalars_dev = a.scalars_dev;
             one.scalars = a.scalars;
             std::memcpy(one.word, a.word, (per_seg + kPlainRecord) * sizeof one.word[0]);
             if (blocks <= kFewGroups)
-                start_kernel<kOne, true>(g32, o32, R, one, grid, blocks, stream);
+                st = start_fused<kOne, true>(g32, o32, R, one, grid, blocks, stream);
             else
-                start_kernel<kOne, false>(g32, o32, R, one, grid, blocks, stream);
+                st = start_fused<kOne, false>(g32, o32, R, one, grid, blocks, stream);
         } else if (a.grid2d && !shared && !a.lookup) {
             if (few)
-                start_kernel<kPlain, true>(g32, o32, R, a, grid, blocks, stream);
+                st = start_fused<kPlain, true>(g32, o32, R, a, grid, blocks, stream);
             else
-                start_kernel<kPlain, false>(g32, o32, R, a, grid, blocks, stream);
+                st = start_fused<kPlain, false>(g32, o32, R, a, grid, blocks, stream);
         } else {
             if (few)
-                start_kernel<kSearched, true>(g32, o32, R, a, grid, blocks, stream);
+                st = start_fused<kSearched, true>(g32, o32, R, a, grid, blocks, stream);
             else
-                start_kernel<kSearched, false>(g32, o32, R, a, grid, blocks, stream);
+                st = start_fused<kSearched, false>(g32, o32, R, a, grid, blocks, stream);
         }
-        hzp_status_t st = check_launch("hzp_adamw_shard");
         if (st != HZP_OK) return st;
         for (uint32_t c = 0; c < cnt; ++c) {
             done += part[c].n;
@@ -1085,8 +1094,7 @@ static hzp_status_t copy_list(const Move *moves, size_t n, hipStream_t stream, c
         longest = std::max(longest, moves[s].nvec);
     }
     const dim3 grid((uint32_t)((longest + kWave - 1) / kWave), (uint32_t)n), block(kWave);
-    hipLaunchKernelGGL(copy_list_kernel<Args>, grid, block, 0, stream, a);
-    return check_launch(who);
+    return start(who, copy_list_kernel<Args>, grid, block, 0, stream, a);
 }
 
 // Most tiles of 64 vectors in one launch of a copy of many pieces (600 MB, about 180 us).  Over a longer launch the XCDs drift apart, as in the
@@ -1205,8 +1213,7 @@ static hzp_status_t copy_shared(const void *const *srcs, uint32_t per_layer, con
             a.layer[i] = {reinterpret_cast<uint64_t>(dsts[l]), (int32_t)(d / 16), (uint32_t)(bytes_per_piece[l] / 16)};
         }
         const dim3 grid((uint32_t)tiles_of(longest), n_src, (uint32_t)cnt), block(kWave);
-        hipLaunchKernelGGL(copy_shared_kernel, grid, block, 0, stream, a);
-        const hzp_status_t st = check_launch("hzp_gather_layers");
+        const hzp_status_t st = start("hzp_gather_layers", copy_shared_kernel, grid, block, 0, stream, a);
         if (st != HZP_OK) return st;
         at += cnt;
     }
@@ -1294,8 +1301,7 @@ static hzp_status_t copy_ranges(const Move *moves, uint32_t n, uint32_t tiles, h
         a.nvec[s] = (uint32_t)moves[s].nvec;
         a.tile_end[s] = end += (uint32_t)tiles_of(moves[s].nvec);
     }
-    hipLaunchKernelGGL(copy_ranges_kernel<Args>, dim3(tiles), dim3(kWave), 0, stream, a);
-    return check_launch("hzp_gather_shard");
+    return start("hzp_gather_shard", copy_ranges_kernel<Args>, dim3(tiles), dim3(kWave), 0, stream, a);
 }
 
 hzp_status_t launch_concat_ranges(const void *const *srcs, const uint64_t *dst_off, const uint64_t *bytes,
@@ -1400,8 +1406,7 @@ static hzp_status_t unpack_list(const Parts &parts, size_t n, uint64_t cut, hipS
         std::fill(a.tile_end + cnt, std::end(a.tile_end), ~0u);
         grid = dim3(tiles);
     }
-    hipLaunchKernelGGL((unpack_list_kernel<ES, Args>), grid, dim3(kWave), 0, stream, a);
-    return check_launch(who);
+    return start(who, unpack_list_kernel<ES, Args>, grid, dim3(kWave), 0, stream, a);
 }
 
 // Launches over a list of parts: each takes parts while they fit its table and hold no more than kMaxTilesPerLaunch tiles.
@@ -1469,7 +1474,8 @@ struct UnpackCall {
 };
 
 // One launch: tensors [t0, t1), whose pieces are [p0, p1).
-static void start_unpack(const UnpackCall &u, void *const *tensors, uint32_t t0, uint32_t t1, size_t p0, size_t p1)
+static hzp_status_t start_unpack(const UnpackCall &u, void *const *tensors, uint32_t t0, uint32_t t1, size_t p0, size_t p1,
+                                 const char *who)
 {
     UnpackArgs a;
     a.pieces = u.pieces;
@@ -1480,11 +1486,7 @@ static void start_unpack(const UnpackCall &u, void *const *tensors, uint32_t t0,
     a.tensor0 = t0;
     for (uint32_t s = 0; s < u.n_shards; ++s) a.shard[s] = u.shards[s];
     for (uint32_t t = t0; t < t1; ++t) a.tensor[t - t0] = tensors[t - t0];
-    const dim3 grid(a.chunk_end - a.chunk0), block(kWave);
-    if (u.b.cls == HZP_CLASS_F32)
-        hipLaunchKernelGGL(unpack_kernel<4>, grid, block, 0, u.stream, a);
-    else
-        hipLaunchKernelGGL(unpack_kernel<2>, grid, block, 0, u.stream, a);
+    return start(who, u.b.cls == HZP_CLASS_F32 ? unpack_kernel<4> : unpack_kernel<2>, dim3(a.chunk_end - a.chunk0), dim3(kWave), 0, u.stream, a);
 }
 
 // First piece at or behind `from` of a tensor or a later one (pieces are sorted by tensor).
@@ -1503,8 +1505,7 @@ static hzp_status_t launch_unpack_with(const UnpackCall &u, void *const *tensors
     for (uint32_t t0 = t_begin; t0 < t_end; t0 += kUnpackTensorCap) {
         const uint32_t t1 = std::min<uint32_t>(t_end, t0 + kUnpackTensorCap);
         const size_t p1 = first_piece(u.b, p0, t1);
-        start_unpack(u, tensors + (t0 - t_begin), t0, t1, p0, p1);
-        hzp_status_t st = check_launch(who);
+        const hzp_status_t st = start_unpack(u, tensors + (t0 - t_begin), t0, t1, p0, p1, who);
         if (st != HZP_OK) return st;
         p0 = p1;
     }
@@ -1646,8 +1647,7 @@ static hzp_status_t fill_table(void *dst, const void *src, size_t bytes, hipStre
         a.n = (uint32_t)std::min<size_t>(left, kFillWords);
         std::memcpy(a.word, w, (size_t)a.n * 4);
         a.dst = d;
-        hipLaunchKernelGGL(table_fill_kernel, dim3(1), dim3(256), 0, stream, a);
-        hzp_status_t st = check_launch("hzp_gather_layer_static");
+        const hzp_status_t st = start("hzp_gather_layer_static", table_fill_kernel, dim3(1), dim3(256), 0, stream, a);
         if (st != HZP_OK) return st;
         w += a.n;
         d += a.n;
