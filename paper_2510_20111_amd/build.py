@@ -13,6 +13,8 @@ def build(verbose=False):
     cmd = ["hipcc", "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",
            # packed fp32 instructions stay off (see the hipcc flag of the same name)
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+           # a kernel's leading arguments that are no structs arrive in scalar registers (14 words are the most that fit)
+           "-mllvm", "-amdgpu-kernarg-preload-count=14",
            "-Wall", "-Wno-unused-command-line-argument", "-pthread",
            "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(HERE, "csrc")]
     cmd += [os.path.join(HERE, "csrc", s) for s in SOURCES]

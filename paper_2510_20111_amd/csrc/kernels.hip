@@ -35,6 +35,8 @@ namespace hzp {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+typedef uint64_t u64x4 __attribute__((ext_vector_type(4)));
 // Same vector with element alignment only, for sources that follow an unaligned destination.
 typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
 typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
@@ -205,11 +207,8 @@ __device__ __forceinline__ void sum_contributions(uint64_t (&at)[MOST], const ui
 // ---------------------------------------------------------------------------------------
 // Standalone reduction (bit-exact with the scalar definition: fixed order, no contraction).
 // ---------------------------------------------------------------------------------------
-struct ReduceArgs {
-    uint64_t g[HZP_MAX_REPLICAS];
-    float *out;
-    uint32_t nquad;     // 4-element quads in the slice
-    float scale;
+struct ReduceRest {
+    uint64_t g[HZP_MAX_REPLICAS];       // all pointers; the first four are arguments of their own
 };
 
 // The forms of a launch: contributions in flight (chunk), quads per lane, and whether the sum that is accumulated onto is requested
@@ -223,19 +222,24 @@ constexpr uint32_t reduce_chunk(uint32_t R, ReduceForm form)
 // occupancy (25 M elements: 5.89 TB/s; with two quads 6.22).
 constexpr int reduce_quads(uint32_t R, bool g32, ReduceForm form) { return form == kReduceNarrow || (R == 1 && !g32) ? 2 : 1; }
 
+// What the first requests need, the first four pointers and the output (out[1]: number of quads, scale), is in scalar registers when a
+// wavefront starts: leading arguments that are no structs arrive there (the build asks for 14 words; vectors, because the host spends 15 ns
+// on every argument).  With all of it read from the argument block, us: bf16 R = 4 / 8 of 2.1 M elements 5.8 / 8.2 (now 5.5 / 8.1), R = 32
+// of 0.5 M 7.4 (6.9), R = 8 of 25 M 76.6 (75.8); fp32 R = 4 accumulating, 1 / 6.3 M 6.0 / 25.1 (5.8 / 25.0), R = 16 of 0.26 M, the one that
+// lost, 5.0 (5.3: its later pointers now queue behind the first requests).
 template <uint32_t R, bool G32, bool ACC, ReduceForm FORM>
-__global__ __launch_bounds__(kWave) void reduce_kernel(const ReduceArgs a)
+__global__ __launch_bounds__(kWave) void reduce_kernel(const u64x4 g, const u64x2 o, const ReduceRest rest)
 {
 #pragma clang fp contract(off)
     constexpr int Q = reduce_quads(R, G32, FORM);
     constexpr uint32_t CHUNK = reduce_chunk(R, FORM);
     constexpr bool LATE = FORM == kReduceNarrow;
-    uint64_t out = reinterpret_cast<uint64_t>(a.out), at[CHUNK];
+    const uint64_t out = o[0];
+    const uint32_t nquad = (uint32_t)o[1];
+    const float scale = __uint_as_float((uint32_t)(o[1] >> 32));
+    uint64_t at[CHUNK];
 #pragma unroll
-    for (uint32_t c = 0; c < CHUNK; ++c) at[c] = c < R ? a.g[c] : 0;
-    uint32_t nquad = a.nquad;
-    float scale = a.scale;
-    pin(out, at[0], at[1], at[CHUNK > 2 ? 2 : 0], at[CHUNK > 2 ? 3 : 0], nquad, scale);
+    for (uint32_t c = 0; c < CHUNK; ++c) at[c] = c >= R ? 0 : c < 4 ? g[c] : rest.g[c];
     uint32_t q0[Q], quad[Q];
     f32x4 t[Q];
 #pragma unroll
@@ -245,7 +249,7 @@ __global__ __launch_bounds__(kWave) void reduce_kernel(const ReduceArgs a)
         if (ACC && !LATE) t[q] = ld_stream<f32x4>(out, quad[q]);
     }
     float s[Q][4];
-    sum_contributions<R, CHUNK, G32>(at, a.g, 0, quad, s);
+    sum_contributions<R, CHUNK, G32>(at, rest.g, 0, quad, s);
 #pragma unroll
     for (int q = 0; q < Q; ++q)
         if (ACC && LATE) t[q] = ld_stream<f32x4>(out, quad[q]);
@@ -743,8 +747,9 @@ static hzp_status_t start(const char *who, void (*kernel)(P...), dim3 grid, dim3
 // One kernel per number of contributions: the loads of a chunk are then straight-line code (a run-time R
 // puts a wait between any two of them), and all of a launch's pointers arrive in one round of scalar loads.
 // (the other forms are for more than 8 contributions)
+typedef void (*ReduceKernel)(u64x4, u64x2, ReduceRest);
 template <bool G32, bool ACC, ReduceForm FORM, size_t... I>
-static constexpr std::array<void (*)(ReduceArgs), sizeof...(I)> reduce_kernels(std::index_sequence<I...>)
+static constexpr std::array<ReduceKernel, sizeof...(I)> reduce_kernels(std::index_sequence<I...>)
 {
     return {reduce_kernel<I + 1, G32, ACC, I < 8 ? kReducePlain : FORM>...};
 }
@@ -806,7 +811,7 @@ hzp_status_t launch_reduce(bool g32, const void *const *slices, uint32_t R, uint
     if (n == 0) return HZP_OK;
     const uint32_t es = g32 ? 4u : 2u;
     constexpr std::make_index_sequence<HZP_MAX_REPLICAS> all;
-    static constexpr std::array<void (*)(ReduceArgs), HZP_MAX_REPLICAS> kernels[2][2][3] = {
+    static constexpr std::array<ReduceKernel, HZP_MAX_REPLICAS> kernels[2][2][3] = {
         {{reduce_kernels<false, false, kReducePlain>(all), reduce_kernels<false, false, kReduceFew>(all), reduce_kernels<false, false, kReduceNarrow>(all)},
          {reduce_kernels<false, true, kReducePlain>(all), reduce_kernels<false, true, kReduceFew>(all), reduce_kernels<false, true, kReduceNarrow>(all)}},
         {{reduce_kernels<true, false, kReducePlain>(all), reduce_kernels<true, false, kReduceFew>(all), reduce_kernels<true, false, kReduceNarrow>(all)},
@@ -817,16 +822,18 @@ hzp_status_t launch_reduce(bool g32, const void *const *slices, uint32_t R, uint
     const uint64_t most = ((n + launches - 1) / launches + kTwoGroups - 1) / kTwoGroups * kTwoGroups;
     for (uint64_t first = 0; first < n; first += most) {
         const uint64_t here = std::min(n - first, most);
-        ReduceArgs a{};
+        ReduceRest a;               // a kernel reads its R pointers, and of the first four whatever there is
         for (uint32_t r = 0; r < R; ++r) a.g[r] = reinterpret_cast<uint64_t>(slices[r]) + first * es;
-        a.out = out + first;
-        a.nquad = (uint32_t)(here / 4);
-        a.scale = scale;
-        const ReduceForm form = reduce_form(g32, R, (a.nquad + kGroupQuads - 1) / kGroupQuads);
+        for (uint32_t r = R; r < 4; ++r) a.g[r] = 0;
+        const uint32_t nquad = (uint32_t)(here / 4);
+        uint32_t scale_bits;
+        std::memcpy(&scale_bits, &scale, sizeof scale_bits);
+        const ReduceForm form = reduce_form(g32, R, (nquad + kGroupQuads - 1) / kGroupQuads);
         const uint32_t quads = kGroupQuads * reduce_quads(R, g32, form);        // to a wavefront
         const unsigned waves = form == kReduceNarrow ? 0 : reduce_waves(g32, R, here, accumulate);
-        const hzp_status_t st = start("hzp_reduce_shard", kernels[g32][accumulate != 0][form][R - 1], dim3((a.nquad + quads - 1) / quads), dim3(kWave),
-                                      lds_for(waves), stream, a);
+        const hzp_status_t st = start("hzp_reduce_shard", kernels[g32][accumulate != 0][form][R - 1], dim3((nquad + quads - 1) / quads), dim3(kWave),
+                                      lds_for(waves), stream, u64x4{a.g[0], a.g[1], a.g[2], a.g[3]},
+                                      u64x2{reinterpret_cast<uint64_t>(out + first), nquad | (uint64_t)scale_bits << 32}, a);
         if (st != HZP_OK) return st;
     }
     return HZP_OK;
