@@ -170,10 +170,11 @@ __device__ __forceinline__ void pin(T &x, Rest &...rest)
 }
 
 // Left-to-right fp32 sum of R contributions, ((g0 + g1) + g2) + ..., at most `MOST` of them in flight, for
-// Q quads; slice[r] + shift is contribution r, and `at` holds the first chunk's pointers.
-template <uint32_t R, uint32_t MOST, bool G32, int Q>
+// Q quads; slice[r] + shift is contribution r, and `at` holds the first chunk's pointers.  meanwhile() runs when the first chunk
+// is requested.
+template <uint32_t R, uint32_t MOST, bool G32, int Q, class Meanwhile>
 __device__ __forceinline__ void sum_contributions(uint64_t (&at)[MOST], const uint64_t *slice, int64_t shift,
-                                                  const uint32_t (&quad)[Q], float (&s)[Q][4])
+                                                  const uint32_t (&quad)[Q], float (&s)[Q][4], Meanwhile meanwhile)
 {
     constexpr uint32_t C = chunk_of(R, MOST);
 #pragma unroll
@@ -188,6 +189,7 @@ __device__ __forceinline__ void sum_contributions(uint64_t (&at)[MOST], const ui
         for (uint32_t c = 0; c < C; ++c)
             if (base + C + c < R) at[c] = slice[base + C + c];
         __builtin_amdgcn_sched_barrier(0);      // the whole chunk is requested (and the next one's pointers) before its first add,
+        if (base == 0) meanwhile();
 #pragma unroll
         for (uint32_t c = 0; c < C; ++c)
 #pragma unroll
@@ -249,7 +251,7 @@ __global__ __launch_bounds__(kWave) void reduce_kernel(const u64x4 g, const u64x
         if (ACC && !LATE) t[q] = ld_stream<f32x4>(out, quad[q]);
     }
     float s[Q][4];
-    sum_contributions<R, CHUNK, G32>(at, rest.g, 0, quad, s);
+    sum_contributions<R, CHUNK, G32>(at, rest.g, 0, quad, s, [] {});
 #pragma unroll
     for (int q = 0; q < Q; ++q)
         if (ACC && LATE) t[q] = ld_stream<f32x4>(out, quad[q]);
@@ -290,13 +292,20 @@ struct FusedArgs {
     uint64_t word[kTableWords];
 };
 static_assert(sizeof(FusedArgs) <= 4096, "kernel arguments");
-// The same for one segment with pointers of its own and one multiplier: a tenth of the block, and launching costs
-// 2.4-2.8 us with the smallest blocks and 2.7-4.0 us with the largest (the host writes it to device memory).
+// The same for one segment with pointers of its own and one multiplier, whose leading arguments (FusedLead) are in scalar registers when a
+// wavefront starts: all that its first requests need, up to two contributions.  The block is a tenth of the other, and
+// launching costs 2.3 us with the smallest blocks and 2.6 with the largest (the host writes it to device memory).
 struct FusedOneArgs {
-    const AdamScalars *scalars_dev;
+    uint64_t out;
     AdamScalars scalars;
-    uint64_t word[HZP_MAX_REPLICAS + 4 + kPlainRecord];
+    uint64_t g[HZP_MAX_REPLICAS];
 };
+struct FusedLead {
+    u64x4 p;                                // master, m, v, the first contribution
+    u64x2 w;                                // the second, the step's scalars in device memory (or null: they are in the block)
+    uint64_t size;                          // number of quads, decay multiplier
+};
+constexpr uint32_t kLeadBytes = 56;         // of the argument block; the struct follows
 enum FusedForm { kSearched, kPlain, kOne };
 
 // The decay runs that a group meets, found while the streams arrive: begin() narrows the search to 64
@@ -351,68 +360,99 @@ struct DecayRuns {
 // with bf16 contributions (R = 4 / 8 / 16, 100 M elements): 6.74 / 6.68 / 6.58 -> 6.77 / 6.78 / 6.72 TB/s;
 // quadruples lose again (6.66 / 6.73 / 6.66), and where all streams are fp32 pairs lose 1 % (6.79 -> 6.73).
 //
-// kPlain: a 2-D grid over segments with pointers of their own and one multiplier each; kOne: a single such segment
-// (a whole arena of equal decay is one).  Everything a wavefront needs then lies at an address that blockIdx gives and
-// arrives in one round of scalar loads.  kSearched: a uniform binary search may have to find the segment, three more
-// rounds, which the few resident wavefronts hide badly (105 M elements, R = 8, one segment: 6.65 TB/s at the best
-// number of wavefronts, 6.73 with the one round).
-template <uint32_t R, bool G32, bool O32, FusedForm FORM, uint32_t CHUNK>
-__global__ __launch_bounds__(kWave) void fused_adamw_kernel(const std::conditional_t<FORM == kOne, FusedOneArgs, FusedArgs> a)
+// kPlain: a 2-D grid over segments with pointers of their own and one multiplier each; everything a wavefront needs lies at an
+// address that blockIdx gives and arrives in one round of scalar loads.  kOne: a single such segment (a whole arena of equal decay
+// is one); what its first requests need is there when it starts (read from the argument block / in registers, us: bf16 R = 4 of
+// 0.46 M elements 5.0 / 4.6, R = 1 and 8 of 2.1 M 11.5 / 11.3 and 16.6 / 16.4, fp32 R = 12 of 0.26 M 5.9 / 5.5; from 25 M the same).
+// kSearched: a uniform binary search may have to find the segment, three more rounds, which the few resident wavefronts hide badly
+// (105 M elements, R = 8, one segment: 6.65 TB/s at the best number of wavefronts, 6.73 with one round).
+template <uint32_t R, bool G32, bool O32, FusedForm FORM, uint32_t CHUNK, class Args>
+__device__ __forceinline__ void fused_adamw(const FusedLead lead, const Args &a)
 {
     constexpr bool PAIRS = !G32;
     // Which segment and which group of it?
-    uint32_t grp = blockIdx.x, before = 0;      // workgroups of the segments ahead of it
-    const uint64_t *ptr, *rec;
+    uint32_t grp = blockIdx.x;
+    const uint64_t *slice, *rec = nullptr;      // the contributions' pointers, the segment's record
     int64_t shift = 0, out_shift = 0;           // of the segment against the pointers, in quads
     bool lookup = false;
     DecayRuns runs;
     uint64_t pos = 0;                           // of the group's first element in its bucket
-    if constexpr (FORM != kSearched) {
-        ptr = a.word + (FORM == kOne ? 0 : blockIdx.y * (R + 4 + kPlainRecord));
-        rec = ptr + R + 4;
-    } else {
-        uint32_t segments = a.segments, stride = a.stride, ptr_stride = a.ptr_stride, dist = a.dist, grid2d = a.grid2d, look = a.lookup;
-        pin(segments, stride, ptr_stride, dist, grid2d, look);
-        lookup = look;
-        const uint64_t *const records = a.word + R + 4;
-        uint32_t seg = blockIdx.y;
-        if (!grid2d) {
-            uint32_t lo = 0, hi = segments - 1;
-            while (lo < hi) {
-                const uint32_t mid = (lo + hi) >> 1;
-                if (blockIdx.x < (uint32_t)records[mid * stride])
-                    hi = mid;
-                else
-                    lo = mid + 1;
-            }
-            seg = lo;
-            before = seg ? (uint32_t)records[(seg - 1) * stride] : 0u;
-        }
-        rec = records + seg * stride;
-        ptr = a.word + seg * ptr_stride;
-        grp -= before;
-        if (dist) {
-            const uint64_t d = rec[dist];
-            shift = (int32_t)(uint32_t)d;
-            out_shift = (int32_t)(uint32_t)(d >> 32);
-        }
-    }
-    uint64_t P = ptr[0], M = ptr[1], V = ptr[2], OUT = ptr[3], extent = rec[0], decay = rec[1];
-    uint64_t at[CHUNK];
+    uint64_t P, M, V, OUT, decay, at[CHUNK], scalars_dev;
+    uint32_t groups, nquad;
+    AdamScalars h;
+    if constexpr (FORM == kOne) {
+        P = lead.p[0];
+        M = lead.p[1];
+        V = lead.p[2];
+        OUT = a.out;
+        scalars_dev = lead.w[1];
+        nquad = (uint32_t)lead.size;
+        decay = lead.size >> 32;
+        groups = (nquad + kGroupQuads - 1) / kGroupQuads;
+        slice = a.g;
 #pragma unroll
-    for (uint32_t c = 0; c < CHUNK; ++c) at[c] = c < R ? ptr[4 + c] : 0;
-    AdamScalars h = a.scalars;
-    uint64_t scalars_dev = reinterpret_cast<uint64_t>(a.scalars_dev);
-    pin(P, M, V, OUT, extent, decay, at[0], at[1], at[2], at[CHUNK > 3 ? 3 : 2], scalars_dev);
-    pin(h.lr, h.beta1, h.beta2, h.one_minus_beta1, h.one_minus_beta2, h.eps, h.weight_decay, h.grad_scale, h.inv_bc1, h.inv_bc2);
-    const uint32_t groups = (uint32_t)extent - before, nquad = (uint32_t)(extent >> 32);
-    if (grp >= groups) return;                  // of a longer segment of a 2-D grid
+        for (uint32_t c = 0; c < CHUNK; ++c) at[c] = c >= R ? 0 : c == 0 ? lead.p[3] : c == 1 ? lead.w[0] : a.g[c];
+    } else {
+        const uint64_t *ptr;
+        uint32_t before = 0;                    // workgroups of the segments ahead of it
+        if constexpr (FORM == kPlain) {
+            ptr = a.word + blockIdx.y * (R + 4 + kPlainRecord);
+            rec = ptr + R + 4;
+        } else {
+            uint32_t segments = a.segments, stride = a.stride, ptr_stride = a.ptr_stride, dist = a.dist, grid2d = a.grid2d, look = a.lookup;
+            pin(segments, stride, ptr_stride, dist, grid2d, look);
+            lookup = look;
+            const uint64_t *const records = a.word + R + 4;
+            uint32_t seg = blockIdx.y;
+            if (!grid2d) {
+                uint32_t lo = 0, hi = segments - 1;
+                while (lo < hi) {
+                    const uint32_t mid = (lo + hi) >> 1;
+                    if (blockIdx.x < (uint32_t)records[mid * stride])
+                        hi = mid;
+                    else
+                        lo = mid + 1;
+                }
+                seg = lo;
+                before = seg ? (uint32_t)records[(seg - 1) * stride] : 0u;
+            }
+            rec = records + seg * stride;
+            ptr = a.word + seg * ptr_stride;
+            grp -= before;
+            if (dist) {
+                const uint64_t d = rec[dist];
+                shift = (int32_t)(uint32_t)d;
+                out_shift = (int32_t)(uint32_t)(d >> 32);
+            }
+        }
+        slice = ptr + 4;
+        uint64_t extent = rec[0];
+        P = ptr[0];
+        M = ptr[1];
+        V = ptr[2];
+        OUT = ptr[3];
+        decay = rec[1];
+#pragma unroll
+        for (uint32_t c = 0; c < CHUNK; ++c) at[c] = c < R ? slice[c] : 0;
+        h = a.scalars;
+        scalars_dev = reinterpret_cast<uint64_t>(a.scalars_dev);
+        pin(P, M, V, OUT, extent, decay, at[0], at[1], at[2], at[CHUNK > 3 ? 3 : 2], scalars_dev);
+        pin(h.lr, h.beta1, h.beta2, h.one_minus_beta1, h.one_minus_beta2, h.eps, h.weight_decay, h.grad_scale, h.inv_bc1, h.inv_bc2);
+        groups = (uint32_t)extent - before;
+        nquad = (uint32_t)(extent >> 32);
+        if (grp >= groups) return;              // of a longer segment of a 2-D grid
+    }
+    // (ahead of the requests: behind a branch, an offset that was used before it no longer goes with a scalar base)
+    if (FORM == kOne && !scalars_dev) scalars_dev = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr() + kLeadBytes + offsetof(Args, scalars);
+    if (FORM == kOne || scalars_dev) {
+        typedef const __attribute__((address_space(4))) float const_float;      // scalar loads
+        const_float *c = reinterpret_cast<const_float *>(scalars_dev);
+        h = {c[0], c[1], c[2], c[3], c[4], c[5], c[6], c[7], c[8], c[9]};
+    }
     if (PAIRS && grp < (groups & ~15u)) grp = (grp & ~15u) | ((grp & 7u) << 1) | ((grp >> 3) & 1u);
-    const bool has_out = OUT != 0;
     P += shift * 16;
     M += shift * 16;
     V += shift * 16;
-    OUT += out_shift * (O32 ? 16 : 8);
 
     const uint32_t q0 = grp * kGroupQuads + threadIdx.x;
     const uint32_t quad = q0 < nquad ? q0 : nquad - 1;
@@ -432,32 +472,34 @@ __global__ __launch_bounds__(kWave) void fused_adamw_kernel(const std::condition
     f32x4 v = ld_stream<f32x4>(V, quad);
     __builtin_amdgcn_sched_barrier(0);
     if (FORM == kSearched && lookup) runs.find(pos);
-    if (scalars_dev) {
-        typedef const __attribute__((address_space(4))) float const_float;      // scalar loads
-        const_float *c = reinterpret_cast<const_float *>(scalars_dev);
-        h = {c[0], c[1], c[2], c[3], c[4], c[5], c[6], c[7], c[8], c[9]};
-    }
     float g[1][4];
-    sum_contributions<R, CHUNK, G32>(at, ptr + 4, shift * (G32 ? 16 : 8), quads, g);
+    sum_contributions<R, CHUNK, G32>(at, slice, shift * (G32 ? 16 : 8), quads, g, [&] {
+        if (FORM == kOne)       // needed last, but read by now
+            pin(OUT, h.lr, h.beta1, h.beta2, h.one_minus_beta1, h.one_minus_beta2, h.eps, h.weight_decay, h.grad_scale, h.inv_bc1, h.inv_bc2);
+    });
 
     const float wd = h.weight_decay * (FORM == kSearched && lookup ? runs.get(pos) : __uint_as_float((uint32_t)decay));
 
     // The arithmetic is hardly hidden behind other wavefronts (few are resident by design), so it is
     // kept short: hardware square root and reciprocal (1 ulp each) instead of the correctly
-    // rounded expansions.  Their error enters p only through lr*u, far below the tolerance.
+    // rounded expansions.  Their error enters p only through lr*u, far below the tolerance.  Which products are
+    // fused into a sum is written out, so that every form gives the same bits.
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
+#pragma clang fp contract(off)
         const float ge = h.grad_scale * g[0][e];
-        const float mn = h.beta1 * m[e] + h.one_minus_beta1 * ge;
-        const float vn = h.beta2 * v[e] + (h.one_minus_beta2 * ge) * ge;
+        const float mn = __builtin_fmaf(h.beta1, m[e], h.one_minus_beta1 * ge);
+        const float vn = __builtin_fmaf(h.beta2, v[e], (h.one_minus_beta2 * ge) * ge);
         const float denom = __builtin_amdgcn_sqrtf(vn * h.inv_bc2) + h.eps;
         const float u = (mn * h.inv_bc1) * __builtin_amdgcn_rcpf(denom);
         const float pe = p[e];
         m[e] = mn;
         v[e] = vn;
-        p[e] = pe - h.lr * (u + wd * pe);
+        p[e] = __builtin_fmaf(-h.lr, __builtin_fmaf(wd, pe, u), pe);
     }
     if (q0 >= nquad) return;
+    const bool has_out = OUT != 0;
+    OUT += out_shift * (O32 ? 16 : 8);
     st_writethrough(P, quad * 16u, p);
     st_writethrough(M, quad * 16u, m);
     st_writethrough(V, quad * 16u, v);
@@ -471,6 +513,17 @@ __global__ __launch_bounds__(kWave) void fused_adamw_kernel(const std::condition
             st_writethrough(OUT, quad * 8u, o);
         }
     }
+}
+
+template <uint32_t R, bool G32, bool O32, uint32_t CHUNK>
+__global__ __launch_bounds__(kWave) void fused_one_kernel(const u64x4 p, const u64x2 w, const uint64_t size, const FusedOneArgs a)
+{
+    fused_adamw<R, G32, O32, kOne, CHUNK>({p, w, size}, a);
+}
+template <uint32_t R, bool G32, bool O32, FusedForm FORM, uint32_t CHUNK>
+__global__ __launch_bounds__(kWave) void fused_adamw_kernel(const FusedArgs a)
+{
+    fused_adamw<R, G32, O32, FORM, CHUNK>({}, a);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -753,10 +806,18 @@ static constexpr std::array<ReduceKernel, sizeof...(I)> reduce_kernels(std::inde
 {
     return {reduce_kernel<I + 1, G32, ACC, I < 8 ? kReducePlain : FORM>...};
 }
-template <bool G32, bool O32, FusedForm FORM, bool FEW, class Args, size_t... I>
-static constexpr std::array<void (*)(Args), sizeof...(I)> fused_kernels(std::index_sequence<I...>)
+typedef void (*FusedKernel)(FusedArgs);
+typedef void (*FusedOneKernel)(u64x4, u64x2, uint64_t, FusedOneArgs);
+constexpr uint32_t fused_chunk(bool g32, uint32_t R, bool few) { return few ? few_chunk(R, fused_chunk(g32)) : fused_chunk(g32); }
+template <bool G32, bool O32, FusedForm FORM, bool FEW, size_t... I>
+static constexpr std::array<FusedKernel, sizeof...(I)> fused_kernels(std::index_sequence<I...>)
 {
-    return {fused_adamw_kernel<I + 1, G32, O32, FORM, FEW ? few_chunk(I + 1, fused_chunk(G32)) : fused_chunk(G32)>...};
+    return {fused_adamw_kernel<I + 1, G32, O32, FORM, fused_chunk(G32, I + 1, FEW)>...};
+}
+template <bool G32, bool O32, bool FEW, size_t... I>
+static constexpr std::array<FusedOneKernel, sizeof...(I)> fused_one_kernels(std::index_sequence<I...>)
+{
+    return {fused_one_kernel<I + 1, G32, O32, fused_chunk(G32, I + 1, FEW)>...};
 }
 
 // Wavefronts per CU for the reduction: what keeps so many KiB in flight per CU.  Where the contributions fit one chunk 48; where
@@ -926,23 +987,44 @@ static void list_runs(const hzp_plan_t *plan, const FusedSegment *segs, size_t n
 // and 9.4 / 14.2 / 16.8, 1.3 M 11.4 / 19.4 / 22.9 and 11.5 / 19.2 / 22.7; beyond, the order of the requests counts (below).
 constexpr uint32_t kUncappedGroups = 5120;
 
-template <FusedForm FORM, bool FEW, class Args>
-static hzp_status_t start_fused(bool g32, bool o32, uint32_t R, const Args &a, dim3 grid, uint32_t groups, hipStream_t stream)
+// Dynamic LDS of a launch, from the wavefronts per CU.  bf16 contributions: 10 (R = 8, 105 M elements: 8 / 9 / 10 / 11 / 12 / 14 / 16 6.67 /
+// 6.73 / 6.73 / 6.72 / 6.70 / 6.61 / 6.56 TB/s), more in shorter launches, where filling and draining the chip counts (R = 8, 33 M: 10 /
+// 12 / 14 6.42 / 6.51 / 6.45; R = 16, 4 M: 10 / 12 / 14 / 16 5.58 / 5.79 / 5.82 / 5.77).  fp32: 8, whose chunks hold half as much again
+// (R = 1, 107 M: 7 / 8 / 9 / 10 / 12 6.56 / 6.74 / 6.64 / 6.63 / 6.55; R = 8, 17 M: 8 / 10 / 12 6.57 / 6.45 / 6.25).  Where the
+// segment is searched for or decay looked up a wavefront lives longer: R = 8 with looked-up decay 10 / 11 / 12 / 13 / 14 6.31 /
+// 6.50 / 6.54 / 6.48 / 6.37.
+static unsigned fused_lds(bool g32, FusedForm form, uint32_t groups)
+{
+    if (groups <= kUncappedGroups) return 0;
+    if (g32) return lds_for(form == kSearched ? 10u : 8u);
+    return lds_for(groups > 200000u ? (form == kSearched ? 12u : 10u) : groups > 32768u ? 12u : 14u);
+}
+
+template <FusedForm FORM, bool FEW>
+static hzp_status_t start_fused(bool g32, bool o32, uint32_t R, const FusedArgs &a, dim3 grid, uint32_t groups, hipStream_t stream)
 {
     constexpr std::make_index_sequence<HZP_MAX_REPLICAS> all;
-    static constexpr auto kernels16 = fused_kernels<false, false, FORM, FEW, Args>(all);
-    static constexpr auto kernels32 = fused_kernels<true, true, FORM, FEW, Args>(all);
-    void (*const kernel)(Args) = !g32 ? kernels16[R - 1] : o32 ? kernels32[R - 1] : fused_adamw_kernel<1, true, false, FORM, fused_chunk(true)>;
-    // Wavefronts per CU.  bf16 contributions: 10 (R = 8, 105 M elements: 8 / 9 / 10 / 11 / 12 / 14 / 16 6.67 / 6.73 / 6.73 / 6.72 /
-    // 6.70 / 6.61 / 6.56 TB/s), more in shorter launches, where filling and draining the chip counts (R = 8, 33 M: 10 / 12 / 14
-    // 6.42 / 6.51 / 6.45; R = 16, 4 M: 10 / 12 / 14 / 16 5.58 / 5.79 / 5.82 / 5.77).  fp32: 8, whose chunks hold half as much again
-    // (R = 1, 107 M: 7 / 8 / 9 / 10 / 12 6.56 / 6.74 / 6.64 / 6.63 / 6.55; R = 8, 17 M: 8 / 10 / 12 6.57 / 6.45 / 6.25).  Where the
-    // segment is searched for or decay looked up a wavefront lives longer: R = 8 with looked-up decay 10 / 11 / 12 / 13 / 14 6.31 /
-    // 6.50 / 6.54 / 6.48 / 6.37.
-    const unsigned waves16 = groups > 200000u ? (FORM == kSearched ? 12u : 10u) : groups > 32768u ? 12u : 14u;
-    const unsigned waves32 = FORM == kSearched ? 10u : 8u;
-    const bool capped = groups > kUncappedGroups;
-    return start("hzp_adamw_shard", kernel, grid, dim3(kWave), capped ? lds_for(g32 ? waves32 : waves16) : 0u, stream, a);
+    static constexpr auto kernels16 = fused_kernels<false, false, FORM, FEW>(all);
+    static constexpr auto kernels32 = fused_kernels<true, true, FORM, FEW>(all);
+    const FusedKernel kernel = !g32 ? kernels16[R - 1] : o32 ? kernels32[R - 1] : fused_adamw_kernel<1, true, false, FORM, fused_chunk(true)>;
+    return start("hzp_adamw_shard", kernel, grid, dim3(kWave), fused_lds(g32, FORM, groups), stream, a);
+}
+
+// One segment with one multiplier: its record and pointers are a.word's first.
+template <bool FEW>
+static hzp_status_t start_fused_one(bool g32, bool o32, uint32_t R, const FusedArgs &a, uint32_t groups, hipStream_t stream)
+{
+    constexpr std::make_index_sequence<HZP_MAX_REPLICAS> all;
+    static constexpr auto kernels16 = fused_one_kernels<false, false, FEW>(all);
+    static constexpr auto kernels32 = fused_one_kernels<true, true, FEW>(all);
+    const FusedOneKernel kernel = !g32 ? kernels16[R - 1] : o32 ? kernels32[R - 1] : fused_one_kernel<1, true, false, fused_chunk(true)>;
+    FusedOneArgs one;
+    one.out = a.word[3];
+    one.scalars = a.scalars;
+    std::memcpy(one.g, a.word + 4, R * sizeof one.g[0]);
+    const uint64_t *const w = a.word, *const rec = a.word + R + 4;
+    return start("hzp_adamw_shard", kernel, dim3(groups), dim3(kWave), fused_lds(g32, kOne, groups), stream, u64x4{w[0], w[1], w[2], w[4]},
+                 u64x2{R > 1 ? w[5] : 0, reinterpret_cast<uint64_t>(a.scalars_dev)}, rec[0] >> 32 | rec[1] << 32, one);
 }
 
 hzp_status_t launch_fused(const hzp_plan_t *plan, bool g32, bool o32, uint32_t R, const FusedSegment *segs, size_t nseg,
@@ -1053,14 +1135,10 @@ hzp_status_t launch_fused(const hzp_plan_t *plan, bool g32, bool o32, uint32_t R
         const bool few = blocks <= (g32 ? kFewGroups / 4 * 3 : kFewGroups);
         hzp_status_t st;
         if (cnt == 1 && !a.lookup) {
-            FusedOneArgs one;
-            one.scalars_dev = a.scalars_dev;
-            one.scalars = a.scalars;
-            std::memcpy(one.word, a.word, (per_seg + kPlainRecord) * sizeof one.word[0]);
             if (blocks <= kFewGroups)
-                st = start_fused<kOne, true>(g32, o32, R, one, grid, blocks, stream);
+                st = start_fused_one<true>(g32, o32, R, a, blocks, stream);
             else
-                st = start_fused<kOne, false>(g32, o32, R, one, grid, blocks, stream);
+                st = start_fused_one<false>(g32, o32, R, a, blocks, stream);
         } else if (a.grid2d && !shared && !a.lookup) {
             if (few)
                 st = start_fused<kPlain, true>(g32, o32, R, a, grid, blocks, stream);
