@@ -1,11 +1,13 @@
-"""ctypes binding of libhzp: argument marshalling only, every step runs in the library.
+"""Binding of libhzp: argument marshalling only (ctypes, and native code for the calls of every step), every step runs in the library.
 
 Function names and argument order follow ``include/hzp.h``.  Device buffers may be given as
 torch tensors (their ``data_ptr()`` is taken) or as integer addresses; a stream may be a
 ``torch.cuda.Stream``, an integer ``hipStream_t`` or None (torch's current stream).
-There is no fallback: if ``libhzp.so`` has not been built, importing this module fails.
+There is no fallback: if ``libhzp.so`` and ``_calls.so`` have not been built, importing this module fails.
 """
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -200,6 +202,19 @@ def _load():
 _L = _load()
 
 
+def _load_calls():
+    path = os.path.join(_HERE, "_calls.so")
+    if not os.path.exists(path):
+        raise ImportError("_calls.so is not built: run `python paper_2510_20111_amd/build.py` (or __graft_entry__.build()) first")
+    loader = importlib.machinery.ExtensionFileLoader("_calls", path)
+    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_calls", loader))
+    loader.exec_module(module)
+    return module
+
+
+_calls = _load_calls()
+
+
 def _check(status):
     if status != HZP_OK:
         raise HzpError(status, hzp_last_error())
@@ -223,6 +238,12 @@ def ptr_array(items):
     if isinstance(items, ctypes.Array):
         return items
     return (ctypes.c_void_p * len(items))(*[_addr(x) for x in items])
+
+
+def _native_call(function):
+    """The same call made from native code; `function` converts (or refuses) the arguments that are not recognised there."""
+    entry = ctypes.cast(getattr(_L, function.__name__), ctypes.c_void_p).value
+    return _calls.Call(function.__name__, entry, function, _check, ctypes.Array, ctypes.c_void_p, AdamW)
 
 
 def _stream(stream):
@@ -347,6 +368,7 @@ def hzp_plan_free(plan):
     plan.__del__()
 
 
+@_native_call
 def hzp_reduce_shard(plan, layer, cls, level, rank, grad_slices, scale, accumulate, out_f32,
                      stream=None, R=None, grad_dtype=HZP_GRAD_DEFAULT):
     arr = ptr_array(grad_slices)
@@ -359,6 +381,7 @@ def adamw_hyper(lr, beta1, beta2, eps, weight_decay, grad_scale, step):
     return AdamW(lr, beta1, beta2, eps, weight_decay, grad_scale, step)
 
 
+@_native_call
 def hzp_adamw_shard(plan, layer_begin, layer_end, cls, rank, hyper, grad_slices, R, master, m, v,
                     param_out, stream=None):
     """grad_slices: flat sequence, entry (layer-layer_begin)*max(R,1) + r."""
@@ -375,6 +398,7 @@ def hzp_adamw_scalars(hyper):
     return list(out.f)
 
 
+@_native_call
 def hzp_adamw_shard_dev(plan, layer_begin, layer_end, cls, rank, scalars, grad_slices, R, master, m, v,
                         param_out, stream=None):
     """`scalars`: device tensor (or address) holding hzp_adamw_scalars' 12 floats."""
@@ -384,6 +408,7 @@ def hzp_adamw_shard_dev(plan, layer_begin, layer_end, cls, rank, scalars, grad_s
                                   _stream(stream)))
 
 
+@_native_call
 def hzp_gather_layer(plan, layer, cls, level, shard_ptrs, bucket_out=None, tensor_out=None,
                      stream=None, n_shards=None):
     arr = ptr_array(shard_ptrs)
@@ -393,23 +418,27 @@ def hzp_gather_layer(plan, layer, cls, level, shard_ptrs, bucket_out=None, tenso
                                _stream(stream)))
 
 
+@_native_call
 def hzp_gather_layer_static(plan, layer, cls, shard_ptrs, tensor_out, stream=None, n_shards=None):
     arr = ptr_array(shard_ptrs)
     _check(_L.hzp_gather_layer_static(plan.handle, layer, cls, arr, len(arr) if n_shards is None else n_shards,
                                       ptr_array(tensor_out) if tensor_out is not None else None, _stream(stream)))
 
 
+@_native_call
 def hzp_gather_shard(plan, layer, cls, j, owner_ptrs, shard_out, stream=None, n_owners=None):
     arr = ptr_array(owner_ptrs)
     _check(_L.hzp_gather_shard(plan.handle, layer, cls, j, arr, len(arr) if n_owners is None else n_owners,
                                _addr(shard_out), _stream(stream)))
 
 
+@_native_call
 def hzp_gather_layers(plan, layer_begin, layer_end, cls, level, shard_ptrs, n_shards, bucket_out, stream=None):
     _check(_L.hzp_gather_layers(plan.handle, layer_begin, layer_end, cls, level, ptr_array(shard_ptrs), n_shards,
                                 ptr_array(bucket_out), _stream(stream)))
 
 
+@_native_call
 def hzp_gather_tensor(plan, tensor_id, shard_ptrs, tensor_out, stream=None, n_shards=None):
     arr = ptr_array(shard_ptrs)
     _check(_L.hzp_gather_tensor(plan.handle, tensor_id, arr, len(arr) if n_shards is None else n_shards,

@@ -1,15 +1,20 @@
-"""Build step of libhzp: one hipcc invocation for gfx950 (cross-compiles without a GPU)."""
+"""Build step of libhzp: one hipcc invocation for gfx950 (cross-compiles without a GPU), and of the binding's Python module."""
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 SOURCES = ["planner.cpp", "api.cpp", "scheduler.cpp", "kernels.hip"]
 LIB = os.path.join(HERE, "libhzp.so")
+CALLS = os.path.join(HERE, "_calls.so")
 
 
 def build(verbose=False):
-    """Compile csrc/ into paper_2510_20111_amd/libhzp.so.  Always recompiles."""
+    """Compile csrc/ into paper_2510_20111_amd/libhzp.so and _calls.so.  Always recompiles."""
+    calls = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I" + sysconfig.get_paths()["include"],
+             "-I" + os.path.join(ROOT, "include"), os.path.join(HERE, "csrc", "pycalls.cpp"), "-o", CALLS]
+    subprocess.run(calls, check=True)
     cmd = ["hipcc", "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",
            # packed fp32 instructions stay off (see the hipcc flag of the same name)
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -1,0 +1,202 @@
+"""The calls made from native code hand the C entry points what the binding functions hand them, over all forms of the
+arguments that either accepts, and refuse what those refuse."""
+import ctypes
+import inspect
+import itertools
+
+import pytest
+
+import paper_2510_20111_amd as hzp
+from paper_2510_20111_amd import binding as bd
+
+NAMES = ["hzp_reduce_shard", "hzp_adamw_shard", "hzp_adamw_shard_dev", "hzp_gather_layer", "hzp_gather_layer_static",
+         "hzp_gather_shard", "hzp_gather_layers", "hzp_gather_tensor"]
+
+
+class Tensor:
+    def __init__(self, address):
+        self.address = address
+
+    def data_ptr(self):
+        return self.address
+
+
+class Stream:
+    cuda_stream = 0x7000
+
+
+class Bad:
+    def data_ptr(self):
+        raise RuntimeError("no address")
+
+
+class FakePlan:
+    def __init__(self, address=0x1234560):
+        self.handle = ctypes.c_void_p(address)
+
+
+class Recorder:
+    """Stands in for the library: every entry point notes its arguments, pointers to arrays as what they hold."""
+
+    def __init__(self, status=0):
+        self.got, self.status, self.keep = [], status, []
+        for name in NAMES:
+            real = getattr(bd._L, name)
+            kinds = [ctypes.c_void_p if t not in (ctypes.c_uint32, ctypes.c_int, ctypes.c_float) else t for t in real.argtypes]
+            fn = ctypes.CFUNCTYPE(ctypes.c_int, *kinds)(lambda *a, name=name: self.note(name, a))
+            fn.argtypes = real.argtypes
+            setattr(self, name, fn)
+
+    def note(self, name, args):
+        # (arrays are three words here; their addresses differ between two calls with lists, what they hold does not)
+        held = {"hzp_reduce_shard": (5,), "hzp_adamw_shard": (6, 8, 9, 10, 11), "hzp_adamw_shard_dev": (6, 8, 9, 10, 11),
+                "hzp_gather_layer": (4, 7), "hzp_gather_layer_static": (3, 5), "hzp_gather_shard": (4,), "hzp_gather_layers": (5, 7),
+                "hzp_gather_tensor": (2,)}[name]
+        out = []
+        for i, a in enumerate(args):
+            if i in held and a:
+                out.append(list((ctypes.c_uint64 * 3).from_address(a)))
+            elif name == "hzp_adamw_shard" and i == 5 and a:
+                out.append(bytes((ctypes.c_char * ctypes.sizeof(bd.AdamW)).from_address(a)))
+            else:
+                out.append(a)
+        self.got.append((name, out))
+        return self.status
+
+
+def pointers(base):
+    words = [base, base + 0x100, base + 0x200]
+    return [(ctypes.c_void_p * 3)(*words), (ctypes.c_uint64 * 3)(*words), list(words), tuple(words), [Tensor(w) for w in words],
+            [words[0], Tensor(words[1]), words[2]]]
+
+
+def addresses(a):
+    return [a, Tensor(a), None, 0, (1 << 64) - 16]
+
+
+STREAMS = [0, 0x55, (1 << 63) + 8, Stream()]
+HYPER = bd.adamw_hyper(1e-3, 0.9, 0.95, 1e-8, 0.1, 0.25, 7)
+CHOICES = {
+    "plan": [FakePlan()], "layer": [3, 0, (1 << 32) - 1, True], "cls": [1], "level": [2, 1], "rank": [5], "j": [4], "tensor_id": [9],
+    "layer_begin": [1], "layer_end": [6], "grad_slices": pointers(0x10000), "shard_ptrs": pointers(0x20000), "owner_ptrs": pointers(0x30000),
+    "scale": [0.25, 1, 1e-60, float("inf")], "accumulate": [True, False, 1, 0, [], "yes"], "out_f32": addresses(0x4000), "R": [3, 0, 17],
+    "grad_dtype": [0, 1, 2], "hyper": [HYPER], "scalars": addresses(0x5000), "master": pointers(0x60000), "m": pointers(0x70000),
+    "v": pointers(0x80000), "param_out": [None] + pointers(0x90000), "bucket_out": None, "tensor_out": [None] + pointers(0xA0000),
+    "shard_out": addresses(0x6000), "n_shards": [3, 2], "n_owners": [3, 64], "stream": STREAMS,
+}
+
+
+def forms(name):
+    """Argument sets: a plain one, and it with each argument in each of its forms; by position and by name, defaults left out."""
+    parameters = inspect.signature(getattr(bd, name)).parameters
+    def choices(p):
+        if p == "bucket_out":
+            return pointers(0xB0000) if name == "hzp_gather_layers" else [None] + addresses(0x7000)
+        if p == "tensor_out" and name == "hzp_gather_tensor":
+            return addresses(0x8000)
+        if p == "tensor_out" and name == "hzp_gather_layer_static":
+            return [None] + pointers(0xA0000)
+        if p in ("R", "n_shards", "n_owners") and parameters[p].default is None:
+            return CHOICES[p] + [None]
+        return CHOICES[p]
+    plain = {p: choices(p)[0] for p in parameters}
+    for p in parameters:
+        for c in choices(p):
+            yield dict(plain, **{p: c})
+    short = {p: x for p, x in plain.items() if parameters[p].default is inspect.Parameter.empty}
+    yield dict(short, stream=0x66)
+
+
+def both(monkeypatch, name, args, kwargs, status=0):
+    """(what the binding function did, what the native call did)"""
+    native = getattr(bd, name)
+    assert type(native).__name__ == "Call"
+    out = []
+    for side in (0, 1):
+        rec = Recorder(status)
+        monkeypatch.setattr(bd, "_L", Spy(rec, monkeypatch))
+        entry = ctypes.cast(getattr(rec, name), ctypes.c_void_p).value
+        call = native.__wrapped__ if side == 0 else bd._calls.Call(name, entry, native.__wrapped__, bd._check, ctypes.Array, ctypes.c_void_p, bd.AdamW)
+        try:
+            result = call(*args, **kwargs)
+        except Exception as e:      # noqa: BLE001
+            result = (type(e), str(e))
+        out.append((result, rec.got))
+        monkeypatch.undo()
+    return out
+
+
+class Spy:
+    def __init__(self, rec, monkeypatch):
+        self.rec, self.real = rec, bd._L
+
+    def __getattr__(self, name):
+        return getattr(self.rec, name) if name in NAMES else getattr(self.real, name)
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_native_calls_hand_over_what_the_binding_functions_do(monkeypatch, name):
+    parameters = list(inspect.signature(getattr(bd, name)).parameters)
+    n = 0
+    for values in forms(name):
+        given = [p for p in parameters if p in values]
+        for by_position in {0, 1, len([p for p, q in zip(parameters, given) if p == q])}:
+            args = [values[p] for p in given[:by_position]]
+            kwargs = {p: values[p] for p in given[by_position:]}
+            a, b = both(monkeypatch, name, args, kwargs)
+            assert a == b, (args, kwargs)
+            n += len(a[1])
+    assert n > 20
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_native_calls_refuse_what_the_binding_functions_refuse(monkeypatch, name):
+    parameters = inspect.signature(getattr(bd, name)).parameters
+    plain = next(forms(name))
+    plain["stream"] = 0x77
+    wrong = [dict(plain, **{p: x}) for p, x in itertools.product(parameters, (Bad(), "text", 1.5, -1, 1 << 32, 1 << 70, b"x", object()))
+             if not (p in ("stream",) and x is None)]
+    wrong += [dict(plain, no_such_argument=1)] + [{q: x for q, x in plain.items() if q != p} for p in parameters
+                                                  if parameters[p].default is inspect.Parameter.empty]
+    for kwargs in wrong:
+        a, b = both(monkeypatch, name, [], kwargs)
+        if a[1]:    # taken, with the number or the bytes as they are: so does the native call
+            assert len(b[1]) == 1 and a[0] == b[0], kwargs
+            if not any(isinstance(x, bytes) for x in kwargs.values()):
+                assert a == b, kwargs
+        else:
+            assert a == b, kwargs
+    for args in ([], [1] * 20, list(plain.values()) + [1]):
+        a, b = both(monkeypatch, name, args, {})
+        assert a == b
+    a, b = both(monkeypatch, name, list(plain.values())[:1], dict(plain))      # an argument twice
+    assert a == b
+    # a status of the library is the same exception
+    a, b = both(monkeypatch, name, [], plain, status=hzp.HZP_ERR_RANGE)
+    assert a == b and a[0][0] is hzp.HzpError
+
+
+def test_native_calls_look_like_the_binding_functions():
+    for name in NAMES:
+        f = getattr(hzp, name)
+        assert callable(f) and f.__name__ == name and f.__doc__ == f.__wrapped__.__doc__
+        assert inspect.signature(f) == inspect.signature(f.__wrapped__)
+
+
+def test_usual_calls_do_not_go_through_the_binding_functions():
+    def not_this_way(*a, **k):
+        raise AssertionError("went to the binding function")
+    rec = Recorder()
+    for name in NAMES:
+        call = bd._calls.Call(name, ctypes.cast(getattr(rec, name), ctypes.c_void_p).value, not_this_way, bd._check, ctypes.Array,
+                              ctypes.c_void_p, bd.AdamW)
+        signature = inspect.signature(getattr(bd, name)).parameters
+        values = next(forms(name))
+        call(**values)
+        call(*values.values())
+        stream = {"stream": 0x99}
+        call(*[x for p, x in values.items() if signature[p].default is inspect.Parameter.empty], **stream)
+        for p, x in values.items():
+            if isinstance(x, ctypes.Array):
+                call(**dict(values, **{p: [Tensor(1 << 20), 1 << 21, Tensor(1 << 22)]}))
+    assert len(rec.got) >= 4 * len(NAMES)
