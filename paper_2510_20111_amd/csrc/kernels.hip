@@ -113,13 +113,17 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
 constexpr int kWave = 64;
 constexpr uint32_t kGroupQuads = 64;        // quads per group (256 elements)
 
-// Dynamic LDS that leaves room for `waves` single-wavefront workgroups per CU (160 KiB).
-constexpr unsigned lds_for(unsigned waves) { return waves ? 163840u / waves / 512u * 512u : 0u; }
+// Dynamic LDS that leaves room for `waves` single-wavefront workgroups per CU, or the next smaller number that there is: a CU's 160 KiB
+// are given out in 128 units of 1280 bytes (so 13 are 12, 15 are 14, 19 and 20 are 18, 22 to 24 are 21).
+constexpr unsigned lds_for(unsigned waves) { return waves ? (128u / (waves + 1) + 1) * 1280u : 0u; }
 
-// Contributions one wavefront has in flight.  Measured at 100 M elements: bf16 R = 8 with chunks of 2 / 3 / 4 / 6 / 8
-// 6.76 / 6.78 / 6.78 / 6.76 / 6.78 TB/s, R = 16 6.73 / 6.68 / 6.72 / 6.74 / 6.71; fp32 R = 8 with 2 / 3 / 4 / 8
-// 6.73 / 6.77 / 6.73 / 6.72, R = 16 6.57 / 6.57 / 6.47 / 6.45.
-constexpr uint32_t fused_chunk(bool g32) { return g32 ? 3u : 4u; }
+// Most contributions one wavefront of the update has in flight.  Few large chunks beat many small ones (a wavefront waits once for each),
+// with so many fewer wavefronts that a CU has about 50 KiB in flight (fused_lds).  Chunks of at most 4 / 6 / 8, each with the best number
+// of wavefronts, mean over 9 to 105 M elements against chunks of 4 with 9 or 11: bf16 R = 10 .995 / .981 / .982, R = 14 .996 / .979 /
+// .974, R = 16 .996 / .986 / .979, R = 20 .996 / .985 / .979, R = 24 .999 / .991 / .988, R = 28 .997 / .990 / .989, R = 32 .997 /
+// .996 / .991, but 2 % more at 2-6 M; R = 8 .997 / - / 1.001.  fp32 with chunks of at most 3 / 4 / 6, over 1.5 to 71 M: R = 4 .989 / .978 / -,
+// R = 8 .993 / .973 / -, R = 12 .982 / .980 / .975, R = 16 .996 / .983 / .983, R = 24 .991 / .992 / 1.004, R = 32 .997 / .998 / 1.019.
+constexpr uint32_t fused_chunk(bool g32, uint32_t R) { return g32 ? (R > 16 ? 3u : 4u) : R <= 5 ? 5u : R <= 8 || R > 28 ? 4u : 8u; }
 constexpr uint32_t kReduceChunk = 4;
 // A launch of so few groups that all wavefronts are resident at once lasts as long as one wavefront, whose chunks follow
 // each other: there, more than 8 contributions are requested up to 16 at a time (chunks of 4 / 16, us a call: 64 k elements, R = 32:
@@ -127,6 +131,11 @@ constexpr uint32_t kReduceChunk = 4;
 // several segments, 0.15 M elements, R = 16 / 32: 5.8 -> 5.1 and 7.3 -> 5.3; with R <= 8 no difference).
 constexpr uint32_t kFewGroups = 2048;
 constexpr uint32_t few_chunk(uint32_t R, uint32_t chunk) { return R > 8 ? 16u : chunk; }
+// The update of 6 to 8 bf16 contributions takes them in one chunk in launches of at most so many groups (one chunk against two, both with
+// the best number of wavefronts: R = 7 1.5 / 2.7 / 6.3 / 9.1 / 21 / 48 M elements .98 / .98 / .99 / 1.00 / 1.00 / 1.005, R = 8 .986 / .98 /
+// .99 / 1.00 / 1.00 / 1.00, 105 M 1.01; R = 6 9.1 / 21 / 33 M .98 / .99 / 1.01).
+constexpr uint32_t kOneChunkGroups = 65536;
+constexpr bool one_chunk(uint32_t R) { return R > 5 && R <= 8; }
 
 // Four gradient elements of one contribution, widened to fp32 on access.
 template <bool G32>
@@ -148,7 +157,7 @@ struct GradQuad<true> {
     __device__ __forceinline__ float get(int e) const { return a[e]; }
 };
 
-// Contributions per chunk: R spread evenly over the fewest chunks of at most `most`.
+// Contributions in the largest chunk: R spread evenly over the fewest chunks of at most `most`.
 constexpr uint32_t chunk_of(uint32_t R, uint32_t most)
 {
     const uint32_t chunks = (R + most - 1) / most;
@@ -176,18 +185,19 @@ template <uint32_t R, uint32_t MOST, bool G32, int Q, class Meanwhile>
 __device__ __forceinline__ void sum_contributions(uint64_t (&at)[MOST], const uint64_t *slice, int64_t shift,
                                                   const uint32_t (&quad)[Q], float (&s)[Q][4], Meanwhile meanwhile)
 {
-    constexpr uint32_t C = chunk_of(R, MOST);
+    constexpr uint32_t C = chunk_of(R, MOST), CHUNKS = (R + C - 1) / C;
 #pragma unroll
-    for (uint32_t base = 0; base < R; base += C) {
+    for (uint32_t k = 0; k < CHUNKS; ++k) {
+        const uint32_t base = k * R / CHUNKS, end = (k + 1) * R / CHUNKS, next = (k + 2) * R / CHUNKS;
         GradQuad<G32> g[C][Q];
 #pragma unroll
         for (uint32_t c = 0; c < C; ++c)
 #pragma unroll
             for (int q = 0; q < Q; ++q)
-                if (base + c < R) g[c][q].load(at[c] + shift, quad[q]);
+                if (base + c < end) g[c][q].load(at[c] + shift, quad[q]);
 #pragma unroll
         for (uint32_t c = 0; c < C; ++c)
-            if (base + C + c < R) at[c] = slice[base + C + c];
+            if (k + 1 < CHUNKS && end + c < next) at[c] = slice[end + c];
         __builtin_amdgcn_sched_barrier(0);      // the whole chunk is requested (and the next one's pointers) before its first add,
         if (base == 0) meanwhile();
 #pragma unroll
@@ -196,7 +206,7 @@ __device__ __forceinline__ void sum_contributions(uint64_t (&at)[MOST], const ui
             for (int q = 0; q < Q; ++q)
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    if (base + c < R) s[q][e] = base + c ? s[q][e] + g[c][q].get(e) : g[c][q].get(e);
+                    if (base + c < end) s[q][e] = base + c ? s[q][e] + g[c][q].get(e) : g[c][q].get(e);
         // and the next chunk only behind its last: the sum is pinned here, or the adds sink to the sum's use
 #pragma unroll
         for (int q = 0; q < Q; ++q)
@@ -808,7 +818,11 @@ static constexpr std::array<ReduceKernel, sizeof...(I)> reduce_kernels(std::inde
 }
 typedef void (*FusedKernel)(FusedArgs);
 typedef void (*FusedOneKernel)(u64x4, u64x2, uint64_t, FusedOneArgs);
-constexpr uint32_t fused_chunk(bool g32, uint32_t R, bool few) { return few ? few_chunk(R, fused_chunk(g32)) : fused_chunk(g32); }
+constexpr uint32_t fused_chunk(bool g32, uint32_t R, bool few)
+{
+    if (few && !g32 && one_chunk(R)) return R;
+    return few ? few_chunk(R, fused_chunk(g32, R)) : fused_chunk(g32, R);
+}
 template <bool G32, bool O32, FusedForm FORM, bool FEW, size_t... I>
 static constexpr std::array<FusedKernel, sizeof...(I)> fused_kernels(std::index_sequence<I...>)
 {
@@ -843,7 +857,8 @@ static unsigned reduce_waves(bool g32, uint32_t R, uint64_t n, int accumulate)
         half_kib = brief ? 114 : R > 8 ? (accumulate ? 67 : 62) : accumulate ? 72 : 64;
     else
         half_kib = brief ? 102 : R <= 16 && bytes >= 1000000000u ? (accumulate ? 65 : 60) : 68;
-    return std::min(28u, half_kib * 512u / asked);
+    const unsigned waves = std::min(28u, half_kib * 512u / asked);
+    return waves >= 10 && waves <= 12 ? waves - 1 : waves;          // (measured with one fewer)
 }
 
 // The form of a launch of `groups` groups.  Where all wavefronts are resident at once there is no cap, and a CU has groups / 256 x chunk
@@ -987,17 +1002,21 @@ static void list_runs(const hzp_plan_t *plan, const FusedSegment *segs, size_t n
 // and 9.4 / 14.2 / 16.8, 1.3 M 11.4 / 19.4 / 22.9 and 11.5 / 19.2 / 22.7; beyond, the order of the requests counts (below).
 constexpr uint32_t kUncappedGroups = 5120;
 
-// Dynamic LDS of a launch, from the wavefronts per CU.  bf16 contributions: 10 (R = 8, 105 M elements: 8 / 9 / 10 / 11 / 12 / 14 / 16 6.67 /
-// 6.73 / 6.73 / 6.72 / 6.70 / 6.61 / 6.56 TB/s), more in shorter launches, where filling and draining the chip counts (R = 8, 33 M: 10 /
-// 12 / 14 6.42 / 6.51 / 6.45; R = 16, 4 M: 10 / 12 / 14 / 16 5.58 / 5.79 / 5.82 / 5.77).  fp32: 8, whose chunks hold half as much again
-// (R = 1, 107 M: 7 / 8 / 9 / 10 / 12 6.56 / 6.74 / 6.64 / 6.63 / 6.55; R = 8, 17 M: 8 / 10 / 12 6.57 / 6.45 / 6.25).  Where the
-// segment is searched for or decay looked up a wavefront lives longer: R = 8 with looked-up decay 10 / 11 / 12 / 13 / 14 6.31 /
-// 6.50 / 6.54 / 6.48 / 6.37.
-static unsigned fused_lds(bool g32, FusedForm form, uint32_t groups)
+// Dynamic LDS of a launch: as many wavefronts per CU as keep about 50 KiB (bf16, 10 wavefronts at the most) or 44 KiB (fp32; 7, or 8 of
+// single contributions) in flight.  One or two more where a wavefront reads pointers or tables before it asks for data, and in shorter
+// launches of chunks of 4.  Means over 9 to 105 M elements against chunks of at most 4 (fp32 3) and 9 or 11 (8) wavefronts, by wavefronts 6 / 7 / 8 / 9 / 10 / 11: bf16 R = 5 1.022 / .996 /
+// .990 / .990 / .988 / .987, R = 10 1.045 / .997 / .984 / .982 / .983 / .984, R = 16 .987 / .979 / .986 / .991 / .996 / 1.001, R = 24
+// .992 / .988 / .996 / .999 / 1.004 / 1.010; R = 8 in two chunks 1.094 / 1.032 / 1.005 / .997 / .998 / 1.000; over 1.5 to 71 M with 4 / 5 / 6 / 7 / 8: fp32 R = 2 1.175 /
+// 1.045 / .990 / .981 / .989, R = 4 1.077 / .991 / .978 / .987 / .993, R = 8 1.057 / .978 / .973 / .991 / 1.000, R = 16 1.074 / .991 / .983 /
+// .999 / 1.008; R = 24 in chunks of 3 1.230 / 1.094 / 1.022 / .991 / .994.
+static unsigned fused_lds(bool g32, uint32_t R, bool few, FusedForm form, uint32_t groups)
 {
     if (groups <= kUncappedGroups) return 0;
-    if (g32) return lds_for(form == kSearched ? 10u : 8u);
-    return lds_for(groups > 200000u ? (form == kSearched ? 12u : 10u) : groups > 32768u ? 12u : 14u);
+    const uint32_t chunk = chunk_of(R, fused_chunk(g32, R, few)), asked = (chunk * (g32 ? 4u : 2u) + 12u) * 4u * kGroupQuads;
+    const bool late = form == kSearched || (form == kPlain && groups <= 32768u);
+    if (g32) return lds_for(late && chunk < 4 ? 9u : late + (R > 16 || chunk == 1 ? 8u : chunk < 4 || groups <= 16384u ? 7u : 45056u / asked));
+    if (R > 28 || (late && chunk <= 4)) return lds_for(groups <= 32768u ? 14u : late || groups <= 200000u ? 11u : 10u);
+    return lds_for(late + (one_chunk(R) && few ? 10u : chunk == 4 ? 9u : std::min(10u, 51200u / asked)));
 }
 
 template <FusedForm FORM, bool FEW>
@@ -1006,8 +1025,8 @@ static hzp_status_t start_fused(bool g32, bool o32, uint32_t R, const FusedArgs 
     constexpr std::make_index_sequence<HZP_MAX_REPLICAS> all;
     static constexpr auto kernels16 = fused_kernels<false, false, FORM, FEW>(all);
     static constexpr auto kernels32 = fused_kernels<true, true, FORM, FEW>(all);
-    const FusedKernel kernel = !g32 ? kernels16[R - 1] : o32 ? kernels32[R - 1] : fused_adamw_kernel<1, true, false, FORM, fused_chunk(true)>;
-    return start("hzp_adamw_shard", kernel, grid, dim3(kWave), fused_lds(g32, FORM, groups), stream, a);
+    const FusedKernel kernel = !g32 ? kernels16[R - 1] : o32 ? kernels32[R - 1] : fused_adamw_kernel<1, true, false, FORM, fused_chunk(true, 1)>;
+    return start("hzp_adamw_shard", kernel, grid, dim3(kWave), fused_lds(g32, R, FEW, FORM, groups), stream, a);
 }
 
 // One segment with one multiplier: its record and pointers are a.word's first.
@@ -1017,13 +1036,13 @@ static hzp_status_t start_fused_one(bool g32, bool o32, uint32_t R, const FusedA
     constexpr std::make_index_sequence<HZP_MAX_REPLICAS> all;
     static constexpr auto kernels16 = fused_one_kernels<false, false, FEW>(all);
     static constexpr auto kernels32 = fused_one_kernels<true, true, FEW>(all);
-    const FusedOneKernel kernel = !g32 ? kernels16[R - 1] : o32 ? kernels32[R - 1] : fused_one_kernel<1, true, false, fused_chunk(true)>;
+    const FusedOneKernel kernel = !g32 ? kernels16[R - 1] : o32 ? kernels32[R - 1] : fused_one_kernel<1, true, false, fused_chunk(true, 1)>;
     FusedOneArgs one;
     one.out = a.word[3];
     one.scalars = a.scalars;
     std::memcpy(one.g, a.word + 4, R * sizeof one.g[0]);
     const uint64_t *const w = a.word, *const rec = a.word + R + 4;
-    return start("hzp_adamw_shard", kernel, dim3(groups), dim3(kWave), fused_lds(g32, kOne, groups), stream, u64x4{w[0], w[1], w[2], w[4]},
+    return start("hzp_adamw_shard", kernel, dim3(groups), dim3(kWave), fused_lds(g32, R, FEW, kOne, groups), stream, u64x4{w[0], w[1], w[2], w[4]},
                  u64x2{R > 1 ? w[5] : 0, reinterpret_cast<uint64_t>(a.scalars_dev)}, rec[0] >> 32 | rec[1] << 32, one);
 }
 
@@ -1132,10 +1151,10 @@ hzp_status_t launch_fused(const hzp_plan_t *plan, bool g32, bool o32, uint32_t R
         }
         // (where wavefronts also read tables, 16 fp32 contributions are too many a little earlier: 32 segments of 0.52 M elements together,
         // R = 16, 10.1 us without and 10.5 with them; 0.38 M 8.6 and 8.4)
-        const bool few = blocks <= (g32 ? kFewGroups / 4 * 3 : kFewGroups);
+        const bool few = blocks <= (!g32 && one_chunk(R) ? kOneChunkGroups : g32 ? kFewGroups / 4 * 3 : kFewGroups);
         hzp_status_t st;
         if (cnt == 1 && !a.lookup) {
-            if (blocks <= kFewGroups)
+            if (few || blocks <= kFewGroups)
                 st = start_fused_one<true>(g32, o32, R, a, blocks, stream);
             else
                 st = start_fused_one<false>(g32, o32, R, a, blocks, stream);

@@ -88,6 +88,43 @@ def test_every_number_of_contributions_at_group_edges(R, cls):
         assert all(np.array_equal(s.view(np.uint32), t.view(np.uint32)) for s, t in zip(x, y))
 
 
+@pytest.mark.parametrize("R", [6, 7, 8])
+@pytest.mark.parametrize("groups", [(65537,), (32769, 32768), (60000, 6000)])
+def test_contributions_in_two_chunks_and_in_one(R, groups):
+    """bf16 updates of more than 65536 groups take 6 to 8 contributions in two chunks, shorter ones in one: the same bits (one segment,
+    segments of like length, and found by search; the last group is not full)."""
+    sizes = [g * 256 - 8 for g in groups]
+    total = sum(sizes)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(R)
+    grads = [torch.empty(total, device=DEV).normal_(0, 1e-3, generator=gen).bfloat16() for _ in range(R)]
+    start = [torch.empty(total, device=DEV).normal_(0, s, generator=gen) for s in (0.02, 1e-4, 1e-4)]
+    start[2].square_()
+    hy = hzp.adamw_hyper(HP["lr"], HP["beta1"], HP["beta2"], HP["eps"], HP["weight_decay"], 1.0 / R, 3)
+    results = []
+    for parts in (1, 4):            # one call over the segments; a call for each quarter of each
+        at, spans = 0, []
+        for n in sizes:
+            q = n // parts // 8 * 8
+            spans += [(at + k * q, q if k + 1 < parts else n - k * q) for k in range(parts)]
+            at += n
+        plan = hzp.hzp_plan([1] * len(spans), [n for _, n in spans], 8, 1, 1)
+        apart = parts == 1 and len(spans) > 1       # copies that do not follow each other, so that they stay segments
+        def views(t):
+            return [t[a:a + n].clone() if apart else t[a:a + n] for a, n in spans]
+        g = [views(t) for t in grads]
+        s = [views(t.clone()) for t in start]
+        o = views(torch.zeros(total, dtype=torch.bfloat16, device=DEV))
+        calls = [(0, len(spans))] if parts == 1 else [(k, k + 1) for k in range(len(spans))]
+        for lo, hi in calls:
+            hzp.hzp_adamw_shard(plan, lo, hi, 0, 0, hy, [g[r][k] for k in range(lo, hi) for r in range(R)], R, *(x[lo:hi] for x in s), o[lo:hi])
+        torch.cuda.synchronize()
+        results.append([torch.cat(x) for x in s] + [torch.cat(o)])
+    for a, b in zip(*results):
+        assert torch.equal(a.view(torch.int16 if a.dtype == torch.bfloat16 else torch.int32), b.view(torch.int16 if b.dtype == torch.bfloat16 else torch.int32))
+    assert not torch.equal(results[0][0], start[0])
+
+
 @pytest.mark.parametrize("place,out_place", [("packed", None), ("spread", None), ("down", None), ("packed", "spread"),
                                              ("spread", "down"), ("own", None), ("spread", "own"), ("own", "packed")])
 @pytest.mark.parametrize("R,layers,ragged", [(8, 50, False), (8, 50, True), (32, 30, True), (3, 200, True)])
