@@ -834,26 +834,36 @@ static constexpr std::array<FusedOneKernel, sizeof...(I)> fused_one_kernels(std:
     return {fused_one_kernel<I + 1, G32, O32, fused_chunk(G32, I + 1, FEW)>...};
 }
 
-// Wavefronts per CU for the reduction: what keeps so many KiB in flight per CU.  Where the contributions fit one chunk 48; where
-// several chunks follow each other about 30, from what a wavefront asks for on average; in a short launch (below about
-// 30 us) half as much again, because there filling and draining the chip weighs more than the order of the requests.
+// Wavefronts per CU for the reduction, from the bytes that they ask for.  Where several chunks follow each other about 30 KiB per CU, from
+// what a wavefront asks for on average; in a short launch (below about 30 us) half as much again, because there filling and draining
+// the chip weighs more than the order of the requests.
 // Measured at 100 M elements, TB/s with 7 / 8 / 9 / 12 wavefronts: fp32 R = 8 6.83 / 7.00 / 6.84 / 6.61, R = 16 6.92 / 6.79 / 6.61 / 6.49,
-// accumulating 6.93 / 6.95 / 6.78 / 6.65 and 6.90 / 6.74 / 6.61 / 6.51; bf16 with 12 / 14 / 16 / 18 / 22: R = 6 5.54 / 6.35 / 6.74 /
-// 6.85 / 6.72, R = 8 accumulating (12 / 13 / 14 / 16 / 18) 6.70 / 6.80 / 6.73 / 6.54 / 6.45, R = 12 6.37 / 6.71 / 6.60 / 6.56 / 6.41,
-// R = 16 6.28 / 6.55 / 6.52 / 6.43 / 6.30, R = 32 6.07 / 6.32 / 6.40 / 6.29 / 6.11.
-// At 25 M / 6.3 M elements with 28 -> by this rule: bf16 R = 4 6.57 / 5.81 -> 6.64 / 5.80, R = 8 6.33 / 6.04 -> 6.59 / 6.05, R = 16
-// 6.31 / 6.10 -> 6.60 / 6.30; fp32 R = 4 (accumulating) 6.22 / 5.89 -> 6.30 / 5.89, R = 8 6.00 / 5.86 -> 6.49 / 6.09.
+// accumulating 6.93 / 6.95 / 6.78 / 6.65 and 6.90 / 6.74 / 6.61 / 6.51; bf16 with 11 / 14 / 16 / 21: R = 6 5.54 / 6.35 / 6.74 /
+// 6.72, R = 8 accumulating (11 / 12 / 14 / 16) 6.70 / 6.80 / 6.73 / 6.54, R = 12 6.37 / 6.71 / 6.60 / 6.41,
+// R = 16 6.28 / 6.55 / 6.52 / 6.30, R = 32 6.07 / 6.32 / 6.40 / 6.11.
+// At 25 M / 6.3 M elements with 25 -> by this rule: bf16 R = 8 6.33 / 6.04 -> 6.59 / 6.05, R = 16 6.31 / 6.10 -> 6.60 / 6.30; fp32 R = 8
+// 6.00 / 5.86 -> 6.49 / 6.09.
+// Where the contributions fit one chunk a wavefront has all of its bytes in flight: 42 KiB per CU, with fp32 more in short launches (66 KiB
+// below 80 MB, 54 below 200 MB), and no more than 21.  With 9 / 12 / 16 / 25, against 25 in launches of up to 256 MB (160 with bf16) and 48 KiB beyond: fp32 R = 4
+// accumulating 3.1 M elements 1.02 / .99 / .99 / 1.00, 6.3 M .99 / .98 / .99 / 1.00, 12.6 M .96 / .97 / 1.00 / 1.00, 25 M 1.00 / 1.04 / 1.06 /
+// 1.07; R = 2 accumulating (12 / 16 / 21 / 25) 3.1 M 1.02 / .99 / .98 / .98, 12.6 M .97 / .97 / .99 / 1.00; bf16 R = 4 (16 / 18 / 21 / 25) 3.1 M .98 / .96 /
+// .95 / .96, 25 M 1.01 / .99 / 1.00 / 1.01, accumulating .99 / .97 / .97 / .98 and .99 / 1.00 / 1.01 / 1.02.
 static unsigned reduce_waves(bool g32, uint32_t R, uint64_t n, int accumulate)
 {
     if (n <= 256u * 32u * 4u * kGroupQuads) return 0;       // all resident at once
     const uint32_t chunk = chunk_of(R, kReduceChunk), chunks = (R + chunk - 1) / chunk, es = g32 ? 4u : 2u;
     const uint64_t bytes = n * (R * es + 4u);
+    const int quads = reduce_quads(R, g32, kReducePlain);
+    if (chunks == 1) {
+        if (quads > 1 || R * es + (accumulate ? 2u : 0u) <= 4u) return 25;
+        const uint64_t moved = bytes + (accumulate ? n * 4 : 0);
+        const unsigned kib = !g32 || moved >= 200000000u ? 42 : moved >= 80000000u ? 54 : 66;
+        return std::min(21u, kib * 1024u / (R * es * 256u + (accumulate ? 512u : 0u)));
+    }
     const bool brief = bytes < (g32 ? 256u << 20 : 160u << 20);
-    const unsigned asked = (brief ? chunk * es * 256u : R * es * 256u / chunks) * reduce_quads(R, g32, kReducePlain) + (accumulate ? 512u : 0u);
+    const unsigned asked = (brief ? chunk * es * 256u : R * es * 256u / chunks) + (accumulate ? 512u : 0u);
     unsigned half_kib;
-    if (chunks == 1)
-        half_kib = brief ? 144 : 96;
-    else if (g32)
+    if (g32)
         half_kib = brief ? 114 : R > 8 ? (accumulate ? 67 : 62) : accumulate ? 72 : 64;
     else
         half_kib = brief ? 102 : R <= 16 && bytes >= 1000000000u ? (accumulate ? 65 : 60) : 68;
