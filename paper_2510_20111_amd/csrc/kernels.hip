@@ -117,13 +117,6 @@ constexpr uint32_t kGroupQuads = 64;        // quads per group (256 elements)
 // are given out in 128 units of 1280 bytes (so 13 are 12, 15 are 14, 19 and 20 are 18, 22 to 24 are 21).
 constexpr unsigned lds_for(unsigned waves) { return waves ? (128u / (waves + 1) + 1) * 1280u : 0u; }
 
-// Most contributions one wavefront of the update has in flight.  Few large chunks beat many small ones (a wavefront waits once for each),
-// with so many fewer wavefronts that a CU has about 50 KiB in flight (fused_lds).  Chunks of at most 4 / 6 / 8, each with the best number
-// of wavefronts, mean over 9 to 105 M elements against chunks of 4 with 9 or 11: bf16 R = 10 .995 / .981 / .982, R = 14 .996 / .979 /
-// .974, R = 16 .996 / .986 / .979, R = 20 .996 / .985 / .979, R = 24 .999 / .991 / .988, R = 28 .997 / .990 / .989, R = 32 .997 /
-// .996 / .991, but 2 % more at 2-6 M; R = 8 .997 / - / 1.001.  fp32 with chunks of at most 3 / 4 / 6, over 1.5 to 71 M: R = 4 .989 / .978 / -,
-// R = 8 .993 / .973 / -, R = 12 .982 / .980 / .975, R = 16 .996 / .983 / .983, R = 24 .991 / .992 / 1.004, R = 32 .997 / .998 / 1.019.
-constexpr uint32_t fused_chunk(bool g32, uint32_t R) { return g32 ? (R > 16 ? 3u : 4u) : R <= 5 ? 5u : R <= 8 || R > 28 ? 4u : 8u; }
 constexpr uint32_t kReduceChunk = 4;
 // A launch of so few groups that all wavefronts are resident at once lasts as long as one wavefront, whose chunks follow
 // each other: there, more than 8 contributions are requested up to 16 at a time (chunks of 4 / 16, us a call: 64 k elements, R = 32:
@@ -131,11 +124,24 @@ constexpr uint32_t kReduceChunk = 4;
 // several segments, 0.15 M elements, R = 16 / 32: 5.8 -> 5.1 and 7.3 -> 5.3; with R <= 8 no difference).
 constexpr uint32_t kFewGroups = 2048;
 constexpr uint32_t few_chunk(uint32_t R, uint32_t chunk) { return R > 8 ? 16u : chunk; }
-// The update of 6 to 8 bf16 contributions takes them in one chunk in launches of at most so many groups (one chunk against two, both with
-// the best number of wavefronts: R = 7 1.5 / 2.7 / 6.3 / 9.1 / 21 / 48 M elements .98 / .98 / .99 / 1.00 / 1.00 / 1.005, R = 8 .986 / .98 /
-// .99 / 1.00 / 1.00 / 1.00, 105 M 1.01; R = 6 9.1 / 21 / 33 M .98 / .99 / 1.01).
-constexpr uint32_t kOneChunkGroups = 65536;
-constexpr bool one_chunk(uint32_t R) { return R > 5 && R <= 8; }
+// Most contributions one wavefront of the update has in flight, by the launch's class (fused_class).
+//   kLarge: few large chunks beat many small ones (a wavefront waits once for each), with so many fewer wavefronts that a CU has about
+//   50 KiB in flight (fused_lds).  Chunks of at most 4 / 6 / 8, each with the best number of wavefronts, mean over 9 to 105 M
+//   elements against chunks of 4 with 9 or 11: bf16 R = 10 .995 / .981 / .982, R = 14 .996 / .979 / .974, R = 16 .996 / .986 / .979,
+//   R = 20 .996 / .985 / .979, R = 24 .999 / .991 / .988, R = 28 .997 / .990 / .989, R = 32 .997 / .996 / .991, but 2 % more at 2-6 M.
+//   fp32 with chunks of at most 3 / 4 / 6, over 1.5 to 71 M: R = 4 .989 / .978 / -, R = 8 .993 / .973 / -, R = 12 .982 / .980 / .975,
+//   R = 16 .996 / .983 / .983, R = 24 .991 / .992 / 1.004, R = 32 .997 / .998 / 1.019.
+//   kMid: in shorter launches large chunks read too many streams side by side, and where no cap holds the wavefronts back they ask for
+//   too much (bf16 R = 12 / 24 of 0.66 M elements 7.6 / 9.9 us, with chunks of 8 7.9 / 10.2; fp32 R = 4 6.1, with chunks of 4 6.4).
+//   kFew: all resident, and so few that latency counts.
+enum ChunkClass { kFew, kMid, kLarge };
+constexpr uint32_t fused_chunk(bool g32, uint32_t R, ChunkClass c)
+{
+    const uint32_t mid = g32 ? 3u : 4u;
+    if (c == kFew) return few_chunk(R, mid);
+    if (c == kMid || (g32 ? R > 16 : R > 28)) return mid;
+    return g32 || R <= 4 ? 4u : R <= 8 ? R : 8u;
+}
 
 // Four gradient elements of one contribution, widened to fp32 on access.
 template <bool G32>
@@ -818,20 +824,15 @@ static constexpr std::array<ReduceKernel, sizeof...(I)> reduce_kernels(std::inde
 }
 typedef void (*FusedKernel)(FusedArgs);
 typedef void (*FusedOneKernel)(u64x4, u64x2, uint64_t, FusedOneArgs);
-constexpr uint32_t fused_chunk(bool g32, uint32_t R, bool few)
-{
-    if (few && !g32 && one_chunk(R)) return R;
-    return few ? few_chunk(R, fused_chunk(g32, R)) : fused_chunk(g32, R);
-}
-template <bool G32, bool O32, FusedForm FORM, bool FEW, size_t... I>
+template <bool G32, bool O32, FusedForm FORM, ChunkClass CLASS, size_t... I>
 static constexpr std::array<FusedKernel, sizeof...(I)> fused_kernels(std::index_sequence<I...>)
 {
-    return {fused_adamw_kernel<I + 1, G32, O32, FORM, fused_chunk(G32, I + 1, FEW)>...};
+    return {fused_adamw_kernel<I + 1, G32, O32, FORM, fused_chunk(G32, I + 1, CLASS)>...};
 }
-template <bool G32, bool O32, bool FEW, size_t... I>
+template <bool G32, bool O32, ChunkClass CLASS, size_t... I>
 static constexpr std::array<FusedOneKernel, sizeof...(I)> fused_one_kernels(std::index_sequence<I...>)
 {
-    return {fused_one_kernel<I + 1, G32, O32, fused_chunk(G32, I + 1, FEW)>...};
+    return {fused_one_kernel<I + 1, G32, O32, fused_chunk(G32, I + 1, CLASS)>...};
 }
 
 // Wavefronts per CU for the reduction, from the bytes that they ask for.  Where several chunks follow each other about 30 KiB per CU, from
@@ -1012,47 +1013,77 @@ static void list_runs(const hzp_plan_t *plan, const FusedSegment *segs, size_t n
 // and 9.4 / 14.2 / 16.8, 1.3 M 11.4 / 19.4 / 22.9 and 11.5 / 19.2 / 22.7; beyond, the order of the requests counts (below).
 constexpr uint32_t kUncappedGroups = 5120;
 
-// Dynamic LDS of a launch: as many wavefronts per CU as keep about 50 KiB (bf16, 10 wavefronts at the most) or 44 KiB (fp32; 7, or 8 of
-// single contributions) in flight.  One or two more where a wavefront reads pointers or tables before it asks for data, and in shorter
-// launches of chunks of 4.  Means over 9 to 105 M elements against chunks of at most 4 (fp32 3) and 9 or 11 (8) wavefronts, by wavefronts 6 / 7 / 8 / 9 / 10 / 11: bf16 R = 5 1.022 / .996 /
-// .990 / .990 / .988 / .987, R = 10 1.045 / .997 / .984 / .982 / .983 / .984, R = 16 .987 / .979 / .986 / .991 / .996 / 1.001, R = 24
-// .992 / .988 / .996 / .999 / 1.004 / 1.010; R = 8 in two chunks 1.094 / 1.032 / 1.005 / .997 / .998 / 1.000; over 1.5 to 71 M with 4 / 5 / 6 / 7 / 8: fp32 R = 2 1.175 /
-// 1.045 / .990 / .981 / .989, R = 4 1.077 / .991 / .978 / .987 / .993, R = 8 1.057 / .978 / .973 / .991 / 1.000, R = 16 1.074 / .991 / .983 /
-// .999 / 1.008; R = 24 in chunks of 3 1.230 / 1.094 / 1.022 / .991 / .994.
-static unsigned fused_lds(bool g32, uint32_t R, bool few, FusedForm form, uint32_t groups)
+// Chunks are small up to 20480 groups (fp32 10240): the streams then lie a few MB apart and partly in the memory-side cache, and what counts is
+// how many of them are read side by side (buffers of one call's size, R = 12 / 16 / 24 of 1.8 M elements 17.3 / 20.1 / 24.4 us, with
+// chunks of 8 18.5 / 23.9 / 28.3; 4.4 M 38.0 / 46.5 / 54, 41.8 / 46.5 / 54; from 5 M chunks of 8 take 1-4 % less; fp32 R = 4 / 8 of 1.8 M 14.6 /
+// 19.9, with chunks of 4 14.9 / 20.2).  Beyond, 6 to 8 bf16 contributions go in one chunk up to 65536 groups and in two above (one
+// against two, both with the best number of wavefronts: R = 7 9.1 / 21 / 48 M elements 1.00 / 1.00 / 1.005, R = 8 1.00 / 1.00 / 1.00,
+// 105 M 1.01; R = 6 9.1 / 21 / 33 M .98 / .99 / 1.01).
+static ChunkClass fused_class(bool g32, uint32_t R, FusedForm form, uint32_t groups)
 {
-    if (groups <= kUncappedGroups) return 0;
-    const uint32_t chunk = chunk_of(R, fused_chunk(g32, R, few)), asked = (chunk * (g32 ? 4u : 2u) + 12u) * 4u * kGroupQuads;
-    const bool late = form == kSearched || (form == kPlain && groups <= 32768u);
-    if (g32) return lds_for(late && chunk < 4 ? 9u : late + (R > 16 || chunk == 1 ? 8u : chunk < 4 || groups <= 16384u ? 7u : 45056u / asked));
-    if (R > 28 || (late && chunk <= 4)) return lds_for(groups <= 32768u ? 14u : late || groups <= 200000u ? 11u : 10u);
-    return lds_for(late + (one_chunk(R) && few ? 10u : chunk == 4 ? 9u : std::min(10u, 51200u / asked)));
+    // (where wavefronts also read tables, 16 fp32 contributions are too many a little earlier: 32 segments of 0.52 M elements together,
+    // R = 16, 10.1 us without and 10.5 with them; 0.38 M 8.6 and 8.4)
+    if (groups <= (g32 && form != kOne ? kFewGroups / 4 * 3 : kFewGroups)) return kFew;
+    if (groups <= (g32 ? 10240u : 20480u)) return kMid;
+    return !g32 && R > 5 && R <= 8 && groups > 65536u ? kMid : kLarge;
 }
 
-template <FusedForm FORM, bool FEW>
-static hzp_status_t start_fused(bool g32, bool o32, uint32_t R, const FusedArgs &a, dim3 grid, uint32_t groups, hipStream_t stream)
+// Dynamic LDS of a launch: as many wavefronts per CU as keep about 50 KiB (bf16, 10 wavefronts at the most) or 44 KiB (fp32; 7, or 8 of
+// single contributions) in flight.  One or two more where a wavefront reads pointers or tables before it asks for data, and in shorter
+// launches of chunks of 4.  Means over 9 to 105 M elements against chunks of at most 4 and 9 or 11 wavefronts, by wavefronts 6 / 7 / 8 / 9 /
+// 10 / 11: bf16 R = 5 1.022 / .996 / .990 / .990 / .988 / .987, R = 10 1.045 / .997 / .984 / .982 / .983 / .984, R = 16 .987 / .979 / .986 /
+// .991 / .996 / 1.001, R = 24 .992 / .988 / .996 / .999 / 1.004 / 1.010; R = 8 in two chunks 1.094 / 1.032 / 1.005 / .997 / .998 / 1.000.
+// Over 1.5 to 71 M against chunks of 3 and 8 wavefronts, by 4 / 5 / 6 / 7 / 8: fp32 R = 2 1.175 / 1.045 / .990 / .981 / .989, R = 4 1.077 /
+// .991 / .978 / .987 / .993, R = 8 1.057 / .978 / .973 / .991 / 1.000, R = 16 1.074 / .991 / .983 / .999 / 1.008; R = 24 in chunks of 3
+// 1.230 / 1.094 / 1.022 / .991 / .994.
+static unsigned fused_lds(bool g32, uint32_t R, ChunkClass c, FusedForm form, uint32_t groups)
+{
+    if (groups <= kUncappedGroups) return 0;
+    const uint32_t chunk = chunk_of(R, fused_chunk(g32, R, c)), asked = (chunk * (g32 ? 4u : 2u) + 12u) * 4u * kGroupQuads;
+    const bool late = form == kSearched || (form == kPlain && groups <= 32768u);
+    if (c == kMid && groups <= 20480u && chunk < R) return lds_for(g32 ? (late ? 9u : 8u) : 14u);
+    if (g32) return lds_for(late && chunk < 4 ? 9u : late + (R > 16 || chunk == 1 ? 8u : chunk < 4 || groups <= 16384u ? 7u : 45056u / asked));
+    if (R > 28 || (late && chunk <= 4)) return lds_for(groups <= 32768u ? 14u : late || groups <= 200000u ? 11u : 10u);
+    return lds_for(late + (R > 5 && R <= 8 && chunk == R ? 10u : chunk == 4 ? 9u : std::min(10u, 51200u / asked)));
+}
+
+// The kernel of a form and class for each R; fp32 contributions with a bf16 output are one, already summed.
+template <FusedForm FORM, ChunkClass CLASS>
+static FusedKernel fused_kernel(bool g32, bool o32, uint32_t R)
 {
     constexpr std::make_index_sequence<HZP_MAX_REPLICAS> all;
-    static constexpr auto kernels16 = fused_kernels<false, false, FORM, FEW>(all);
-    static constexpr auto kernels32 = fused_kernels<true, true, FORM, FEW>(all);
-    const FusedKernel kernel = !g32 ? kernels16[R - 1] : o32 ? kernels32[R - 1] : fused_adamw_kernel<1, true, false, FORM, fused_chunk(true, 1)>;
-    return start("hzp_adamw_shard", kernel, grid, dim3(kWave), fused_lds(g32, R, FEW, FORM, groups), stream, a);
+    static constexpr auto kernels16 = fused_kernels<false, false, FORM, CLASS>(all);
+    static constexpr auto kernels32 = fused_kernels<true, true, FORM, CLASS>(all);
+    return !g32 ? kernels16[R - 1] : o32 ? kernels32[R - 1] : fused_adamw_kernel<1, true, false, FORM, fused_chunk(true, 1, CLASS)>;
+}
+template <ChunkClass CLASS>
+static FusedOneKernel fused_one_kernel_of(bool g32, bool o32, uint32_t R)
+{
+    constexpr std::make_index_sequence<HZP_MAX_REPLICAS> all;
+    static constexpr auto kernels16 = fused_one_kernels<false, false, CLASS>(all);
+    static constexpr auto kernels32 = fused_one_kernels<true, true, CLASS>(all);
+    return !g32 ? kernels16[R - 1] : o32 ? kernels32[R - 1] : fused_one_kernel<1, true, false, fused_chunk(true, 1, CLASS)>;
+}
+
+template <FusedForm FORM>
+static hzp_status_t start_fused(bool g32, bool o32, uint32_t R, const FusedArgs &a, dim3 grid, uint32_t groups, hipStream_t stream)
+{
+    const ChunkClass c = fused_class(g32, R, FORM, groups);
+    const FusedKernel kernel = c == kFew ? fused_kernel<FORM, kFew>(g32, o32, R) : c == kMid ? fused_kernel<FORM, kMid>(g32, o32, R) : fused_kernel<FORM, kLarge>(g32, o32, R);
+    return start("hzp_adamw_shard", kernel, grid, dim3(kWave), fused_lds(g32, R, c, FORM, groups), stream, a);
 }
 
 // One segment with one multiplier: its record and pointers are a.word's first.
-template <bool FEW>
 static hzp_status_t start_fused_one(bool g32, bool o32, uint32_t R, const FusedArgs &a, uint32_t groups, hipStream_t stream)
 {
-    constexpr std::make_index_sequence<HZP_MAX_REPLICAS> all;
-    static constexpr auto kernels16 = fused_one_kernels<false, false, FEW>(all);
-    static constexpr auto kernels32 = fused_one_kernels<true, true, FEW>(all);
-    const FusedOneKernel kernel = !g32 ? kernels16[R - 1] : o32 ? kernels32[R - 1] : fused_one_kernel<1, true, false, fused_chunk(true, 1)>;
+    const ChunkClass c = fused_class(g32, R, kOne, groups);
+    const FusedOneKernel kernel = c == kFew ? fused_one_kernel_of<kFew>(g32, o32, R) : c == kMid ? fused_one_kernel_of<kMid>(g32, o32, R) : fused_one_kernel_of<kLarge>(g32, o32, R);
     FusedOneArgs one;
     one.out = a.word[3];
     one.scalars = a.scalars;
     std::memcpy(one.g, a.word + 4, R * sizeof one.g[0]);
     const uint64_t *const w = a.word, *const rec = a.word + R + 4;
-    return start("hzp_adamw_shard", kernel, dim3(groups), dim3(kWave), fused_lds(g32, R, FEW, kOne, groups), stream, u64x4{w[0], w[1], w[2], w[4]},
+    return start("hzp_adamw_shard", kernel, dim3(groups), dim3(kWave), fused_lds(g32, R, c, kOne, groups), stream, u64x4{w[0], w[1], w[2], w[4]},
                  u64x2{R > 1 ? w[5] : 0, reinterpret_cast<uint64_t>(a.scalars_dev)}, rec[0] >> 32 | rec[1] << 32, one);
 }
 
@@ -1159,26 +1190,9 @@ hzp_status_t launch_fused(const hzp_plan_t *plan, bool g32, bool o32, uint32_t R
             for (uint32_t c = cnt; c-- > 1;) w[(size_t)c * a.stride] -= (uint32_t)w[(size_t)(c - 1) * a.stride];
             grid = dim3(longest, cnt);
         }
-        // (where wavefronts also read tables, 16 fp32 contributions are too many a little earlier: 32 segments of 0.52 M elements together,
-        // R = 16, 10.1 us without and 10.5 with them; 0.38 M 8.6 and 8.4)
-        const bool few = blocks <= (!g32 && one_chunk(R) ? kOneChunkGroups : g32 ? kFewGroups / 4 * 3 : kFewGroups);
-        hzp_status_t st;
-        if (cnt == 1 && !a.lookup) {
-            if (few || blocks <= kFewGroups)
-                st = start_fused_one<true>(g32, o32, R, a, blocks, stream);
-            else
-                st = start_fused_one<false>(g32, o32, R, a, blocks, stream);
-        } else if (a.grid2d && !shared && !a.lookup) {
-            if (few)
-                st = start_fused<kPlain, true>(g32, o32, R, a, grid, blocks, stream);
-            else
-                st = start_fused<kPlain, false>(g32, o32, R, a, grid, blocks, stream);
-        } else {
-            if (few)
-                st = start_fused<kSearched, true>(g32, o32, R, a, grid, blocks, stream);
-            else
-                st = start_fused<kSearched, false>(g32, o32, R, a, grid, blocks, stream);
-        }
+        const hzp_status_t st = cnt == 1 && !a.lookup                ? start_fused_one(g32, o32, R, a, blocks, stream)
+                                : a.grid2d && !shared && !a.lookup ? start_fused<kPlain>(g32, o32, R, a, grid, blocks, stream)
+                                                                   : start_fused<kSearched>(g32, o32, R, a, grid, blocks, stream);
         if (st != HZP_OK) return st;
         for (uint32_t c = 0; c < cnt; ++c) {
             done += part[c].n;

@@ -88,16 +88,18 @@ def test_every_number_of_contributions_at_group_edges(R, cls):
         assert all(np.array_equal(s.view(np.uint32), t.view(np.uint32)) for s, t in zip(x, y))
 
 
-@pytest.mark.parametrize("R", [6, 7, 8])
-@pytest.mark.parametrize("groups", [(65537,), (32769, 32768), (60000, 6000)])
-def test_contributions_in_two_chunks_and_in_one(R, groups):
-    """bf16 updates of more than 65536 groups take 6 to 8 contributions in two chunks, shorter ones in one: the same bits (one segment,
-    segments of like length, and found by search; the last group is not full)."""
+@pytest.mark.parametrize("cls,R,groups", [(0, R, g) for R in (6, 7, 8) for g in ((65537,), (32769, 32768), (60000, 6000))] +
+                         [(0, R, g) for R in (5, 8, 9, 16, 28, 29) for g in ((20481,), (10241, 10240), (18000, 2481))] +
+                         [(1, R, g) for R in (4, 7, 16, 17) for g in ((10241,), (5121, 5120), (9000, 1241))])
+def test_long_launches_and_their_quarters(cls, R, groups):
+    """Launches just long enough for another number of contributions at a time, and the same elements in calls of a quarter of each
+    segment: the same bits (one segment, segments of like length, and found by search; the last group is not full)."""
     sizes = [g * 256 - 8 for g in groups]
     total = sum(sizes)
     gen = torch.Generator(device=DEV)
     gen.manual_seed(R)
-    grads = [torch.empty(total, device=DEV).normal_(0, 1e-3, generator=gen).bfloat16() for _ in range(R)]
+    dtype, bits = (torch.float32, torch.int32) if cls else (torch.bfloat16, torch.int16)
+    grads = [torch.empty(total, device=DEV).normal_(0, 1e-3, generator=gen).to(dtype) for _ in range(R)]
     start = [torch.empty(total, device=DEV).normal_(0, s, generator=gen) for s in (0.02, 1e-4, 1e-4)]
     start[2].square_()
     hy = hzp.adamw_hyper(HP["lr"], HP["beta1"], HP["beta2"], HP["eps"], HP["weight_decay"], 1.0 / R, 3)
@@ -108,20 +110,20 @@ def test_contributions_in_two_chunks_and_in_one(R, groups):
             q = n // parts // 8 * 8
             spans += [(at + k * q, q if k + 1 < parts else n - k * q) for k in range(parts)]
             at += n
-        plan = hzp.hzp_plan([1] * len(spans), [n for _, n in spans], 8, 1, 1)
+        plan = hzp.hzp_plan([1] * len(spans), [n for _, n in spans], 8, 1, 1, tensor_class=[cls] * len(spans))
         apart = parts == 1 and len(spans) > 1       # copies that do not follow each other, so that they stay segments
         def views(t):
             return [t[a:a + n].clone() if apart else t[a:a + n] for a, n in spans]
         g = [views(t) for t in grads]
         s = [views(t.clone()) for t in start]
-        o = views(torch.zeros(total, dtype=torch.bfloat16, device=DEV))
+        o = views(torch.zeros(total, dtype=dtype, device=DEV))
         calls = [(0, len(spans))] if parts == 1 else [(k, k + 1) for k in range(len(spans))]
         for lo, hi in calls:
-            hzp.hzp_adamw_shard(plan, lo, hi, 0, 0, hy, [g[r][k] for k in range(lo, hi) for r in range(R)], R, *(x[lo:hi] for x in s), o[lo:hi])
+            hzp.hzp_adamw_shard(plan, lo, hi, cls, 0, hy, [g[r][k] for k in range(lo, hi) for r in range(R)], R, *(x[lo:hi] for x in s), o[lo:hi])
         torch.cuda.synchronize()
         results.append([torch.cat(x) for x in s] + [torch.cat(o)])
     for a, b in zip(*results):
-        assert torch.equal(a.view(torch.int16 if a.dtype == torch.bfloat16 else torch.int32), b.view(torch.int16 if b.dtype == torch.bfloat16 else torch.int32))
+        assert torch.equal(a.view(bits if a.dtype == dtype else torch.int32), b.view(bits if b.dtype == dtype else torch.int32))
     assert not torch.equal(results[0][0], start[0])
 
 
