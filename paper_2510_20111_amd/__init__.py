@@ -1,7 +1,7 @@
 """MI355X-native shard-update hot path of hierarchical ZeRO parallelism (AsyncHZP).
 
 The product is ``libhzp.so`` (HIP kernels for gfx950 behind the C ABI of ``include/hzp.h``);
-this package is its thin ctypes binding.  Importing it requires the built library.
+this package is its thin binding.  Importing it requires the built library.
 """
 from .binding import (  # noqa: F401
     HZP_CLASS_BF16, HZP_CLASS_F32, HZP_GRAD_DEFAULT, HZP_GRAD_BF16, HZP_GRAD_F32, HZP_MAX_GROUP,

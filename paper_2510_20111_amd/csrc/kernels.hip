@@ -244,7 +244,8 @@ constexpr int reduce_quads(uint32_t R, bool g32, ReduceForm form) { return form 
 // wavefront starts: leading arguments that are no structs arrive there (the build asks for 14 words; vectors, because the host spends 15 ns
 // on every argument).  With all of it read from the argument block, us: bf16 R = 4 / 8 of 2.1 M elements 5.8 / 8.2 (now 5.5 / 8.1), R = 32
 // of 0.5 M 7.4 (6.9), R = 8 of 25 M 76.6 (75.8); fp32 R = 4 accumulating, 1 / 6.3 M 6.0 / 25.1 (5.8 / 25.0), R = 16 of 0.26 M, the one that
-// lost, 5.0 (5.3: its later pointers now queue behind the first requests).
+// lost, 5.0 (5.3: its later pointers now queue behind the first requests).  Filling the registers costs the device 0.15 us, which shows only
+// where a graph replays reductions of 0.2 M elements and less (1.85, now 2.0).
 template <uint32_t R, bool G32, bool ACC, ReduceForm FORM>
 __global__ __launch_bounds__(kWave) void reduce_kernel(const u64x4 g, const u64x2 o, const ReduceRest rest)
 {
