@@ -323,6 +323,7 @@ struct FusedLead {
     uint64_t size;                          // number of quads, decay multiplier
 };
 constexpr uint32_t kLeadBytes = 56;         // of the argument block; the struct follows
+static_assert(sizeof(u64x4) + sizeof(u64x2) + sizeof(uint64_t) == kLeadBytes && alignof(FusedOneArgs) == 8, "argument block");
 enum FusedForm { kSearched, kPlain, kOne };
 
 // The decay runs that a group meets, found while the streams arrive: begin() narrows the search to 64
