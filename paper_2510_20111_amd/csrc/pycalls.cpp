@@ -12,6 +12,7 @@
 #include <cstddef>
 #include <cstdint>
 #include <cstring>
+#include <initializer_list>
 
 #include "hzp.h"
 
@@ -131,6 +132,8 @@ struct CallObject {
     PyObject *otherwise;            // the binding function
     PyObject *check;                // raises where a status is not HZP_OK
     PyObject *array, *void_p, *hyper;   // ctypes.Array, ctypes.c_void_p, the binding's AdamW
+    PyObject *code, *defaults;      // the binding function's when this was made
+    PyObject *weak;                 // weak references
 };
 
 PyObject *name_handle, *name_data_ptr, *name_cuda_stream;      // interned
@@ -272,12 +275,19 @@ bool convert_all(const CallObject *self, PyObject *const *args, Py_ssize_t n, Py
     return true;
 }
 
+// The binding function is still what this stands for (a program may have given it other defaults or another body).
+bool as_made(const CallObject *self)
+{
+    PyObject *const f = self->otherwise;
+    return PyFunction_GET_CODE(f) == self->code && PyFunction_GET_DEFAULTS(f) == self->defaults && !PyFunction_GET_KW_DEFAULTS(f);
+}
+
 PyObject *call(PyObject *object, PyObject *const *args, size_t nargsf, PyObject *kwnames)
 {
     CallObject *const self = reinterpret_cast<CallObject *>(object);
     Value v[kMostArgs];
     void *listed[kMostListed];
-    if (!convert_all(self, args, PyVectorcall_NARGS(nargsf), kwnames, v, listed)) {
+    if (!as_made(self) || !convert_all(self, args, PyVectorcall_NARGS(nargsf), kwnames, v, listed)) {
         PyErr_Clear();
         return PyObject_Vectorcall(self->otherwise, args, nargsf, kwnames);
     }
@@ -295,7 +305,7 @@ PyObject *make(PyTypeObject *type, PyObject *args, PyObject *)
     const char *name;
     unsigned long long entry;
     PyObject *otherwise, *check, *array, *void_p, *hyper;
-    if (!PyArg_ParseTuple(args, "sKOOO!O!O!", &name, &entry, &otherwise, &check, &PyType_Type, &array, &PyType_Type, &void_p, &PyType_Type, &hyper))
+    if (!PyArg_ParseTuple(args, "sKO!OO!O!O!", &name, &entry, &PyFunction_Type, &otherwise, &check, &PyType_Type, &array, &PyType_Type, &void_p, &PyType_Type, &hyper))
         return nullptr;
     const Function *function = nullptr;
     for (const Function &f : kFunctions)
@@ -320,10 +330,10 @@ PyObject *make(PyTypeObject *type, PyObject *args, PyObject *)
     self->function = function;
     self->entry = reinterpret_cast<void *>(static_cast<uintptr_t>(entry));
     self->names = names;
-    PyObject **const kept[] = {&self->otherwise, &self->check, &self->array, &self->void_p, &self->hyper};
-    PyObject *const given[] = {otherwise, check, array, void_p, hyper};
-    for (int i = 0; i < 5; ++i) {
-        Py_INCREF(given[i]);
+    PyObject **const kept[] = {&self->otherwise, &self->check, &self->array, &self->void_p, &self->hyper, &self->code, &self->defaults};
+    PyObject *const given[] = {otherwise, check, array, void_p, hyper, PyFunction_GET_CODE(otherwise), PyFunction_GET_DEFAULTS(otherwise)};
+    for (int i = 0; i < 7; ++i) {
+        Py_XINCREF(given[i]);
         *kept[i] = given[i];
     }
     return reinterpret_cast<PyObject *>(self);
@@ -333,17 +343,21 @@ void drop(PyObject *object)
 {
     CallObject *const self = reinterpret_cast<CallObject *>(object);
     PyTypeObject *const type = Py_TYPE(object);
+    if (self->weak) PyObject_ClearWeakRefs(object);
     Py_XDECREF(self->names);
     Py_XDECREF(self->otherwise);
     Py_XDECREF(self->check);
     Py_XDECREF(self->array);
     Py_XDECREF(self->void_p);
     Py_XDECREF(self->hyper);
+    Py_XDECREF(self->code);
+    Py_XDECREF(self->defaults);
     type->tp_free(object);
     Py_DECREF(type);
 }
 
-// Name, documentation and the like are the binding function's.
+// To Python the object is the binding function: attributes of all kinds are that function's (its class among them, so that it counts as
+// a function), it shows as that function does, becomes a method in a class, and is pickled and copied by its qualified name.
 PyObject *attribute(PyObject *object, PyObject *name)
 {
     CallObject *const self = reinterpret_cast<CallObject *>(object);
@@ -351,15 +365,42 @@ PyObject *attribute(PyObject *object, PyObject *name)
         Py_INCREF(self->otherwise);
         return self->otherwise;
     }
-    if (PyUnicode_CompareWithASCIIString(name, "__class__") == 0) return PyObject_GenericGetAttr(object, name);
+    for (const char *own : {"__reduce__", "__reduce_ex__", "__get__", "__call__", "__eq__", "__ne__", "__hash__"})
+        if (PyUnicode_CompareWithASCIIString(name, own) == 0) return PyObject_GenericGetAttr(object, name);
     return PyObject_GetAttr(self->otherwise, name);
 }
 
-PyMemberDef members[] = {{"__vectorcalloffset__", T_PYSSIZET, offsetof(CallObject, vectorcall), READONLY, nullptr}, {nullptr}};
+int set_attribute(PyObject *object, PyObject *name, PyObject *value)
+{
+    return PyObject_SetAttr(reinterpret_cast<CallObject *>(object)->otherwise, name, value);
+}
+
+PyObject *represent(PyObject *object) { return PyObject_Repr(reinterpret_cast<CallObject *>(object)->otherwise); }
+
+PyObject *bound(PyObject *object, PyObject *instance, PyObject *)
+{
+    if (instance && instance != Py_None) return PyMethod_New(object, instance);
+    Py_INCREF(object);
+    return object;
+}
+
+PyObject *reduce(PyObject *object, PyObject *)
+{
+    return PyObject_GetAttrString(reinterpret_cast<CallObject *>(object)->otherwise, "__qualname__");
+}
+
+PyMethodDef methods[] = {{"__reduce__", reduce, METH_NOARGS, nullptr}, {nullptr}};
+PyMemberDef members[] = {{"__vectorcalloffset__", T_PYSSIZET, offsetof(CallObject, vectorcall), READONLY, nullptr},
+                         {"__weaklistoffset__", T_PYSSIZET, offsetof(CallObject, weak), READONLY, nullptr},
+                         {nullptr}};
 PyType_Slot slots[] = {{Py_tp_new, reinterpret_cast<void *>(make)},
                        {Py_tp_dealloc, reinterpret_cast<void *>(drop)},
                        {Py_tp_call, reinterpret_cast<void *>(PyVectorcall_Call)},
                        {Py_tp_getattro, reinterpret_cast<void *>(attribute)},
+                       {Py_tp_setattro, reinterpret_cast<void *>(set_attribute)},
+                       {Py_tp_repr, reinterpret_cast<void *>(represent)},
+                       {Py_tp_descr_get, reinterpret_cast<void *>(bound)},
+                       {Py_tp_methods, methods},
                        {Py_tp_members, members},
                        {0, nullptr}};
 PyType_Spec spec = {"_calls.Call", sizeof(CallObject), 0, Py_TPFLAGS_DEFAULT | Py_TPFLAGS_HAVE_VECTORCALL, slots};

@@ -1,8 +1,12 @@
 """The calls made from native code hand the C entry points what the binding functions hand them, over all forms of the
 arguments that either accepts, and refuse what those refuse."""
+import copy
 import ctypes
+import functools
 import inspect
 import itertools
+import pickle
+import weakref
 
 import pytest
 
@@ -200,3 +204,59 @@ def test_usual_calls_do_not_go_through_the_binding_functions():
             if isinstance(x, ctypes.Array):
                 call(**dict(values, **{p: [Tensor(1 << 20), 1 << 21, Tensor(1 << 22)]}))
     assert len(rec.got) >= 4 * len(NAMES)
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_native_calls_behave_as_functions(name):
+    """A program can hold, copy, send, wrap, annotate and bind them as it can the functions beside them."""
+    f, plain = getattr(hzp, name), hzp.hzp_plan_free
+    for g in (plain, f):
+        for protocol in range(pickle.HIGHEST_PROTOCOL + 1):
+            assert pickle.loads(pickle.dumps(g, protocol)) is g
+        assert pickle.loads(pickle.dumps(functools.partial(g, 1))).func is g
+        assert copy.copy(g) is g and copy.deepcopy({"call": [g]})["call"][0] is g
+        assert weakref.ref(g)() is g
+        assert inspect.isfunction(g) and inspect.isroutine(g) and callable(g) and isinstance(g, type(plain))
+        assert repr(g).startswith("<function %s at 0x" % g.__name__)
+        assert g == g and g != f.__wrapped__ and {g: 1}[g] == 1 and g.__eq__(g) is True
+        g.mark = 5
+        assert g.mark == 5 and vars(g)["mark"] == 5 and "mark" in dir(g)
+        del g.mark
+        assert not hasattr(g, "mark")
+        with pytest.raises(AttributeError):
+            del g.mark
+        wrapped = functools.wraps(g)(lambda: None)
+        assert wrapped.__name__ == g.__name__ and wrapped.__module__ == g.__module__
+
+        class Holder:
+            method = g
+        holder = Holder()
+        assert holder.method.__self__ is holder and holder.method.__func__ is g and Holder.method is g
+        assert inspect.ismethod(holder.method) and inspect.ismethod(g.__get__(holder))
+
+
+def test_other_defaults_are_used(monkeypatch):
+    """A default that the program sets on the function counts, as it does for any function."""
+    rec = Recorder()
+    monkeypatch.setattr(bd, "_L", Spy(rec, monkeypatch))
+    function = bd.hzp_gather_shard.__wrapped__
+    call = bd._calls.Call("hzp_gather_shard", ctypes.cast(rec.hzp_gather_shard, ctypes.c_void_p).value, function, bd._check, ctypes.Array,
+                          ctypes.c_void_p, bd.AdamW)
+    args = (FakePlan(), 0, 0, 1, [1 << 20, 1 << 21, 1 << 22], 1 << 23)
+    call(*args, stream=7)
+    monkeypatch.setattr(call, "__defaults__", (9, 2))
+    call(*args)
+    monkeypatch.undo()
+    call(*args, stream=7)
+    assert [got[1][-1] for got in rec.got] == [7, 9, 7] and [got[1][5] for got in rec.got] == [3, 2, 3]
+
+
+def test_calls_are_let_go():
+    rec = Recorder()
+    call = bd._calls.Call("hzp_gather_shard", ctypes.cast(rec.hzp_gather_shard, ctypes.c_void_p).value, lambda: None, bd._check,
+                          ctypes.Array, ctypes.c_void_p, bd.AdamW)
+    gone = weakref.ref(call)
+    del call
+    assert gone() is None
+    with pytest.raises(TypeError):
+        bd._calls.Call("hzp_gather_shard", 1, print, bd._check, ctypes.Array, ctypes.c_void_p, bd.AdamW)
