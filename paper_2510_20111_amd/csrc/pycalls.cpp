@@ -142,17 +142,26 @@ PyObject *name_handle, *name_data_ptr, *name_cuda_stream;      // interned
 bool memory_of(PyObject *o, void **address)
 {
     Py_buffer view;
-    if (PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) != 0) return false;
+    if (PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) != 0) {
+        PyErr_Clear();
+        return false;
+    }
     *address = view.buf;
     PyBuffer_Release(&view);
     return true;
 }
 
+// The functions from here to convert_all return false where the binding function has to look at the arguments, and also,
+// with the error set, where an argument's own code (data_ptr(), cuda_stream) raised: then that is the call's error.
 bool word_of(PyObject *o, uint64_t most, uint64_t *out)
 {
     if (!PyLong_CheckExact(o)) return false;
     *out = PyLong_AsUnsignedLongLong(o);
-    return !(*out == (uint64_t)-1 && PyErr_Occurred()) && *out <= most;
+    if (*out == (uint64_t)-1 && PyErr_Occurred()) {     // negative or too long
+        PyErr_Clear();
+        return false;
+    }
+    return *out <= most;
 }
 
 bool address_of(PyObject *o, uint64_t *out)
@@ -175,7 +184,10 @@ bool convert(const CallObject *self, const Arg &arg, PyObject *o, Value *v, void
     switch (arg.kind) {
     case kPlan: {
         PyObject *const handle = PyObject_GetAttr(o, name_handle);
-        if (!handle) return false;
+        if (!handle) {
+            if (PyErr_ExceptionMatches(PyExc_AttributeError)) PyErr_Clear();
+            return false;
+        }
         void *at = nullptr;
         const bool ok = (PyObject *)Py_TYPE(handle) == self->void_p && memory_of(handle, &at);
         if (ok) std::memcpy(&v->word, at, sizeof v->word);
@@ -237,7 +249,7 @@ bool convert(const CallObject *self, const Arg &arg, PyObject *o, Value *v, void
     return false;
 }
 
-// Fills the values of all arguments; false where the binding function has to look at them.
+// Fills the values of all arguments.
 bool convert_all(const CallObject *self, PyObject *const *args, Py_ssize_t n, PyObject *kwnames, Value *v, void **listed)
 {
     const Function &f = *self->function;
@@ -287,10 +299,8 @@ PyObject *call(PyObject *object, PyObject *const *args, size_t nargsf, PyObject 
     CallObject *const self = reinterpret_cast<CallObject *>(object);
     Value v[kMostArgs];
     void *listed[kMostListed];
-    if (!as_made(self) || !convert_all(self, args, PyVectorcall_NARGS(nargsf), kwnames, v, listed)) {
-        PyErr_Clear();
-        return PyObject_Vectorcall(self->otherwise, args, nargsf, kwnames);
-    }
+    if (!as_made(self) || !convert_all(self, args, PyVectorcall_NARGS(nargsf), kwnames, v, listed))
+        return PyErr_Occurred() ? nullptr : PyObject_Vectorcall(self->otherwise, args, nargsf, kwnames);
     hzp_status_t st;
     Py_BEGIN_ALLOW_THREADS
     st = self->function->call(self->entry, v);

@@ -260,3 +260,60 @@ def test_calls_are_let_go():
     assert gone() is None
     with pytest.raises(TypeError):
         bd._calls.Call("hzp_gather_shard", 1, print, bd._check, ctypes.Array, ctypes.c_void_p, bd.AdamW)
+
+
+class Counted(Tensor):
+    """A tensor that counts how often its address was asked for, and may refuse to give it."""
+
+    def __init__(self, address, error=None):
+        super().__init__(address)
+        self.asked, self.error = 0, error
+
+    def data_ptr(self):
+        self.asked += 1
+        if self.error is not None:
+            error, self.error = self.error, None        # the first time only
+            raise error
+        return self.address
+
+
+def counted(name, n=3):
+    """Arguments of a plain call, with tensors for all device buffers; and these tensors."""
+    values = {p: x for p, x in next(forms(name)).items() if p != "stream"}
+    tensors = []
+    for p in values:
+        if p in ("grad_slices", "shard_ptrs", "owner_ptrs", "master", "m", "v", "param_out") or (p == "bucket_out" and name == "hzp_gather_layers"):
+            values[p] = [Counted((len(tensors) + 1 + i) << 12) for i in range(n)]
+            tensors += values[p]
+        elif p in ("out_f32", "scalars", "shard_out", "bucket_out"):
+            values[p] = Counted(1 << 40)
+            tensors.append(values[p])
+    return values, tensors
+
+
+def native(monkeypatch, name, function=None):
+    """(recorder, the native call with it in the library's place)"""
+    rec = Recorder()
+    monkeypatch.setattr(bd, "_L", Spy(rec, monkeypatch))
+    return rec, bd._native_call(function or getattr(bd, name).__wrapped__)
+
+
+@pytest.mark.parametrize("name", NAMES)
+@pytest.mark.parametrize("error", [KeyboardInterrupt, SystemExit, TimeoutError, RuntimeError, AttributeError])
+def test_errors_of_the_arguments_are_not_lost(monkeypatch, name, error):
+    """What an argument's own code raises ends the call, as it does in the binding function."""
+    rec, call = native(monkeypatch, name)
+    n = len(counted(name)[1])
+    for at in range(n):
+        for f in (call, call.__wrapped__):
+            values, tensors = counted(name)
+            tensors[at].error = error("at %d" % at)
+            with pytest.raises(error, match="^at %d$" % at):
+                f(**values, stream=7)
+            assert [t.asked for t in tensors] == [1] * (at + 1) + [0] * (n - at - 1)
+    values, tensors = counted(name)
+    raising = type("S", (), {"cuda_stream": property(lambda self: (_ for _ in ()).throw(error("stream")))})()
+    for f in (call, call.__wrapped__):
+        with pytest.raises(error):
+            f(**values, stream=raising)
+    assert not rec.got
