@@ -243,7 +243,7 @@ def ptr_array(items):
 def _native_call(function):
     """The same call made from native code; `function` converts (or refuses) the arguments that are not recognised there."""
     entry = ctypes.cast(getattr(_L, function.__name__), ctypes.c_void_p).value
-    return _calls.Call(function.__name__, entry, function, _check, ctypes.Array, ctypes.c_void_p, AdamW)
+    return _calls.Call(function.__name__, entry, function, _check, ctypes.Array, ctypes.c_void_p, AdamW, _stream)
 
 
 def _stream(stream):

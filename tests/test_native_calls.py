@@ -298,6 +298,56 @@ def native(monkeypatch, name, function=None):
     return rec, bd._native_call(function or getattr(bd, name).__wrapped__)
 
 
+def elsewhere(name):
+    def function(*args, **kwargs):
+        raise AssertionError("went to the binding function")
+    function.__name__ = name
+    return function
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_the_current_stream_is_looked_up_in_native_calls(monkeypatch, name):
+    """A call without a stream takes torch's current one, and asks every tensor for its address once."""
+    monkeypatch.setattr("torch.cuda.current_stream", lambda: Stream())
+    rec, call = native(monkeypatch, name, elsewhere(name))
+    for extra in ({}, {"stream": None}):
+        values, tensors = counted(name)
+        call(**values, **extra)
+        assert [t.asked for t in tensors] == [1] * len(tensors) and len(tensors) > 2
+    assert [got[1][-1] for got in rec.got] == [Stream.cuda_stream] * 2
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_addresses_are_asked_for_once(monkeypatch, name):
+    """Whatever sends a call to the binding function is seen before a tensor is asked: numbers of other types, longer lists, no stream
+    (there is no GPU here: looking it up fails as it does in the binding function)."""
+    rec, call = native(monkeypatch, name)
+    def error(f, values):
+        try:
+            f(**values)
+        except Exception as e:      # noqa: BLE001
+            return type(e), str(e)
+    monkeypatch.setattr("torch.cuda.current_stream", lambda: 1 // 0)
+    got = []
+    for f in (call, call.__wrapped__):
+        values, tensors = counted(name)
+        got.append((error(f, values), [t.asked for t in tensors]))
+    assert got[0] == got[1] and got[0][0][0] is ZeroDivisionError and set(got[0][1]) == {1}
+    parameters = inspect.signature(call).parameters
+    others = [{}] + [{p: x} for p, x in (("scale", 1), ("accumulate", 1), ("cls", True), ("grad_dtype", True), ("n_shards", True), ("n_owners", True))
+                     if p in parameters]
+    for other in others:
+        values, tensors = counted(name, 3 if other else 600)
+        call(**dict(values, stream=7, **other) if not set(other) & set(values) else dict(values, stream=7) | other)
+        assert [t.asked for t in tensors] == [1] * len(tensors), other
+    assert len(rec.got) == len(others)
+    for values in ({p: x for p, x in values.items() if p != "plan"}, dict(values, no_such_argument=1), dict(values, stream=object())):
+        tensors = [t for x in values.values() if isinstance(x, list) for t in x]
+        before = [t.asked for t in tensors]
+        assert error(call, values)[0] in (TypeError, AttributeError)
+        assert [t.asked for t in tensors] in (before, [n + 1 for n in before])
+
+
 @pytest.mark.parametrize("name", NAMES)
 @pytest.mark.parametrize("error", [KeyboardInterrupt, SystemExit, TimeoutError, RuntimeError, AttributeError])
 def test_errors_of_the_arguments_are_not_lost(monkeypatch, name, error):
