@@ -3,7 +3,7 @@
 Function names and argument order follow ``include/hzp.h``.  Device buffers may be given as
 torch tensors (their ``data_ptr()`` is taken) or as integer addresses; a stream may be a
 ``torch.cuda.Stream``, an integer ``hipStream_t`` or None (torch's current stream).
-There is no fallback: if ``libhzp.so`` and ``_calls.so`` have not been built, importing this module fails.
+There is no fallback: if ``libhzp.so`` and the ``_calls`` module have not been built, importing this module fails.
 """
 import ctypes
 import importlib.machinery
@@ -203,9 +203,10 @@ _L = _load()
 
 
 def _load_calls():
-    path = os.path.join(_HERE, "_calls.so")
+    # (the suffix names the interpreter that it was built for: another one's is not found)
+    path = os.path.join(_HERE, "_calls" + importlib.machinery.EXTENSION_SUFFIXES[0])
     if not os.path.exists(path):
-        raise ImportError("_calls.so is not built: run `python paper_2510_20111_amd/build.py` (or __graft_entry__.build()) first")
+        raise ImportError(os.path.basename(path) + " is not built: run `python paper_2510_20111_amd/build.py` (or __graft_entry__.build()) first")
     loader = importlib.machinery.ExtensionFileLoader("_calls", path)
     module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_calls", loader))
     loader.exec_module(module)

@@ -1,4 +1,5 @@
 """Build step of libhzp: one hipcc invocation for gfx950 (cross-compiles without a GPU), and of the binding's Python module."""
+import importlib.machinery
 import os
 import subprocess
 import sysconfig
@@ -7,11 +8,11 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 SOURCES = ["planner.cpp", "api.cpp", "scheduler.cpp", "kernels.hip"]
 LIB = os.path.join(HERE, "libhzp.so")
-CALLS = os.path.join(HERE, "_calls.so")
+CALLS = os.path.join(HERE, "_calls" + importlib.machinery.EXTENSION_SUFFIXES[0])       # of this interpreter
 
 
 def build(verbose=False):
-    """Compile csrc/ into paper_2510_20111_amd/libhzp.so and _calls.so.  Always recompiles."""
+    """Compile csrc/ into paper_2510_20111_amd/libhzp.so and the _calls module.  Always recompiles."""
     calls = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I" + sysconfig.get_paths()["include"],
              "-I" + os.path.join(ROOT, "include"), os.path.join(HERE, "csrc", "pycalls.cpp"), "-o", CALLS]
     subprocess.run(calls, check=True)

@@ -3,9 +3,12 @@ arguments that either accepts, and refuse what those refuse."""
 import copy
 import ctypes
 import functools
+import importlib.machinery
 import inspect
 import itertools
+import os
 import pickle
+import shutil
 import weakref
 
 import pytest
@@ -367,3 +370,16 @@ def test_errors_of_the_arguments_are_not_lost(monkeypatch, name, error):
         with pytest.raises(error):
             f(**values, stream=raising)
     assert not rec.got
+
+
+def test_only_a_module_built_for_this_interpreter_is_loaded(monkeypatch, tmp_path):
+    """The module reads the interpreter's own structures, so one that was built for another must not be taken for it."""
+    suffix = importlib.machinery.EXTENSION_SUFFIXES[0]
+    assert "cpython" in suffix and bd._calls.__file__.endswith(os.sep + "_calls" + suffix)
+    monkeypatch.setattr(bd, "_HERE", str(tmp_path))
+    for other in ("_calls.so", "_calls.cpython-399-x86_64-linux-gnu.so", "_calls.abi3.so"):
+        (tmp_path / other).write_bytes(b"not for this interpreter")
+    with pytest.raises(ImportError, match="is not built"):
+        bd._load_calls()
+    shutil.copy(bd._calls.__file__, tmp_path)
+    assert bd._load_calls().Call
