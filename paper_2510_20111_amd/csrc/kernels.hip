@@ -185,16 +185,16 @@ __device__ __forceinline__ void pin(T &x, Rest &...rest)
 }
 
 // Left-to-right fp32 sum of R contributions, ((g0 + g1) + g2) + ..., at most `MOST` of them in flight, for
-// Q quads; slice[r] + shift is contribution r, and `at` holds the first chunk's pointers.  meanwhile() runs when the first chunk
-// is requested.
-template <uint32_t R, uint32_t MOST, bool G32, int Q, class Meanwhile>
-__device__ __forceinline__ void sum_contributions(uint64_t (&at)[MOST], const uint64_t *slice, int64_t shift,
+// Q quads; slice(r) + shift is contribution r, and `at` holds the first chunk's pointers.  meanwhile() runs when the first chunk
+// is requested.  Where the chunks are not all of one size the larger ones are the first (LARGER_FIRST) or the last.
+template <uint32_t R, uint32_t MOST, bool G32, int Q, bool LARGER_FIRST, class Slice, class Meanwhile>
+__device__ __forceinline__ void sum_contributions(uint64_t (&at)[MOST], Slice slice, int64_t shift,
                                                   const uint32_t (&quad)[Q], float (&s)[Q][4], Meanwhile meanwhile)
 {
-    constexpr uint32_t C = chunk_of(R, MOST), CHUNKS = (R + C - 1) / C;
+    constexpr uint32_t C = chunk_of(R, MOST), CHUNKS = (R + C - 1) / C, UP = LARGER_FIRST ? CHUNKS - 1 : 0;
 #pragma unroll
     for (uint32_t k = 0; k < CHUNKS; ++k) {
-        const uint32_t base = k * R / CHUNKS, end = (k + 1) * R / CHUNKS, next = (k + 2) * R / CHUNKS;
+        const uint32_t base = (k * R + UP) / CHUNKS, end = ((k + 1) * R + UP) / CHUNKS, next = ((k + 2) * R + UP) / CHUNKS;
         GradQuad<G32> g[C][Q];
 #pragma unroll
         for (uint32_t c = 0; c < C; ++c)
@@ -203,7 +203,7 @@ __device__ __forceinline__ void sum_contributions(uint64_t (&at)[MOST], const ui
                 if (base + c < end) g[c][q].load(at[c] + shift, quad[q]);
 #pragma unroll
         for (uint32_t c = 0; c < C; ++c)
-            if (k + 1 < CHUNKS && end + c < next) at[c] = slice[end + c];
+            if (k + 1 < CHUNKS && end + c < next) at[c] = slice(end + c);
         __builtin_amdgcn_sched_barrier(0);      // the whole chunk is requested (and the next one's pointers) before its first add,
         if (base == 0) meanwhile();
 #pragma unroll
@@ -226,7 +226,13 @@ __device__ __forceinline__ void sum_contributions(uint64_t (&at)[MOST], const ui
 // Standalone reduction (bit-exact with the scalar definition: fixed order, no contraction).
 // ---------------------------------------------------------------------------------------
 struct ReduceRest {
-    uint64_t g[HZP_MAX_REPLICAS];       // all pointers; the first four are arguments of their own
+    uint64_t g[HZP_MAX_REPLICAS];       // all pointers
+};
+struct ReduceArgs {
+    uint64_t out;
+    uint32_t nquad;                     // 4-element quads in the slice
+    float scale;
+    ReduceRest rest;
 };
 
 // The forms of a launch: contributions in flight (chunk), quads per lane, and whether the sum that is accumulated onto is requested
@@ -240,25 +246,14 @@ constexpr uint32_t reduce_chunk(uint32_t R, ReduceForm form)
 // occupancy (25 M elements: 5.89 TB/s; with two quads 6.22).
 constexpr int reduce_quads(uint32_t R, bool g32, ReduceForm form) { return form == kReduceNarrow || (R == 1 && !g32) ? 2 : 1; }
 
-// What the first requests need, the first four pointers and the output (out[1]: number of quads, scale), is in scalar registers when a
-// wavefront starts: leading arguments that are no structs arrive there (the build asks for 14 words; vectors, because the host spends 15 ns
-// on every argument).  With all of it read from the argument block, us: bf16 R = 4 / 8 of 2.1 M elements 5.8 / 8.2 (now 5.5 / 8.1), R = 32
-// of 0.5 M 7.4 (6.9), R = 8 of 25 M 76.6 (75.8); fp32 R = 4 accumulating, 1 / 6.3 M 6.0 / 25.1 (5.8 / 25.0), R = 16 of 0.26 M, the one that
-// lost, 5.0 (5.3: its later pointers now queue behind the first requests).  Filling the registers costs the device 0.15 us, which shows only
-// where a graph replays reductions of 0.2 M elements and less (1.85, now 2.0).
-template <uint32_t R, bool G32, bool ACC, ReduceForm FORM>
-__global__ __launch_bounds__(kWave) void reduce_kernel(const u64x4 g, const u64x2 o, const ReduceRest rest)
+template <uint32_t R, bool G32, bool ACC, ReduceForm FORM, uint32_t CHUNK, class Slice>
+__device__ __forceinline__ void reduce(uint64_t out, uint32_t nquad, float scale, uint64_t (&at)[CHUNK], Slice slice)
 {
 #pragma clang fp contract(off)
     constexpr int Q = reduce_quads(R, G32, FORM);
-    constexpr uint32_t CHUNK = reduce_chunk(R, FORM);
+    // (in chunks of 2 a first chunk of one loses: fp32 R = 9 / 13 of 1.5 M elements 10.3 / 13.8 us, 10.0 / 13.5 with the larger ones first; in longer
+    // chunks it gains: R = 5 / 10 accumulating of 7.4 M 33.0 / 55.7, 33.5 / 56.8)
     constexpr bool LATE = FORM == kReduceNarrow;
-    const uint64_t out = o[0];
-    const uint32_t nquad = (uint32_t)o[1];
-    const float scale = __uint_as_float((uint32_t)(o[1] >> 32));
-    uint64_t at[CHUNK];
-#pragma unroll
-    for (uint32_t c = 0; c < CHUNK; ++c) at[c] = c >= R ? 0 : c < 4 ? g[c] : rest.g[c];
     uint32_t q0[Q], quad[Q];
     f32x4 t[Q];
 #pragma unroll
@@ -268,7 +263,7 @@ __global__ __launch_bounds__(kWave) void reduce_kernel(const u64x4 g, const u64x
         if (ACC && !LATE) t[q] = ld_stream<f32x4>(out, quad[q]);
     }
     float s[Q][4];
-    sum_contributions<R, CHUNK, G32>(at, rest.g, 0, quad, s, [] {});
+    sum_contributions<R, CHUNK, G32, Q, LATE>(at, slice, 0, quad, s, [] {});
 #pragma unroll
     for (int q = 0; q < Q; ++q)
         if (ACC && LATE) t[q] = ld_stream<f32x4>(out, quad[q]);
@@ -281,6 +276,35 @@ __global__ __launch_bounds__(kWave) void reduce_kernel(const u64x4 g, const u64x
         }
         if (q0[q] < nquad) st_writethrough(out, quad[q] * 16u, t[q]);
     }
+}
+
+// What the first requests need, the first four pointers and the output (o[1]: number of quads, scale), is in scalar registers when a
+// wavefront starts: leading arguments that are no structs arrive there (the build asks for 14 words; vectors, because the host spends 15 ns
+// on every argument).  With all of it read from the argument block, us: bf16 R = 4 / 8 of 2.1 M elements 5.8 / 8.2 (here 5.5 / 8.1), R = 32
+// of 0.5 M 7.4 (6.9), R = 8 of 25 M 76.6 (75.8); fp32 R = 4 accumulating, 1 / 6.3 M 6.0 / 25.1 (5.8 / 25.0).
+template <uint32_t R, bool G32, bool ACC, ReduceForm FORM>
+__global__ __launch_bounds__(kWave) void reduce_kernel(const u64x4 g, const u64x2 o, const ReduceRest rest)
+{
+    constexpr uint32_t CHUNK = reduce_chunk(R, FORM);
+    uint64_t at[CHUNK];
+#pragma unroll
+    for (uint32_t c = 0; c < CHUNK; ++c) at[c] = c >= R ? 0 : c < 4 ? g[c] : rest.g[c];
+    reduce<R, G32, ACC, FORM>(o[0], (uint32_t)o[1], __uint_as_float((uint32_t)(o[1] >> 32)), at,
+                              [&](uint32_t r) { return r < 4 ? g[r] : rest.g[r]; });
+}
+
+// The same with all of it read from the argument block in one round of scalar loads, for the launches of reduce_from_block().
+template <uint32_t R, bool G32, bool ACC, ReduceForm FORM>
+__global__ __launch_bounds__(kWave) void reduce_block_kernel(const ReduceArgs a)
+{
+    constexpr uint32_t CHUNK = reduce_chunk(R, FORM);
+    uint64_t out = a.out, at[CHUNK];
+    uint32_t nquad = a.nquad;
+    float scale = a.scale;
+#pragma unroll
+    for (uint32_t c = 0; c < CHUNK; ++c) at[c] = c < R ? a.rest.g[c] : 0;
+    pin(out, at[0], at[1], at[CHUNK > 2 ? 2 : 0], at[CHUNK > 2 ? 3 : 0], nquad, scale);
+    reduce<R, G32, ACC, FORM>(out, nquad, scale, at, [&](uint32_t r) { return a.rest.g[r]; });
 }
 
 // ---------------------------------------------------------------------------------------
@@ -491,7 +515,7 @@ __device__ __forceinline__ void fused_adamw(const FusedLead lead, const Args &a)
     __builtin_amdgcn_sched_barrier(0);
     if (FORM == kSearched && lookup) runs.find(pos);
     float g[1][4];
-    sum_contributions<R, CHUNK, G32>(at, slice, shift * (G32 ? 16 : 8), quads, g, [&] {
+    sum_contributions<R, CHUNK, G32, 1, false>(at, [slice](uint32_t r) { return slice[r]; }, shift * (G32 ? 16 : 8), quads, g, [&] {
         if (FORM == kOne)       // needed last, but read by now
             pin(OUT, h.lr, h.beta1, h.beta2, h.one_minus_beta1, h.one_minus_beta2, h.eps, h.weight_decay, h.grad_scale, h.inv_bc1, h.inv_bc2);
     });
@@ -819,10 +843,24 @@ static hzp_status_t start(const char *who, void (*kernel)(P...), dim3 grid, dim3
 // puts a wait between any two of them), and all of a launch's pointers arrive in one round of scalar loads.
 // (the other forms are for more than 8 contributions)
 typedef void (*ReduceKernel)(u64x4, u64x2, ReduceRest);
+typedef void (*ReduceBlockKernel)(ReduceArgs);
 template <bool G32, bool ACC, ReduceForm FORM, size_t... I>
 static constexpr std::array<ReduceKernel, sizeof...(I)> reduce_kernels(std::index_sequence<I...>)
 {
     return {reduce_kernel<I + 1, G32, ACC, I < 8 ? kReducePlain : FORM>...};
+}
+template <uint32_t R, bool G32, bool ACC, ReduceForm FORM>
+static constexpr ReduceBlockKernel reduce_block_kernel_of()
+{
+    if constexpr (R <= 8 && FORM == kReduceNarrow)
+        return nullptr;
+    else
+        return reduce_block_kernel<R, G32, ACC, R <= 8 ? kReducePlain : FORM>;
+}
+template <bool G32, bool ACC, ReduceForm FORM, size_t... I>
+static constexpr std::array<ReduceBlockKernel, sizeof...(I)> reduce_block_kernels(std::index_sequence<I...>)
+{
+    return {reduce_block_kernel_of<I + 1, G32, ACC, FORM>()...};
 }
 typedef void (*FusedKernel)(FusedArgs);
 typedef void (*FusedOneKernel)(u64x4, u64x2, uint64_t, FusedOneArgs);
@@ -889,6 +927,20 @@ static ReduceForm reduce_form(bool g32, uint32_t R, uint64_t groups)
     return in_flight > (g32 ? 48u << 10 : 40u << 10) && groups <= (g32 ? 8192u : 10240u) ? kReduceNarrow : kReducePlain;
 }
 
+// Launches whose wavefronts read their arguments from the block.
+// So short that the launch's own time on the device is all there is (1.9 us in a graph): filling the registers adds 0.15 us to it.  With registers /
+// with the block, graph replay: bf16 R = 1 of 16 k / 0.26 / 0.5 M elements 2.02 / 1.88, 2.00 / 1.92, 2.14 / 2.09 us, R = 4 of 64 / 131 / 262 k
+// 2.01 / 1.88, 1.99 / 1.90, 2.33 / 2.33, R = 9 of 33 / 66 k 1.99 / 1.89, 1.99 / 1.92; fp32 R = 1 of 0.26 / 0.46 / 0.5 M 2.08 / 2.03, 2.56 / 2.59,
+// 2.67 / 2.60.  (An accumulating launch takes longer: even, or up to 2 % less with registers.)
+// And bf16 in chunks of 2, whose wavefronts all start at once and ask for more than the memory serves in order; the round of scalar loads
+// spreads them and brings the later pointers along (2.1 M elements R = 9 / 13 / 16 / 32 8.95 / 11.3 / 13.1 / 23.0 us, with the block 8.6 /
+// 10.9 / 12.7 / 22.6; fp32 1.1 / 2.1 M the other way round, 2 and 0 %).
+static bool reduce_from_block(bool g32, uint32_t R, ReduceForm form, uint64_t n, int accumulate)
+{
+    const uint32_t es = g32 ? 4u : 2u;
+    return form == kReduceNarrow ? !g32 : !accumulate && n * R * es <= (R * es <= 4 ? 2u << 20 : 1250000u);
+}
+
 // Most bytes one launch of the reduction moves (0.45 / 0.9 ms); with more streams a drift of the XCDs (below) costs more.  285 M elements
 // in 1 / 2 / 4 / 8 launches: bf16 R = 16 (10.3 GB) 6.53 / 6.57 / 6.59 / 6.58 TB/s, fp32 R = 16 accumulating (20.6 GB) 6.72 / 6.78 /
 // 6.84 / 6.85, bf16 R = 8 (5.7 GB) 6.89 / 6.88 / 6.82 / 6.70, R = 4 (3.4 GB) 6.84 / 6.82 / 6.80 / 6.68.
@@ -901,28 +953,41 @@ hzp_status_t launch_reduce(bool g32, const void *const *slices, uint32_t R, uint
     const uint32_t es = g32 ? 4u : 2u;
     constexpr std::make_index_sequence<HZP_MAX_REPLICAS> all;
     static constexpr std::array<ReduceKernel, HZP_MAX_REPLICAS> kernels[2][2][3] = {
-        {{reduce_kernels<false, false, kReducePlain>(all), reduce_kernels<false, false, kReduceFew>(all), reduce_kernels<false, false, kReduceNarrow>(all)},
-         {reduce_kernels<false, true, kReducePlain>(all), reduce_kernels<false, true, kReduceFew>(all), reduce_kernels<false, true, kReduceNarrow>(all)}},
+        {{reduce_kernels<false, false, kReducePlain>(all), reduce_kernels<false, false, kReduceFew>(all), {}},
+         {reduce_kernels<false, true, kReducePlain>(all), reduce_kernels<false, true, kReduceFew>(all), {}}},
         {{reduce_kernels<true, false, kReducePlain>(all), reduce_kernels<true, false, kReduceFew>(all), reduce_kernels<true, false, kReduceNarrow>(all)},
          {reduce_kernels<true, true, kReducePlain>(all), reduce_kernels<true, true, kReduceFew>(all), reduce_kernels<true, true, kReduceNarrow>(all)}}};
+    static constexpr std::array<ReduceBlockKernel, HZP_MAX_REPLICAS> narrow_block[2] = {reduce_block_kernels<false, false, kReduceNarrow>(all),
+                                                                                        reduce_block_kernels<false, true, kReduceNarrow>(all)};
+    static constexpr std::array<ReduceBlockKernel, HZP_MAX_REPLICAS> short_block[2] = {reduce_block_kernels<false, false, kReduceFew>(all),
+                                                                                       reduce_block_kernels<true, false, kReduceFew>(all)};
     // Launches of about equal length; over a longer one the XCDs drift apart, as in the update below.
     const uint64_t launches = (n * (R * es + (accumulate ? 8u : 4u)) + most_reduce_bytes(R) - 1) / most_reduce_bytes(R);
     constexpr uint64_t kTwoGroups = 8 * kGroupQuads;        // what a wavefront with two quads per lane takes
     const uint64_t most = ((n + launches - 1) / launches + kTwoGroups - 1) / kTwoGroups * kTwoGroups;
     for (uint64_t first = 0; first < n; first += most) {
         const uint64_t here = std::min(n - first, most);
-        ReduceRest a;               // a kernel reads its R pointers, and of the first four whatever there is
-        for (uint32_t r = 0; r < R; ++r) a.g[r] = reinterpret_cast<uint64_t>(slices[r]) + first * es;
-        for (uint32_t r = R; r < 4; ++r) a.g[r] = 0;
         const uint32_t nquad = (uint32_t)(here / 4);
-        uint32_t scale_bits;
-        std::memcpy(&scale_bits, &scale, sizeof scale_bits);
         const ReduceForm form = reduce_form(g32, R, (nquad + kGroupQuads - 1) / kGroupQuads);
         const uint32_t quads = kGroupQuads * reduce_quads(R, g32, form);        // to a wavefront
-        const unsigned waves = form == kReduceNarrow ? 0 : reduce_waves(g32, R, here, accumulate);
-        const hzp_status_t st = start("hzp_reduce_shard", kernels[g32][accumulate != 0][form][R - 1], dim3((nquad + quads - 1) / quads), dim3(kWave),
-                                      lds_for(waves), stream, u64x4{a.g[0], a.g[1], a.g[2], a.g[3]},
-                                      u64x2{reinterpret_cast<uint64_t>(out + first), nquad | (uint64_t)scale_bits << 32}, a);
+        const dim3 grid((nquad + quads - 1) / quads), block(kWave);
+        const unsigned lds = lds_for(form == kReduceNarrow ? 0 : reduce_waves(g32, R, here, accumulate));
+        ReduceArgs a;               // a kernel reads its R pointers, and of the first four whatever there is
+        a.out = reinterpret_cast<uint64_t>(out + first);
+        a.nquad = nquad;
+        a.scale = scale;
+        uint64_t *const g = a.rest.g;
+        for (uint32_t r = 0; r < R; ++r) g[r] = reinterpret_cast<uint64_t>(slices[r]) + first * es;
+        for (uint32_t r = R; r < 4; ++r) g[r] = 0;
+        hzp_status_t st;
+        if (reduce_from_block(g32, R, form, here, accumulate)) {
+            st = start("hzp_reduce_shard", form == kReduceNarrow ? narrow_block[accumulate != 0][R - 1] : short_block[g32][R - 1], grid, block, lds, stream, a);
+        } else {
+            uint32_t scale_bits;
+            std::memcpy(&scale_bits, &scale, sizeof scale_bits);
+            st = start("hzp_reduce_shard", kernels[g32][accumulate != 0][form][R - 1], grid, block, lds, stream, u64x4{g[0], g[1], g[2], g[3]},
+                       u64x2{a.out, nquad | (uint64_t)scale_bits << 32}, a.rest);
+        }
         if (st != HZP_OK) return st;
     }
     return HZP_OK;

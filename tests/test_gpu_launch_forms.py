@@ -424,3 +424,56 @@ def test_reduction_forms_at_their_edges(R, g32, few, fours, twos, acc):
             call()
             torch.cuda.synchronize()
             assert torch.equal(out[:n], want[:n]) and bool((out[n:] == 0.5).all())
+
+
+def in_order_sum(g, acc):
+    """0.3 times the left-to-right fp32 sum, added to 0.5 where `acc`."""
+    want = g[0].to(torch.float32, copy=True)
+    for x in g[1:]:
+        want += x
+    want *= 0.3
+    return want + 0.5 if acc else want
+
+
+# The longest launches, in bytes of contributions, whose arguments are all read from the block; longer ones, and accumulating ones of
+# any length, have other kernels.
+@pytest.mark.parametrize("R,g32", [(1, False), (2, False), (3, False), (4, False), (8, False), (9, False), (13, False), (32, False),
+                                   (1, True), (2, True), (5, True), (8, True), (11, True), (32, True)])
+def test_short_reductions_read_their_arguments_from_the_block(R, g32):
+    dt, gd, es = (torch.float32, hzp.HZP_GRAD_F32, 4) if g32 else (torch.bfloat16, hzp.HZP_GRAD_BF16, 2)
+    longest = (2 << 20 if R * es <= 4 else 1250000) // (R * es) // 8 * 8
+    torch.manual_seed(R)
+    g = [torch.empty(longest + 8, dtype=dt, device=DEV).normal_() for _ in range(R)]
+    kernels = []
+    for n in (8, 256, longest, longest + 8):
+        for acc in (False, True):
+            print(R, g32, n, acc, flush=True)
+            plan, out = reduce_plan(n), torch.full((n + 64,), 0.5, device=DEV)
+
+            def call():
+                hzp.hzp_reduce_shard(plan, 0, 0, 1, 0, [x[:n] for x in g], 0.3, acc, out[:n], grad_dtype=gd)
+            (_, _, kernel), = launches_of(call)
+            kernels.append(kernel)
+            call()
+            torch.cuda.synchronize()
+            assert torch.equal(out[:n], in_order_sum([x[:n] for x in g], acc)) and bool((out[n:] == 0.5).all())
+    block, registers, accumulating = kernels[0], kernels[6], kernels[1]
+    assert kernels == [block, accumulating] * 3 + [registers, accumulating] and len({block, registers, accumulating}) == 3
+
+
+@pytest.mark.parametrize("R", [5, 7, 10, 11, 13, 14, 19, 23, 29, 31])
+@pytest.mark.parametrize("g32", [False, True])
+def test_reduction_in_chunks_of_different_sizes(R, g32):
+    """Numbers of contributions that are no multiple of a chunk, in each form of a launch (up to 2048 groups, all resident, chunks of 2,
+    capped): the sum in order, bit for bit."""
+    dt, gd = (torch.float32, hzp.HZP_GRAD_F32) if g32 else (torch.bfloat16, hzp.HZP_GRAD_BF16)
+    torch.manual_seed(R)
+    g = [torch.empty(12000 * 256, dtype=dt, device=DEV).normal_() for _ in range(R)]
+    for groups in (2048, 2900, 7500, 10000, 12000):
+        n = groups * 256 - 8
+        for acc in (False, True):
+            print(R, g32, n, acc, flush=True)
+            plan, out = reduce_plan(n), torch.full((n + 64,), 0.5, device=DEV)
+            hzp.hzp_reduce_shard(plan, 0, 0, 1, 0, [x[:n] for x in g], 0.3, acc, out[:n], grad_dtype=gd)
+            torch.cuda.synchronize()
+            assert torch.equal(out[:n], in_order_sum([x[:n] for x in g], acc)) and bool((out[n:] == 0.5).all())
