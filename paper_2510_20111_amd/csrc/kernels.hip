@@ -135,13 +135,22 @@ constexpr uint32_t few_chunk(uint32_t R, uint32_t chunk) { return R > 8 ? 16u : 
 //   too much (bf16 R = 12 / 24 of 0.66 M elements 7.6 / 9.9 us, with chunks of 8 7.9 / 10.2; fp32 R = 4 6.1, with chunks of 4 6.4).
 //   kFew: all resident, and so few that latency counts.
 enum ChunkClass { kFew, kMid, kLarge };
-constexpr uint32_t fused_chunk(bool g32, uint32_t R, ChunkClass c)
+constexpr uint32_t fused_most(bool g32, uint32_t R, ChunkClass c)
 {
     const uint32_t mid = g32 ? 3u : 4u;
     if (c == kFew) return few_chunk(R, mid);
     if (c == kMid || (g32 ? R > 16 : R > 28)) return mid;
     return g32 || R <= 4 ? 4u : R <= 8 ? R : 8u;
 }
+
+// Contributions in the largest chunk: R spread evenly over the fewest chunks of at most `most`.
+constexpr uint32_t chunk_of(uint32_t R, uint32_t most)
+{
+    const uint32_t chunks = (R + most - 1) / most;
+    return (R + chunks - 1) / chunks;
+}
+// (a kernel is made for the chunk and not for the most, so that classes that come to the same share one)
+constexpr uint32_t fused_chunk(bool g32, uint32_t R, ChunkClass c) { return chunk_of(R, fused_most(g32, R, c)); }
 
 // Four gradient elements of one contribution, widened to fp32 on access.
 template <bool G32>
@@ -162,13 +171,6 @@ struct GradQuad<true> {
     __device__ __forceinline__ void load(uint64_t base, uint32_t quad) { a = ld_stream<f32x4>(base, quad); }
     __device__ __forceinline__ float get(int e) const { return a[e]; }
 };
-
-// Contributions in the largest chunk: R spread evenly over the fewest chunks of at most `most`.
-constexpr uint32_t chunk_of(uint32_t R, uint32_t most)
-{
-    const uint32_t chunks = (R + most - 1) / most;
-    return (R + chunks - 1) / chunks;
-}
 
 // Pins uniform values: they are read (from the arguments) no later than here, and not where they are used, with
 // nothing to hide the read behind.
@@ -478,7 +480,7 @@ __device__ __forceinline__ void fused_adamw(const FusedLead lead, const Args &a)
         for (uint32_t c = 0; c < CHUNK; ++c) at[c] = c < R ? slice[c] : 0;
         h = a.scalars;
         scalars_dev = reinterpret_cast<uint64_t>(a.scalars_dev);
-        pin(P, M, V, OUT, extent, decay, at[0], at[1], at[2], at[CHUNK > 3 ? 3 : 2], scalars_dev);
+        pin(P, M, V, OUT, extent, decay, at[0], at[CHUNK > 1 ? 1 : 0], at[CHUNK > 2 ? 2 : 0], at[CHUNK > 3 ? 3 : 0], scalars_dev);
         pin(h.lr, h.beta1, h.beta2, h.one_minus_beta1, h.one_minus_beta2, h.eps, h.weight_decay, h.grad_scale, h.inv_bc1, h.inv_bc2);
         groups = (uint32_t)extent - before;
         nquad = (uint32_t)(extent >> 32);
@@ -1106,7 +1108,7 @@ static ChunkClass fused_class(bool g32, uint32_t R, FusedForm form, uint32_t gro
 static unsigned fused_lds(bool g32, uint32_t R, ChunkClass c, FusedForm form, uint32_t groups)
 {
     if (groups <= kUncappedGroups) return 0;
-    const uint32_t chunk = chunk_of(R, fused_chunk(g32, R, c)), asked = (chunk * (g32 ? 4u : 2u) + 12u) * 4u * kGroupQuads;
+    const uint32_t chunk = fused_chunk(g32, R, c), asked = (chunk * (g32 ? 4u : 2u) + 12u) * 4u * kGroupQuads;
     const bool late = form == kSearched || (form == kPlain && groups <= 32768u);
     if (c == kMid && groups <= 20480u && chunk < R) return lds_for(g32 ? (late ? 9u : 8u) : 14u);
     if (g32) return lds_for(late && chunk < 4 ? 9u : late + (R > 16 || chunk == 1 ? 8u : chunk < 4 || groups <= 16384u ? 7u : 45056u / asked));
