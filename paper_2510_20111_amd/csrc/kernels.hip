@@ -1085,21 +1085,47 @@ constexpr uint32_t kUncappedGroups = 5120;
 // Chunks are small up to 20480 groups (fp32 10240): the streams then lie a few MB apart and partly in the memory-side cache, and what counts is
 // how many of them are read side by side (buffers of one call's size, R = 12 / 16 / 24 of 1.8 M elements 17.3 / 20.1 / 24.4 us, with
 // chunks of 8 18.5 / 23.9 / 28.3; 4.4 M 38.0 / 46.5 / 54, 41.8 / 46.5 / 54; from 5 M chunks of 8 take 1-4 % less; fp32 R = 4 / 8 of 1.8 M 14.6 /
-// 19.9, with chunks of 4 14.9 / 20.2).  Beyond, 6 to 8 bf16 contributions go in one chunk up to 65536 groups and in two above (one
-// against two, both with the best number of wavefronts: R = 7 9.1 / 21 / 48 M elements 1.00 / 1.00 / 1.005, R = 8 1.00 / 1.00 / 1.00,
-// 105 M 1.01; R = 6 9.1 / 21 / 33 M .98 / .99 / 1.01).
+// 19.9, with chunks of 4 14.9 / 20.2).  One segment whose chunks would be few and not much larger keeps small ones a little longer (small / large
+// chunks on buffers of one call's size, against small ones with the pointers in the argument block: bf16 R = 7 5.3 to 7.7 M 1.00 / 1.02, 8.4 M .98 /
+// .98; R = 9 / 11 / 12 5.3 to 6.1 M .99-1.00 / 1.01-1.02, 1.04-1.05, 1.02-1.03, 6.7 M .99 / .99, 1.00 / 1.00, 1.00 / 1.00; R = 13 / 16 5.3 M .98 / .96, 1.00 / .98; fp32 R = 4
+// 3.6 / 4.6 / 6.1 / 7.2 M .99 / 1.05, .99 / 1.07, .99 / 1.01, .99 / .99; R = 5 / 6 / 8 2.6 to 4.1 M .98-.99 / 1.01-1.02, 1.00 / 1.01-1.03, .98 / 1.00-1.01, 4.6 M .98 /
+// 1.00, 1.00 / 1.01, .98 / .96; R = 10 2.8 M .97 / .97.  In a larger allocation the large ones are 1-3 % ahead everywhere.)  Beyond, 6 to 8 bf16 contributions
+// go in one chunk up to 65536 groups and in two above (one against two, both with the best number of wavefronts: R = 7 9.1 / 21 / 48 M elements
+// 1.00 / 1.00 / 1.005, R = 8 1.00 / 1.00 / 1.00, 105 M 1.01; R = 6 9.1 / 21 / 33 M .98 / .99 / 1.01; several segments of 10 M together R = 6 / 8 .97 / .99).
 static ChunkClass fused_class(bool g32, uint32_t R, FusedForm form, uint32_t groups)
 {
     // (where wavefronts also read tables, 16 fp32 contributions are too many a little earlier: 32 segments of 0.52 M elements together,
     // R = 16, 10.1 us without and 10.5 with them; 0.38 M 8.6 and 8.4)
     if (groups <= (g32 && form != kOne ? kFewGroups / 4 * 3 : kFewGroups)) return kFew;
-    if (groups <= (g32 ? 10240u : 20480u)) return kMid;
+    uint32_t small = g32 ? 10240u : 20480u;
+    if (form == kOne && g32 && R <= 9) small = R == 4 ? 24576u : 16384u;
+    if (form == kOne && !g32 && R > 6 && R <= 12) small = R <= 8 ? 32768u : 24576u;
+    if (groups <= small) return kMid;
     return !g32 && R > 5 && R <= 8 && groups > 65536u ? kMid : kLarge;
 }
 
-// Dynamic LDS of a launch: as many wavefronts per CU as keep about 50 KiB (bf16, 10 wavefronts at the most) or 44 KiB (fp32; 7, or 8 of
-// single contributions) in flight.  One or two more where a wavefront reads pointers or tables before it asks for data, and in shorter
-// launches of chunks of 4.  Means over 9 to 105 M elements against chunks of at most 4 and 9 or 11 wavefronts, by wavefronts 6 / 7 / 8 / 9 /
+// Longest launch without a cap.  One segment's wavefronts all ask at once (their pointers are there when they start), so where a few streams
+// make them ask for much they are capped earlier.  Without / with a cap (bf16 14, fp32 8), against the same with the pointers in the argument block, on
+// buffers of one call's size: bf16 R = 5 / 6 / 7 / 8 of 1.25 M elements .98 / .91, 1.00 / .93, .97 / .95, .98 / .96, of 1.1 M .99 / 1.03, .97 / 1.00,
+// .97 / .98, .97 / .97; R = 4 / 9 of 1.25 M .96 / .98, .97 / .99; fp32 R = 2 / 3 of 0.72 M .92 / .99, .96 / .92, of 0.79 M 1.07 / .86, 1.44 / .72, of 1.3 M
+// 1.10 / .90, 1.03 / .90; R = 1 of 0.92 M 1.01 / 1.02.
+static uint32_t uncapped_groups(bool g32, uint32_t R, FusedForm form)
+{
+    if (form == kOne && g32 && (R == 2 || R == 3)) return 2816u;
+    return form == kOne && !g32 && R > 4 && R <= 8 ? 4608u : kUncappedGroups;
+}
+
+// Dynamic LDS of a launch, for so many wavefronts per CU:
+//   bf16, chunks of 5 to 8: what keeps about 50 KiB in flight, 7 to 10; one more where a wavefront reads pointers or tables before it asks for data.
+//   bf16, several chunks of at most 4: 14 up to 32768 groups.  Beyond, R = 6 10, R = 7 and 8 9, R > 28 11 (14 / 12 / 11 / 10 / 9: R = 29 of 8.7 M
+//   elements - / .97 / .98 / 1.00 / 1.02, of 74 M - / .96 / .96 / .97 / .99; R = 32 1.00 / 1.00 / 1.00 / 1.01 / 1.02 and - / .99 / .98 / .98 / 1.00).
+//   bf16, one chunk: R = 1 to 4 11 up to 20480 groups (14 / 12 / 11 / 10 / 9 against the 14 of block arguments, mean over 1.3 to 5.2 M: R = 1 .982 / .977 /
+//   .971 / .974 / .983, R = 2 .976 / .975 / .970 / .977 / .985, R = 3 .985 / .971 / .965 / .969 / .975, R = 4 .991 / .982 / .974 / .973 / .985), then 10 and, R = 4, 9;
+//   R = 6 to 8 10.  With tables in between 14 up to 32768 groups and 11 beyond.
+//   fp32: chunks of 4 6; small chunks 8; of R = 2, 3, 5, 6 and 9 beyond 32768 groups 7 (8 / 7: R = 2 1.8 to 7.2 M elements .99 / 1.02, 8.7 M 1.00 / 1.00;
+//   R = 3 1.00 / 1.02, 1.00 / .99; R > 16 stays at 8: R = 24 / 28 of 9 to 21 M .99 / 1.01, 48 to 71 M 1.00 / .99 and .99 / 1.01).  One more with tables, and chunks
+//   below 4 9.
+// Means over 9 to 105 M elements against chunks of at most 4 and 9 or 11 wavefronts, by wavefronts 6 / 7 / 8 / 9 /
 // 10 / 11: bf16 R = 5 1.022 / .996 / .990 / .990 / .988 / .987, R = 10 1.045 / .997 / .984 / .982 / .983 / .984, R = 16 .987 / .979 / .986 /
 // .991 / .996 / 1.001, R = 24 .992 / .988 / .996 / .999 / 1.004 / 1.010; R = 8 in two chunks 1.094 / 1.032 / 1.005 / .997 / .998 / 1.000.
 // Over 1.5 to 71 M against chunks of 3 and 8 wavefronts, by 4 / 5 / 6 / 7 / 8: fp32 R = 2 1.175 / 1.045 / .990 / .981 / .989, R = 4 1.077 /
@@ -1107,12 +1133,14 @@ static ChunkClass fused_class(bool g32, uint32_t R, FusedForm form, uint32_t gro
 // 1.230 / 1.094 / 1.022 / .991 / .994.
 static unsigned fused_lds(bool g32, uint32_t R, ChunkClass c, FusedForm form, uint32_t groups)
 {
-    if (groups <= kUncappedGroups) return 0;
+    if (groups <= uncapped_groups(g32, R, form)) return 0;
     const uint32_t chunk = fused_chunk(g32, R, c), asked = (chunk * (g32 ? 4u : 2u) + 12u) * 4u * kGroupQuads;
     const bool late = form == kSearched || (form == kPlain && groups <= 32768u);
-    if (c == kMid && groups <= 20480u && chunk < R) return lds_for(g32 ? (late ? 9u : 8u) : 14u);
-    if (g32) return lds_for(late && chunk < 4 ? 9u : late + (R > 16 || chunk == 1 ? 8u : chunk < 4 || groups <= 16384u ? 7u : 45056u / asked));
-    if (R > 28 || (late && chunk <= 4)) return lds_for(groups <= 32768u ? 14u : late || groups <= 200000u ? 11u : 10u);
+    if (c == kMid && groups <= 32768u && chunk < R) return lds_for(g32 ? (late ? 9u : 8u) : 14u);
+    if (g32 && chunk < 4) return lds_for(late ? 9u : R > 16 || chunk == 1 || groups <= 32768u ? 8u : 7u);
+    if (g32) return lds_for(late + (groups <= 16384u ? 7u : 6u));       // (chunks of 4 in so short a launch: several segments, or R > 9)
+    if (R > 28 || (late && chunk <= 4)) return lds_for(groups <= 32768u ? 14u : 11u);
+    if (form == kOne && R <= 4 && groups <= 20480u) return lds_for(11u);
     return lds_for(late + (R > 5 && R <= 8 && chunk == R ? 10u : chunk == 4 ? 9u : std::min(10u, 51200u / asked)));
 }
 

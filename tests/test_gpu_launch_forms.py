@@ -10,7 +10,7 @@ import paper_2510_20111_amd as hzp
 from oracle import numeric as on
 from oracle import planner as op
 
-from gpu_util import DEV, assert_cast_of, assert_close_f32, launches_of, oracle_plan, to_dev, to_host, wd_mult_array
+from gpu_util import DEV, REL_TOL, RMS_FLOOR, U_ERR, assert_cast_of, assert_close_f32, launches_of, oracle_plan, to_dev, to_host, wd_mult_array
 
 pytestmark = pytest.mark.gpu
 
@@ -88,11 +88,14 @@ def test_every_number_of_contributions_at_group_edges(R, cls):
         assert all(np.array_equal(s.view(np.uint32), t.view(np.uint32)) for s, t in zip(x, y))
 
 
-@pytest.mark.parametrize("cls,R,groups", [(0, R, g) for R in (6, 7, 8) for g in ((65537,), (32769, 32768), (60000, 6000))] +
+@pytest.mark.parametrize("cls,R,groups", [(0, R, g) for R in (6, 7, 8) for g in ((32769,), (65536,), (32768, 32768), (60000, 5536), (10241, 10240), (18000, 2481))] +
+                         [(0, R, g) for R in (6, 7, 8) for g in ((65537,), (32769, 32768), (60000, 6000))] +
                          [(0, R, g) for R in (5, 8, 9, 16, 28, 29) for g in ((20481,), (10241, 10240), (18000, 2481))] +
-                         [(1, R, g) for R in (4, 7, 16, 17) for g in ((10241,), (5121, 5120), (9000, 1241))])
+                         [(0, R, (g,)) for R, g in ((5, 20481), (6, 20481), (9, 24577), (12, 24577), (13, 20481), (28, 20481))] +
+                         [(1, R, g) for R in (4, 7, 16, 17) for g in ((10241,), (5121, 5120), (9000, 1241))] +
+                         [(1, R, (g,)) for R, g in ((4, 24577), (7, 16385), (8, 16385), (10, 10241), (16, 10241))])
 def test_long_launches_and_their_quarters(cls, R, groups):
-    """Launches just long enough for another number of contributions at a time, and the same elements in calls of a quarter of each
+    """Launches at the lengths where the number of contributions at a time changes, and the same elements in calls of a quarter of each
     segment: the same bits (one segment, segments of like length, and found by search; the last group is not full)."""
     sizes = [g * 256 - 8 for g in groups]
     total = sum(sizes)
@@ -125,6 +128,78 @@ def test_long_launches_and_their_quarters(cls, R, groups):
     for a, b in zip(*results):
         assert torch.equal(a.view(bits if a.dtype == dtype else torch.int32), b.view(bits if b.dtype == dtype else torch.int32))
     assert not torch.equal(results[0][0], start[0])
+
+
+def larger_chunks_from(cls, R, one):
+    """Longest launch, in groups, in small chunks (one segment, or several), or None where a longer one has the same."""
+    if cls:
+        return None if R <= 3 or R in (5, 6, 9) or R > 16 else 24576 if one and R == 4 else 16384 if one and R <= 9 else 10240
+    return None if R <= 4 or R > 28 else 32768 if one and R in (7, 8) else 24576 if one and 9 <= R <= 12 else 20480
+
+
+@pytest.mark.parametrize("cls,R", [(0, R) for R in range(1, 33)] + [(1, R) for R in range(1, 33)])
+def test_the_number_of_contributions_at_a_time_follows_the_length(cls, R):
+    """One segment: the launches on the two sides of each limit have different kernels, and those within it the same."""
+    limit = larger_chunks_from(cls, R, True)
+    kernel = [update_launches(groups, cls, R)[0][2] for groups in (2049, limit or 24577, (limit or 24577) + 1)]
+    assert kernel[0] == kernel[1] and (kernel[1] != kernel[2]) == (limit is not None)
+    if not cls and 5 < R <= 8:          # in one chunk between the limits
+        assert update_launches(65536, cls, R)[0][2] == kernel[2] and update_launches(65537, cls, R)[0][2] == kernel[1]
+
+
+@pytest.mark.parametrize("cls,R", [(0, R) for R in range(1, 33)] + [(1, R) for R in range(1, 33)])
+def test_update_of_every_number_of_contributions_in_longer_launches(cls, R):
+    """Small and large chunks of every R in the three forms of a launch (one segment, two of a length, two of very different ones that are
+    found by search), against the fp32 sum in order and an update in 64 bits."""
+    dtype = torch.float32 if cls else torch.bfloat16
+    one, several = (larger_chunks_from(cls, R, True) or 20480) + 1, (larger_chunks_from(cls, R, False) or 10240) + 2
+    forms = ((3000,), (one,), (several // 2, several // 2), (several - several // 8, several // 8))
+    longest = max(map(sum, forms)) * 256
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(R)
+    grads = [torch.empty(longest, device=DEV).normal_(0, 1e-3, generator=gen).to(dtype) for _ in range(R)]
+    start = [torch.empty(longest, device=DEV).normal_(0, s, generator=gen) for s in (0.02, 1e-4, 1e-4)]
+    start[2].square_()
+    total = grads[0].to(torch.float32, copy=True)
+    for x in grads[1:]:
+        total += x
+    total *= torch.tensor(1.0 / R, dtype=torch.float32, device=DEV)
+    # (the hyper-parameters as the fp32 numbers that the entry point takes; bias corrections in 64 bits)
+    lr, b1, b2, eps, wd = (float(np.float32(HP[k])) for k in ("lr", "beta1", "beta2", "eps", "weight_decay"))
+    ge, p, m, v = total.double(), *(x.double() for x in start)
+    terms = b1 * m.abs() + (1 - b1) * ge.abs()
+    m = b1 * m + (1 - b1) * ge
+    v = b2 * v + (1 - b2) * ge * ge
+    denom = (v / (1 - b2 ** 3)).sqrt() + eps
+    u = (m / (1 - b1 ** 3)) / denom
+    p = p - lr * (u + wd * p)
+    want = (p, m, v)
+    # u is good to half of U_ERR relative (where |u| stays below 2; here it does not, as v comes close to 0), and to the two roundings of m, a
+    # 2^-24 of its terms each, over the denominator
+    step_error = lr * (U_ERR / 2 * u.abs() + 2 ** -23 * terms / (1 - b1 ** 3) / denom)
+    hy = hzp.adamw_hyper(HP["lr"], HP["beta1"], HP["beta2"], HP["eps"], HP["weight_decay"], 1.0 / R, 3)
+    for groups in forms:
+        sizes = [g * 256 for g in groups]
+        sizes[-1] -= 8
+        print("class %d R=%d groups %s" % (cls, R, groups), flush=True)
+        spans = [(sum(sizes[:k]), sum(sizes[:k + 1])) for k in range(len(sizes))]
+        assert spans[-1][1] <= longest
+        def views(t):           # (copies, so that segments do not follow each other)
+            return [torch.cat([t[a:b], torch.full((64,), 0.5, dtype=t.dtype, device=DEV)]) for a, b in spans]
+        g, s, o = [views(t) for t in grads], [views(t) for t in start], views(torch.zeros(longest, dtype=dtype, device=DEV))
+        plan = hzp.hzp_plan([1] * len(sizes), sizes, 8, 1, 1, tensor_class=[cls] * len(sizes))
+        hzp.hzp_adamw_shard(plan, 0, len(sizes), cls, 0, hy, [g[r][k] for k in range(len(sizes)) for r in range(R)], R, *s, o)
+        torch.cuda.synchronize()
+        for k, (a, b) in enumerate(spans):
+            for key, have, ref in zip("pmv", s, want):
+                w = ref[a:b].float().double()
+                got = have[k][:b - a].double()
+                bound = REL_TOL * torch.maximum(got.abs(), w.abs()) + RMS_FLOOR[key] * float(w.square().mean().sqrt()) + 1e-37
+                if key == "p":
+                    bound += step_error[a:b]
+                assert bool(((got - w).abs() <= bound).all()), key
+            assert torch.equal(o[k][:b - a], s[0][k][:b - a].to(dtype))
+            assert all(bool((x[k][b - a:] == 0.5).all()) for x in (*s, o))
 
 
 @pytest.mark.parametrize("place,out_place", [("packed", None), ("spread", None), ("down", None), ("packed", "spread"),
