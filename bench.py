@@ -754,6 +754,11 @@ def fused_launch_count(w):
     return count + (1 if cnt else 0)
 
 
+def fused_kernel_name(w):
+    """The kernel of a call over all buckets: one segment where the slices follow each other in every stream, else the general one."""
+    return "fused_adamw_kernel" if w.layout == "separate" else "fused_one_kernel"
+
+
 COPY_MAX_TILES = 600000         # 1 KiB tiles one launch of the layer-range gather covers at most
 
 
@@ -848,7 +853,7 @@ def time_workload(idx, args, torch, np, hzp, hzp_inputs, steps, warmup, keep=Fal
     fused_launches = fused_launch_count(w)
     rooflines = {}
     if "fused" in phases:
-        rooflines["fused_adamw"] = roof("fused_adamw_kernel<R=%d,bf16>" % R, fused_bytes, fused_ms,
+        rooflines["fused_adamw"] = roof("%s<R=%d,bf16>" % (fused_kernel_name(w), R), fused_bytes, fused_ms,
                                         fused_launches, "fused_adamw_%s" % cfg["name"], ph[:, 0])
         # context, outside the timed steps: the update alone, call after call (inside the step it starts behind
         # the level-3 gather's trailing writes)
@@ -1004,9 +1009,9 @@ def main():
                      "accumulate": "reduce_kernel<f32,R=%d,accumulate>" % R,
                      "inplace": "fused update writing into the ZeRO-3 shard + level-1 gather of the other %d pieces" % (w.K - 1),
                      "notinplace": "fused update + level-1 gather of all %d pieces" % w.K,
-                     "f32class": "fused_adamw_kernel<R=%d, fp32 gradients, fp32 output> (class F32 on the same shapes)" % R,
-                     "perlayer": "fused_adamw_kernel<R=%d,bf16>, one call per layer" % R,
-                     "prereduced": "fused_adamw_kernel<R=1,f32 gradient> (update from a reduced fp32 shard)",
+                     "f32class": "fused_one_kernel<R=%d, fp32 gradients, fp32 output> (class F32 on the same shapes)" % R,
+                     "perlayer": "fused_one_kernel<R=%d,bf16>, one call per layer" % R,
+                     "prereduced": "%s<R=1,f32 gradient> (update from a reduced fp32 shard)" % fused_kernel_name(w),
                      "freegroups": "copy_ranges_kernel (Z1=%d over Z3=%d: ZeRO-3 shard from partial owners)"
                                    % (getattr(w, "free_z1", 0), w.z3)}[phase]
             launches = fused_launches if phase in ("prereduced", "f32class") else 1 if phase in ("inplace", "notinplace") else w.n_layers
