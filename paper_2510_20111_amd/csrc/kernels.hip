@@ -186,10 +186,24 @@ __device__ __forceinline__ void pin(T &x, Rest &...rest)
     pin(rest...);
 }
 
+// So many wait states (a multiple of 8) between the requests before and behind it.
+template <uint32_t STATES>
+__device__ __forceinline__ void gap()
+{
+    static_assert(STATES % 8 == 0, "whole s_nop 7");
+    if constexpr (STATES > 0) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (uint32_t k = 0; k < STATES / 8; ++k) asm volatile("s_nop 7");
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
 // Left-to-right fp32 sum of R contributions, ((g0 + g1) + g2) + ..., at most `MOST` of them in flight, for
 // Q quads; slice(r) + shift is contribution r, and `at` holds the first chunk's pointers.  meanwhile() runs when the first chunk
-// is requested.  Where the chunks are not all of one size the larger ones are the first (LARGER_FIRST) or the last.
-template <uint32_t R, uint32_t MOST, bool G32, int Q, bool LARGER_FIRST, class Slice, class Meanwhile>
+// is requested.  Where the chunks are not all of one size the larger ones are the first (LARGER_FIRST) or the last.  GAP wait states
+// lie between any two contributions' requests.
+template <uint32_t R, uint32_t MOST, bool G32, int Q, bool LARGER_FIRST, uint32_t GAP, class Slice, class Meanwhile>
 __device__ __forceinline__ void sum_contributions(uint64_t (&at)[MOST], Slice slice, int64_t shift,
                                                   const uint32_t (&quad)[Q], float (&s)[Q][4], Meanwhile meanwhile)
 {
@@ -200,9 +214,11 @@ __device__ __forceinline__ void sum_contributions(uint64_t (&at)[MOST], Slice sl
         GradQuad<G32> g[C][Q];
 #pragma unroll
         for (uint32_t c = 0; c < C; ++c)
+            if (base + c < end) {
 #pragma unroll
-            for (int q = 0; q < Q; ++q)
-                if (base + c < end) g[c][q].load(at[c] + shift, quad[q]);
+                for (int q = 0; q < Q; ++q) g[c][q].load(at[c] + shift, quad[q]);
+                gap<GAP>();
+            }
 #pragma unroll
         for (uint32_t c = 0; c < C; ++c)
             if (k + 1 < CHUNKS && end + c < next) at[c] = slice(end + c);
@@ -265,7 +281,7 @@ __device__ __forceinline__ void reduce(uint64_t out, uint32_t nquad, float scale
         if (ACC && !LATE) t[q] = ld_stream<f32x4>(out, quad[q]);
     }
     float s[Q][4];
-    sum_contributions<R, CHUNK, G32, Q, LATE>(at, slice, 0, quad, s, [] {});
+    sum_contributions<R, CHUNK, G32, Q, LATE, 0>(at, slice, 0, quad, s, [] {});
 #pragma unroll
     for (int q = 0; q < Q; ++q)
         if (ACC && LATE) t[q] = ld_stream<f32x4>(out, quad[q]);
@@ -410,7 +426,17 @@ struct DecayRuns {
 // 0.46 M elements 5.0 / 4.6, R = 1 and 8 of 2.1 M 11.5 / 11.3 and 16.6 / 16.4, fp32 R = 12 of 0.26 M 5.9 / 5.5; from 25 M the same).
 // kSearched: a uniform binary search may have to find the segment, three more rounds, which the few resident wavefronts hide badly
 // (105 M elements, R = 8, one segment: 6.65 TB/s at the best number of wavefronts, 6.73 with one round).
-template <uint32_t R, bool G32, bool O32, FusedForm FORM, uint32_t CHUNK, class Args>
+//
+// Where all of one segment's wavefronts are resident they start with their pointers at hand and ask for everything at once, and
+// streams that lie at the wrong distance from each other then collide in the memory channels.  A pause between
+// requests avoids that (s_nop; where the pointers came from the argument block, the compiler's 64-bit address arithmetic lay there): 8 wait states between any two
+// contributions' where up to 16 go at a time, and HEAD between the state's requests and the contributions' where one or two follow in a launch
+// of 12 to 20 wavefronts per CU.  Against the pointers in the argument block, on buffers of one call's size, without / with 8 states: fp32 of 0.2 to 0.3 M elements,
+// streams 2, 4, .. 18 MiB apart, R = 9 to 16, 210 sets, mean 1.02 / 0.90, worst 1.72 / 1.10 (R = 14 of 0.26 M, 6 MiB apart, 9.3 us, 5.8 now); 0.08 to 0.5 M,
+// R = 9 to 32, bf16 .95 / .93, fp32 .98 / .93, in a larger allocation .95 / .93 and .95 / .95.  Without / with 96 states, 0.85 to 1.05 M: bf16 R = 1 1.00 / .93, R = 2
+// .99 / .90, fp32 R = 1 1.04 / .94, in a larger allocation 1.02 / .94, .98 / .94, .99 / .95.  (Longer launches are capped, and a pause only delays them: 96 states 0 to 1 %
+// more, 16 between requests 0 to 2 %.)
+template <uint32_t R, bool G32, bool O32, FusedForm FORM, uint32_t CHUNK, uint32_t HEAD, class Args>
 __device__ __forceinline__ void fused_adamw(const FusedLead lead, const Args &a)
 {
     constexpr bool PAIRS = !G32;
@@ -517,7 +543,8 @@ __device__ __forceinline__ void fused_adamw(const FusedLead lead, const Args &a)
     __builtin_amdgcn_sched_barrier(0);
     if (FORM == kSearched && lookup) runs.find(pos);
     float g[1][4];
-    sum_contributions<R, CHUNK, G32, 1, false>(at, [slice](uint32_t r) { return slice[r]; }, shift * (G32 ? 16 : 8), quads, g, [&] {
+    gap<HEAD>();
+    sum_contributions<R, CHUNK, G32, 1, false, (FORM == kOne && CHUNK > 8 ? 8u : 0u)>(at, [slice](uint32_t r) { return slice[r]; }, shift * (G32 ? 16 : 8), quads, g, [&] {
         if (FORM == kOne)       // needed last, but read by now
             pin(OUT, h.lr, h.beta1, h.beta2, h.one_minus_beta1, h.one_minus_beta2, h.eps, h.weight_decay, h.grad_scale, h.inv_bc1, h.inv_bc2);
     });
@@ -559,15 +586,15 @@ __device__ __forceinline__ void fused_adamw(const FusedLead lead, const Args &a)
     }
 }
 
-template <uint32_t R, bool G32, bool O32, uint32_t CHUNK>
+template <uint32_t R, bool G32, bool O32, uint32_t CHUNK, uint32_t HEAD>
 __global__ __launch_bounds__(kWave) void fused_one_kernel(const u64x4 p, const u64x2 w, const uint64_t size, const FusedOneArgs a)
 {
-    fused_adamw<R, G32, O32, kOne, CHUNK>({p, w, size}, a);
+    fused_adamw<R, G32, O32, kOne, CHUNK, HEAD>({p, w, size}, a);
 }
 template <uint32_t R, bool G32, bool O32, FusedForm FORM, uint32_t CHUNK>
 __global__ __launch_bounds__(kWave) void fused_adamw_kernel(const FusedArgs a)
 {
-    fused_adamw<R, G32, O32, FORM, CHUNK>({}, a);
+    fused_adamw<R, G32, O32, FORM, CHUNK, 0>({}, a);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -874,7 +901,7 @@ static constexpr std::array<FusedKernel, sizeof...(I)> fused_kernels(std::index_
 template <bool G32, bool O32, ChunkClass CLASS, size_t... I>
 static constexpr std::array<FusedOneKernel, sizeof...(I)> fused_one_kernels(std::index_sequence<I...>)
 {
-    return {fused_one_kernel<I + 1, G32, O32, fused_chunk(G32, I + 1, CLASS)>...};
+    return {fused_one_kernel<I + 1, G32, O32, fused_chunk(G32, I + 1, CLASS), 0>...};
 }
 
 // Wavefronts per CU for the reduction, from the bytes that they ask for.  Where several chunks follow each other about 30 KiB per CU, from
@@ -1159,7 +1186,7 @@ static FusedOneKernel fused_one_kernel_of(bool g32, bool o32, uint32_t R)
     constexpr std::make_index_sequence<HZP_MAX_REPLICAS> all;
     static constexpr auto kernels16 = fused_one_kernels<false, false, CLASS>(all);
     static constexpr auto kernels32 = fused_one_kernels<true, true, CLASS>(all);
-    return !g32 ? kernels16[R - 1] : o32 ? kernels32[R - 1] : fused_one_kernel<1, true, false, fused_chunk(true, 1, CLASS)>;
+    return !g32 ? kernels16[R - 1] : o32 ? kernels32[R - 1] : fused_one_kernel<1, true, false, fused_chunk(true, 1, CLASS), 0>;
 }
 
 template <FusedForm FORM>
@@ -1174,7 +1201,10 @@ static hzp_status_t start_fused(bool g32, bool o32, uint32_t R, const FusedArgs 
 static hzp_status_t start_fused_one(bool g32, bool o32, uint32_t R, const FusedArgs &a, uint32_t groups, hipStream_t stream)
 {
     const ChunkClass c = fused_class(g32, R, kOne, groups);
-    const FusedOneKernel kernel = c == kFew ? fused_one_kernel_of<kFew>(g32, o32, R) : c == kMid ? fused_one_kernel_of<kMid>(g32, o32, R) : fused_one_kernel_of<kLarge>(g32, o32, R);
+    FusedOneKernel kernel = c == kFew ? fused_one_kernel_of<kFew>(g32, o32, R) : c == kMid ? fused_one_kernel_of<kMid>(g32, o32, R) : fused_one_kernel_of<kLarge>(g32, o32, R);
+    if (groups > 3072 && groups <= uncapped_groups(g32, R, kOne) && (R == 1 || (R == 2 && !g32)))       // with a pause behind the state's requests
+        kernel = R == 2 ? fused_one_kernel<2, false, false, 2, 96> : !g32 ? fused_one_kernel<1, false, false, 1, 96>
+                 : o32 ? fused_one_kernel<1, true, true, 1, 96> : fused_one_kernel<1, true, false, 1, 96>;
     FusedOneArgs one;
     one.out = a.word[3];
     one.scalars = a.scalars;

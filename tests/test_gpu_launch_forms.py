@@ -147,6 +147,40 @@ def test_the_number_of_contributions_at_a_time_follows_the_length(cls, R):
         assert update_launches(65536, cls, R)[0][2] == kernel[2] and update_launches(65537, cls, R)[0][2] == kernel[1]
 
 
+@pytest.mark.parametrize("cls,R", [(0, 1), (0, 2), (1, 1), (0, 0)])
+@pytest.mark.parametrize("groups", [3073, 4000, 5120])
+def test_updates_with_a_pause_between_their_requests(cls, R, groups):
+    """One segment whose wavefronts are 12 to 20 to a CU has a kernel of its own; the bits are those of its two halves, which have not
+    (R = 0: from an already reduced fp32 shard)."""
+    n = groups * 256 - 8
+    half = n // 16 * 8
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(groups)
+    g32, dtype = cls or R == 0, torch.float32 if cls else torch.bfloat16
+    g = [torch.empty(n, device=DEV).normal_(0, 1e-3, generator=gen).to(torch.float32 if g32 else dtype) for _ in range(max(R, 1))]
+    start = [torch.empty(n, device=DEV).normal_(0, s, generator=gen) for s in (0.02, 1e-4, 1e-4)]
+    start[2].square_()
+    hy = hzp.adamw_hyper(HP["lr"], HP["beta1"], HP["beta2"], HP["eps"], HP["weight_decay"], 1.0, 3)
+    results, kernels = [], []
+    for spans in ([(0, n)], [(0, half), (half, n)]):
+        plan = hzp.hzp_plan([1] * len(spans), [b - a for a, b in spans], 8, 1, 1, tensor_class=[cls] * len(spans))
+        plan.prepare()
+        s, out = [x.clone() for x in start], torch.full((n + 64,), 0.5, dtype=dtype, device=DEV)
+
+        def call(k, a, b):
+            hzp.hzp_adamw_shard(plan, k, k + 1, cls, 0, hy, [x[a:b] for x in g], R, *([x[a:b]] for x in s), [out[a:b]])
+        kernels += [launches_of(lambda: call(0, *spans[0]))[0][2]]
+        for k, (a, b) in enumerate(spans):
+            call(k, a, b)
+        torch.cuda.synchronize()
+        results.append([*s, out])
+        assert bool((out[n:] == 0.5).all())
+    assert kernels[0] != kernels[1]
+    for a, b in zip(*results):
+        assert torch.equal(a.view(torch.int32 if a.dtype == torch.float32 else torch.int16), b.view(torch.int32 if a.dtype == torch.float32 else torch.int16))
+    assert not torch.equal(results[0][0], start[0])
+
+
 @pytest.mark.parametrize("cls,R", [(0, R) for R in range(1, 33)] + [(1, R) for R in range(1, 33)])
 def test_update_of_every_number_of_contributions_in_longer_launches(cls, R):
     """Small and large chunks of every R in the three forms of a launch (one segment, two of a length, two of very different ones that are
