@@ -114,7 +114,7 @@ constexpr int kWave = 64;
 constexpr uint32_t kGroupQuads = 64;        // quads per group (256 elements)
 
 // Dynamic LDS that leaves room for `waves` single-wavefront workgroups per CU, or the next smaller number that there is: a CU's 160 KiB
-// are given out in 128 units of 1280 bytes (so 13 are 12, 15 are 14, 19 and 20 are 18, 22 to 24 are 21).
+// are given out in 128 units of 1280 bytes (so 13 are 12, 15 are 14, 17 are 16, 19 and 20 are 18, 22 to 24 are 21, 26 to 31 are 25).
 constexpr unsigned lds_for(unsigned waves) { return waves ? (128u / (waves + 1) + 1) * 1280u : 0u; }
 
 constexpr uint32_t kReduceChunk = 4;
@@ -128,7 +128,7 @@ constexpr uint32_t few_chunk(uint32_t R, uint32_t chunk) { return R > 8 ? 16u : 
 //   kLarge: few large chunks beat many small ones (a wavefront waits once for each), with so many fewer wavefronts that a CU has about
 //   50 KiB in flight (fused_lds).  Chunks of at most 4 / 6 / 8, each with the best number of wavefronts, mean over 9 to 105 M
 //   elements against chunks of 4 with 9 or 11: bf16 R = 10 .995 / .981 / .982, R = 14 .996 / .979 / .974, R = 16 .996 / .986 / .979,
-//   R = 20 .996 / .985 / .979, R = 24 .999 / .991 / .988, R = 28 .997 / .990 / .989, R = 32 .997 / .996 / .991, but 2 % more at 2-6 M.
+//   R = 20 .996 / .985 / .979, R = 24 .999 / .991 / .988, R = 28 .997 / .990 / .989, R = 32 .997 / .996 / .991.
 //   fp32 with chunks of at most 3 / 4 / 6, over 1.5 to 71 M: R = 4 .989 / .978 / -, R = 8 .993 / .973 / -, R = 12 .982 / .980 / .975,
 //   R = 16 .996 / .983 / .983, R = 24 .991 / .992 / 1.004, R = 32 .997 / .998 / 1.019.
 //   kMid: in shorter launches large chunks read too many streams side by side, and where no cap holds the wavefronts back they ask for
@@ -139,7 +139,7 @@ constexpr uint32_t fused_most(bool g32, uint32_t R, ChunkClass c)
 {
     const uint32_t mid = g32 ? 3u : 4u;
     if (c == kFew) return few_chunk(R, mid);
-    if (c == kMid || (g32 ? R > 16 : R > 28)) return mid;
+    if (c == kMid || (g32 && R > 16)) return mid;
     return g32 || R <= 4 ? 4u : R <= 8 ? R : 8u;
 }
 
@@ -1144,8 +1144,7 @@ static uint32_t uncapped_groups(bool g32, uint32_t R, FusedForm form)
 
 // Dynamic LDS of a launch, for so many wavefronts per CU:
 //   bf16, chunks of 5 to 8: what keeps about 50 KiB in flight, 7 to 10; one more where a wavefront reads pointers or tables before it asks for data.
-//   bf16, several chunks of at most 4: 14 up to 32768 groups.  Beyond, R = 6 10, R = 7 and 8 9, R > 28 11 (14 / 12 / 11 / 10 / 9: R = 29 of 8.7 M
-//   elements - / .97 / .98 / 1.00 / 1.02, of 74 M - / .96 / .96 / .97 / .99; R = 32 1.00 / 1.00 / 1.00 / 1.01 / 1.02 and - / .99 / .98 / .98 / 1.00).
+//   bf16, several chunks of at most 4: 14 up to 32768 groups.  Beyond, R = 6 10, R = 7 and 8 9.
 //   bf16, one chunk: R = 1 to 4 11 up to 20480 groups (14 / 12 / 11 / 10 / 9 against the 14 of block arguments, mean over 1.3 to 5.2 M: R = 1 .982 / .977 /
 //   .971 / .974 / .983, R = 2 .976 / .975 / .970 / .977 / .985, R = 3 .985 / .971 / .965 / .969 / .975, R = 4 .991 / .982 / .974 / .973 / .985), then 10 and, R = 4, 9;
 //   R = 6 to 8 10.  With tables in between 14 up to 32768 groups and 11 beyond.
@@ -1166,7 +1165,7 @@ static unsigned fused_lds(bool g32, uint32_t R, ChunkClass c, FusedForm form, ui
     if (c == kMid && groups <= 32768u && chunk < R) return lds_for(g32 ? (late ? 9u : 8u) : 14u);
     if (g32 && chunk < 4) return lds_for(late ? 9u : R > 16 || chunk == 1 || groups <= 32768u ? 8u : 7u);
     if (g32) return lds_for(late + (groups <= 16384u ? 7u : 6u));       // (chunks of 4 in so short a launch: several segments, or R > 9)
-    if (R > 28 || (late && chunk <= 4)) return lds_for(groups <= 32768u ? 14u : 11u);
+    if (late && chunk <= 4) return lds_for(groups <= 32768u ? 14u : 11u);
     if (form == kOne && R <= 4 && groups <= 20480u) return lds_for(11u);
     return lds_for(late + (R > 5 && R <= 8 && chunk == R ? 10u : chunk == 4 ? 9u : std::min(10u, 51200u / asked)));
 }

@@ -134,7 +134,7 @@ def larger_chunks_from(cls, R, one):
     """Longest launch, in groups, in small chunks (one segment, or several), or None where a longer one has the same."""
     if cls:
         return None if R <= 3 or R in (5, 6, 9) or R > 16 else 24576 if one and R == 4 else 16384 if one and R <= 9 else 10240
-    return None if R <= 4 or R > 28 else 32768 if one and R in (7, 8) else 24576 if one and 9 <= R <= 12 else 20480
+    return None if R <= 4 else 32768 if one and R in (7, 8) else 24576 if one and 9 <= R <= 12 else 20480
 
 
 @pytest.mark.parametrize("cls,R", [(0, R) for R in range(1, 33)] + [(1, R) for R in range(1, 33)])
