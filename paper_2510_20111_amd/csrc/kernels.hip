@@ -430,10 +430,10 @@ struct DecayRuns {
 // Where all of one segment's wavefronts are resident they start with their pointers at hand and ask for everything at once, and
 // streams that lie at the wrong distance from each other then collide in the memory channels.  A pause between
 // requests avoids that (s_nop; where the pointers came from the argument block, the compiler's 64-bit address arithmetic lay there): 8 wait states between any two
-// contributions' where up to 16 go at a time, and HEAD between the state's requests and the contributions' where one or two follow in a launch
+// fp32 contributions' where up to 16 go at a time, and HEAD between the state's requests and the contributions' where one or two follow in a launch
 // of 12 to 20 wavefronts per CU.  Against the pointers in the argument block, on buffers of one call's size, without / with 8 states: fp32 of 0.2 to 0.3 M elements,
 // streams 2, 4, .. 18 MiB apart, R = 9 to 16, 210 sets, mean 1.02 / 0.90, worst 1.72 / 1.10 (R = 14 of 0.26 M, 6 MiB apart, 9.3 us, 5.8 now); 0.08 to 0.5 M,
-// R = 9 to 32, bf16 .95 / .93, fp32 .98 / .93, in a larger allocation .95 / .93 and .95 / .95.  Without / with 96 states, 0.85 to 1.05 M: bf16 R = 1 1.00 / .93, R = 2
+// R = 9 to 32, .98 / .93, in a larger allocation .95 / .95; bf16, which has none, .95 / .93, but near 2048 groups up to 1.16 / 1.42.  Without / with 96 states, 0.85 to 1.05 M: bf16 R = 1 1.00 / .93, R = 2
 // .99 / .90, fp32 R = 1 1.04 / .94, in a larger allocation 1.02 / .94, .98 / .94, .99 / .95.  (Longer launches are capped, and a pause only delays them: 96 states 0 to 1 %
 // more, 16 between requests 0 to 2 %.)
 template <uint32_t R, bool G32, bool O32, FusedForm FORM, uint32_t CHUNK, uint32_t HEAD, class Args>
@@ -544,7 +544,7 @@ __device__ __forceinline__ void fused_adamw(const FusedLead lead, const Args &a)
     if (FORM == kSearched && lookup) runs.find(pos);
     float g[1][4];
     gap<HEAD>();
-    sum_contributions<R, CHUNK, G32, 1, false, (FORM == kOne && CHUNK > 8 ? 8u : 0u)>(at, [slice](uint32_t r) { return slice[r]; }, shift * (G32 ? 16 : 8), quads, g, [&] {
+    sum_contributions<R, CHUNK, G32, 1, false, (FORM == kOne && G32 && CHUNK > 8 ? 8u : 0u)>(at, [slice](uint32_t r) { return slice[r]; }, shift * (G32 ? 16 : 8), quads, g, [&] {
         if (FORM == kOne)       // needed last, but read by now
             pin(OUT, h.lr, h.beta1, h.beta2, h.one_minus_beta1, h.one_minus_beta2, h.eps, h.weight_decay, h.grad_scale, h.inv_bc1, h.inv_bc2);
     });
