@@ -1,4 +1,4 @@
-"""Binding of libhzp: argument marshalling only (ctypes, and native code for the calls of every step), every step runs in the library.
+"""Binding of libhzp: argument marshalling only (ctypes, and native code for eight calls that a step makes per layer), every step runs in the library.
 
 Function names and argument order follow ``include/hzp.h``.  Device buffers may be given as
 torch tensors (their ``data_ptr()`` is taken) or as integer addresses; a stream may be a
