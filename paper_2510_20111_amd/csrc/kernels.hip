@@ -111,6 +111,10 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
 // read its last quad again and store nothing.
 // ---------------------------------------------------------------------------------------
 constexpr int kWave = 64;
+// The runtime copies a launch's arguments into memory that another of its threads gives back, a thousand launches at a time.  Where copies
+// are longer than this the two threads wait for each other: calls in a row, in a process that has PyTorch loaded, blocks of 96 / 104 / 112 / 120 / 128 / 256 /
+// 816 bytes, us a launch: 2.80 / 2.81 / 2.78 / 3.25-3.6 / 3.55 / 3.65 / 3.9.
+constexpr size_t kFewBytes = 112;
 constexpr uint32_t kGroupQuads = 64;        // quads per group (256 elements)
 
 // Dynamic LDS that leaves room for `waves` single-wavefront workgroups per CU, or the next smaller number that there is: a CU's 160 KiB
@@ -243,15 +247,23 @@ __device__ __forceinline__ void sum_contributions(uint64_t (&at)[MOST], Slice sl
 // ---------------------------------------------------------------------------------------
 // Standalone reduction (bit-exact with the scalar definition: fixed order, no contraction).
 // ---------------------------------------------------------------------------------------
-struct ReduceRest {
-    uint64_t g[HZP_MAX_REPLICAS];       // all pointers
+// Argument blocks hold as many pointers as the kernel reads (kFewBytes).
+template <uint32_t N>
+struct Pointers {
+    uint64_t g[N];
 };
+template <uint32_t R>
 struct ReduceArgs {
     uint64_t out;
     uint32_t nquad;                     // 4-element quads in the slice
     float scale;
-    ReduceRest rest;
+    Pointers<R> all;
 };
+static_assert(sizeof(ReduceArgs<12>) == kFewBytes, "up to 12 contributions");
+// Pointer `r` of those behind the leading arguments, of which there may be none.
+__device__ __forceinline__ uint64_t behind(uint32_t) { return 0; }
+template <uint32_t N>
+__device__ __forceinline__ uint64_t behind(uint32_t r, const Pointers<N> &p) { return p.g[r]; }
 
 // The forms of a launch: contributions in flight (chunk), quads per lane, and whether the sum that is accumulated onto is requested
 // behind the contributions instead of ahead of them.
@@ -300,29 +312,30 @@ __device__ __forceinline__ void reduce(uint64_t out, uint32_t nquad, float scale
 // wavefront starts: leading arguments that are no structs arrive there (the build asks for 14 words; vectors, because the host spends 15 ns
 // on every argument).  With all of it read from the argument block, us: bf16 R = 4 / 8 of 2.1 M elements 5.8 / 8.2 (here 5.5 / 8.1), R = 32
 // of 0.5 M 7.4 (6.9), R = 8 of 25 M 76.6 (75.8); fp32 R = 4 accumulating, 1 / 6.3 M 6.0 / 25.1 (5.8 / 25.0).
-template <uint32_t R, bool G32, bool ACC, ReduceForm FORM>
-__global__ __launch_bounds__(kWave) void reduce_kernel(const u64x4 g, const u64x2 o, const ReduceRest rest)
+// REST is Pointers<R - 4>, or nothing.
+template <uint32_t R, bool G32, bool ACC, ReduceForm FORM, class... REST>
+__global__ __launch_bounds__(kWave) void reduce_kernel(const u64x4 g, const u64x2 o, const REST... rest)
 {
     constexpr uint32_t CHUNK = reduce_chunk(R, FORM);
     uint64_t at[CHUNK];
 #pragma unroll
-    for (uint32_t c = 0; c < CHUNK; ++c) at[c] = c >= R ? 0 : c < 4 ? g[c] : rest.g[c];
+    for (uint32_t c = 0; c < CHUNK; ++c) at[c] = c >= R ? 0 : c < 4 ? g[c] : behind(c - 4, rest...);
     reduce<R, G32, ACC, FORM>(o[0], (uint32_t)o[1], __uint_as_float((uint32_t)(o[1] >> 32)), at,
-                              [&](uint32_t r) { return r < 4 ? g[r] : rest.g[r]; });
+                              [&](uint32_t r) { return r < 4 ? g[r] : behind(r - 4, rest...); });
 }
 
 // The same with all of it read from the argument block in one round of scalar loads, for the launches of reduce_from_block().
 template <uint32_t R, bool G32, bool ACC, ReduceForm FORM>
-__global__ __launch_bounds__(kWave) void reduce_block_kernel(const ReduceArgs a)
+__global__ __launch_bounds__(kWave) void reduce_block_kernel(const ReduceArgs<R> a)
 {
     constexpr uint32_t CHUNK = reduce_chunk(R, FORM);
     uint64_t out = a.out, at[CHUNK];
     uint32_t nquad = a.nquad;
     float scale = a.scale;
 #pragma unroll
-    for (uint32_t c = 0; c < CHUNK; ++c) at[c] = c < R ? a.rest.g[c] : 0;
+    for (uint32_t c = 0; c < CHUNK; ++c) at[c] = c < R ? a.all.g[c] : 0;
     pin(out, at[0], at[1], at[CHUNK > 2 ? 2 : 0], at[CHUNK > 2 ? 3 : 0], nquad, scale);
-    reduce<R, G32, ACC, FORM>(out, nquad, scale, at, [&](uint32_t r) { return a.rest.g[r]; });
+    reduce<R, G32, ACC, FORM>(out, nquad, scale, at, [&](uint32_t r) { return a.all.g[r]; });
 }
 
 // ---------------------------------------------------------------------------------------
@@ -856,41 +869,55 @@ template <class T>
 struct AsIs {
     typedef T type;
 };
+// Launches a kernel whose arguments lie at `args`; it reads as many bytes there as its own parameters have.
+template <class... P>
+static hzp_status_t start_any(const char *who, const void *kernel, dim3 grid, dim3 block, unsigned lds, hipStream_t stream, const P *...args)
+{
+    void *ptrs[] = {const_cast<void *>(static_cast<const void *>(args))...};
+    (void)hipLaunchKernel(kernel, grid, block, ptrs, lds, stream);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return fail(HZP_ERR_HIP, "%s: launch failed: %s", who, hipGetErrorString(e));
+    return HZP_OK;
+}
 // Launches `kernel`.  (The <<<>>> form first pushes the launch shape for a stub that pops it again: 0.1 us more a launch.)
 template <class... P>
 static hzp_status_t start(const char *who, void (*kernel)(P...), dim3 grid, dim3 block, unsigned lds, hipStream_t stream,
                           const typename AsIs<P>::type &...args)
 {
-    void *ptrs[] = {const_cast<void *>(static_cast<const void *>(&args))...};
-    (void)hipLaunchKernel(reinterpret_cast<const void *>(kernel), grid, block, ptrs, lds, stream);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return fail(HZP_ERR_HIP, "%s: launch failed: %s", who, hipGetErrorString(e));
-    return HZP_OK;
+    return start_any(who, reinterpret_cast<const void *>(kernel), grid, block, lds, stream, &args...);
 }
 
 // One kernel per number of contributions: the loads of a chunk are then straight-line code (a run-time R
 // puts a wait between any two of them), and all of a launch's pointers arrive in one round of scalar loads.
 // (the other forms are for more than 8 contributions)
-typedef void (*ReduceKernel)(u64x4, u64x2, ReduceRest);
-typedef void (*ReduceBlockKernel)(ReduceArgs);
-template <bool G32, bool ACC, ReduceForm FORM, size_t... I>
-static constexpr std::array<ReduceKernel, sizeof...(I)> reduce_kernels(std::index_sequence<I...>)
+typedef std::array<const void *, HZP_MAX_REPLICAS> KernelOfR;
+template <uint32_t R, bool G32, bool ACC, ReduceForm FORM>
+static const void *reduce_kernel_of()
 {
-    return {reduce_kernel<I + 1, G32, ACC, I < 8 ? kReducePlain : FORM>...};
+    if constexpr (R <= 4)
+        return reinterpret_cast<const void *>(reduce_kernel<R, G32, ACC, FORM>);
+    else
+        return reinterpret_cast<const void *>(reduce_kernel<R, G32, ACC, FORM, Pointers<R - 4>>);
+}
+template <bool G32, bool ACC, ReduceForm FORM, size_t... I>
+static KernelOfR reduce_kernels(std::index_sequence<I...>)
+{
+    return {reduce_kernel_of<I + 1, G32, ACC, I < 8 ? kReducePlain : FORM>()...};
 }
 template <uint32_t R, bool G32, bool ACC, ReduceForm FORM>
-static constexpr ReduceBlockKernel reduce_block_kernel_of()
+static const void *reduce_block_kernel_of()
 {
     if constexpr (R <= 8 && FORM == kReduceNarrow)
         return nullptr;
     else
-        return reduce_block_kernel<R, G32, ACC, R <= 8 ? kReducePlain : FORM>;
+        return reinterpret_cast<const void *>(reduce_block_kernel<R, G32, ACC, R <= 8 ? kReducePlain : FORM>);
 }
 template <bool G32, bool ACC, ReduceForm FORM, size_t... I>
-static constexpr std::array<ReduceBlockKernel, sizeof...(I)> reduce_block_kernels(std::index_sequence<I...>)
+static KernelOfR reduce_block_kernels(std::index_sequence<I...>)
 {
     return {reduce_block_kernel_of<I + 1, G32, ACC, FORM>()...};
 }
+
 typedef void (*FusedKernel)(FusedArgs);
 typedef void (*FusedOneKernel)(u64x4, u64x2, uint64_t, FusedOneArgs);
 template <bool G32, bool O32, FusedForm FORM, ChunkClass CLASS, size_t... I>
@@ -981,15 +1008,13 @@ hzp_status_t launch_reduce(bool g32, const void *const *slices, uint32_t R, uint
     if (n == 0) return HZP_OK;
     const uint32_t es = g32 ? 4u : 2u;
     constexpr std::make_index_sequence<HZP_MAX_REPLICAS> all;
-    static constexpr std::array<ReduceKernel, HZP_MAX_REPLICAS> kernels[2][2][3] = {
+    static const KernelOfR kernels[2][2][3] = {
         {{reduce_kernels<false, false, kReducePlain>(all), reduce_kernels<false, false, kReduceFew>(all), {}},
          {reduce_kernels<false, true, kReducePlain>(all), reduce_kernels<false, true, kReduceFew>(all), {}}},
         {{reduce_kernels<true, false, kReducePlain>(all), reduce_kernels<true, false, kReduceFew>(all), reduce_kernels<true, false, kReduceNarrow>(all)},
          {reduce_kernels<true, true, kReducePlain>(all), reduce_kernels<true, true, kReduceFew>(all), reduce_kernels<true, true, kReduceNarrow>(all)}}};
-    static constexpr std::array<ReduceBlockKernel, HZP_MAX_REPLICAS> narrow_block[2] = {reduce_block_kernels<false, false, kReduceNarrow>(all),
-                                                                                        reduce_block_kernels<false, true, kReduceNarrow>(all)};
-    static constexpr std::array<ReduceBlockKernel, HZP_MAX_REPLICAS> short_block[2] = {reduce_block_kernels<false, false, kReduceFew>(all),
-                                                                                       reduce_block_kernels<true, false, kReduceFew>(all)};
+    static const KernelOfR narrow_block[2] = {reduce_block_kernels<false, false, kReduceNarrow>(all), reduce_block_kernels<false, true, kReduceNarrow>(all)};
+    static const KernelOfR short_block[2] = {reduce_block_kernels<false, false, kReduceFew>(all), reduce_block_kernels<true, false, kReduceFew>(all)};
     // Launches of about equal length; over a longer one the XCDs drift apart, as in the update below.
     const uint64_t launches = (n * (R * es + (accumulate ? 8u : 4u)) + most_reduce_bytes(R) - 1) / most_reduce_bytes(R);
     constexpr uint64_t kTwoGroups = 8 * kGroupQuads;        // what a wavefront with two quads per lane takes
@@ -1001,21 +1026,22 @@ hzp_status_t launch_reduce(bool g32, const void *const *slices, uint32_t R, uint
         const uint32_t quads = kGroupQuads * reduce_quads(R, g32, form);        // to a wavefront
         const dim3 grid((nquad + quads - 1) / quads), block(kWave);
         const unsigned lds = lds_for(form == kReduceNarrow ? 0 : reduce_waves(g32, R, here, accumulate));
-        ReduceArgs a;               // a kernel reads its R pointers, and of the first four whatever there is
+        ReduceArgs<HZP_MAX_REPLICAS> a;         // a kernel reads its R pointers, and of the first four whatever there is
         a.out = reinterpret_cast<uint64_t>(out + first);
         a.nquad = nquad;
         a.scale = scale;
-        uint64_t *const g = a.rest.g;
+        uint64_t *const g = a.all.g;
         for (uint32_t r = 0; r < R; ++r) g[r] = reinterpret_cast<uint64_t>(slices[r]) + first * es;
         for (uint32_t r = R; r < 4; ++r) g[r] = 0;
         hzp_status_t st;
         if (reduce_from_block(g32, R, form, here, accumulate)) {
-            st = start("hzp_reduce_shard", form == kReduceNarrow ? narrow_block[accumulate != 0][R - 1] : short_block[g32][R - 1], grid, block, lds, stream, a);
+            st = start_any("hzp_reduce_shard", form == kReduceNarrow ? narrow_block[accumulate != 0][R - 1] : short_block[g32][R - 1], grid, block, lds, stream, &a);
         } else {
             uint32_t scale_bits;
             std::memcpy(&scale_bits, &scale, sizeof scale_bits);
-            st = start("hzp_reduce_shard", kernels[g32][accumulate != 0][form][R - 1], grid, block, lds, stream, u64x4{g[0], g[1], g[2], g[3]},
-                       u64x2{a.out, nquad | (uint64_t)scale_bits << 32}, a.rest);
+            const u64x4 lead{g[0], g[1], g[2], g[3]};
+            const u64x2 o{a.out, nquad | (uint64_t)scale_bits << 32};
+            st = start_any("hzp_reduce_shard", kernels[g32][accumulate != 0][form][R - 1], grid, block, lds, stream, &lead, &o, g + 4);
         }
         if (st != HZP_OK) return st;
     }
