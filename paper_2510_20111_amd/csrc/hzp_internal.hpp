@@ -114,7 +114,7 @@ hzp_status_t launch_concat(const void *const *srcs, uint32_t n_shards, uint64_t 
 hzp_status_t launch_concat_layers(const void *const *srcs, uint32_t per_layer, const uint64_t *bytes_per_piece,
                                   void *const *dsts, uint32_t n_layers, hipStream_t stream);
 // Copies n pieces of different lengths: piece s goes from srcs[s] to dst + dst_off[s] (bytes, all
-// multiples of 16).
+// multiples of 16), one right behind the other.
 hzp_status_t launch_concat_ranges(const void *const *srcs, const uint64_t *dst_off, const uint64_t *bytes,
                                   uint32_t n, void *dst, hipStream_t stream);
 // Unpacks tensors [t_begin, t_end) of the bucket (indices in the bucket); tensors[0] is t_begin's.

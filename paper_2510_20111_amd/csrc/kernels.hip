@@ -637,10 +637,11 @@ struct CopyListArgs {
     uint64_t src[PIECES], dst[PIECES];
     uint32_t nvec[PIECES];                  // length in 16-byte vectors
 };
+typedef CopyListArgs<5> CopyLeastArgs;
 typedef CopyListArgs<8> CopyFewArgs;
 typedef CopyListArgs<64> CopyGroupArgs;
 typedef CopyListArgs<192> CopyManyArgs;
-static_assert(sizeof(CopyManyArgs) <= 4096, "kernel arguments");
+static_assert(sizeof(CopyManyArgs) <= 4096 && sizeof(CopyLeastArgs) <= kFewBytes, "kernel arguments");
 template <class Args>
 __global__ __launch_bounds__(kWave) void copy_list_kernel(const Args a)
 {
@@ -648,6 +649,23 @@ __global__ __launch_bounds__(kWave) void copy_list_kernel(const Args a)
     uint32_t nvec = a.nvec[blockIdx.y];
     pin(src, dst, nvec);
     copy_tile(blockIdx.x, src, dst, nvec);
+}
+
+// Up to 8 pieces of one bucket: all of one length, each to its place in the bucket.  grid = (tiles of a piece, pieces).
+struct CopyBucketArgs {
+    static constexpr uint32_t kPieces = 8;
+    uint64_t src[kPieces];
+    uint64_t dst;
+    uint64_t slots;                         // a piece's place in the bucket, 8 bits each
+    uint32_t nvec;
+};
+static_assert(sizeof(CopyBucketArgs) <= kFewBytes && HZP_MAX_GROUP <= 256, "kernel arguments");
+__global__ __launch_bounds__(kWave) void copy_bucket_kernel(const CopyBucketArgs a)
+{
+    uint64_t src = a.src[blockIdx.y], dst = a.dst, slots = a.slots;
+    uint32_t nvec = a.nvec;
+    pin(src, dst, slots, nvec);
+    copy_tile(blockIdx.x, src, dst + (slots >> (8 * blockIdx.y) & 255u) * nvec * 16, nvec);
 }
 
 // Many layers whose pieces lie at the same distances from the first layer's in every source (the layers of an arena, or
@@ -677,30 +695,35 @@ __global__ __launch_bounds__(kWave) void copy_shared_kernel(const CopySharedArgs
 // ZeRO-1 shards when the group sizes do not nest).  One-dimensional grid over the 64-vector tiles
 // of all pieces, so no workgroup is launched for nothing; a workgroup counts the pieces that end at or before
 // its tile, eight to a scalar load.
+// The pieces follow each other in the output.
 template <int PIECES>
 struct CopyRangesArgs {
     static constexpr int kPieces = PIECES;
+    uint64_t dst;
+    uint64_t src[PIECES];
     uint32_t tile_end[PIECES];              // running count of tiles up to and including the piece; ~0 behind the last
-    uint64_t src[PIECES], dst[PIECES];
-    uint32_t nvec[PIECES];
+    uint32_t vec[PIECES + 1];               // vectors ahead of the piece (modulo 2^32 behind the last)
     uint32_t n;
 };
+typedef CopyRangesArgs<6> CopyRangesFewArgs;
+static_assert(sizeof(CopyRangesFewArgs) <= kFewBytes && HZP_MAX_GROUP % 8 == 0, "kernel arguments");
 template <class Args>
 __global__ __launch_bounds__(kWave) void copy_ranges_kernel(const Args a)
 {
+    constexpr uint32_t kRound = Args::kPieces < 8 ? Args::kPieces : 8;
     uint32_t s = 0, first = 0;              // the workgroup's piece and its first tile
-    for (uint32_t i = 0; i < (Args::kPieces == 8 ? 8u : a.n); i += 8) {
+    for (uint32_t i = 0; i < (Args::kPieces == kRound ? kRound : a.n); i += kRound) {
 #pragma unroll
-        for (uint32_t k = 0; k < 8; ++k)
+        for (uint32_t k = 0; k < kRound; ++k)
             if (blockIdx.x >= a.tile_end[i + k]) {
                 s = i + k + 1;
                 first = a.tile_end[i + k];
             }
     }
-    uint64_t src = a.src[s], dst = a.dst[s];
-    uint32_t nvec = a.nvec[s];
-    pin(src, dst, nvec);
-    copy_tile(blockIdx.x - first, src, dst, nvec);
+    uint64_t src = a.src[s], dst = a.dst;
+    uint32_t begin = a.vec[s], end = a.vec[s + 1];
+    pin(src, dst, begin, end);
+    copy_tile(blockIdx.x - first, src, dst + (uint64_t)begin * 16, end - begin);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -730,7 +753,33 @@ struct UnpackListArgs {
     uint32_t n[PARTS];                  // elements
     uint32_t n_bucket[BOTH ? PARTS : 1];
     uint32_t tile_end[FLAT ? (PARTS + kWave - 1) / kWave * kWave : 1];      // running count of tiles; behind the last part ~0
+    template <int ES>
+    __device__ __forceinline__ void target(uint32_t part, uint64_t &to, uint32_t &count) const { to = dst[part], count = n[part]; }
 };
+template <int PARTS>
+struct UnpackListArgs<PARTS, false, false> {
+    static constexpr int kParts = PARTS;
+    static constexpr bool kBoth = false, kFlat = false;
+    uint64_t src[PARTS], dst[PARTS];
+    uint32_t n[PARTS];
+    template <int ES>
+    __device__ __forceinline__ void target(uint32_t part, uint64_t &to, uint32_t &count) const { to = dst[part], count = n[part]; }
+};
+// Up to 8 parts of one tensor, which follow each other there.
+struct UnpackTensorArgs {
+    static constexpr int kParts = 8;
+    static constexpr bool kBoth = false, kFlat = false;
+    uint64_t src[kParts], dst;
+    uint32_t begin[kParts + 1];         // elements of the tensor ahead of the part
+    template <int ES>
+    __device__ __forceinline__ void target(uint32_t part, uint64_t &to, uint32_t &count) const
+    {
+        const uint32_t first = begin[part], end = begin[part + 1];
+        to = dst + (uint64_t)first * ES, count = end - first;
+    }
+};
+static_assert(sizeof(UnpackTensorArgs) <= kFewBytes, "kernel arguments");
+typedef UnpackListArgs<5, false, false> UnpackList5;
 typedef UnpackListArgs<8, false, false> UnpackList8;
 typedef UnpackListArgs<72, false, false> UnpackList72;
 typedef UnpackListArgs<200, false, false> UnpackList200;
@@ -740,7 +789,7 @@ typedef UnpackListArgs<124, true, false> UnpackBoth124;
 typedef UnpackListArgs<64, true, true> UnpackBothFlat64;
 typedef UnpackListArgs<108, true, true> UnpackBothFlat108;
 static_assert(sizeof(UnpackList200) <= 4096 && sizeof(UnpackFlat160) <= 4096 && sizeof(UnpackBoth124) <= 4096 &&
-              sizeof(UnpackBothFlat108) <= 4096, "kernel arguments");
+              sizeof(UnpackBothFlat108) <= 4096 && sizeof(UnpackList5) <= kFewBytes, "kernel arguments");
 
 template <int ES, class Args>   // element size in bytes: 2 or 4
 __global__ __launch_bounds__(kWave) void unpack_list_kernel(const Args a)
@@ -760,8 +809,9 @@ __global__ __launch_bounds__(kWave) void unpack_list_kernel(const Args a)
         part = __builtin_amdgcn_readfirstlane(part);
         tile -= part ? a.tile_end[part - 1] : 0u;
     }
-    uint64_t src = a.src[part], dst = a.dst[part], bucket = 0;
-    uint32_t n = a.n[part], n_bucket = 0;
+    uint64_t src = a.src[part], dst, bucket = 0;
+    uint32_t n, n_bucket = 0;
+    a.template target<ES>(part, dst, n);
     if constexpr (Args::kBoth) {
         bucket = a.bucket[part];
         n_bucket = a.n_bucket[part];
@@ -1417,10 +1467,11 @@ static size_t units_of_launch(size_t left, size_t most, uint64_t rows, TilesAt t
     return all ? all : take_units(left, most, rows, kSurplusEven, kSurplusEven, tiles_at);
 }
 
-// One launch, with the smallest block that holds the pieces (buckets of 64 KiB to 1 MiB from 9 to 64 shards, call after call: 4.75 us
+// One launch, with the smallest block that holds the pieces (up to 5 stay within kFewBytes; buckets of 64 KiB to 1 MiB from 9 to 64 shards, call after call: 4.75 us
 // with the block of 192, 4.55 with the block of 64; up to 8 shards 4.4 with the block of 8).
 static hzp_status_t copy_one(const Move *moves, size_t n, hipStream_t stream, const char *who)
 {
+    if (n <= (size_t)CopyLeastArgs::kPieces) return copy_list<CopyLeastArgs>(moves, n, stream, who);
     if (n <= (size_t)CopyFewArgs::kPieces) return copy_list<CopyFewArgs>(moves, n, stream, who);
     if (n <= (size_t)CopyGroupArgs::kPieces) return copy_list<CopyGroupArgs>(moves, n, stream, who);
     return copy_list<CopyManyArgs>(moves, n, stream, who);
@@ -1444,14 +1495,26 @@ hzp_status_t launch_concat(const void *const *srcs, uint32_t n_shards, uint64_t 
     if (bytes_per_shard == 0) return HZP_OK;
     const uint64_t nvec = bytes_per_shard / 16;
     if (nvec > kMostVectors) return fail(HZP_ERR_UNSUPPORTED, "hzp_gather_layer: shard of 64 GiB or more");
+    const uint64_t to = reinterpret_cast<uint64_t>(dst);
+    CopyBucketArgs few;
+    few.dst = to;
+    few.slots = 0;
+    few.nvec = (uint32_t)nvec;
     Move moves[HZP_MAX_GROUP];
     size_t n = 0;
     for (uint32_t s = 0; s < n_shards; ++s) {
-        const uint64_t from = reinterpret_cast<uint64_t>(srcs[s]), to = reinterpret_cast<uint64_t>(dst) + s * bytes_per_shard;
-        if (from != to) moves[n++] = {from, to, nvec};          // else it lies in place
+        const uint64_t from = reinterpret_cast<uint64_t>(srcs[s]), place = to + s * bytes_per_shard;
+        if (from == place) continue;                            // it lies in place
+        if (n < few.kPieces) {
+            few.src[n] = from;
+            few.slots |= (uint64_t)s << (8 * n);
+        }
+        moves[n++] = {from, place, nvec};
     }
     // (one bucket's pieces stay one launch: cut into launches, 1.7-2.3 GB buckets copy no faster)
-    return n ? copy_one(moves, n, stream, "hzp_gather_layer") : HZP_OK;
+    if (n == 0) return HZP_OK;
+    if (n > few.kPieces) return copy_one(moves, n, stream, "hzp_gather_layer");
+    return start("hzp_gather_layer", copy_bucket_kernel, dim3((uint32_t)tiles_of(nvec), (uint32_t)n), dim3(kWave), 0, stream, few);
 }
 
 // Layers whose pieces lie at equal distances, in launches of kSharedLayers; *done is false (and nothing launched) where
@@ -1569,17 +1632,18 @@ hzp_status_t launch_concat_layers(const void *const *srcs, uint32_t per_layer, c
 }
 
 template <class Args>
-static hzp_status_t copy_ranges(const Move *moves, uint32_t n, uint32_t tiles, hipStream_t stream)
+static hzp_status_t copy_ranges(const Move *moves, uint32_t n, void *dst, uint32_t tiles, hipStream_t stream)
 {
     Args a;
     std::fill(std::begin(a.tile_end), std::end(a.tile_end), ~0u);
+    a.dst = reinterpret_cast<uint64_t>(dst);
     a.n = n;
-    uint32_t end = 0;
+    uint32_t end = 0, vec = 0;
     for (uint32_t s = 0; s < n; ++s) {
         a.src[s] = moves[s].src;
-        a.dst[s] = moves[s].dst;
-        a.nvec[s] = (uint32_t)moves[s].nvec;
         a.tile_end[s] = end += (uint32_t)tiles_of(moves[s].nvec);
+        a.vec[s] = vec;
+        a.vec[s + 1] = vec += (uint32_t)moves[s].nvec;
     }
     return start("hzp_gather_shard", copy_ranges_kernel<Args>, dim3(tiles), dim3(kWave), 0, stream, a);
 }
@@ -1601,8 +1665,9 @@ hzp_status_t launch_concat_ranges(const void *const *srcs, const uint64_t *dst_o
     if (total == 0) return HZP_OK;
     if (uniform) return launch_concat(srcs, n, bytes[0], dst, stream);     // equal whole pieces
     if (tiles > 0x7FFFFFFFull) return fail(HZP_ERR_UNSUPPORTED, "hzp_gather_shard: shard too large for one launch");
-    if (n <= 8) return copy_ranges<CopyRangesArgs<8>>(moves, n, (uint32_t)tiles, stream);
-    return copy_ranges<CopyRangesArgs<HZP_MAX_GROUP>>(moves, n, (uint32_t)tiles, stream);
+    if (n <= (uint32_t)CopyRangesFewArgs::kPieces) return copy_ranges<CopyRangesFewArgs>(moves, n, dst, (uint32_t)tiles, stream);
+    if (n <= 8) return copy_ranges<CopyRangesArgs<8>>(moves, n, dst, (uint32_t)tiles, stream);
+    return copy_ranges<CopyRangesArgs<HZP_MAX_GROUP>>(moves, n, dst, (uint32_t)tiles, stream);
 }
 
 // A run of elements to move; with a bucket beside the tensors, its place there and its length with the padding behind it.
@@ -1690,7 +1755,7 @@ static hzp_status_t unpack_list(const Parts &parts, size_t n, uint64_t cut, hipS
 }
 
 // Launches over a list of parts: each takes parts while they fit its table and hold no more than kMaxTilesPerLaunch tiles.
-// The smaller blocks save the host what they leave out (4 MB in 24 / 48 / 72 even parts, block of 72 / of 200, us: 4.9 / 5.1, 5.1 / 5.4, 5.3 / 5.5).
+// The smaller blocks save the host what they leave out (5 parts stay within kFewBytes; 4 MB in 24 / 48 / 72 even parts, block of 72 / of 200, us: 4.9 / 5.1, 5.1 / 5.4, 5.3 / 5.5).
 template <int ES, bool BOTH, class Parts>
 static hzp_status_t unpack_parts(const Parts &parts, size_t n, hipStream_t stream, const char *who)
 {
@@ -1735,12 +1800,28 @@ static hzp_status_t unpack_parts(const Parts &parts, size_t n, hipStream_t strea
             st = !cut                  ? (cnt <= 64 ? unpack_list<UnpackFlat64, ES>(first, cnt, longest, stream, who)
                                                     : unpack_list<UnpackFlat160, ES>(first, cnt, longest, stream, who))
                  : cut < longest || cnt > 72 ? unpack_list<UnpackList200, ES>(first, cnt, cut, stream, who)
+                 : cnt <= 5            ? unpack_list<UnpackList5, ES>(first, cnt, cut, stream, who)
                  : cnt <= 8            ? unpack_list<UnpackList8, ES>(first, cnt, cut, stream, who)
                                        : unpack_list<UnpackList72, ES>(first, cnt, cut, stream, who);
         if (st != HZP_OK) return st;
         at += cnt;
     }
     return HZP_OK;
+}
+
+// One tensor of below 2^32 elements in up to 8 parts of about equal length.
+template <int ES>
+static hzp_status_t unpack_tensor(const Piece *pieces, size_t n, const void *const *shards, void *tensor, uint64_t longest, hipStream_t stream)
+{
+    UnpackTensorArgs a;
+    a.dst = reinterpret_cast<uint64_t>(tensor);
+    a.begin[0] = 0;
+    for (size_t i = 0; i < n; ++i) {
+        a.src[i] = reinterpret_cast<uint64_t>(shards[pieces[i].shard]) + pieces[i].src_off * ES;
+        a.begin[i + 1] = (uint32_t)(pieces[i].dst_off + pieces[i].len);
+    }
+    const dim3 grid((uint32_t)std::max<uint64_t>(1, tiles_of(longest * ES / 16)), (uint32_t)n);
+    return start("hzp_gather_layer", unpack_list_kernel<ES, UnpackTensorArgs>, grid, dim3(kWave), 0, stream, a);
 }
 
 // What the launches of one unpacking call share.
@@ -1816,6 +1897,16 @@ hzp_status_t launch_unpack(const hzp_plan_t *plan, const BucketRec &b, const voi
         }
     }
     const Piece *const piece = b.pieces.data() + p0;
+    if (t_end - t_begin == 1 && n <= (size_t)UnpackTensorArgs::kParts) {
+        uint64_t total = 0, longest = 0;
+        for (size_t i = 0; i < n; ++i) {
+            total += piece[i].len;
+            longest = std::max(longest, piece[i].len);
+        }
+        const uint64_t tile = kWave * 16 / es;
+        if (total / tile <= kMaxTilesPerLaunch && even_parts(n, total, longest, tile))      // (what unpack_parts puts into one uncut launch)
+            return es == 4 ? unpack_tensor<4>(piece, n, shards, tensors[0], longest, stream) : unpack_tensor<2>(piece, n, shards, tensors[0], longest, stream);
+    }
     return es == 4 ? unpack_parts<4, false>(PieceParts<4>{piece, shards, tensors, t_begin}, n, stream, "hzp_gather_layer")
                    : unpack_parts<2, false>(PieceParts<2>{piece, shards, tensors, t_begin}, n, stream, "hzp_gather_layer");
 }

@@ -586,3 +586,82 @@ def test_reduction_in_chunks_of_different_sizes(R, g32):
             hzp.hzp_reduce_shard(plan, 0, 0, 1, 0, [x[:n] for x in g], 0.3, acc, out[:n], grad_dtype=gd)
             torch.cuda.synchronize()
             assert torch.equal(out[:n], in_order_sum([x[:n] for x in g], acc)) and bool((out[n:] == 0.5).all())
+
+
+def guarded(n, shift=0):
+    """n elements of -1 at `shift` elements behind a 16-byte boundary, with eight more on both sides."""
+    whole = torch.full((n + 24,), -1, dtype=torch.int16, device=DEV)
+    return whole, whole[8 + shift:8 + shift + n]
+
+
+def assert_only(whole, view, want):
+    torch.cuda.synchronize()
+    at = (view.data_ptr() - whole.data_ptr()) // 2
+    got = whole.cpu().numpy()
+    assert np.array_equal(got[at:at + len(want)], want)
+    assert (got[:at] == -1).all() and (got[at + len(want):] == -1).all()
+
+
+@pytest.mark.parametrize("numel", [5, 1023, 70001])
+@pytest.mark.parametrize("k", [1, 2, 4, 5, 6, 7, 8, 9, 10])
+def test_calls_of_few_pieces(k, numel):
+    """Numbers of pieces around those whose argument blocks are the smallest: buckets (a shard in place or none), several layers' shards,
+    one tensor and several tensors, all to the bit and nothing beside them."""
+    print(k, numel, flush=True)
+    rng = np.random.default_rng(k + numel)
+    # one bucket of k shards, which holds one tensor
+    plan = hzp.hzp_plan([1], [numel * k], align=8, z3=k, z1=k)
+    s3 = plan.bucket(0).s3
+    host = rng.integers(0, 30000, (k, s3)).astype(np.int16)
+    shards = [to_dev(h) for h in host]
+    for own in {None, 0, k - 1}:
+        whole, out = guarded(k * s3)
+        given = [out[j * s3:(j + 1) * s3] if j == own else s for j, s in enumerate(shards)]
+        if own is not None:
+            given[own].copy_(shards[own])
+        hzp.hzp_gather_layer(plan, 0, 0, 3, given, out, None)
+        assert_only(whole, out, host.reshape(-1))
+    for shift in (0, 1, 5):
+        whole, out = guarded(numel * k, shift)
+        hzp.hzp_gather_tensor(plan, 0, shards, out)
+        assert_only(whole, out, host.reshape(-1)[:numel * k])
+    # the middle one of three tensors, whose first and last parts are short
+    plan = hzp.hzp_plan([3], [numel, numel * k, 3], align=8, z3=k + 1, z1=k + 1)
+    info, s3 = plan.tensor(1), plan.bucket(0).s3
+    host = rng.integers(0, 30000, (k + 1, s3)).astype(np.int16)
+    for shift in (0, 3):
+        whole, out = guarded(numel * k, shift)
+        hzp.hzp_gather_tensor(plan, 1, [to_dev(h) for h in host], out)
+        assert_only(whole, out, host.reshape(-1)[info.offset:info.offset + numel * k])
+    # k tensors of one shard
+    plan = hzp.hzp_plan([k], [numel + t for t in range(k)], align=8, z3=1, z1=1)
+    host = rng.integers(0, 30000, plan.bucket(0).s3).astype(np.int16)
+    outs = [guarded(numel + t, t % 8) for t in range(k)]
+    hzp.hzp_gather_layer(plan, 0, 0, 3, [to_dev(host)], None, [o for _, o in outs])
+    for t, (whole, out) in enumerate(outs):
+        at = plan.tensor(t).offset
+        assert_only(whole, out, host[at:at + numel + t])
+    # several layers' shards, k pieces in all
+    for layers in {n for n in (1, 2, 3, k) if k % n == 0}:
+        plan = hzp.hzp_plan([1] * layers, [numel * (n + 1) for n in range(layers)], align=8, z3=1, z1=k // layers)
+        sizes = [plan.bucket(n).s1 for n in range(layers)]
+        host = [rng.integers(0, 30000, (k // layers, n)).astype(np.int16) for n in sizes]
+        outs = [guarded(h.size) for h in host]
+        hzp.hzp_gather_layers(plan, 0, layers, 0, 1, [to_dev(x) for h in host for x in h], k // layers, [o for _, o in outs])
+        for h, (whole, out) in zip(host, outs):
+            assert_only(whole, out, h.reshape(-1))
+
+
+@pytest.mark.parametrize("z1,z3", [(3, 2), (7, 2), (9, 2), (11, 2), (13, 2), (15, 2), (17, 2), (31, 2), (64, 3)])
+def test_shard_from_few_and_many_owners(z1, z3):
+    """2 to 9 and more whole and partial pieces: those that the smallest argument block holds, one more, one list of eight and longer."""
+    print(z1, z3, flush=True)
+    rng = np.random.default_rng(z1)
+    plan = hzp.hzp_plan([1], [90001], align=8, z3=z3, z1=z1)
+    b = plan.bucket(0)
+    bucket = rng.integers(0, 30000, b.padded).astype(np.int16)
+    for j in range(z3):
+        first, n = plan.cover(0, 0, j)
+        whole, out = guarded(b.s3)
+        hzp.hzp_gather_shard(plan, 0, 0, j, [to_dev(bucket[(first + q) * b.s1:(first + q + 1) * b.s1]) for q in range(n)], out)
+        assert_only(whole, out, bucket[j * b.s3:(j + 1) * b.s3])
