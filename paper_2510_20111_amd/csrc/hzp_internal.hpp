@@ -44,6 +44,7 @@ struct BucketRec {
     std::vector<Piece> pieces;
     uint32_t n_chunks;
     uint32_t piece_slot;    // first entry of this bucket in the device piece table
+    uint32_t tensor_slot;   // and in the device table of the tensors' spans
 };
 
 // Lookup tables of one plan on one device.
@@ -53,6 +54,7 @@ struct DeviceTables {
     float *run_wd = nullptr;
     Piece *pieces = nullptr;            // all buckets' pieces, bucket after bucket
     uint32_t *piece_chunk = nullptr;    // chunk_begin of the same pieces, densely packed
+    uint32_t *span = nullptr;           // begin and end of each tensor in its bucket (behind piece_chunk, in the same allocation)
 };
 
 #ifndef HZP_UNPACK_CHUNK

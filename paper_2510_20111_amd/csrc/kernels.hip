@@ -843,6 +843,74 @@ __global__ __launch_bounds__(kWave) void unpack_list_kernel(const Args a)
     }
 }
 
+// Tensors that lie in one buffer as they do in the bucket (its parameters are views of a flat buffer of the same alignment): every
+// vector's place is known without its tensor, and which of its elements belong to one is looked up while the data arrive, in the plan's
+// device table of the tensors' begins and ends.  Up to 8 shards.  grid = (tiles of a shard, shards).
+// One round of memory instead of a list's two (three in a flat grid), and a block of 96 bytes whatever the number of tensors.
+struct UnpackPlacedArgs {
+    static constexpr uint32_t kShards = 8;
+    uint64_t src[kShards];
+    uint64_t dst;                       // of bucket position 0
+    uint64_t bucket;                    // BOTH: the layer bucket
+    const u32x2 *span;                  // device: begin and end of each tensor in the bucket, in elements
+    uint32_t n;                         // tensors
+    uint32_t nvec;                      // vectors of a shard
+    uint32_t end;                       // of the last tensor
+};
+static_assert(sizeof(UnpackPlacedArgs) <= kFewBytes, "kernel arguments");
+
+// FEW: at most 64 tensors, whose spans are asked for together with the data; else 64 pivots a round lead to the first that a tile meets (asking
+// for up to 256 spans at once, four a lane, took as long: 100 tensors of 0.07 MB 2.61 us, with pivots 2.46).
+template <int ES, bool BOTH, bool FEW>
+__global__ __launch_bounds__(kWave) void unpack_placed_kernel(const UnpackPlacedArgs a)
+{
+    constexpr uint32_t VE = 16 / ES, TILE = kWave * VE;         // elements of a vector, of a tile
+    typedef typename std::conditional<ES == 2, uint16_t, uint32_t>::type elem_t;
+    typedef const __attribute__((address_space(1))) u32x2 *spans;
+    typedef __attribute__((address_space(1))) elem_t *elements_out;
+    uint64_t src = a.src[blockIdx.y], dst = a.dst, bucket = BOTH ? a.bucket : 0, table = reinterpret_cast<uint64_t>(a.span);
+    uint32_t nvec = a.nvec, n = a.n, end = a.end;
+    pin(src, dst, bucket, table, nvec, n, end);
+    const uint32_t lane = threadIdx.x, vec = blockIdx.x * kWave + lane;
+    const uint32_t first = (blockIdx.y * nvec + blockIdx.x * kWave) * VE, mine = first + lane * VE;     // bucket positions
+    if (!BOTH && first >= end) return;  // padding behind the last tensor
+    const u32x4 val = ld_stream<u32x4>(src, vec < nvec ? vec : nvec - 1);
+    uint32_t at = 0;                    // no tensor ahead of this one meets the tile
+    for (uint32_t left = n; !FEW && left > kWave;) {
+        const uint32_t stride = (left + kWave - 1) / kWave, off = lane * stride;
+        const bool le = off < left && ((spans)table)[at + off][0] <= first;
+        const uint32_t step = ((uint32_t)__popcll(__ballot(le)) - 1u) * stride;
+        left = left - step < stride ? left - step : stride;
+        at += step;
+    }
+    uint32_t until = 0;                 // end of the tensor that the lane's vector belongs to
+    for (;;) {
+        const uint32_t here = n - at;   // (64 tensors at a time; a tile meets up to 65)
+        const u32x2 span = ((spans)table)[at + (lane < here ? lane : here - 1)];
+        const bool is = lane < here;
+        uint32_t ahead = (uint32_t)__popcll(__ballot(is && span[0] <= first));         // begin up to the tile's first element,
+        uint32_t met = (uint32_t)__popcll(__ballot(is && span[0] < first + TILE));     // up to its last
+        ahead = __builtin_amdgcn_readfirstlane(ahead);
+        met = __builtin_amdgcn_readfirstlane(met);
+        for (uint32_t k = ahead - (ahead != 0); k < met; ++k) {
+            const uint32_t b = __builtin_amdgcn_readlane(span[0], k), e = __builtin_amdgcn_readlane(span[1], k);
+            until = mine >= b ? e : until;
+        }
+        if (FEW || met < (uint32_t)kWave || here <= (uint32_t)kWave) break;
+        at += kWave;
+    }
+    if (vec >= nvec) return;
+    if (BOTH && src != bucket + (uint64_t)(blockIdx.y * nvec) * 16) st_writethrough(bucket, mine * ES, __builtin_bit_cast(f32x4, val));        // (else it lies in place)
+    if (mine >= until) return;
+    if (until - mine >= VE) {
+        st_writethrough(dst, mine * ES, __builtin_bit_cast(f32x4, val));
+    } else {                            // the tensor's last elements
+#pragma unroll
+        for (uint32_t e = 0; e < VE - 1; ++e)
+            if (mine + e < until) ((elements_out)dst)[mine + e] = (elem_t)(ES == 4 ? val[e] : val[e / 2] >> (e % 2 * 16));
+    }
+}
+
 // The same for buckets of very many tensors in short copies: one single-wavefront workgroup per chunk of at most
 // kUnpackChunk elements of one piece (a run of one tensor inside one shard), found in the plan's device tables, so that a
 // launch covers 400 tensors whatever their sizes.
@@ -1873,6 +1941,64 @@ static hzp_status_t launch_unpack_with(const UnpackCall &u, void *const *tensors
     return HZP_OK;
 }
 
+// Do all tensors of the bucket lie in one buffer as they do in the bucket?  Then *origin is where position 0 would be.
+static bool placed_as_in_bucket(const hzp_plan_t *plan, const BucketRec &b, void *const *tensors, uint32_t es, uint64_t *origin)
+{
+    auto place = [&](uint32_t t) { return reinterpret_cast<uint64_t>(tensors[t]) - plan->tensors[b.tensor_ids[t]].offset * es; };
+    *origin = place(0);
+    if (*origin % 16) return false;
+    for (uint32_t t = 1; t < b.n_tensors; ++t)
+        if (place(t) != *origin) return false;
+    return true;
+}
+
+// Is the one launch of unpack_placed the better way to write the bucket's tensors, where lists would hold `n` pieces?  Lists / placed, us, calls
+// in a row (collisions of kFewBytes included) and on the device alone (graph):
+//   up to 64 tensors: 6 / 9 / 64 of 0.04-0.1 MB in all 4.2 / 3.8, 4.3 / 3.9, 4.4 / 4.0 and 2.07 / 2.16, 2.08 / 2.12, 2.24 / 2.18, 9 of 1.8 / 18 / 360 MB
+//   4.35 / 3.8, 7.8 / 7.5, 107 / 106 and 3.02 / 2.80, 7.9 / 7.75, 108.7 / 107.8; even ones 2.01 / 2.05 and 3.59 / 3.57 on the device, from 20 MB the same.
+//   more, where lists are one launch: 100 uneven ones of 0.07 / 2 / 20 MB 2.28 / 2.46, 3.5 / 3.1, 9.4 / 9.7 on the device, even ones 2.1 / 2.4, 2.9 / 3.0, 8.3 / 9.3.
+//   more, where lists are several launches (or tables): 170 of 3.4 / 30 / 340 MB 4.4 / 3.7, 14.9 / 13.3, 110 / 111; 400 of 8 / 80 MB 6.6 / 5.9, 30 / 30; 1000 of
+//   0.7 / 20 / 200 MB 8.4 / 2.9, 17.9 / 11.4, 79 / 73.
+static bool placed_pays(const BucketRec &b, const Piece *piece, size_t n, uint32_t n_shards, uint32_t es)
+{
+    const uint64_t bytes = b.P * es;
+    if (n_shards > UnpackPlacedArgs::kShards || bytes >= 1ull << 32) return false;      // (kernels address with 32 bits)
+    uint64_t total = 0, longest = 0;
+    for (size_t i = 0; i < n; ++i) {
+        total += piece[i].len;
+        longest = std::max(longest, piece[i].len);
+    }
+    const bool even = n <= (size_t)UnpackList200::kParts && even_parts(n, total, longest, kWave * 16 / es);
+    if (b.n_tensors <= (uint32_t)kWave) return !even || bytes <= 4u << 20;
+    if (even) return false;
+    const size_t launches = (n + UnpackFlat160::kParts - 1) / UnpackFlat160::kParts;
+    return launches == 1 ? bytes >= 512u << 10 && bytes <= 4u << 20 : bytes <= launches * (8u << 20);
+}
+// The same with the bucket written too, where lists (`one_pass`) are one launch; else there are two passes: 100 tensors of 0.07 / 2 / 20 / 200 MB 3.8 / 2.5, 6.2 /
+// 3.2, 16.9 / 12.9, 124 / 97, 170 of 340 MB 209 / 162, 1000 of 0.7 / 200 MB 11 / 3.0, 139 / 106.  In one launch of lists: 6 / 30 of 0.04-0.07 MB 2.04 / 2.16, 2.07 / 2.19 on the
+// device and 4.35 / 3.8, 4.8 / 3.9 in a row, 9 of 1.8 / 18 / 360 MB 3.5 / 3.1, 11.2 / 10.7, 172 / 173; 100 even ones of 0.08 / 2 / 20 MB 2.1 / 2.4, 3.2 / 3.1, 11.6 / 12.4.
+static bool placed_pays_both(const BucketRec &b, uint32_t n_shards, uint32_t es, bool one_pass)
+{
+    const uint64_t bytes = b.P * es;
+    if (n_shards > UnpackPlacedArgs::kShards || bytes >= 1ull << 32) return false;
+    return !one_pass || (bytes <= 4u << 20 && (b.n_tensors <= (uint32_t)kWave || bytes >= 512u << 10));
+}
+
+template <int ES, bool BOTH>
+static hzp_status_t unpack_placed(const DeviceTables &tab, const BucketRec &b, const void *const *shards, uint32_t n_shards, uint64_t origin, void *bucket, hipStream_t stream)
+{
+    UnpackPlacedArgs a;
+    for (uint32_t j = 0; j < n_shards; ++j) a.src[j] = reinterpret_cast<uint64_t>(shards[j]);
+    a.dst = origin;
+    a.bucket = reinterpret_cast<uint64_t>(bucket);
+    a.span = reinterpret_cast<const u32x2 *>(tab.span) + b.tensor_slot;
+    a.n = b.n_tensors;
+    a.nvec = (uint32_t)(b.S3 * ES / 16);
+    a.end = (uint32_t)b.payload_end;
+    const auto kernel = b.n_tensors <= (uint32_t)kWave ? unpack_placed_kernel<ES, BOTH, true> : unpack_placed_kernel<ES, BOTH, false>;
+    return start("hzp_gather_layer", kernel, dim3((uint32_t)tiles_of(a.nvec), n_shards), dim3(kWave), 0, stream, a);
+}
+
 hzp_status_t launch_unpack(const hzp_plan_t *plan, const BucketRec &b, const void *const *shards,
                            uint32_t n_shards, void *const *tensors, uint32_t t_begin, uint32_t t_end,
                            hipStream_t stream)
@@ -1882,6 +2008,10 @@ hzp_status_t launch_unpack(const hzp_plan_t *plan, const BucketRec &b, const voi
     const DeviceTables *tab = nullptr;
     const hzp_status_t st = device_tables(plan, &tab);
     if (st != HZP_OK) return st;
+    uint64_t origin = 0;
+    if (n > (size_t)UnpackList5::kParts && t_end - t_begin == b.n_tensors && placed_as_in_bucket(plan, b, tensors, es, &origin) &&
+        placed_pays(b, b.pieces.data(), n, n_shards, es))
+        return es == 4 ? unpack_placed<4, false>(*tab, b, shards, n_shards, origin, nullptr, stream) : unpack_placed<2, false>(*tab, b, shards, n_shards, origin, nullptr, stream);
     if (n > (size_t)UnpackFlat160::kParts) {            // (fewer are one launch)
         uint64_t total = 0;
         size_t longest = p0;
@@ -1926,6 +2056,9 @@ hzp_status_t launch_unpack_both(const hzp_plan_t *plan, const BucketRec &b, cons
     const DeviceTables *tab = nullptr;
     hzp_status_t st = device_tables(plan, &tab);
     if (st != HZP_OK) return st;
+    uint64_t origin = 0;
+    if (placed_pays_both(b, n_shards, es, one_pass) && placed_as_in_bucket(plan, b, tensors, es, &origin))
+        return es == 4 ? unpack_placed<4, true>(*tab, b, shards, n_shards, origin, bucket, stream) : unpack_placed<2, true>(*tab, b, shards, n_shards, origin, bucket, stream);
     if (!one_pass) {
         st = launch_concat(shards, n_shards, b.S3 * es, bucket, stream);
         if (st != HZP_OK) return st;
@@ -2072,9 +2205,17 @@ hzp_status_t device_tables(const hzp_plan_t *plan, const DeviceTables **out)
     e = upload((void **)&t.run_off, plan->run_off.data(), nr * sizeof(uint64_t));
     if (e == hipSuccess) e = upload((void **)&t.run_wd, plan->run_wd.data(), nr * sizeof(float));
     if (e == hipSuccess) e = upload((void **)&t.pieces, all.data(), all.size() * sizeof(Piece));
-    std::vector<uint32_t> chunk_begin(all.size());
+    std::vector<uint32_t> chunk_begin(all.size() + all.size() % 2);         // and behind them the tensors' spans
     for (size_t i = 0; i < all.size(); ++i) chunk_begin[i] = all[i].chunk_begin;
+    const size_t span_at = chunk_begin.size();
+    for (const BucketRec &b : plan->buckets)
+        for (uint32_t id : b.tensor_ids) {
+            const TensorRec &r = plan->tensors[id];
+            chunk_begin.push_back((uint32_t)r.offset);              // (read only where the bucket is short)
+            chunk_begin.push_back((uint32_t)(r.offset + r.numel));
+        }
     if (e == hipSuccess) e = upload((void **)&t.piece_chunk, chunk_begin.data(), chunk_begin.size() * sizeof(uint32_t));
+    t.span = t.piece_chunk + span_at;
     if (e != hipSuccess) {
         (void)hipFree(t.piece_chunk);
         (void)hipFree(t.run_off);

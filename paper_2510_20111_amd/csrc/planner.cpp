@@ -146,7 +146,7 @@ extern "C" hzp_status_t hzp_plan(const hzp_plan_desc_t *d, hzp_plan_t **out)
         p->bucket_of.assign((size_t)d->n_layers * 2, -1);
         const uint64_t quantum = (uint64_t)A * world;     // every level's shard is a multiple of A
         uint64_t base = 0;
-        uint32_t tid0 = 0, piece_slot = 0;
+        uint32_t tid0 = 0, piece_slot = 0, tensor_slot = 0;
         for (uint32_t l = 0; l < d->n_layers; ++l) {
             const uint32_t cnt = d->tensors_per_layer[l];
             for (uint32_t cls = 0; cls < 2; ++cls) {
@@ -185,6 +185,8 @@ extern "C" hzp_status_t hzp_plan(const hzp_plan_desc_t *d, hzp_plan_t **out)
                 b.S2 = b.P / z2;
                 b.S1 = b.P / d->z1;
                 b.piece_slot = piece_slot;
+                b.tensor_slot = tensor_slot;
+                tensor_slot += b.n_tensors;
                 if (!build_pieces(p, b)) {
                     delete p;
                     return fail(HZP_ERR_UNSUPPORTED, "hzp_plan: layer %u is too large to unpack", l);

@@ -665,3 +665,80 @@ def test_shard_from_few_and_many_owners(z1, z3):
         whole, out = guarded(b.s3)
         hzp.hzp_gather_shard(plan, 0, 0, j, [to_dev(bucket[(first + q) * b.s1:(first + q + 1) * b.s1]) for q in range(n)], out)
         assert_only(whole, out, bucket[j * b.s3:(j + 1) * b.s3])
+
+
+def lengths(kind, n, rng):
+    """n tensor lengths: of 1 to 8 elements (a tile of 512 meets 65 of them at an alignment of 8), alike, or very different."""
+    return [int(x) for x in {"tiny": lambda: rng.integers(1, 9, n), "even": lambda: np.full(n, 1003),
+                             "spread": lambda: np.maximum(1, np.exp(rng.normal(6.5, 1.5, n)))}[kind]()]
+
+
+@pytest.mark.parametrize("cls", [0, 1])
+@pytest.mark.parametrize("z3", [1, 3, 8, 9])
+@pytest.mark.parametrize("kind,n", [("tiny", 6), ("tiny", 64), ("tiny", 65), ("tiny", 700), ("even", 7), ("even", 64), ("even", 300),
+                                    ("spread", 3), ("spread", 40), ("spread", 64), ("spread", 65), ("spread", 129), ("spread", 500)])
+def test_tensors_that_lie_as_in_the_bucket(kind, n, z3, cls):
+    """Views of one flat buffer at the bucket's own offsets (one pass over the bucket, each vector's tensor looked up), and the same with one
+    tensor elsewhere (lists): tensors, gaps between them untouched, with and without the bucket, a shard in place or none, in or beside the bucket."""
+    print(kind, n, z3, cls, flush=True)
+    rng = np.random.default_rng(n * 31 + z3)
+    numel = lengths(kind, n, rng)
+    plan = hzp.hzp_plan([n], numel, align=8, z3=z3, z1=z3, tensor_class=[cls] * n)
+    b = plan.bucket(0, cls)
+    dtype = torch.int32 if cls else torch.int16
+    host = rng.integers(0, 30000, b.padded).astype(np.int32 if cls else np.int16)
+    at = [plan.tensor(t).offset for t in range(n)]
+    inside = np.zeros(b.padded, dtype=bool)
+    for a, k in zip(at, numel):
+        inside[a:a + k] = True
+    whole = to_dev(host)
+    shards = [whole[j * b.s3:(j + 1) * b.s3].clone() for j in range(z3)]
+    for moved in (None, n // 2):
+        for own in (False, None, 0, z3 - 1):                # False: no bucket
+            flat = torch.full((b.padded + 16,), -1, dtype=dtype, device=DEV)
+            views = [flat[8 + a:8 + a + k] for a, k in zip(at, numel)]
+            apart = torch.full((numel[n // 2] + 1,), -1, dtype=dtype, device=DEV)
+            if moved is not None:
+                views[moved] = apart[1:]
+            bucket = None if own is False else torch.full((b.padded,), -1, dtype=dtype, device=DEV)
+            given = list(shards)
+            if own is not None and own is not False:
+                given[own] = bucket[own * b.s3:(own + 1) * b.s3]
+                given[own].copy_(shards[own])
+            hzp.hzp_gather_layer(plan, 0, cls, 3, given, bucket, views)
+            torch.cuda.synchronize()
+            want = np.where(inside, host, -1)
+            if moved is not None:
+                want[at[moved]:at[moved] + numel[moved]] = -1
+                assert np.array_equal(apart.cpu().numpy()[1:], host[at[moved]:at[moved] + numel[moved]]) and int(apart[0]) == -1
+            got = flat.cpu().numpy()
+            assert np.array_equal(got[8:-8], want) and (got[:8] == -1).all() and (got[-8:] == -1).all()
+            if bucket is not None:
+                assert np.array_equal(bucket.cpu().numpy(), host)
+    bucket = torch.full((b.padded,), -1, dtype=dtype, device=DEV)          # the tensors are views of the bucket
+    hzp.hzp_gather_layer(plan, 0, cls, 3, shards, bucket, [bucket[a:a + k] for a, k in zip(at, numel)])
+    torch.cuda.synchronize()
+    assert np.array_equal(bucket.cpu().numpy(), host)
+
+
+@pytest.mark.parametrize("numel,both,launches", [([1000] * 9, False, 1), ([300000] * 9, False, 1), ([200, 90000] * 5, False, 1), ([3000] * 100, False, 1),
+                                                 ([100, 9000] * 50, False, 1), ([100, 90000] * 50, False, 1), ([100, 9000] * 300, False, 1),
+                                                 ([9000] * 200, True, 1), ([1000] * 9, True, 1), ([300000] * 9, True, 1)])
+def test_every_choice_between_lists_and_the_bucket_s_own_layout(numel, both, launches):
+    """Sizes on both sides of each line of the choice, from 3 shards, to the bit and in one launch."""
+    n = len(numel)
+    plan = hzp.hzp_plan([n], numel, align=64, z3=3, z1=3)
+    plan.prepare()
+    b = plan.bucket(0)
+    whole = torch.randint(0, 30000, (b.padded,), dtype=torch.int16, device=DEV)
+    shards = [whole[j * b.s3:(j + 1) * b.s3].clone() for j in range(3)]
+    flat = torch.full((b.padded,), -1, dtype=torch.int16, device=DEV)
+    views = [flat[plan.tensor(t).offset:plan.tensor(t).offset + numel[t]] for t in range(n)]
+    bucket = torch.empty_like(whole) if both else None
+    got = launches_of(lambda: hzp.hzp_gather_layer(plan, 0, 0, 3, shards, bucket, views))
+    assert len(got) == launches
+    hzp.hzp_gather_layer(plan, 0, 0, 3, shards, bucket, views)
+    torch.cuda.synchronize()
+    for t, v in enumerate(views):
+        assert torch.equal(v, whole[plan.tensor(t).offset:plan.tensor(t).offset + numel[t]]), t
+    assert not both or torch.equal(bucket, whole)
