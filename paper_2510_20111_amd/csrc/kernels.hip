@@ -371,7 +371,11 @@ struct FusedOneArgs {
     uint64_t out;
     AdamScalars scalars;
     uint64_t g[HZP_MAX_REPLICAS];
+    static constexpr size_t kScalars = 8;       // where the scalars lie behind the leading arguments
+    __device__ __forceinline__ uint64_t output() const { return out; }
+    __device__ __forceinline__ uint64_t contribution(uint32_t r) const { return g[r]; }
 };
+static_assert(offsetof(FusedOneArgs, scalars) == FusedOneArgs::kScalars, "argument block");
 struct FusedLead {
     u64x4 p;                                // master, m, v, the first contribution
     u64x2 w;                                // the second, the step's scalars in device memory (or null: they are in the block)
@@ -379,6 +383,28 @@ struct FusedLead {
 };
 constexpr uint32_t kLeadBytes = 56;         // of the argument block; the struct follows
 static_assert(sizeof(u64x4) + sizeof(u64x2) + sizeof(uint64_t) == kLeadBytes && alignof(FusedOneArgs) == 8, "argument block");
+// The same for short launches of up to 8 contributions, whose block stays within kFewBytes: two pointers, and the distances of the others in
+// 16 bytes, momentum, variance and output from the master weights and contributions from the first.
+constexpr uint32_t kNearR = 8;
+template <uint32_t R>
+struct FusedNearArgs {
+    AdamScalars scalars;
+    int32_t g[R > 4 ? R - 4 : 1];           // from the fifth contribution on
+};
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+typedef int32_t i32x2 __attribute__((ext_vector_type(2)));
+constexpr uint64_t kHasOut = 1ull << 31;    // in `size`, whose number of quads has 28 bits
+static_assert(kLeadBytes + sizeof(FusedNearArgs<kNearR>) == kFewBytes && alignof(FusedNearArgs<kNearR>) == 4, "argument block");
+__device__ __forceinline__ uint64_t at_distance(uint64_t base, int32_t d) { return base + (int64_t)d * 16; }
+template <uint32_t R>
+struct FusedNear {                          // what fused_adamw asks of them
+    const FusedNearArgs<R> &a;
+    uint64_t out, first;
+    i32x2 d;
+    static constexpr size_t kScalars = 0;
+    __device__ __forceinline__ uint64_t output() const { return out; }
+    __device__ __forceinline__ uint64_t contribution(uint32_t r) const { return at_distance(first, r < 4 ? d[r - 2] : a.g[r - 4]); }
+};
 enum FusedForm { kSearched, kPlain, kOne };
 
 // The decay runs that a group meets, found while the streams arrive: begin() narrows the search to 64
@@ -455,7 +481,7 @@ __device__ __forceinline__ void fused_adamw(const FusedLead lead, const Args &a)
     constexpr bool PAIRS = !G32;
     // Which segment and which group of it?
     uint32_t grp = blockIdx.x;
-    const uint64_t *slice, *rec = nullptr;      // the contributions' pointers, the segment's record
+    const uint64_t *slice = nullptr, *rec = nullptr;        // the contributions' pointers, the segment's record
     int64_t shift = 0, out_shift = 0;           // of the segment against the pointers, in quads
     bool lookup = false;
     DecayRuns runs;
@@ -467,14 +493,13 @@ __device__ __forceinline__ void fused_adamw(const FusedLead lead, const Args &a)
         P = lead.p[0];
         M = lead.p[1];
         V = lead.p[2];
-        OUT = a.out;
+        OUT = a.output();
         scalars_dev = lead.w[1];
         nquad = (uint32_t)lead.size;
         decay = lead.size >> 32;
         groups = (nquad + kGroupQuads - 1) / kGroupQuads;
-        slice = a.g;
 #pragma unroll
-        for (uint32_t c = 0; c < CHUNK; ++c) at[c] = c >= R ? 0 : c == 0 ? lead.p[3] : c == 1 ? lead.w[0] : a.g[c];
+        for (uint32_t c = 0; c < CHUNK; ++c) at[c] = c >= R ? 0 : c == 0 ? lead.p[3] : c == 1 ? lead.w[0] : a.contribution(c);
     } else {
         const uint64_t *ptr;
         uint32_t before = 0;                    // workgroups of the segments ahead of it
@@ -526,7 +551,8 @@ __device__ __forceinline__ void fused_adamw(const FusedLead lead, const Args &a)
         if (grp >= groups) return;              // of a longer segment of a 2-D grid
     }
     // (ahead of the requests: behind a branch, an offset that was used before it no longer goes with a scalar base)
-    if (FORM == kOne && !scalars_dev) scalars_dev = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr() + kLeadBytes + offsetof(Args, scalars);
+    if constexpr (FORM == kOne)
+        if (!scalars_dev) scalars_dev = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr() + kLeadBytes + Args::kScalars;
     if (FORM == kOne || scalars_dev) {
         typedef const __attribute__((address_space(4))) float const_float;      // scalar loads
         const_float *c = reinterpret_cast<const_float *>(scalars_dev);
@@ -557,7 +583,13 @@ __device__ __forceinline__ void fused_adamw(const FusedLead lead, const Args &a)
     if (FORM == kSearched && lookup) runs.find(pos);
     float g[1][4];
     gap<HEAD>();
-    sum_contributions<R, CHUNK, G32, 1, false, (FORM == kOne && G32 && CHUNK > 8 ? 8u : 0u)>(at, [slice](uint32_t r) { return slice[r]; }, shift * (G32 ? 16 : 8), quads, g, [&] {
+    auto contribution = [&](uint32_t r) {
+        if constexpr (FORM == kOne)
+            return a.contribution(r);
+        else
+            return slice[r];
+    };
+    sum_contributions<R, CHUNK, G32, 1, false, (FORM == kOne && G32 && CHUNK > 8 ? 8u : 0u)>(at, contribution, shift * (G32 ? 16 : 8), quads, g, [&] {
         if (FORM == kOne)       // needed last, but read by now
             pin(OUT, h.lr, h.beta1, h.beta2, h.one_minus_beta1, h.one_minus_beta2, h.eps, h.weight_decay, h.grad_scale, h.inv_bc1, h.inv_bc2);
     });
@@ -603,6 +635,15 @@ template <uint32_t R, bool G32, bool O32, uint32_t CHUNK, uint32_t HEAD>
 __global__ __launch_bounds__(kWave) void fused_one_kernel(const u64x4 p, const u64x2 w, const uint64_t size, const FusedOneArgs a)
 {
     fused_adamw<R, G32, O32, kOne, CHUNK, HEAD>({p, w, size}, a);
+}
+// base: master weights, first contribution; d: distances of momentum, variance, output and the second contribution; d2: of the third and fourth.
+template <uint32_t R, bool G32, bool O32, uint32_t CHUNK>
+__global__ __launch_bounds__(kWave) void fused_near_kernel(const u64x2 base, const i32x4 d, const i32x2 d2, const uint64_t size, const uint64_t scalars_dev,
+                                                           const FusedNearArgs<R> a)
+{
+    const uint64_t p = base[0], g = base[1];
+    const FusedLead lead{{p, at_distance(p, d[0]), at_distance(p, d[1]), g}, {at_distance(g, d[3]), scalars_dev}, size & ~kHasOut};
+    fused_adamw<R, G32, O32, kOne, CHUNK, 0>(lead, FusedNear<R>{a, size & kHasOut ? at_distance(p, d[2]) : 0, g, d2});
 }
 template <uint32_t R, bool G32, bool O32, FusedForm FORM, uint32_t CHUNK>
 __global__ __launch_bounds__(kWave) void fused_adamw_kernel(const FusedArgs a)
@@ -1332,6 +1373,12 @@ static FusedOneKernel fused_one_kernel_of(bool g32, bool o32, uint32_t R)
     return !g32 ? kernels16[R - 1] : o32 ? kernels32[R - 1] : fused_one_kernel<1, true, false, fused_chunk(true, 1, CLASS), 0>;
 }
 
+template <bool G32, bool O32, size_t... I>
+static std::array<const void *, sizeof...(I)> fused_near_kernels(std::index_sequence<I...>)
+{
+    return {reinterpret_cast<const void *>(fused_near_kernel<I + 1, G32, O32, fused_chunk(G32, I + 1, kFew)>)...};
+}
+
 template <FusedForm FORM>
 static hzp_status_t start_fused(bool g32, bool o32, uint32_t R, const FusedArgs &a, dim3 grid, uint32_t groups, hipStream_t stream)
 {
@@ -1348,11 +1395,39 @@ static hzp_status_t start_fused_one(bool g32, bool o32, uint32_t R, const FusedA
     if (groups > 3072 && groups <= uncapped_groups(g32, R, kOne) && (R == 1 || (R == 2 && !g32)))       // with a pause behind the state's requests
         kernel = R == 2 ? fused_one_kernel<2, false, false, 2, 96> : !g32 ? fused_one_kernel<1, false, false, 1, 96>
                  : o32 ? fused_one_kernel<1, true, true, 1, 96> : fused_one_kernel<1, true, false, 1, 96>;
+    const uint64_t *const w = a.word, *const rec = a.word + R + 4;
+    // Launches of up to 5.5 MB take the host longer than the device, and their blocks stay within kFewBytes.  Two pointers and distances / pointers, us, bf16 of
+    // 16 k and 0.13 M elements, calls in a row: R = 1 3.8 / 4.2, 3.75 / 4.4, R = 4 3.8 / 4.3, 3.8 / 4.4, R = 8 3.8 / 4.35, 3.7 / 4.1 (a mean of -9 % over both types); on the
+    // device alone (graph) R = 4 2.46 / 2.42, 2.65 / 2.65, R = 8 2.60 / 2.55, 3.26 / 3.22: the addresses are worked out before the first requests.  Beyond, the
+    // device's time shows: R = 8 of 0.15 / 0.2 M 3.39 / 3.27, 3.83 / 3.50, R = 4 of 0.46 M 4.6 / 4.3 in a row.
+    const uint64_t bytes = (uint64_t)groups * kGroupQuads * 4 * (R * (g32 ? 4u : 2u) + 24 + (o32 ? 4u : 2u));
+    if (bytes <= 5500000 && groups <= kFewGroups && R <= kNearR) {
+        bool fits = true;
+        auto distance = [&](uint64_t to, uint64_t from) {
+            const int64_t d = (int64_t)(to - from) / 16;        // (all are multiples of 16)
+            fits = fits && d == (int32_t)d;
+            return (int32_t)d;
+        };
+        const u64x2 base{w[0], w[4]};
+        const i32x4 d{distance(w[1], w[0]), distance(w[2], w[0]), w[3] ? distance(w[3], w[0]) : 0, R > 1 ? distance(w[5], w[4]) : 0};
+        const i32x2 d2{R > 2 ? distance(w[6], w[4]) : 0, R > 3 ? distance(w[7], w[4]) : 0};
+        const uint64_t size = rec[0] >> 32 | rec[1] << 32 | (w[3] ? kHasOut : 0), dev = reinterpret_cast<uint64_t>(a.scalars_dev);
+        FusedNearArgs<kNearR> near;
+        near.scalars = a.scalars;
+        for (uint32_t r = 4; r < R; ++r) near.g[r - 4] = distance(w[4 + r], w[4]);
+        if (fits) {
+            constexpr std::make_index_sequence<kNearR> all;
+            static const auto kernels16 = fused_near_kernels<false, false>(all), kernels32 = fused_near_kernels<true, true>(all);
+            const void *const k = !g32  ? kernels16[R - 1]
+                                  : o32 ? kernels32[R - 1]
+                                        : reinterpret_cast<const void *>(fused_near_kernel<1, true, false, fused_chunk(true, 1, kFew)>);
+            return start_any("hzp_adamw_shard", k, dim3(groups), dim3(kWave), 0, stream, &base, &d, &d2, &size, &dev, &near);
+        }
+    }
     FusedOneArgs one;
     one.out = a.word[3];
     one.scalars = a.scalars;
     std::memcpy(one.g, a.word + 4, R * sizeof one.g[0]);
-    const uint64_t *const w = a.word, *const rec = a.word + R + 4;
     return start("hzp_adamw_shard", kernel, dim3(groups), dim3(kWave), fused_lds(g32, R, c, kOne, groups), stream, u64x4{w[0], w[1], w[2], w[4]},
                  u64x2{R > 1 ? w[5] : 0, reinterpret_cast<uint64_t>(a.scalars_dev)}, rec[0] >> 32 | rec[1] << 32, one);
 }

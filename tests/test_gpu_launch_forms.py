@@ -742,3 +742,43 @@ def test_every_choice_between_lists_and_the_bucket_s_own_layout(numel, both, lau
     for t, v in enumerate(views):
         assert torch.equal(v, whole[plan.tensor(t).offset:plan.tensor(t).offset + numel[t]]), t
     assert not both or torch.equal(bucket, whole)
+
+
+@pytest.fixture(scope="module")
+def wide_room():
+    """An allocation whose ends lie further apart than 32 bits of 16-byte units reach."""
+    yield torch.empty((33 << 30) + (1 << 20), dtype=torch.uint8, device=DEV)
+
+
+@pytest.mark.parametrize("cls,R", [(0, R) for R in range(1, 10)] + [(1, R) for R in range(1, 10)] + [(0, 0)])
+@pytest.mark.parametrize("n", [8, 248, 256, 504, 10248])
+def test_short_updates_with_streams_near_and_far(cls, R, n, wide_room):
+    """Streams in any order, near each other (two pointers and distances) and with one of them 33 GiB away (pointers): the same bits, with
+    scalars from the call and from device memory, with an output and without."""
+    print(cls, R, n, flush=True)
+    rng = np.random.default_rng(R * 7 + n)
+    k, wide = max(R, 1), cls == 1 or R == 0
+    types = [torch.float32 if wide else torch.bfloat16] * k + [torch.float32] * 3 + [torch.float32 if cls else torch.bfloat16]
+    room = 4 * n + 256
+    start = [torch.from_numpy(rng.standard_normal(n, dtype=np.float32) * np.float32(s)).to(DEV).to(t)
+             for s, t in zip([1e-3] * k + [0.02, 1e-4, 1e-4], types)]
+    start[-1].square_()
+    plan = hzp.hzp_plan([1], [n], align=8, z3=1, z1=1, tensor_class=[cls])
+    hy = hzp.adamw_hyper(HP["lr"], HP["beta1"], HP["beta2"], HP["eps"], HP["weight_decay"], 1.0 / k, 3)
+    scalars = torch.tensor(hzp.hzp_adamw_scalars(hy), dtype=torch.float32, device=DEV)
+    first = None
+    for far in (None, k - 1, k, k + 2, k + 3):              # the last contribution, master weights, variance, output
+        at = [int(p) * room + ((33 << 30) if i == far else 0) for i, p in enumerate(rng.permutation(k + 4))]
+        streams = [wide_room[a:a + n * t.itemsize].view(t) for a, t in zip(at, types)]
+        for call, scal in ((hzp.hzp_adamw_shard, hy), (hzp.hzp_adamw_shard_dev, scalars)):
+            for given in (True, False):
+                for t, s in zip(streams, start):
+                    t.copy_(s)
+                streams[-1].fill_(7)
+                call(plan, 0, 1, cls, 0, scal, streams[:k], R, [streams[k]], [streams[k + 1]], [streams[k + 2]], [streams[k + 3]] if given else None)
+                torch.cuda.synchronize()
+                got = [t.clone() for t in streams[k:k + 3]]
+                first = first or got
+                assert all(torch.equal(a, b) for a, b in zip(got, first)), (far, call, given)
+                want = got[0].to(types[-1]) if given else torch.full_like(streams[-1], 7)
+                assert torch.equal(streams[-1], want), (far, call, given)
