@@ -42,6 +42,7 @@ struct BucketRec {
     uint64_t payload_end, P, S3, S2, S1, base;
     std::vector<uint32_t> tensor_ids;
     std::vector<Piece> pieces;
+    uint64_t payload, longest;      // elements of all pieces, of the longest one
     uint32_t n_chunks;
     uint32_t piece_slot;    // first entry of this bucket in the device piece table
     uint32_t tensor_slot;   // and in the device table of the tensors' spans

@@ -190,6 +190,9 @@ __device__ __forceinline__ void pin(T &x, Rest &...rest)
     pin(rest...);
 }
 
+// Address `d` units of 16 bytes from another.
+__device__ __forceinline__ uint64_t at_distance(uint64_t base, int32_t d) { return base + (int64_t)d * 16; }
+
 // So many wait states (a multiple of 8) between the requests before and behind it.
 template <uint32_t STATES>
 __device__ __forceinline__ void gap()
@@ -395,7 +398,6 @@ typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 typedef int32_t i32x2 __attribute__((ext_vector_type(2)));
 constexpr uint64_t kHasOut = 1ull << 31;    // in `size`, whose number of quads has 28 bits
 static_assert(kLeadBytes + sizeof(FusedNearArgs<kNearR>) == kFewBytes && alignof(FusedNearArgs<kNearR>) == 4, "argument block");
-__device__ __forceinline__ uint64_t at_distance(uint64_t base, int32_t d) { return base + (int64_t)d * 16; }
 template <uint32_t R>
 struct FusedNear {                          // what fused_adamw asks of them
     const FusedNearArgs<R> &a;
@@ -900,22 +902,40 @@ struct UnpackPlacedArgs {
 };
 static_assert(sizeof(UnpackPlacedArgs) <= kFewBytes, "kernel arguments");
 
+// The same for up to 64 tensors that lie anywhere on 16 bytes, but no further apart than 32 bits of such units reach (nor the shards): a lane finds
+// its tensor's distance with its end.  For 12 tensors the block stays within kFewBytes.
+template <uint32_t N>
+struct UnpackNearArgs {
+    static constexpr uint32_t kTensors = N;
+    uint64_t src, dst;                  // the first shard; the first tensor
+    const u32x2 *span;
+    uint32_t n, nvec;
+    int32_t shard[UnpackPlacedArgs::kShards];       // distances from the first one, in 16 bytes
+    int32_t tensor[N];
+};
+typedef UnpackNearArgs<12> UnpackNear12;
+typedef UnpackNearArgs<64> UnpackNear64;
+static_assert(sizeof(UnpackNear12) <= kFewBytes, "kernel arguments");
+
+constexpr int32_t kNoDistance = INT32_MIN;
+
 // FEW: at most 64 tensors, whose spans are asked for together with the data; else 64 pivots a round lead to the first that a tile meets (asking
-// for up to 256 spans at once, four a lane, took as long: 100 tensors of 0.07 MB 2.61 us, with pivots 2.46).
-template <int ES, bool BOTH, bool FEW>
-__global__ __launch_bounds__(kWave) void unpack_placed_kernel(const UnpackPlacedArgs a)
+// for up to 256 spans at once, four a lane, took as long: 100 tensors of 0.07 MB 2.61 us, with pivots 2.46).  NEAR: lane t's `distance` is tensor t's.
+template <int ES, bool BOTH, bool FEW, bool NEAR>
+__device__ __forceinline__ void unpack_spans(uint64_t src, uint64_t dst, uint64_t bucket, uint64_t table, uint32_t nvec, uint32_t n, uint32_t end, const int32_t *distances)
 {
     constexpr uint32_t VE = 16 / ES, TILE = kWave * VE;         // elements of a vector, of a tile
     typedef typename std::conditional<ES == 2, uint16_t, uint32_t>::type elem_t;
     typedef const __attribute__((address_space(1))) u32x2 *spans;
     typedef __attribute__((address_space(1))) elem_t *elements_out;
-    uint64_t src = a.src[blockIdx.y], dst = a.dst, bucket = BOTH ? a.bucket : 0, table = reinterpret_cast<uint64_t>(a.span);
-    uint32_t nvec = a.nvec, n = a.n, end = a.end;
-    pin(src, dst, bucket, table, nvec, n, end);
     const uint32_t lane = threadIdx.x, vec = blockIdx.x * kWave + lane;
     const uint32_t first = (blockIdx.y * nvec + blockIdx.x * kWave) * VE, mine = first + lane * VE;     // bucket positions
     if (!BOTH && first >= end) return;  // padding behind the last tensor
     const u32x4 val = ld_stream<u32x4>(src, vec < nvec ? vec : nvec - 1);
+    // (the bucket's store needs the data alone, so there they are asked for first, 30 tensors of 1.8 MB 3.4 -> 3.2 us; else the spans, 64 of 12.8 MB 6.7 -> 6.3)
+    if (BOTH) __builtin_amdgcn_sched_barrier(0);
+    int32_t distance = 0, away = 0;     // tensor `lane`'s, the one's that the lane's vector belongs to
+    if (NEAR) distance = distances[lane < n ? lane : n - 1];
     uint32_t at = 0;                    // no tensor ahead of this one meets the tile
     for (uint32_t left = n; !FEW && left > kWave;) {
         const uint32_t stride = (left + kWave - 1) / kWave, off = lane * stride;
@@ -924,18 +944,24 @@ __global__ __launch_bounds__(kWave) void unpack_placed_kernel(const UnpackPlaced
         left = left - step < stride ? left - step : stride;
         at += step;
     }
-    uint32_t until = 0;                 // end of the tensor that the lane's vector belongs to
+    uint32_t from = 0, until = 0;       // begin and end of that tensor
     for (;;) {
         const uint32_t here = n - at;   // (64 tensors at a time; a tile meets up to 65)
         const u32x2 span = ((spans)table)[at + (lane < here ? lane : here - 1)];
-        const bool is = lane < here;
+        const bool is = lane < here && distance != kNoDistance;        // (always; so that the distance is asked for with the span)
         uint32_t ahead = (uint32_t)__popcll(__ballot(is && span[0] <= first));         // begin up to the tile's first element,
         uint32_t met = (uint32_t)__popcll(__ballot(is && span[0] < first + TILE));     // up to its last
         ahead = __builtin_amdgcn_readfirstlane(ahead);
         met = __builtin_amdgcn_readfirstlane(met);
         for (uint32_t k = ahead - (ahead != 0); k < met; ++k) {
             const uint32_t b = __builtin_amdgcn_readlane(span[0], k), e = __builtin_amdgcn_readlane(span[1], k);
-            until = mine >= b ? e : until;
+            const bool in = mine >= b;
+            until = in ? e : until;
+            if (NEAR) {
+                const int32_t d = (int32_t)__builtin_amdgcn_readlane((uint32_t)distance, k);
+                from = in ? b : from;
+                away = in ? d : away;
+            }
         }
         if (FEW || met < (uint32_t)kWave || here <= (uint32_t)kWave) break;
         at += kWave;
@@ -943,13 +969,34 @@ __global__ __launch_bounds__(kWave) void unpack_placed_kernel(const UnpackPlaced
     if (vec >= nvec) return;
     if (BOTH && src != bucket + (uint64_t)(blockIdx.y * nvec) * 16) st_writethrough(bucket, mine * ES, __builtin_bit_cast(f32x4, val));        // (else it lies in place)
     if (mine >= until) return;
+    const uint64_t to = NEAR ? dst + (int64_t)away * 16 + (uint64_t)(mine - from) * ES : dst + (uint64_t)mine * ES;
     if (until - mine >= VE) {
-        st_writethrough(dst, mine * ES, __builtin_bit_cast(f32x4, val));
+        if (NEAR)
+            st_writethrough(reinterpret_cast<u32x4 *>(to), val);
+        else
+            st_writethrough(dst, mine * ES, __builtin_bit_cast(f32x4, val));
     } else {                            // the tensor's last elements
 #pragma unroll
         for (uint32_t e = 0; e < VE - 1; ++e)
-            if (mine + e < until) ((elements_out)dst)[mine + e] = (elem_t)(ES == 4 ? val[e] : val[e / 2] >> (e % 2 * 16));
+            if (mine + e < until) ((elements_out)to)[e] = (elem_t)(ES == 4 ? val[e] : val[e / 2] >> (e % 2 * 16));
     }
+}
+template <int ES, bool BOTH, bool FEW>
+__global__ __launch_bounds__(kWave) void unpack_placed_kernel(const UnpackPlacedArgs a)
+{
+    uint64_t src = a.src[blockIdx.y], dst = a.dst, bucket = BOTH ? a.bucket : 0, table = reinterpret_cast<uint64_t>(a.span);
+    uint32_t nvec = a.nvec, n = a.n, end = a.end;
+    pin(src, dst, bucket, table, nvec, n, end);
+    unpack_spans<ES, BOTH, FEW, false>(src, dst, bucket, table, nvec, n, end, nullptr);
+}
+template <int ES, class Args>
+__global__ __launch_bounds__(kWave) void unpack_near_kernel(const Args a)
+{
+    int32_t shard = a.shard[blockIdx.y];
+    uint64_t src = a.src, dst = a.dst, table = reinterpret_cast<uint64_t>(a.span);
+    uint32_t nvec = a.nvec, n = a.n;
+    pin(shard, src, dst, table, nvec, n);
+    unpack_spans<ES, false, true, true>(at_distance(src, shard), dst, 0, table, nvec, n, ~0u, a.tensor);
 }
 
 // The same for buckets of very many tensors in short copies: one single-wavefront workgroup per chunk of at most
@@ -1044,6 +1091,14 @@ static hzp_status_t start(const char *who, void (*kernel)(P...), dim3 grid, dim3
                           const typename AsIs<P>::type &...args)
 {
     return start_any(who, reinterpret_cast<const void *>(kernel), grid, block, lds, stream, &args...);
+}
+
+// Is the call being captured?  A replay costs the host nothing for each launch, so there the device's time alone decides.
+static bool captured(hipStream_t stream)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &status) != hipSuccess) (void)hipGetLastError();       // (no later launch is to find it)
+    return status != hipStreamCaptureStatusNone;
 }
 
 // One kernel per number of contributions: the loads of a chunk are then straight-line code (a run-time R
@@ -1398,10 +1453,10 @@ static hzp_status_t start_fused_one(bool g32, bool o32, uint32_t R, const FusedA
     const uint64_t *const w = a.word, *const rec = a.word + R + 4;
     // Launches of up to 5.5 MB take the host longer than the device, and their blocks stay within kFewBytes.  Two pointers and distances / pointers, us, bf16 of
     // 16 k and 0.13 M elements, calls in a row: R = 1 3.8 / 4.2, 3.75 / 4.4, R = 4 3.8 / 4.3, 3.8 / 4.4, R = 8 3.8 / 4.35, 3.7 / 4.1 (a mean of -9 % over both types); on the
-    // device alone (graph) R = 4 2.46 / 2.42, 2.65 / 2.65, R = 8 2.60 / 2.55, 3.26 / 3.22: the addresses are worked out before the first requests.  Beyond, the
+    // device alone R = 4 2.46 / 2.42, 2.65 / 2.65, R = 8 2.60 / 2.55, 3.26 / 3.22 (the addresses are worked out before the first requests), so captured ones take pointers.  Beyond, the
     // device's time shows: R = 8 of 0.15 / 0.2 M 3.39 / 3.27, 3.83 / 3.50, R = 4 of 0.46 M 4.6 / 4.3 in a row.
     const uint64_t bytes = (uint64_t)groups * kGroupQuads * 4 * (R * (g32 ? 4u : 2u) + 24 + (o32 ? 4u : 2u));
-    if (bytes <= 5500000 && groups <= kFewGroups && R <= kNearR) {
+    if (bytes <= 5500000 && groups <= kFewGroups && R <= kNearR && !captured(stream)) {
         bool fits = true;
         auto distance = [&](uint64_t to, uint64_t from) {
             const int64_t d = (int64_t)(to - from) / 16;        // (all are multiples of 16)
@@ -2016,6 +2071,14 @@ static hzp_status_t launch_unpack_with(const UnpackCall &u, void *const *tensors
     return HZP_OK;
 }
 
+// Distance of one address from another in units of 16 bytes, where it is a whole number that fits 32 bits (else *fits becomes false).
+static int32_t units_apart(uint64_t to, uint64_t from, bool *fits)
+{
+    const int64_t d = (int64_t)(to - from) / 16;
+    *fits = *fits && d == (int32_t)d && d != kNoDistance && (to - from) % 16 == 0;
+    return (int32_t)d;
+}
+
 // Do all tensors of the bucket lie in one buffer as they do in the bucket?  Then *origin is where position 0 would be.
 static bool placed_as_in_bucket(const hzp_plan_t *plan, const BucketRec &b, void *const *tensors, uint32_t es, uint64_t *origin)
 {
@@ -2027,35 +2090,56 @@ static bool placed_as_in_bucket(const hzp_plan_t *plan, const BucketRec &b, void
     return true;
 }
 
-// Is the one launch of unpack_placed the better way to write the bucket's tensors, where lists would hold `n` pieces?  Lists / placed, us, calls
-// in a row (collisions of kFewBytes included) and on the device alone (graph):
+// The launches that lists of a bucket's parts take.
+struct ListShape {
+    bool even;          // one launch of even parts
+    size_t launches;
+};
+static ListShape list_shape(const BucketRec &b, uint32_t es)
+{
+    const size_t n = b.pieces.size();
+    const bool even = n <= (size_t)UnpackList200::kParts && even_parts(n, b.payload, b.longest, kWave * 16 / es);
+    return {even, even ? 1 : (n + UnpackFlat160::kParts - 1) / UnpackFlat160::kParts};
+}
+static bool spans_reach(const BucketRec &b, uint32_t n_shards, uint32_t es)
+{
+    return n_shards <= UnpackPlacedArgs::kShards && b.P * es < 1ull << 32;      // (kernels address with 32 bits)
+}
+// Most bytes of a bucket that are written by the bucket's lines of 128 bytes where those are not the tensors' own (a wavefront then writes parts of lines).  Lists / so,
+// us: tensors in the bucket's layout, 9 of 18 / 72 / 360 MB 9.0 / 8.6, 27.2 / 27.0, 127 / 128, of 720 MB 249 / 255; elsewhere, 9 of 7 / 18 / 72 / 360 MB 5.2 / 5.2, 8.6 / 8.6, 26.5 / 27.1,
+// 116 / 123, 64 of 13 / 128 MB 7.6 / 7.2, 45 / 47.
+constexpr uint64_t kOffLinesPlaced = 64u << 20, kOffLinesNear = 16u << 20;
+// Is the one launch of unpack_placed the better way to write the bucket's tensors?  Lists / placed, us, calls in a row (collisions of kFewBytes
+// included) and on the device alone (graph):
 //   up to 64 tensors: 6 / 9 / 64 of 0.04-0.1 MB in all 4.2 / 3.8, 4.3 / 3.9, 4.4 / 4.0 and 2.07 / 2.16, 2.08 / 2.12, 2.24 / 2.18, 9 of 1.8 / 18 / 360 MB
 //   4.35 / 3.8, 7.8 / 7.5, 107 / 106 and 3.02 / 2.80, 7.9 / 7.75, 108.7 / 107.8; even ones 2.01 / 2.05 and 3.59 / 3.57 on the device, from 20 MB the same.
+//   (captured, below 0.5 MB and even ones by lists)
 //   more, where lists are one launch: 100 uneven ones of 0.07 / 2 / 20 MB 2.28 / 2.46, 3.5 / 3.1, 9.4 / 9.7 on the device, even ones 2.1 / 2.4, 2.9 / 3.0, 8.3 / 9.3.
 //   more, where lists are several launches (or tables): 170 of 3.4 / 30 / 340 MB 4.4 / 3.7, 14.9 / 13.3, 110 / 111; 400 of 8 / 80 MB 6.6 / 5.9, 30 / 30; 1000 of
 //   0.7 / 20 / 200 MB 8.4 / 2.9, 17.9 / 11.4, 79 / 73.
-static bool placed_pays(const BucketRec &b, const Piece *piece, size_t n, uint32_t n_shards, uint32_t es)
+static bool placed_pays(const BucketRec &b, const ListShape &lists, uint32_t es)
 {
     const uint64_t bytes = b.P * es;
-    if (n_shards > UnpackPlacedArgs::kShards || bytes >= 1ull << 32) return false;      // (kernels address with 32 bits)
-    uint64_t total = 0, longest = 0;
-    for (size_t i = 0; i < n; ++i) {
-        total += piece[i].len;
-        longest = std::max(longest, piece[i].len);
-    }
-    const bool even = n <= (size_t)UnpackList200::kParts && even_parts(n, total, longest, kWave * 16 / es);
-    if (b.n_tensors <= (uint32_t)kWave) return !even || bytes <= 4u << 20;
-    if (even) return false;
-    const size_t launches = (n + UnpackFlat160::kParts - 1) / UnpackFlat160::kParts;
-    return launches == 1 ? bytes >= 512u << 10 && bytes <= 4u << 20 : bytes <= launches * (8u << 20);
+    if (b.n_tensors <= (uint32_t)kWave) return !lists.even || bytes <= 4u << 20;
+    if (lists.even) return false;
+    return lists.launches == 1 ? bytes >= 512u << 10 && bytes <= 4u << 20 : bytes <= lists.launches * (8u << 20);
+}
+// And that of unpack_near?  Up to 12 tensors as above: 6 / 9 / 12 of 0.04-0.07 MB 4.6 / 3.7, 4.55 / 4.0, 4.4 / 4.1 and 2.07 / 2.23, 2.10 / 2.15, 2.10 / 2.16, 9 of 1.8 / 18 / 360 MB
+// 4.5 / 4.0, 8.0 / 7.5, 107 / 107.  More only where they are uneven and long enough: 64 of 0.05 / 0.76 / 12.8 / 128 MB 4.6 / 4.35, 4.5 / 4.3, 7.3 / 6.6, 41.6 / 39.0 and 2.26 / 2.32, 2.50 / 2.45, 7.3 / 6.4, 42.9 / 40.4.
+// On other than the bucket's 128-byte lines even ones of 0.36 MB take 2.02 / 2.28 on the device.
+// (With the bucket beside them 0.2 us more on the device than lists: 9 of 0.06 MB 2.08 / 2.33.)
+static bool near_pays(const BucketRec &b, const ListShape &lists, uint32_t es)
+{
+    if (b.n_tensors <= UnpackNear12::kTensors) return placed_pays(b, lists, es);
+    return b.n_tensors <= UnpackNear64::kTensors && !lists.even && b.P * es >= 1u << 20;
 }
 // The same with the bucket written too, where lists (`one_pass`) are one launch; else there are two passes: 100 tensors of 0.07 / 2 / 20 / 200 MB 3.8 / 2.5, 6.2 /
 // 3.2, 16.9 / 12.9, 124 / 97, 170 of 340 MB 209 / 162, 1000 of 0.7 / 200 MB 11 / 3.0, 139 / 106.  In one launch of lists: 6 / 30 of 0.04-0.07 MB 2.04 / 2.16, 2.07 / 2.19 on the
 // device and 4.35 / 3.8, 4.8 / 3.9 in a row, 9 of 1.8 / 18 / 360 MB 3.5 / 3.1, 11.2 / 10.7, 172 / 173; 100 even ones of 0.08 / 2 / 20 MB 2.1 / 2.4, 3.2 / 3.1, 11.6 / 12.4.
-static bool placed_pays_both(const BucketRec &b, uint32_t n_shards, uint32_t es, bool one_pass)
+// (Captured, below 1 MB by lists, even ones below 2 MB: 30 of 1.8 MB 3.08 / 3.18, uneven 3.53 / 3.29.)
+static bool placed_pays_both(const BucketRec &b, uint32_t es, bool one_pass)
 {
     const uint64_t bytes = b.P * es;
-    if (n_shards > UnpackPlacedArgs::kShards || bytes >= 1ull << 32) return false;
     return !one_pass || (bytes <= 4u << 20 && (b.n_tensors <= (uint32_t)kWave || bytes >= 512u << 10));
 }
 
@@ -2074,6 +2158,34 @@ static hzp_status_t unpack_placed(const DeviceTables &tab, const BucketRec &b, c
     return start("hzp_gather_layer", kernel, dim3((uint32_t)tiles_of(a.nvec), n_shards), dim3(kWave), 0, stream, a);
 }
 
+// The same for tensors that lie elsewhere; *done is false (and nothing launched) where they or the shards lie too far apart, or off 16 bytes.
+template <int ES, class Args>
+static hzp_status_t unpack_near(const hzp_plan_t *plan, const DeviceTables &tab, const BucketRec &b, const void *const *shards, uint32_t n_shards, void *const *tensors, hipStream_t stream, bool *done)
+{
+    Args a;
+    a.src = reinterpret_cast<uint64_t>(shards[0]);
+    a.dst = reinterpret_cast<uint64_t>(tensors[0]);
+    a.span = reinterpret_cast<const u32x2 *>(tab.span) + b.tensor_slot;
+    a.n = b.n_tensors;
+    a.nvec = (uint32_t)(b.S3 * ES / 16);
+    bool fits = a.dst % 16 == 0;
+    uint64_t off = 0;                   // by how much any tensor's 128-byte lines are not the bucket's
+    for (uint32_t j = 0; j < n_shards; ++j) a.shard[j] = units_apart(reinterpret_cast<uint64_t>(shards[j]), a.src, &fits);
+    for (uint32_t t = 0; t < b.n_tensors; ++t) {
+        a.tensor[t] = units_apart(reinterpret_cast<uint64_t>(tensors[t]), a.dst, &fits);
+        off |= reinterpret_cast<uint64_t>(tensors[t]) - plan->tensors[b.tensor_ids[t]].offset * ES;
+    }
+    if (off % 128 && b.P * ES > kOffLinesNear) fits = false;
+    *done = fits;
+    return fits ? start("hzp_gather_layer", unpack_near_kernel<ES, Args>, dim3((uint32_t)tiles_of(a.nvec), n_shards), dim3(kWave), 0, stream, a) : HZP_OK;
+}
+template <int ES>
+static hzp_status_t unpack_near(const hzp_plan_t *plan, const DeviceTables &tab, const BucketRec &b, const void *const *shards, uint32_t n_shards, void *const *tensors, hipStream_t stream, bool *done)
+{
+    return b.n_tensors <= UnpackNear12::kTensors ? unpack_near<ES, UnpackNear12>(plan, tab, b, shards, n_shards, tensors, stream, done)
+                                                 : unpack_near<ES, UnpackNear64>(plan, tab, b, shards, n_shards, tensors, stream, done);
+}
+
 hzp_status_t launch_unpack(const hzp_plan_t *plan, const BucketRec &b, const void *const *shards,
                            uint32_t n_shards, void *const *tensors, uint32_t t_begin, uint32_t t_end,
                            hipStream_t stream)
@@ -2083,10 +2195,20 @@ hzp_status_t launch_unpack(const hzp_plan_t *plan, const BucketRec &b, const voi
     const DeviceTables *tab = nullptr;
     const hzp_status_t st = device_tables(plan, &tab);
     if (st != HZP_OK) return st;
-    uint64_t origin = 0;
-    if (n > (size_t)UnpackList5::kParts && t_end - t_begin == b.n_tensors && placed_as_in_bucket(plan, b, tensors, es, &origin) &&
-        placed_pays(b, b.pieces.data(), n, n_shards, es))
-        return es == 4 ? unpack_placed<4, false>(*tab, b, shards, n_shards, origin, nullptr, stream) : unpack_placed<2, false>(*tab, b, shards, n_shards, origin, nullptr, stream);
+    if (n > (size_t)UnpackList5::kParts && t_end - t_begin == b.n_tensors && spans_reach(b, n_shards, es)) {
+        const ListShape lists = list_shape(b, es);
+        auto rather_lists = [&] { return lists.launches == 1 && (lists.even || b.P * es < 512u << 10) && captured(stream); };
+        uint64_t origin = 0;
+        if (placed_pays(b, lists, es) && placed_as_in_bucket(plan, b, tensors, es, &origin) && (origin % 128 == 0 || b.P * es <= kOffLinesPlaced) && !rather_lists())
+            return es == 4 ? unpack_placed<4, false>(*tab, b, shards, n_shards, origin, nullptr, stream)
+                           : unpack_placed<2, false>(*tab, b, shards, n_shards, origin, nullptr, stream);
+        if (near_pays(b, lists, es) && !rather_lists()) {
+            bool done = false;
+            const hzp_status_t near = es == 4 ? unpack_near<4>(plan, *tab, b, shards, n_shards, tensors, stream, &done)
+                                              : unpack_near<2>(plan, *tab, b, shards, n_shards, tensors, stream, &done);
+            if (done) return near;
+        }
+    }
     if (n > (size_t)UnpackFlat160::kParts) {            // (fewer are one launch)
         uint64_t total = 0;
         size_t longest = p0;
@@ -2132,7 +2254,8 @@ hzp_status_t launch_unpack_both(const hzp_plan_t *plan, const BucketRec &b, cons
     hzp_status_t st = device_tables(plan, &tab);
     if (st != HZP_OK) return st;
     uint64_t origin = 0;
-    if (placed_pays_both(b, n_shards, es, one_pass) && placed_as_in_bucket(plan, b, tensors, es, &origin))
+    if (spans_reach(b, n_shards, es) && placed_pays_both(b, es, one_pass) && placed_as_in_bucket(plan, b, tensors, es, &origin) &&
+        !(one_pass && b.P * es < (list_shape(b, es).even ? 2u : 1u) << 20 && captured(stream)))
         return es == 4 ? unpack_placed<4, true>(*tab, b, shards, n_shards, origin, bucket, stream) : unpack_placed<2, true>(*tab, b, shards, n_shards, origin, bucket, stream);
     if (!one_pass) {
         st = launch_concat(shards, n_shards, b.S3 * es, bucket, stream);

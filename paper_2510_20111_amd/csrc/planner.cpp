@@ -86,6 +86,8 @@ static bool build_pieces(const hzp_plan_t *plan, BucketRec &b)
             if (chunks > 0xFFFFFFFFull) return false;
             p.chunk_begin = (uint32_t)chunks;
             chunks += (p.len + kUnpackChunk - 1) / kUnpackChunk;
+            b.payload += p.len;
+            b.longest = std::max(b.longest, p.len);
             b.pieces.push_back(p);
             pos = stop;
         }

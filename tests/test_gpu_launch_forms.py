@@ -747,7 +747,7 @@ def test_every_choice_between_lists_and_the_bucket_s_own_layout(numel, both, lau
 @pytest.fixture(scope="module")
 def wide_room():
     """An allocation whose ends lie further apart than 32 bits of 16-byte units reach."""
-    yield torch.empty((33 << 30) + (1 << 20), dtype=torch.uint8, device=DEV)
+    yield torch.empty((33 << 30) + (16 << 20), dtype=torch.uint8, device=DEV)
 
 
 @pytest.mark.parametrize("cls,R", [(0, R) for R in range(1, 10)] + [(1, R) for R in range(1, 10)] + [(0, 0)])
@@ -782,3 +782,42 @@ def test_short_updates_with_streams_near_and_far(cls, R, n, wide_room):
                 assert all(torch.equal(a, b) for a, b in zip(got, first)), (far, call, given)
                 want = got[0].to(types[-1]) if given else torch.full_like(streams[-1], 7)
                 assert torch.equal(streams[-1], want), (far, call, given)
+
+
+@pytest.mark.parametrize("cls", [0, 1])
+@pytest.mark.parametrize("kind,n,z3", [("tiny", 6, 1), ("tiny", 12, 3), ("spread", 6, 8), ("spread", 12, 8), ("spread", 13, 8), ("even", 12, 2), ("long", 6, 3),
+                                       ("long", 12, 8), ("long", 13, 8), ("long", 64, 8), ("long", 64, 9), ("long", 65, 2)])
+def test_tensors_that_lie_near_each_other_and_far(kind, n, z3, cls, wide_room):
+    """Tensors and shards in any order, on 16 bytes (distances in the argument block), one of them 33 GiB away or off 16 bytes (lists): to the
+    bit, and nothing beside them written."""
+    print(kind, n, z3, cls, flush=True)
+    rng = np.random.default_rng(n * 31 + z3 + cls)
+    numel = [700000 // n * (1 + 5 * (t % 7 == 3)) + t for t in range(n)] if kind == "long" else lengths(kind, n, rng)
+    plan = hzp.hzp_plan([n], numel, align=8, z3=z3, z1=z3, tensor_class=[cls] * n)
+    b, es = plan.bucket(0, cls), 4 if cls else 2
+    dtype = torch.int32 if cls else torch.int16
+    host = torch.from_numpy(rng.integers(0, 30000, b.padded).astype(np.int32 if cls else np.int16)).to(DEV)
+    sizes = [b.s3] * z3 + numel
+    room = [-(-k * es // 16) * 16 + 48 for k in sizes]
+    assert sum(room) < 16 << 20
+    for odd, far in ((None, None), (None, 0), (None, z3 - 1), (None, z3), (None, z3 + n - 1), (z3 + n // 2, None), (z3, None)):
+        raw = wide_room[:sum(room)].view(dtype)
+        raw.fill_(-1)
+        wide_room[33 << 30:].fill_(255)
+        at, places = 0, [0] * len(sizes)
+        for i in rng.permutation(len(sizes)):
+            places[i], at = at, at + room[i]
+        parts = []
+        for i, k in enumerate(sizes):
+            start = (places[i] % (1 << 20) // 16 * 16 + (33 << 30) if i == far else places[i]) + 16 + (es if i == odd else 0)
+            parts.append(wide_room[start:start + k * es].view(dtype))
+        for j in range(z3):
+            parts[j].copy_(host[j * b.s3:(j + 1) * b.s3])
+        before = wide_room[:sum(room)].clone()
+        hzp.hzp_gather_layer(plan, 0, cls, 3, parts[:z3], None, parts[z3:])
+        torch.cuda.synchronize()
+        for t, v in enumerate(parts[z3:]):
+            first = plan.tensor(t).offset
+            assert torch.equal(v, host[first:first + numel[t]]), (odd, far, t)
+            v.fill_(-1)
+        assert torch.equal(wide_room[:sum(room)], before), (odd, far)       # nothing else changed
