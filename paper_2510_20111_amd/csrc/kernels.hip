@@ -386,9 +386,9 @@ struct FusedLead {
 };
 constexpr uint32_t kLeadBytes = 56;         // of the argument block; the struct follows
 static_assert(sizeof(u64x4) + sizeof(u64x2) + sizeof(uint64_t) == kLeadBytes && alignof(FusedOneArgs) == 8, "argument block");
-// The same for short launches of up to 8 contributions, whose block stays within kFewBytes: two pointers, and the distances of the others in
+// The same for short launches of 3 to 8 contributions (fewer are FusedEven's), whose block stays within kFewBytes: two pointers, and the distances of the others in
 // 16 bytes, momentum, variance and output from the master weights and contributions from the first.
-constexpr uint32_t kNearR = 8;
+constexpr uint32_t kNearLeast = 3, kNearR = 8;
 template <uint32_t R>
 struct FusedNearArgs {
     AdamScalars scalars;
@@ -406,6 +406,18 @@ struct FusedNear {                          // what fused_adamw asks of them
     static constexpr size_t kScalars = 0;
     __device__ __forceinline__ uint64_t output() const { return out; }
     __device__ __forceinline__ uint64_t contribution(uint32_t r) const { return at_distance(first, r < 4 ? d[r - 2] : a.g[r - 4]); }
+};
+// The same where contributions lie at equal distances, as in the planner's arena or one receive buffer: any number of them, within kFewBytes.
+struct FusedEvenArgs {
+    uint64_t out;
+    AdamScalars scalars;
+};
+static_assert(kLeadBytes + sizeof(FusedEvenArgs) <= kFewBytes && alignof(FusedEvenArgs) == 8, "argument block");
+struct FusedEven {                          // what fused_adamw asks of them
+    uint64_t out, first, stride;
+    static constexpr size_t kScalars = offsetof(FusedEvenArgs, scalars);
+    __device__ __forceinline__ uint64_t output() const { return out; }
+    __device__ __forceinline__ uint64_t contribution(uint32_t r) const { return first + r * stride; }
 };
 enum FusedForm { kSearched, kPlain, kOne };
 
@@ -646,6 +658,12 @@ __global__ __launch_bounds__(kWave) void fused_near_kernel(const u64x2 base, con
     const uint64_t p = base[0], g = base[1];
     const FusedLead lead{{p, at_distance(p, d[0]), at_distance(p, d[1]), g}, {at_distance(g, d[3]), scalars_dev}, size & ~kHasOut};
     fused_adamw<R, G32, O32, kOne, CHUNK, 0>(lead, FusedNear<R>{a, size & kHasOut ? at_distance(p, d[2]) : 0, g, d2});
+}
+// w: distance from one contribution to the next, the step's scalars in device memory.
+template <uint32_t R, bool G32, bool O32, uint32_t CHUNK>
+__global__ __launch_bounds__(kWave) void fused_even_kernel(const u64x4 p, const u64x2 w, const uint64_t size, const FusedEvenArgs a)
+{
+    fused_adamw<R, G32, O32, kOne, CHUNK, 0>({p, {p[3] + w[0], w[1]}, size}, FusedEven{a.out, p[3], w[0]});
 }
 template <uint32_t R, bool G32, bool O32, FusedForm FORM, uint32_t CHUNK>
 __global__ __launch_bounds__(kWave) void fused_adamw_kernel(const FusedArgs a)
@@ -1431,7 +1449,13 @@ static FusedOneKernel fused_one_kernel_of(bool g32, bool o32, uint32_t R)
 template <bool G32, bool O32, size_t... I>
 static std::array<const void *, sizeof...(I)> fused_near_kernels(std::index_sequence<I...>)
 {
-    return {reinterpret_cast<const void *>(fused_near_kernel<I + 1, G32, O32, fused_chunk(G32, I + 1, kFew)>)...};
+    return {reinterpret_cast<const void *>(fused_near_kernel<I + kNearLeast, G32, O32, fused_chunk(G32, I + kNearLeast, kFew)>)...};
+}
+
+template <bool G32, bool O32, size_t... I>
+static std::array<const void *, sizeof...(I)> fused_even_kernels(std::index_sequence<I...>)
+{
+    return {reinterpret_cast<const void *>(fused_even_kernel<I + 1, G32, O32, fused_chunk(G32, I + 1, kFew)>)...};
 }
 
 template <FusedForm FORM>
@@ -1440,6 +1464,16 @@ static hzp_status_t start_fused(bool g32, bool o32, uint32_t R, const FusedArgs 
     const ChunkClass c = fused_class(g32, R, FORM, groups);
     const FusedKernel kernel = c == kFew ? fused_kernel<FORM, kFew>(g32, o32, R) : c == kMid ? fused_kernel<FORM, kMid>(g32, o32, R) : fused_kernel<FORM, kLarge>(g32, o32, R);
     return start("hzp_adamw_shard", kernel, grid, dim3(kWave), fused_lds(g32, R, c, FORM, groups), stream, a);
+}
+
+// Longest launch that takes equally distant contributions by their distance.  Against the other forms, calls in a row on buffers of one call's size, streams 2, 4 .. 18 MiB apart,
+// median (worst) ratio: bf16 R = 1 / 2 of 0.2 to 0.52 M elements .95 / .97 (1.01), R = 5 to 8 .89 (1.00), R = 3 / 4 of 0.16 to 0.39 M .88 / .89 (.96), of 0.49 M 1.0 to 1.2 (1.6 to 1.9), R >= 9 of
+// 0.07 to 0.26 M .87 (1.02), of 0.33 M .90 (1.06); fp32 R <= 8 .90 (1.0), R >= 9 of 0.07 to 0.16 M .87 (1.00), of 0.23 / 0.26 M .91 / .93 (1.13 / 1.7).  R = 16 of 16 k elements 4.5 -> 3.7 us, fp32 R = 8 of
+// 0.26 M 5.1 -> 4.4.  (Longer ones take the device longer than the host, and what starts faster collides in the memory channels.  In graphs 1.00 (.95 to 1.03), so captured ones stay as they were.)
+static uint32_t even_groups(bool g32, uint32_t R)
+{
+    if (R > 8) return g32 ? 640u : 1024u;
+    return !g32 && (R == 3 || R == 4) ? 1536u : kFewGroups;
 }
 
 // One segment with one multiplier: its record and pointers are a.word's first.
@@ -1451,12 +1485,24 @@ static hzp_status_t start_fused_one(bool g32, bool o32, uint32_t R, const FusedA
         kernel = R == 2 ? fused_one_kernel<2, false, false, 2, 96> : !g32 ? fused_one_kernel<1, false, false, 1, 96>
                  : o32 ? fused_one_kernel<1, true, true, 1, 96> : fused_one_kernel<1, true, false, 1, 96>;
     const uint64_t *const w = a.word, *const rec = a.word + R + 4;
-    // Launches of up to 5.5 MB take the host longer than the device, and their blocks stay within kFewBytes.  Two pointers and distances / pointers, us, bf16 of
-    // 16 k and 0.13 M elements, calls in a row: R = 1 3.8 / 4.2, 3.75 / 4.4, R = 4 3.8 / 4.3, 3.8 / 4.4, R = 8 3.8 / 4.35, 3.7 / 4.1 (a mean of -9 % over both types); on the
+    const uint64_t size = rec[0] >> 32 | rec[1] << 32;
+    bool even = groups <= even_groups(g32, R) && !captured(stream);
+    for (uint32_t r = 2; even && r < R; ++r) even = w[4 + r] - w[3 + r] == w[5] - w[4];
+    if (even) {
+        constexpr std::make_index_sequence<HZP_MAX_REPLICAS> all;
+        static const auto kernels16 = fused_even_kernels<false, false>(all), kernels32 = fused_even_kernels<true, true>(all);
+        const void *const k = !g32 ? kernels16[R - 1] : o32 ? kernels32[R - 1] : reinterpret_cast<const void *>(fused_even_kernel<1, true, false, fused_chunk(true, 1, kFew)>);
+        const u64x4 p{w[0], w[1], w[2], w[4]};
+        const u64x2 far{R > 1 ? w[5] - w[4] : 0, reinterpret_cast<uint64_t>(a.scalars_dev)};
+        const FusedEvenArgs rest{w[3], a.scalars};
+        return start_any("hzp_adamw_shard", k, dim3(groups), dim3(kWave), 0, stream, &p, &far, &size, &rest);
+    }
+    // Others of up to 5.5 MB take two pointers and distances.  So / by pointers, us, bf16 of
+    // 16 k and 0.13 M elements, calls in a row: R = 4 3.8 / 4.3, 3.8 / 4.4, R = 8 3.8 / 4.35, 3.7 / 4.1 (a mean of -9 % over both types); on the
     // device alone R = 4 2.46 / 2.42, 2.65 / 2.65, R = 8 2.60 / 2.55, 3.26 / 3.22 (the addresses are worked out before the first requests), so captured ones take pointers.  Beyond, the
     // device's time shows: R = 8 of 0.15 / 0.2 M 3.39 / 3.27, 3.83 / 3.50, R = 4 of 0.46 M 4.6 / 4.3 in a row.
     const uint64_t bytes = (uint64_t)groups * kGroupQuads * 4 * (R * (g32 ? 4u : 2u) + 24 + (o32 ? 4u : 2u));
-    if (bytes <= 5500000 && groups <= kFewGroups && R <= kNearR && !captured(stream)) {
+    if (bytes <= 5500000 && groups <= kFewGroups && R >= kNearLeast && R <= kNearR && !captured(stream)) {
         bool fits = true;
         auto distance = [&](uint64_t to, uint64_t from) {
             const int64_t d = (int64_t)(to - from) / 16;        // (all are multiples of 16)
@@ -1464,19 +1510,16 @@ static hzp_status_t start_fused_one(bool g32, bool o32, uint32_t R, const FusedA
             return (int32_t)d;
         };
         const u64x2 base{w[0], w[4]};
-        const i32x4 d{distance(w[1], w[0]), distance(w[2], w[0]), w[3] ? distance(w[3], w[0]) : 0, R > 1 ? distance(w[5], w[4]) : 0};
-        const i32x2 d2{R > 2 ? distance(w[6], w[4]) : 0, R > 3 ? distance(w[7], w[4]) : 0};
-        const uint64_t size = rec[0] >> 32 | rec[1] << 32 | (w[3] ? kHasOut : 0), dev = reinterpret_cast<uint64_t>(a.scalars_dev);
+        const i32x4 d{distance(w[1], w[0]), distance(w[2], w[0]), w[3] ? distance(w[3], w[0]) : 0, distance(w[5], w[4])};
+        const i32x2 d2{distance(w[6], w[4]), R > 3 ? distance(w[7], w[4]) : 0};
+        const uint64_t out = w[3] ? kHasOut : 0, dev = reinterpret_cast<uint64_t>(a.scalars_dev), flagged = size | out;
         FusedNearArgs<kNearR> near;
         near.scalars = a.scalars;
         for (uint32_t r = 4; r < R; ++r) near.g[r - 4] = distance(w[4 + r], w[4]);
         if (fits) {
-            constexpr std::make_index_sequence<kNearR> all;
-            static const auto kernels16 = fused_near_kernels<false, false>(all), kernels32 = fused_near_kernels<true, true>(all);
-            const void *const k = !g32  ? kernels16[R - 1]
-                                  : o32 ? kernels32[R - 1]
-                                        : reinterpret_cast<const void *>(fused_near_kernel<1, true, false, fused_chunk(true, 1, kFew)>);
-            return start_any("hzp_adamw_shard", k, dim3(groups), dim3(kWave), 0, stream, &base, &d, &d2, &size, &dev, &near);
+            constexpr std::make_index_sequence<kNearR - kNearLeast + 1> some;
+            static const auto kernels16 = fused_near_kernels<false, false>(some), kernels32 = fused_near_kernels<true, true>(some);
+            return start_any("hzp_adamw_shard", (g32 ? kernels32 : kernels16)[R - kNearLeast], dim3(groups), dim3(kWave), 0, stream, &base, &d, &d2, &flagged, &dev, &near);
         }
     }
     FusedOneArgs one;
@@ -1484,7 +1527,7 @@ static hzp_status_t start_fused_one(bool g32, bool o32, uint32_t R, const FusedA
     one.scalars = a.scalars;
     std::memcpy(one.g, a.word + 4, R * sizeof one.g[0]);
     return start("hzp_adamw_shard", kernel, dim3(groups), dim3(kWave), fused_lds(g32, R, c, kOne, groups), stream, u64x4{w[0], w[1], w[2], w[4]},
-                 u64x2{R > 1 ? w[5] : 0, reinterpret_cast<uint64_t>(a.scalars_dev)}, rec[0] >> 32 | rec[1] << 32, one);
+                 u64x2{R > 1 ? w[5] : 0, reinterpret_cast<uint64_t>(a.scalars_dev)}, size, one);
 }
 
 hzp_status_t launch_fused(const hzp_plan_t *plan, bool g32, bool o32, uint32_t R, const FusedSegment *segs, size_t nseg,

@@ -784,6 +784,40 @@ def test_short_updates_with_streams_near_and_far(cls, R, n, wide_room):
                 assert torch.equal(streams[-1], want), (far, call, given)
 
 
+@pytest.mark.parametrize("cls,R", [(c, R) for c in (0, 1) for R in (2, 3, 4, 5, 8, 9, 16, 17, 31, 32)])
+@pytest.mark.parametrize("n", [8, 264, 640 * 256, 640 * 256 + 8, 1024 * 256, 1024 * 256 + 8, 1536 * 256, 1536 * 256 + 8, 2048 * 256 + 8])
+def test_short_updates_with_equally_distant_contributions(cls, R, n):
+    """Contributions at equal distances, upwards and downwards, and with the last one 16 bytes off: the same bits on both sides of each limit, and
+    close to the sum and step in float64."""
+    print(cls, R, n, flush=True)
+    gen = torch.Generator(device=DEV).manual_seed(R + n)
+    gt = torch.float32 if cls else torch.bfloat16
+    grads = [(torch.randn(n, device=DEV, generator=gen) * 1e-3).to(gt) for _ in range(R)]
+    state = [torch.randn(n, device=DEV, generator=gen) * s for s in (0.02, 1e-4, 1e-4)]
+    state[2].square_()
+    plan = hzp.hzp_plan([1], [n], align=8, z3=1, z1=1, tensor_class=[cls])
+    hy = hzp.adamw_hyper(HP["lr"], HP["beta1"], HP["beta2"], HP["eps"], HP["weight_decay"], 1.0 / R, 3)
+    size = n * grads[0].itemsize
+    step = size + 272
+    raw = torch.empty(step * R + 64, dtype=torch.uint8, device=DEV)
+    first = None
+    for placed in ([step * r for r in range(R)], [step * (R - 1 - r) for r in range(R)], [step * r + 16 * (r == R - 1) for r in range(R)]):
+        g = [raw[a:a + size].view(gt) for a in placed]
+        for t, x in zip(g, grads):
+            t.copy_(x)
+        got = [t.clone() for t in state] + [torch.zeros(n, dtype=gt, device=DEV)]
+        hzp.hzp_adamw_shard(plan, 0, 1, cls, 0, hy, g, R, *[[t] for t in got])
+        torch.cuda.synchronize()
+        first = first or got
+        assert all(torch.equal(a, b) for a, b in zip(got, first))
+    mean = sum(t.double() for t in grads) / R
+    m = HP["beta1"] * state[1].double() + (1 - HP["beta1"]) * mean
+    # (each of at most 31 sums rounds by 2^-24 of what is summed so far, the scaling and the step by four times as much)
+    bound = 2.0 ** -24 * ((R + 4) * sum(t.double().abs() for t in grads) / R + 4 * state[1].double().abs())
+    assert ((first[1].double() - m).abs() <= bound).all()
+    assert torch.equal(first[3], first[0].to(gt))
+
+
 @pytest.mark.parametrize("cls", [0, 1])
 @pytest.mark.parametrize("kind,n,z3", [("tiny", 6, 1), ("tiny", 12, 3), ("spread", 6, 8), ("spread", 12, 8), ("spread", 13, 8), ("even", 12, 2), ("long", 6, 3),
                                        ("long", 12, 8), ("long", 13, 8), ("long", 64, 8), ("long", 64, 9), ("long", 65, 2)])
