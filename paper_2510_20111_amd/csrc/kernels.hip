@@ -341,6 +341,29 @@ __global__ __launch_bounds__(kWave) void reduce_block_kernel(const ReduceArgs<R>
     reduce<R, G32, ACC, FORM>(out, nquad, scale, at, [&](uint32_t r) { return a.all.g[r]; });
 }
 
+// Short launches of more contributions than kFewBytes hold pointers of: up to 23 as distances from the first in 16 bytes, more (and equally distant) as one distance.
+// o: output, number of quads and scale.
+constexpr uint32_t kReduceApartLeast = 13, kReduceApartMost = 23;
+template <uint32_t R>
+struct ReduceApart {
+    int32_t d[R - 1];
+    __device__ __forceinline__ uint64_t of(uint64_t first, uint32_t r) const { return r ? at_distance(first, d[r - 1]) : first; }
+};
+struct ReduceEven {
+    uint64_t stride;
+    __device__ __forceinline__ uint64_t of(uint64_t first, uint32_t r) const { return first + r * stride; }
+};
+static_assert(sizeof(u64x2) + sizeof(uint64_t) + sizeof(ReduceApart<kReduceApartMost>) == kFewBytes, "argument block");
+template <uint32_t R, bool G32, bool ACC, class Others>
+__global__ __launch_bounds__(kWave) void reduce_apart_kernel(const u64x2 o, const uint64_t first, const Others others)
+{
+    constexpr uint32_t CHUNK = reduce_chunk(R, kReduceFew);
+    uint64_t at[CHUNK];
+#pragma unroll
+    for (uint32_t c = 0; c < CHUNK; ++c) at[c] = c < R ? others.of(first, c) : 0;
+    reduce<R, G32, ACC, kReduceFew>(o[0], (uint32_t)o[1], __uint_as_float((uint32_t)(o[1] >> 32)), at, [&](uint32_t r) { return others.of(first, r); });
+}
+
 // ---------------------------------------------------------------------------------------
 // Fused reduce + scale + AdamW + cast over many shard segments.
 // ---------------------------------------------------------------------------------------
@@ -1150,6 +1173,20 @@ static KernelOfR reduce_block_kernels(std::index_sequence<I...>)
     return {reduce_block_kernel_of<I + 1, G32, ACC, FORM>()...};
 }
 
+template <bool G32, bool ACC, uint32_t R>
+static const void *reduce_apart_kernel_of()
+{
+    if constexpr (R <= kReduceApartMost)
+        return reinterpret_cast<const void *>(reduce_apart_kernel<R, G32, ACC, ReduceApart<R>>);
+    else
+        return reinterpret_cast<const void *>(reduce_apart_kernel<R, G32, ACC, ReduceEven>);
+}
+template <bool G32, bool ACC, size_t... I>
+static std::array<const void *, sizeof...(I)> reduce_apart_kernels(std::index_sequence<I...>)
+{
+    return {reduce_apart_kernel_of<G32, ACC, I + kReduceApartLeast>()...};
+}
+
 typedef void (*FusedKernel)(FusedArgs);
 typedef void (*FusedOneKernel)(u64x4, u64x2, uint64_t, FusedOneArgs);
 template <bool G32, bool O32, FusedForm FORM, ChunkClass CLASS, size_t... I>
@@ -1234,6 +1271,35 @@ static bool reduce_from_block(bool g32, uint32_t R, ReduceForm form, uint64_t n,
 // 6.84 / 6.85, bf16 R = 8 (5.7 GB) 6.89 / 6.88 / 6.82 / 6.70, R = 4 (3.4 GB) 6.84 / 6.82 / 6.80 / 6.68.
 constexpr uint64_t most_reduce_bytes(uint32_t R) { return R > 8 ? 3000000000ull : 6000000000ull; }
 
+// Longest launch by distances, in groups.  Against pointers (120 to 272 bytes of arguments), calls in a row on buffers of one call's size, streams 2, 4 .. 18 MiB apart, R = 13 to 32, accumulating or
+// not, median (worst) ratio: bf16 of up to 0.2 M elements .88 (1.02), 0.26 M .88 (1.08), 0.46 / 0.52 M .94 (1.12); fp32 of up to 65 k .88 (1.01), 0.13 M .89 (1.08), 0.26 M .97 (1.13), 0.52 M 1.02
+// (1.16): R = 16 of 16 k elements 4.2 -> 3.6 us.  Beyond, what starts faster collides in the memory channels.  On the device alone 1.00 (R <= 23 .99 to 1.05), so captured ones stay as they are.
+static uint32_t apart_groups(bool g32) { return g32 ? 384u : 768u; }
+
+// A launch by distances; *done is false (and nothing launched) where the contributions lie too far apart, or more than 23 not equally so.
+static hzp_status_t start_reduce_apart(bool g32, uint32_t R, bool accumulate, const uint64_t *g, u64x2 o, dim3 grid, unsigned lds, hipStream_t stream, bool *done)
+{
+    constexpr std::make_index_sequence<HZP_MAX_REPLICAS - kReduceApartLeast + 1> all;
+    static const std::array<const void *, HZP_MAX_REPLICAS - kReduceApartLeast + 1> kernels[2][2] = {
+        {reduce_apart_kernels<false, false>(all), reduce_apart_kernels<false, true>(all)}, {reduce_apart_kernels<true, false>(all), reduce_apart_kernels<true, true>(all)}};
+    const void *const kernel = kernels[g32][accumulate][R - kReduceApartLeast];
+    bool fits = true;
+    if (R <= kReduceApartMost) {
+        ReduceApart<kReduceApartMost> others;
+        for (uint32_t r = 1; r < R; ++r) {
+            const int64_t d = (int64_t)(g[r] - g[0]) / 16;          // (all are multiples of 16)
+            fits = fits && d == (int32_t)d;
+            others.d[r - 1] = (int32_t)d;
+        }
+        *done = fits;
+        return fits ? start_any("hzp_reduce_shard", kernel, grid, dim3(kWave), lds, stream, &o, g, &others) : HZP_OK;
+    }
+    const ReduceEven others{g[1] - g[0]};
+    for (uint32_t r = 2; r < R; ++r) fits = fits && g[r] - g[r - 1] == others.stride;
+    *done = fits;
+    return fits ? start_any("hzp_reduce_shard", kernel, grid, dim3(kWave), lds, stream, &o, g, &others) : HZP_OK;
+}
+
 hzp_status_t launch_reduce(bool g32, const void *const *slices, uint32_t R, uint64_t n, float scale,
                            int accumulate, float *out, hipStream_t stream)
 {
@@ -1265,14 +1331,17 @@ hzp_status_t launch_reduce(bool g32, const void *const *slices, uint32_t R, uint
         uint64_t *const g = a.all.g;
         for (uint32_t r = 0; r < R; ++r) g[r] = reinterpret_cast<uint64_t>(slices[r]) + first * es;
         for (uint32_t r = R; r < 4; ++r) g[r] = 0;
-        hzp_status_t st;
-        if (reduce_from_block(g32, R, form, here, accumulate)) {
+        uint32_t scale_bits;
+        std::memcpy(&scale_bits, &scale, sizeof scale_bits);
+        const u64x2 o{a.out, nquad | (uint64_t)scale_bits << 32};
+        hzp_status_t st = HZP_OK;
+        bool done = false;
+        if (R >= kReduceApartLeast && (nquad + kGroupQuads - 1) / kGroupQuads <= apart_groups(g32) && !captured(stream)) st = start_reduce_apart(g32, R, accumulate != 0, g, o, grid, lds, stream, &done);
+        if (done) {
+        } else if (reduce_from_block(g32, R, form, here, accumulate)) {
             st = start_any("hzp_reduce_shard", form == kReduceNarrow ? narrow_block[accumulate != 0][R - 1] : short_block[g32][R - 1], grid, block, lds, stream, &a);
         } else {
-            uint32_t scale_bits;
-            std::memcpy(&scale_bits, &scale, sizeof scale_bits);
             const u64x4 lead{g[0], g[1], g[2], g[3]};
-            const u64x2 o{a.out, nquad | (uint64_t)scale_bits << 32};
             st = start_any("hzp_reduce_shard", kernels[g32][accumulate != 0][form][R - 1], grid, block, lds, stream, &lead, &o, g + 4);
         }
         if (st != HZP_OK) return st;

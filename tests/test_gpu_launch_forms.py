@@ -784,6 +784,39 @@ def test_short_updates_with_streams_near_and_far(cls, R, n, wide_room):
                 assert torch.equal(streams[-1], want), (far, call, given)
 
 
+@pytest.mark.parametrize("accumulate", [0, 1])
+@pytest.mark.parametrize("g32", [0, 1])
+@pytest.mark.parametrize("R", [12, 13, 16, 17, 23, 24, 31, 32])
+@pytest.mark.parametrize("n", [8, 264, 384 * 256, 384 * 256 + 8, 768 * 256, 768 * 256 + 8])
+def test_short_reductions_by_distance(n, R, g32, accumulate, wide_room):
+    """Contributions at equal distances, upwards and downwards, in any order, and one of them 33 GiB away: the sum in order, bit for bit."""
+    print(n, R, g32, accumulate, flush=True)
+    rng = np.random.default_rng(R + n)
+    gt = torch.float32 if g32 else torch.bfloat16
+    grads = [torch.from_numpy(rng.standard_normal(n, dtype=np.float32)).to(DEV).to(gt) for _ in range(R)]
+    before = torch.from_numpy(rng.standard_normal(n, dtype=np.float32)).to(DEV)
+    want = grads[0].float()
+    for t in grads[1:]:
+        want = want + t.float()
+    want = want * 0.5
+    want = before + want if accumulate else want
+    plan = hzp.hzp_plan([1], [n], align=8, z3=1, z1=1)
+    size = n * grads[0].itemsize
+    step = size + 16
+    raw = torch.empty(step * R, dtype=torch.uint8, device=DEV)
+    mixed = [int(r) * step for r in rng.permutation(R)]
+    for placed, far in (([step * r for r in range(R)], False), ([step * (R - 1 - r) for r in range(R)], False), (mixed, False), (mixed, True)):
+        g = [raw[a:a + size].view(gt) for a in placed]
+        if far:
+            g[R // 2] = wide_room[33 << 30:(33 << 30) + size].view(gt)
+        for t, x in zip(g, grads):
+            t.copy_(x)
+        out = before.clone()
+        hzp.hzp_reduce_shard(plan, 0, 0, 3, 0, g, 0.5, accumulate, out, grad_dtype=hzp.HZP_GRAD_F32 if g32 else hzp.HZP_GRAD_BF16)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want), (placed[:3], far)
+
+
 @pytest.mark.parametrize("cls,R", [(c, R) for c in (0, 1) for R in (2, 3, 4, 5, 8, 9, 16, 17, 31, 32)])
 @pytest.mark.parametrize("n", [8, 264, 640 * 256, 640 * 256 + 8, 1024 * 256, 1024 * 256 + 8, 1536 * 256, 1536 * 256 + 8, 2048 * 256 + 8])
 def test_short_updates_with_equally_distant_contributions(cls, R, n):
