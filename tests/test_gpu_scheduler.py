@@ -472,3 +472,45 @@ def test_a_layers_parameters_with_one_call_each():
     assert st.gathers_issued == len(oplan["tensors"]) and st.peak_live_slots == 12
     assert st.wrap_skipped_bytes > 0                                # the ring did wrap
     sched.destroy()
+
+
+@pytest.mark.parametrize("order", ["grgr", "rrgn", "nrng", "gnrb", "bnnb"])
+def test_join_after_gathers_reductions_or_neither(order):
+    """Joins after a gather (g), a reduction (r), both (b) or nothing new (n): what ran before each, on either stream, is there for the
+    consumer, which copies it without any other wait; several consumers in turn."""
+    say("scheduler: join after " + order)
+    oplan, plan, shards = _layers(2, 53)
+    dshards = [[to_dev(s) for s in layer] for layer in shards]
+    lens = [b["P"] for b in oplan["buckets"]]
+    sched = hzp.Sched(plan, gather_slots=2, queue_capacity=8)
+    producer, consumers = torch.cuda.Stream(), [torch.cuda.Stream(), torch.cuda.Stream()]
+    busy = torch.randn(2048, 2048, device=DEV)
+    n = oplan["buckets"][0]["S3"]
+    grads = [torch.full((n,), float(k + 1), device=DEV) for k in range(2)]
+    acc = torch.zeros(n, device=DEV)
+    torch.cuda.synchronize()
+    reduced = 0
+    for i, what in enumerate(order):
+        consumer, layer = consumers[i % 2], i % 2
+        with torch.cuda.stream(producer):
+            busy = busy @ busy * 1e-3                 # keeps what follows pending
+        if what in "gb":
+            sched.prefetch(layer, dshards[layer], producer)
+        if what in "rb":
+            sched.reduce(0, 3, 0, grads, 1.0, True, acc, producer, grad_dtype=hzp.HZP_GRAD_F32)
+            reduced += 1
+        sched.join(consumer)
+        with torch.cuda.stream(consumer):
+            seen = acc.clone()
+        if what in "gb":
+            ptr = sched.acquire(layer, consumer)
+            with torch.cuda.stream(consumer):
+                got = view16(ptr, lens[layer]).clone()
+            sched.release(layer, consumer)
+        consumer.synchronize()
+        assert torch.equal(seen, torch.full_like(seen, 3.0 * reduced)), i
+        if what in "gb":
+            assert np.array_equal(to_host(got, np.uint16), on.gather_concat(shards[layer])), i
+        producer.wait_stream(consumer)                # the next reduction writes what this consumer has read
+    sched.drain()
+    sched.destroy()
