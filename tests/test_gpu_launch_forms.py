@@ -888,3 +888,46 @@ def test_tensors_that_lie_near_each_other_and_far(kind, n, z3, cls, wide_room):
             assert torch.equal(v, host[first:first + numel[t]]), (odd, far, t)
             v.fill_(-1)
         assert torch.equal(wide_room[:sum(room)], before), (odd, far)       # nothing else changed
+
+
+@pytest.mark.parametrize("cls", [0, 1])
+@pytest.mark.parametrize("K,s1", [(1, 8), (2, 520), (8, 64), (9, 128), (10, 8)])
+@pytest.mark.parametrize("layers", [2, 7, 33, 210])
+def test_layers_of_one_length_at_equal_distances(layers, K, s1, cls):
+    """All layers of a post-step gather, upwards and downwards, with the rank's own piece in place, with one layer elsewhere, one source's layers at
+    another distance, one piece of one layer in place and the last layer longer: to the bit, and nothing beside the outputs written."""
+    print(layers, K, s1, cls, flush=True)
+    rng = np.random.default_rng(layers * 11 + K + s1)
+    es, dtype = 4 if cls else 2, torch.int32 if cls else torch.int16
+    for form in ("up", "down", "own", "layer", "source", "piece", "longer"):
+        own = K // 2
+        lens = [s1] * layers
+        if form == "longer":
+            lens[-1] = s1 + 8
+        plan = hzp.hzp_plan([1] * layers, [n * K for n in lens], align=8, z3=1, z1=K, tensor_class=[cls] * layers)
+        assert [plan.bucket(l, cls).s1 for l in range(layers)] == lens
+        step = s1 + 16
+        room = step * (layers + 3)
+        src = torch.from_numpy(rng.integers(0, 30000, (K, room)).astype(np.int32 if cls else np.int16)).to(DEV)
+        out = torch.full((layers + 3, (s1 + 8) * K + 32), -1, dtype=dtype, device=DEV)
+        order = list(range(layers))[::-1] if form == "down" else list(range(layers))
+        if form == "layer":
+            order[layers // 2] = layers + 1
+        dsts = [out[order[l], 16:16 + lens[l] * K] for l in range(layers)]
+        parts, expect = [], torch.full_like(out, -1)
+        for l in range(layers):
+            for k in range(K):
+                at = order[l] * (step + (8 if form == "source" and k == 0 and 8 * layers <= 3 * step else 0))
+                piece = src[k, at:at + lens[l]]
+                if (form == "own" and k == own) or (form == "piece" and k == 0 and l == layers - 1):
+                    place = dsts[l][k * lens[l]:(k + 1) * lens[l]]
+                    place.copy_(piece)
+                    parts.append(place)
+                else:
+                    parts.append(piece)
+                expect[order[l], 16 + k * lens[l]:16 + (k + 1) * lens[l]] = piece
+        before = src.clone()
+        hzp.hzp_gather_layers(plan, 0, layers, cls, 1, parts, K, dsts)
+        torch.cuda.synchronize()
+        assert torch.equal(out, expect), form
+        assert torch.equal(src, before), form
