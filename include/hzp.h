@@ -149,7 +149,7 @@ hzp_status_t hzp_plan(const hzp_plan_desc_t *desc, hzp_plan_t **out);
 void hzp_plan_free(hzp_plan_t *plan);
 
 /* Create the plan's lookup tables on the current device now (tensor offsets and decay multipliers
- * for updates with per-tensor decay, tensor pieces for the unpacking gathers): one allocation and
+ * for updates with per-tensor decay, tensor pieces and spans for the unpacking gathers): one allocation and
  * one blocking copy per table.  This is the one call on a plan that may allocate device memory and
  * synchronise; after it has returned, no kernel-launching call with this plan on this device
  * allocates, copies or waits (without it, the first call that needs a table creates it, and that
