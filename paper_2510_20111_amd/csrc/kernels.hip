@@ -2586,7 +2586,7 @@ hzp_status_t device_tables(const hzp_plan_t *plan, const DeviceTables **out)
     if (e == hipSuccess) e = upload((void **)&t.piece_chunk, chunk_begin.data(), chunk_begin.size() * sizeof(uint32_t));
     t.span = t.piece_chunk + span_at;
     // (a stream created as non-blocking is not ordered behind the null stream's copies, and the call that made the tables may read them)
-    if (e == hipSuccess && hipStreamSynchronize(nullptr) != hipSuccess) (void)hipGetLastError();
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     if (e != hipSuccess) {
         (void)hipFree(t.piece_chunk);
         (void)hipFree(t.run_off);

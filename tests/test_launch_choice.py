@@ -1,0 +1,76 @@
+"""What the entry points launch, without a GPU: libhzp's host code with a stand-in for the HIP runtime that records launches
+(tests/dispatch).  Calls that are captured and calls that are not are told apart by the stand-in's capture status; nothing runs."""
+import ctypes
+import importlib.util
+import os
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def load(name, *path):
+    spec = importlib.util.spec_from_file_location(name, os.path.join(ROOT, *path))
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    return module
+
+
+class Recorder:
+    """The binding over the recording build, and what that recorded."""
+
+    def __init__(self):
+        before = os.environ.get("HZP_LIBRARY")
+        os.environ["HZP_LIBRARY"] = load("dispatch_build", "tests", "dispatch", "build.py").build()
+        try:
+            self.hzp = load("hzp_recorded", "paper_2510_20111_amd", "binding.py")
+        finally:
+            if before is None:
+                del os.environ["HZP_LIBRARY"]
+            else:
+                os.environ["HZP_LIBRARY"] = before
+        self.lib = self.hzp._L
+        self.lib.recorded_kernel.restype = ctypes.c_char_p
+
+    def launches(self, call, captured=False):
+        """(kernel's name with its template arguments, grid, dynamic LDS) of each launch of `call`."""
+        self.lib.forget()
+        self.lib.set_capture(1 if captured else 0)
+        try:
+            call()
+        finally:
+            self.lib.set_capture(0)
+        out = []
+        for i in range(self.lib.recorded()):
+            shape = (ctypes.c_uint * 4)()
+            self.lib.recorded_shape(i, shape)
+            name = self.lib.recorded_kernel(i).decode().replace("hzp::", "").replace("(anonymous namespace)::", "")
+            out.append((name[:name.index("(")].removeprefix("void "), tuple(shape[:3]), shape[3]))
+        return out
+
+
+@pytest.fixture(scope="module")
+def rec():
+    return Recorder()
+
+
+def test_tables_whose_copies_were_not_waited_for_are_not_used(rec):
+    """The wait behind the tables' copies fails: so does the call that makes them, nothing is launched and nothing kept, and the next call
+    makes them anew."""
+    hzp = rec.hzp
+    numel = [100] * 9
+    plan = hzp.hzp_plan([9], numel, align=64, z3=1, z1=1)
+    shard, tensors = 0x7000000000, [0x7100000000 + 4096 * t for t in range(9)]
+    rec.lib.set_wait_status(719)
+    try:
+        for call in (lambda: plan.prepare(stream=0), lambda: hzp.hzp_gather_layer(plan, 0, 0, 3, [shard], None, tensors, stream=0)):
+            with pytest.raises(hzp.HzpError) as caught:
+                rec.launches(call)
+            assert caught.value.status == hzp.HZP_ERR_HIP
+            assert rec.lib.recorded() == 0 and rec.lib.live_allocations() == 0
+    finally:
+        rec.lib.set_wait_status(0)
+    assert len(rec.launches(lambda: hzp.hzp_gather_layer(plan, 0, 0, 3, [shard], None, tensors, stream=0))) == 1
+    assert rec.lib.live_allocations() == 4
+    del plan
+    assert rec.lib.live_allocations() == 0
