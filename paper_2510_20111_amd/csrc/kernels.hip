@@ -2564,7 +2564,25 @@ hzp_status_t device_tables(const hzp_plan_t *plan, const DeviceTables **out)
     DeviceTables t;
     t.device = dev;
     std::vector<Piece> all;
-    for (const BucketRec &b : plan->buckets) all.insert(all.end(), b.pieces.begin(), b.pieces.end());
+    std::vector<uint32_t> words;        // the pieces' first chunks, and behind them the tensors' spans
+    size_t span_at = 0;
+    try {
+        for (const BucketRec &b : plan->buckets) all.insert(all.end(), b.pieces.begin(), b.pieces.end());
+        words.resize(all.size() + all.size() % 2);
+        for (size_t i = 0; i < all.size(); ++i) words[i] = all[i].chunk_begin;
+        span_at = words.size();
+        for (const BucketRec &b : plan->buckets)
+            for (uint32_t id : b.tensor_ids) {
+                const TensorRec &r = plan->tensors[id];
+                words.push_back((uint32_t)r.offset);                // (read only where the bucket is short)
+                words.push_back((uint32_t)(r.offset + r.numel));
+            }
+        // The vector may only grow while no reader holds a pointer into it: reserve once.
+        if (plan->dev.capacity() == 0) plan->dev.reserve(64);
+    } catch (const std::bad_alloc &) {
+        return fail(HZP_ERR_NOMEM, "device tables: out of host memory");
+    }
+    if (plan->dev.size() == plan->dev.capacity()) return fail(HZP_ERR_UNSUPPORTED, "plan used on more than 64 devices");
     const size_t nr = plan->run_off.size();
     auto upload = [&](void **dptr, const void *src, size_t bytes) -> hipError_t {
         hipError_t err = hipMalloc(dptr, bytes ? bytes : 16);
@@ -2574,16 +2592,7 @@ hzp_status_t device_tables(const hzp_plan_t *plan, const DeviceTables **out)
     e = upload((void **)&t.run_off, plan->run_off.data(), nr * sizeof(uint64_t));
     if (e == hipSuccess) e = upload((void **)&t.run_wd, plan->run_wd.data(), nr * sizeof(float));
     if (e == hipSuccess) e = upload((void **)&t.pieces, all.data(), all.size() * sizeof(Piece));
-    std::vector<uint32_t> chunk_begin(all.size() + all.size() % 2);         // and behind them the tensors' spans
-    for (size_t i = 0; i < all.size(); ++i) chunk_begin[i] = all[i].chunk_begin;
-    const size_t span_at = chunk_begin.size();
-    for (const BucketRec &b : plan->buckets)
-        for (uint32_t id : b.tensor_ids) {
-            const TensorRec &r = plan->tensors[id];
-            chunk_begin.push_back((uint32_t)r.offset);              // (read only where the bucket is short)
-            chunk_begin.push_back((uint32_t)(r.offset + r.numel));
-        }
-    if (e == hipSuccess) e = upload((void **)&t.piece_chunk, chunk_begin.data(), chunk_begin.size() * sizeof(uint32_t));
+    if (e == hipSuccess) e = upload((void **)&t.piece_chunk, words.data(), words.size() * sizeof(uint32_t));
     t.span = t.piece_chunk + span_at;
     // (a stream created as non-blocking is not ordered behind the null stream's copies, and the call that made the tables may read them)
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
@@ -2595,10 +2604,6 @@ hzp_status_t device_tables(const hzp_plan_t *plan, const DeviceTables **out)
         return fail(e == hipErrorOutOfMemory ? HZP_ERR_NOMEM : HZP_ERR_HIP, "device tables: %s",
                     hipGetErrorString(e));
     }
-    // The vector may only grow while no reader holds a pointer into it: reserve once.
-    if (plan->dev.capacity() == 0) plan->dev.reserve(64);
-    if (plan->dev.size() == plan->dev.capacity())
-        return fail(HZP_ERR_UNSUPPORTED, "plan used on more than 64 devices");
     plan->dev.push_back(t);
     *out = &plan->dev.back();
     return HZP_OK;

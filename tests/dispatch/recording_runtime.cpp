@@ -8,6 +8,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -26,8 +27,21 @@ std::map<const void *, std::string> &kernels()
     return names;
 }
 std::atomic<int> capture{0}, wait_status{0}, allocations{0};
+std::atomic<long> host_allocations{-1};        // so many more succeed; negative: all do
 
 }  // namespace
+
+void *operator new(size_t bytes)
+{
+    if (host_allocations >= 0 && host_allocations-- == 0) {
+        host_allocations = -1;
+        throw std::bad_alloc();
+    }
+    if (void *const p = std::malloc(bytes ? bytes : 1)) return p;
+    throw std::bad_alloc();
+}
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
 
 extern "C" {
 
@@ -43,6 +57,8 @@ void forget() { launches.clear(); }
 void set_capture(int status) { capture = status; }
 void set_wait_status(int status) { wait_status = status; }
 int live_allocations() { return allocations; }
+void fail_host_allocation(long which) { host_allocations = which; }
+int host_allocation_failed() { return host_allocations.exchange(-1) < 0; }     // (and no further one fails)
 
 void **__hipRegisterFatBinary(const void *)
 {
@@ -65,7 +81,9 @@ hipError_t hipLaunchKernel(const void *function, dim3 grid, dim3, void **, size_
     std::lock_guard<std::mutex> lock(mu);
     const auto known = kernels().find(function);
     if (known == kernels().end()) return hipErrorInvalidDeviceFunction;
+    const long left = host_allocations.exchange(-1);        // (the record's own allocations succeed)
     launches.push_back({known->second, {grid.x, grid.y, grid.z}, (unsigned)lds});
+    host_allocations = left;
     return hipSuccess;
 }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *status)

@@ -74,3 +74,34 @@ def test_tables_whose_copies_were_not_waited_for_are_not_used(rec):
     assert rec.lib.live_allocations() == 4
     del plan
     assert rec.lib.live_allocations() == 0
+
+
+def test_calls_that_run_out_of_host_memory_end_with_a_status(rec):
+    """Each host allocation of a call fails in turn: the call returns HZP_ERR_NOMEM (nothing is thrown through the C boundary), holds no
+    device memory that it had not before, and works afterwards."""
+    hzp = rec.hzp
+    n = 300
+    plan = hzp.hzp_plan([n, n], [700 + t % 5 for t in range(2 * n)], align=8, z3=2, z1=4)
+    hy = hzp.adamw_hyper(1e-4, .9, .95, 1e-8, .1, 1.0, 1)
+    at = lambda k: 0x7000000000 + k * 0x10000000
+    tensors = [at(8) + 4096 * t + 2 for t in range(n)]
+    calls = [lambda: plan.prepare(stream=0),
+             lambda: hzp.hzp_gather_layer(plan, 0, 0, 3, [at(0), at(1)], None, tensors, stream=0),
+             lambda: hzp.hzp_gather_layer(plan, 0, 0, 3, [at(0), at(1)], at(2), [t - 2 for t in tensors], stream=0),
+             lambda: hzp.hzp_gather_layers(plan, 0, 2, 0, 1, [at(0), at(1), at(2), at(3)], 2, [at(4), at(5)], stream=0),
+             lambda: hzp.hzp_adamw_shard(plan, 0, 2, 0, 0, hy, [at(0), at(1)], 1, *[[at(2 * i), at(2 * i + 1)] for i in range(1, 5)], stream=0),
+             lambda: hzp.hzp_reduce_shard(plan, 0, 0, 1, 0, [at(0), at(1)], 1.0, 0, at(2), stream=0)]
+    for call in calls:
+        for which in range(1000):
+            held = rec.lib.live_allocations()
+            rec.lib.fail_host_allocation(which)
+            try:
+                call()
+                failed = None
+            except hzp.HzpError as error:
+                failed = error
+            if not rec.lib.host_allocation_failed():
+                assert failed is None
+                break
+            assert failed is not None and failed.status == hzp.HZP_ERR_NOMEM and rec.lib.live_allocations() == held
+        call()
