@@ -145,13 +145,16 @@ typedef struct {
 hzp_status_t hzp_plan(const hzp_plan_desc_t *desc, hzp_plan_t **out);
 
 /* Free a plan and its device tables.  NULL is allowed.  The caller must make sure that no kernel
- * launched with this plan is still running. */
+ * launched with this plan is still running, and that no HIP graph will be replayed that captured a
+ * call with it which reads the tables: an update of tensors with decay multipliers, or the
+ * unpacking of a bucket of more than 160 tensor pieces.  (Other captured calls hold all that they
+ * read by value.) */
 void hzp_plan_free(hzp_plan_t *plan);
 
 /* Create the plan's lookup tables on the current device now (tensor offsets and decay multipliers
- * for updates with per-tensor decay, tensor pieces and spans for the unpacking gathers): one allocation and
- * one blocking copy per table.  This is the one call on a plan that may allocate device memory and
- * synchronise; after it has returned, no kernel-launching call with this plan on this device
+ * for updates with per-tensor decay, tensor pieces and spans for the unpacking gathers): one
+ * allocation and one blocking copy per table.  This is the one call on a plan that may allocate
+ * device memory and synchronise; after it has returned, no kernel-launching call with this plan on this device
  * allocates, copies or waits (without it, the first call that needs a table creates it, and that
  * call blocks).  `stream` is waited for before returning, together with the copies, so that work
  * enqueued afterwards on any stream finds the tables in place.  May be called again (no effect) and

@@ -257,7 +257,8 @@ def _stream(stream):
 
 
 class Plan:
-    """Owner of an ``hzp_plan_t*``; freed when the object dies."""
+    """Owner of an ``hzp_plan_t*``; freed when the object dies.  Keep it as long as a HIP graph is replayed that captured an update of tensors
+    with decay multipliers or the unpacking of a bucket of more than 160 tensor pieces: those read the plan's device tables."""
 
     def __init__(self, handle, keep):
         self.handle = handle

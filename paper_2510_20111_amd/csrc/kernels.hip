@@ -1151,7 +1151,7 @@ static hzp_status_t start(const char *who, void (*kernel)(P...), dim3 grid, dim3
     return start_any(who, reinterpret_cast<const void *>(kernel), grid, block, lds, stream, &args...);
 }
 
-// Is the call being captured?  A replay costs the host nothing for each launch, so there the device's time alone decides.
+// Is the call being captured?
 static bool captured(hipStream_t stream)
 {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
@@ -2284,7 +2284,6 @@ constexpr uint64_t kOffLinesPlaced = 64u << 20, kOffLinesNear = 16u << 20;
 // included) and on the device alone (graph):
 //   up to 64 tensors: 6 / 9 / 64 of 0.04-0.1 MB in all 4.2 / 3.8, 4.3 / 3.9, 4.4 / 4.0 and 2.07 / 2.16, 2.08 / 2.12, 2.24 / 2.18, 9 of 1.8 / 18 / 360 MB
 //   4.35 / 3.8, 7.8 / 7.5, 107 / 106 and 3.02 / 2.80, 7.9 / 7.75, 108.7 / 107.8; even ones 2.01 / 2.05 and 3.59 / 3.57 on the device, from 20 MB the same.
-//   (captured, below 0.5 MB and even ones by lists)
 //   more, where lists are one launch: 100 uneven ones of 0.07 / 2 / 20 MB 2.28 / 2.46, 3.5 / 3.1, 9.4 / 9.7 on the device, even ones 2.1 / 2.4, 2.9 / 3.0, 8.3 / 9.3.
 //   more, where lists are several launches (or tables): 170 of 3.4 / 30 / 340 MB 4.4 / 3.7, 14.9 / 13.3, 110 / 111; 400 of 8 / 80 MB 6.6 / 5.9, 30 / 30; 1000 of
 //   0.7 / 20 / 200 MB 8.4 / 2.9, 17.9 / 11.4, 79 / 73.
@@ -2307,7 +2306,6 @@ static bool near_pays(const BucketRec &b, const ListShape &lists, uint32_t es)
 // The same with the bucket written too, where lists (`one_pass`) are one launch; else there are two passes: 100 tensors of 0.07 / 2 / 20 / 200 MB 3.8 / 2.5, 6.2 /
 // 3.2, 16.9 / 12.9, 124 / 97, 170 of 340 MB 209 / 162, 1000 of 0.7 / 200 MB 11 / 3.0, 139 / 106.  In one launch of lists: 6 / 30 of 0.04-0.07 MB 2.04 / 2.16, 2.07 / 2.19 on the
 // device and 4.35 / 3.8, 4.8 / 3.9 in a row, 9 of 1.8 / 18 / 360 MB 3.5 / 3.1, 11.2 / 10.7, 172 / 173; 100 even ones of 0.08 / 2 / 20 MB 2.1 / 2.4, 3.2 / 3.1, 11.6 / 12.4.
-// (Captured, below 1 MB by lists, even ones below 2 MB: 30 of 1.8 MB 3.08 / 3.18, uneven 3.53 / 3.29.)
 static bool placed_pays_both(const BucketRec &b, uint32_t es, bool one_pass)
 {
     const uint64_t bytes = b.P * es;
@@ -2357,6 +2355,23 @@ static hzp_status_t unpack_near(const hzp_plan_t *plan, const DeviceTables &tab,
                                                  : unpack_near<ES, UnpackNear64>(plan, tab, b, shards, n_shards, tensors, stream, done);
 }
 
+// Do lists serve the unpacking of pieces [p0, p1), or the plan's tables?  A graph may be replayed after its plan has been freed where nothing of the plan's
+// is read, so captured calls that lists serve take lists and not the spans, which are a table too.
+static bool lists_serve(const BucketRec &b, size_t p0, size_t p1, void *const *tensors, uint32_t t_begin, uint32_t es)
+{
+    const size_t n = p1 - p0;
+    if (n <= (size_t)UnpackFlat160::kParts) return true;        // one launch
+    uint64_t total = 0;
+    size_t longest = p0;
+    for (size_t i = p0; i < p1; ++i) {
+        total += b.pieces[i].len;
+        if (b.pieces[i].len > b.pieces[longest].len) longest = i;
+    }
+    const Piece &l = b.pieces[longest];
+    const bool odd = (reinterpret_cast<uint64_t>(tensors[l.tensor - t_begin]) + l.dst_off * es) & 15u;
+    return lists_pay(n, total, l.len, odd, es);
+}
+
 hzp_status_t launch_unpack(const hzp_plan_t *plan, const BucketRec &b, const void *const *shards,
                            uint32_t n_shards, void *const *tensors, uint32_t t_begin, uint32_t t_end,
                            hipStream_t stream)
@@ -2368,31 +2383,21 @@ hzp_status_t launch_unpack(const hzp_plan_t *plan, const BucketRec &b, const voi
     if (st != HZP_OK) return st;
     if (n > (size_t)UnpackList5::kParts && t_end - t_begin == b.n_tensors && spans_reach(b, n_shards, es)) {
         const ListShape lists = list_shape(b, es);
-        auto rather_lists = [&] { return lists.launches == 1 && (lists.even || b.P * es < 512u << 10) && captured(stream); };
+        auto outlived = [&] { return captured(stream) && lists_serve(b, p0, p1, tensors, t_begin, es); };
         uint64_t origin = 0;
-        if (placed_pays(b, lists, es) && placed_as_in_bucket(plan, b, tensors, es, &origin) && (origin % 128 == 0 || b.P * es <= kOffLinesPlaced) && !rather_lists())
+        if (placed_pays(b, lists, es) && placed_as_in_bucket(plan, b, tensors, es, &origin) && (origin % 128 == 0 || b.P * es <= kOffLinesPlaced) && !outlived())
             return es == 4 ? unpack_placed<4, false>(*tab, b, shards, n_shards, origin, nullptr, stream)
                            : unpack_placed<2, false>(*tab, b, shards, n_shards, origin, nullptr, stream);
-        if (near_pays(b, lists, es) && !rather_lists()) {
+        if (near_pays(b, lists, es) && !outlived()) {
             bool done = false;
             const hzp_status_t near = es == 4 ? unpack_near<4>(plan, *tab, b, shards, n_shards, tensors, stream, &done)
                                               : unpack_near<2>(plan, *tab, b, shards, n_shards, tensors, stream, &done);
             if (done) return near;
         }
     }
-    if (n > (size_t)UnpackFlat160::kParts) {            // (fewer are one launch)
-        uint64_t total = 0;
-        size_t longest = p0;
-        for (size_t i = p0; i < p1; ++i) {
-            total += b.pieces[i].len;
-            if (b.pieces[i].len > b.pieces[longest].len) longest = i;
-        }
-        const Piece &l = b.pieces[longest];
-        const bool odd = (reinterpret_cast<uint64_t>(tensors[l.tensor - t_begin]) + l.dst_off * es) & 15u;
-        if (!lists_pay(n, total, l.len, odd, es)) {
-            const UnpackCall u{tab->pieces + b.piece_slot, tab->piece_chunk + b.piece_slot, b, shards, n_shards, stream};
-            return launch_unpack_with(u, tensors, t_begin, t_end, "hzp_gather_layer");
-        }
+    if (!lists_serve(b, p0, p1, tensors, t_begin, es)) {
+        const UnpackCall u{tab->pieces + b.piece_slot, tab->piece_chunk + b.piece_slot, b, shards, n_shards, stream};
+        return launch_unpack_with(u, tensors, t_begin, t_end, "hzp_gather_layer");
     }
     const Piece *const piece = b.pieces.data() + p0;
     if (t_end - t_begin == 1 && n <= (size_t)UnpackTensorArgs::kParts) {
@@ -2426,7 +2431,7 @@ hzp_status_t launch_unpack_both(const hzp_plan_t *plan, const BucketRec &b, cons
     if (st != HZP_OK) return st;
     uint64_t origin = 0;
     if (spans_reach(b, n_shards, es) && placed_pays_both(b, es, one_pass) && placed_as_in_bucket(plan, b, tensors, es, &origin) &&
-        !(one_pass && b.P * es < (list_shape(b, es).even ? 2u : 1u) << 20 && captured(stream)))
+        !(captured(stream) && (one_pass || lists_serve(b, 0, b.pieces.size(), tensors, 0, es))))
         return es == 4 ? unpack_placed<4, true>(*tab, b, shards, n_shards, origin, bucket, stream) : unpack_placed<2, true>(*tab, b, shards, n_shards, origin, bucket, stream);
     if (!one_pass) {
         st = launch_concat(shards, n_shards, b.S3 * es, bucket, stream);

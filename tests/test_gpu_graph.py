@@ -1,6 +1,8 @@
 """A whole step of the path (fused update of all layers, post-step gather, per-layer gather with
 unpack) captured into a HIP graph and replayed: every replay must leave exactly what the same calls
 issued eagerly leave, with eager work and synchronisations between the replays."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -210,3 +212,39 @@ def test_one_captured_step_replayed_as_successive_training_steps():
         assert_close_f32(to_host(graphed.p[l], np.float32), host[l]["p"], "third replay p layer %d" % l, "p")
         assert_close_f32(to_host(graphed.m[l], np.float32), host[l]["m"], "third replay m layer %d" % l, "m")
         assert_close_f32(to_host(graphed.v[l], np.float32), host[l]["v"], "third replay v layer %d" % l, "v")
+
+
+@pytest.mark.parametrize("both", [False, True])
+@pytest.mark.parametrize("numel", [[30000] * 9, [100, 90000] * 5, [600, 30000] * 30])
+def test_a_captured_unpacking_outlives_its_plan(numel, both):
+    """The plan is freed behind the capture and the memory of its tables is given out again and overwritten: every replay copies as before."""
+    say("graph of an unpacking without its plan", len(numel), both)
+    n = len(numel)
+    plan = hzp.hzp_plan([n], numel, align=64, z3=2, z1=2)
+    plan.prepare()
+    b, at = plan.bucket(0), [plan.tensor(t).offset for t in range(n)]
+    whole = torch.empty(b.padded, dtype=torch.int16, device=DEV)
+    shards = [whole[j * b.s3:(j + 1) * b.s3] for j in range(2)]
+    flat = torch.empty(b.padded, dtype=torch.int16, device=DEV)
+    bucket = torch.empty(b.padded, dtype=torch.int16, device=DEV) if both else None
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        hzp.hzp_gather_layer(plan, 0, 0, 3, shards, bucket, [flat[a:a + k] for a, k in zip(at, numel)])
+    del plan
+    hip, taken = hzp.binding._L, []
+    for _ in range(64):                                 # (of the allocator that the tables came from)
+        p = ctypes.c_void_p()
+        assert hip.hipMalloc(ctypes.byref(p), ctypes.c_size_t(4096)) == 0
+        assert hip.hipMemset(p, 0x55, ctypes.c_size_t(4096)) == 0
+        taken.append(p)
+    for _ in range(3):
+        whole.random_(0, 30000)
+        flat.fill_(-1)
+        graph.replay()
+        torch.cuda.synchronize()
+        want = torch.full_like(flat, -1)
+        for a, k in zip(at, numel):
+            want[a:a + k] = whole[a:a + k]
+        assert torch.equal(flat, want) and (bucket is None or torch.equal(bucket, whole))
+    for p in taken:
+        assert hip.hipFree(p) == 0

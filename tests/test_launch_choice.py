@@ -105,3 +105,32 @@ def test_calls_that_run_out_of_host_memory_end_with_a_status(rec):
                 break
             assert failed is not None and failed.status == hzp.HZP_ERR_NOMEM and rec.lib.live_allocations() == held
         call()
+
+
+def unpacking(rec, numel, both, place, z3=3, align=64, cls=0):
+    """A plan of one bucket and the call that unpacks it: tensors as in the bucket ("placed"), at distances of their own ("near") or one of them
+    off 16 bytes ("off")."""
+    hzp, n, es = rec.hzp, len(numel), 4 if cls else 2
+    plan = hzp.hzp_plan([n], numel, align=align, z3=z3, z1=z3, tensor_class=[cls] * n)
+    plan.prepare(stream=0)
+    shards = [0x7000000000 + j * 0x40000000 for j in range(z3)]
+    at = [plan.tensor(t).offset * es for t in range(n)]
+    if place != "placed":
+        at = [a + 4096 * t for t, a in enumerate(at)]
+    if place == "off":
+        at[n // 2] += es
+    tensors = [0x7800000000 + a for a in at]
+    return plan, lambda: hzp.hzp_gather_layer(plan, 0, cls, 3, shards, 0x7900000000 if both else None, tensors, stream=0)
+
+
+@pytest.mark.parametrize("place", ["placed", "near"])
+@pytest.mark.parametrize("both", [False, True])
+@pytest.mark.parametrize("numel", [[30000] * 9, [100, 90000] * 5, [600, 30000] * 30, [9000, 100] * 50, [300000] * 100, [400000] * 300])
+def test_captured_unpacking_that_lists_serve_reads_nothing_of_the_plan(rec, numel, both, place):
+    """What a graph of such a call reads is in its launches' arguments, so that it outlives the plan: no kernel that reads the spans.  (Where lists
+    do not serve the plan's tables are read in any case.)"""
+    plan, call = unpacking(rec, numel, both, place)
+    names = [k for k, _, _ in rec.launches(call, captured=True)]
+    assert names and all(k.startswith(("unpack_list_kernel", "copy_")) for k in names), names
+    plan, call = unpacking(rec, [3000, 200] * 200, both, "placed")
+    assert [k.split("<")[0] for k, _, _ in rec.launches(call, captured=True)] == ["unpack_placed_kernel"]
