@@ -341,27 +341,17 @@ __global__ __launch_bounds__(kWave) void reduce_block_kernel(const ReduceArgs<R>
     reduce<R, G32, ACC, FORM>(out, nquad, scale, at, [&](uint32_t r) { return a.all.g[r]; });
 }
 
-// Short launches of more contributions than kFewBytes hold pointers of: up to 23 as distances from the first in 16 bytes, more (and equally distant) as one distance.
-// o: output, number of quads and scale.
-constexpr uint32_t kReduceApartLeast = 13, kReduceApartMost = 23;
-template <uint32_t R>
-struct ReduceApart {
-    int32_t d[R - 1];
-    __device__ __forceinline__ uint64_t of(uint64_t first, uint32_t r) const { return r ? at_distance(first, d[r - 1]) : first; }
-};
-struct ReduceEven {
-    uint64_t stride;
-    __device__ __forceinline__ uint64_t of(uint64_t first, uint32_t r) const { return first + r * stride; }
-};
-static_assert(sizeof(u64x2) + sizeof(uint64_t) + sizeof(ReduceApart<kReduceApartMost>) == kFewBytes, "argument block");
-template <uint32_t R, bool G32, bool ACC, class Others>
-__global__ __launch_bounds__(kWave) void reduce_apart_kernel(const u64x2 o, const uint64_t first, const Others others)
+// Short launches of more contributions than kFewBytes holds pointers of, where these lie at equal distances.
+// o: output, number of quads and scale; g: the first contribution, the distance from one to the next.
+constexpr uint32_t kReduceEvenLeast = 13;
+template <uint32_t R, bool G32, bool ACC>
+__global__ __launch_bounds__(kWave) void reduce_even_kernel(const u64x2 o, const u64x2 g)
 {
     constexpr uint32_t CHUNK = reduce_chunk(R, kReduceFew);
     uint64_t at[CHUNK];
 #pragma unroll
-    for (uint32_t c = 0; c < CHUNK; ++c) at[c] = c < R ? others.of(first, c) : 0;
-    reduce<R, G32, ACC, kReduceFew>(o[0], (uint32_t)o[1], __uint_as_float((uint32_t)(o[1] >> 32)), at, [&](uint32_t r) { return others.of(first, r); });
+    for (uint32_t c = 0; c < CHUNK; ++c) at[c] = c < R ? g[0] + c * g[1] : 0;
+    reduce<R, G32, ACC, kReduceFew>(o[0], (uint32_t)o[1], __uint_as_float((uint32_t)(o[1] >> 32)), at, [&](uint32_t r) { return g[0] + r * g[1]; });
 }
 
 // ---------------------------------------------------------------------------------------
@@ -409,28 +399,7 @@ struct FusedLead {
 };
 constexpr uint32_t kLeadBytes = 56;         // of the argument block; the struct follows
 static_assert(sizeof(u64x4) + sizeof(u64x2) + sizeof(uint64_t) == kLeadBytes && alignof(FusedOneArgs) == 8, "argument block");
-// The same for short launches of 3 to 8 contributions (fewer are FusedEven's), whose block stays within kFewBytes: two pointers, and the distances of the others in
-// 16 bytes, momentum, variance and output from the master weights and contributions from the first.
-constexpr uint32_t kNearLeast = 3, kNearR = 8;
-template <uint32_t R>
-struct FusedNearArgs {
-    AdamScalars scalars;
-    int32_t g[R > 4 ? R - 4 : 1];           // from the fifth contribution on
-};
-typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-typedef int32_t i32x2 __attribute__((ext_vector_type(2)));
-constexpr uint64_t kHasOut = 1ull << 31;    // in `size`, whose number of quads has 28 bits
-static_assert(kLeadBytes + sizeof(FusedNearArgs<kNearR>) == kFewBytes && alignof(FusedNearArgs<kNearR>) == 4, "argument block");
-template <uint32_t R>
-struct FusedNear {                          // what fused_adamw asks of them
-    const FusedNearArgs<R> &a;
-    uint64_t out, first;
-    i32x2 d;
-    static constexpr size_t kScalars = 0;
-    __device__ __forceinline__ uint64_t output() const { return out; }
-    __device__ __forceinline__ uint64_t contribution(uint32_t r) const { return at_distance(first, r < 4 ? d[r - 2] : a.g[r - 4]); }
-};
-// The same where contributions lie at equal distances, as in the planner's arena or one receive buffer: any number of them, within kFewBytes.
+// The same for short launches where contributions lie at equal distances, as in the planner's arena or one receive buffer: any number of them, within kFewBytes.
 struct FusedEvenArgs {
     uint64_t out;
     AdamScalars scalars;
@@ -672,15 +641,6 @@ template <uint32_t R, bool G32, bool O32, uint32_t CHUNK, uint32_t HEAD>
 __global__ __launch_bounds__(kWave) void fused_one_kernel(const u64x4 p, const u64x2 w, const uint64_t size, const FusedOneArgs a)
 {
     fused_adamw<R, G32, O32, kOne, CHUNK, HEAD>({p, w, size}, a);
-}
-// base: master weights, first contribution; d: distances of momentum, variance, output and the second contribution; d2: of the third and fourth.
-template <uint32_t R, bool G32, bool O32, uint32_t CHUNK>
-__global__ __launch_bounds__(kWave) void fused_near_kernel(const u64x2 base, const i32x4 d, const i32x2 d2, const uint64_t size, const uint64_t scalars_dev,
-                                                           const FusedNearArgs<R> a)
-{
-    const uint64_t p = base[0], g = base[1];
-    const FusedLead lead{{p, at_distance(p, d[0]), at_distance(p, d[1]), g}, {at_distance(g, d[3]), scalars_dev}, size & ~kHasOut};
-    fused_adamw<R, G32, O32, kOne, CHUNK, 0>(lead, FusedNear<R>{a, size & kHasOut ? at_distance(p, d[2]) : 0, g, d2});
 }
 // w: distance from one contribution to the next, the step's scalars in device memory.
 template <uint32_t R, bool G32, bool O32, uint32_t CHUNK>
@@ -1151,7 +1111,7 @@ static hzp_status_t start(const char *who, void (*kernel)(P...), dim3 grid, dim3
     return start_any(who, reinterpret_cast<const void *>(kernel), grid, block, lds, stream, &args...);
 }
 
-// Is the call being captured?
+// Is the call being captured?  A replay costs the host nothing for each launch, so there the shortest time on the device is all that counts.
 static bool captured(hipStream_t stream)
 {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
@@ -1190,18 +1150,12 @@ static KernelOfR reduce_block_kernels(std::index_sequence<I...>)
     return {reduce_block_kernel_of<I + 1, G32, ACC, FORM>()...};
 }
 
-template <bool G32, bool ACC, uint32_t R>
-static const void *reduce_apart_kernel_of()
-{
-    if constexpr (R <= kReduceApartMost)
-        return reinterpret_cast<const void *>(reduce_apart_kernel<R, G32, ACC, ReduceApart<R>>);
-    else
-        return reinterpret_cast<const void *>(reduce_apart_kernel<R, G32, ACC, ReduceEven>);
-}
+typedef void (*ReduceEvenKernel)(u64x2, u64x2);
+typedef std::array<ReduceEvenKernel, HZP_MAX_REPLICAS - kReduceEvenLeast + 1> ReduceEvenOfR;
 template <bool G32, bool ACC, size_t... I>
-static std::array<const void *, sizeof...(I)> reduce_apart_kernels(std::index_sequence<I...>)
+static ReduceEvenOfR reduce_even_kernels(std::index_sequence<I...>)
 {
-    return {reduce_apart_kernel_of<G32, ACC, I + kReduceApartLeast>()...};
+    return {reduce_even_kernel<I + kReduceEvenLeast, G32, ACC>...};
 }
 
 typedef void (*FusedKernel)(FusedArgs);
@@ -1288,33 +1242,25 @@ static bool reduce_from_block(bool g32, uint32_t R, ReduceForm form, uint64_t n,
 // 6.84 / 6.85, bf16 R = 8 (5.7 GB) 6.89 / 6.88 / 6.82 / 6.70, R = 4 (3.4 GB) 6.84 / 6.82 / 6.80 / 6.68.
 constexpr uint64_t most_reduce_bytes(uint32_t R) { return R > 8 ? 3000000000ull : 6000000000ull; }
 
-// Longest launch by distances, in groups.  Against pointers (120 to 272 bytes of arguments), calls in a row on buffers of one call's size, streams 2, 4 .. 18 MiB apart, R = 13 to 32, accumulating or
-// not, median (worst) ratio: bf16 of up to 0.2 M elements .88 (1.02), 0.26 M .88 (1.08), 0.46 / 0.52 M .94 (1.12); fp32 of up to 65 k .88 (1.01), 0.13 M .89 (1.08), 0.26 M .97 (1.13), 0.52 M 1.02
-// (1.16): R = 16 of 16 k elements 4.2 -> 3.6 us.  Beyond, what starts faster collides in the memory channels.  On the device alone 1.00 (R <= 23 .99 to 1.05), so captured ones stay as they are.
-static uint32_t apart_groups(bool g32) { return g32 ? 384u : 768u; }
+// Longest launch of equally distant contributions by their distance, in groups.  Against pointers (120 to 272 bytes of arguments), R = 13 to 32,
+// up to 0.2 M elements, accumulating or not, streams 2, 4 .. 18 MiB apart, medians over the distances: calls in a row on an idle queue bf16 .86,
+// fp32 .90 (R = 16 of 16 k elements 4.2 -> 3.6 us); behind a long kernel, with the host ahead, .974 and .982 (worst: bf16 R = 16 accumulating
+// 0.1 M elements 1.04, fp32 R = 13 of 4 k 1.07); in graphs 1.008 and 1.003 (worst 1.06), so captured ones take pointers.  Beyond, what starts faster collides in the memory channels (in a
+// row, worst distance: bf16 of 0.46 / 0.52 M elements 1.12, fp32 of 0.26 M 1.13).  Contributions at any distances, 13 to 23 of them each by its
+// own from the first, would take .86 in a row too, but 1.05 on average and up to 1.19 behind a long kernel: these take pointers.
+static uint32_t reduce_even_groups(bool g32) { return g32 ? 384u : 768u; }
 
-// A launch by distances; *done is false (and nothing launched) where the contributions lie too far apart, or more than 23 not equally so.
-static hzp_status_t start_reduce_apart(bool g32, uint32_t R, bool accumulate, const uint64_t *g, u64x2 o, dim3 grid, unsigned lds, hipStream_t stream, bool *done)
+// Such a launch; *done is false (and nothing launched) where the distances differ.
+static hzp_status_t start_reduce_even(bool g32, uint32_t R, bool accumulate, const uint64_t *g, u64x2 o, dim3 grid, unsigned lds, hipStream_t stream, bool *done)
 {
-    constexpr std::make_index_sequence<HZP_MAX_REPLICAS - kReduceApartLeast + 1> all;
-    static const std::array<const void *, HZP_MAX_REPLICAS - kReduceApartLeast + 1> kernels[2][2] = {
-        {reduce_apart_kernels<false, false>(all), reduce_apart_kernels<false, true>(all)}, {reduce_apart_kernels<true, false>(all), reduce_apart_kernels<true, true>(all)}};
-    const void *const kernel = kernels[g32][accumulate][R - kReduceApartLeast];
-    bool fits = true;
-    if (R <= kReduceApartMost) {
-        ReduceApart<kReduceApartMost> others;
-        for (uint32_t r = 1; r < R; ++r) {
-            const int64_t d = (int64_t)(g[r] - g[0]) / 16;          // (all are multiples of 16)
-            fits = fits && d == (int32_t)d;
-            others.d[r - 1] = (int32_t)d;
-        }
-        *done = fits;
-        return fits ? start_any("hzp_reduce_shard", kernel, grid, dim3(kWave), lds, stream, &o, g, &others) : HZP_OK;
-    }
-    const ReduceEven others{g[1] - g[0]};
-    for (uint32_t r = 2; r < R; ++r) fits = fits && g[r] - g[r - 1] == others.stride;
-    *done = fits;
-    return fits ? start_any("hzp_reduce_shard", kernel, grid, dim3(kWave), lds, stream, &o, g, &others) : HZP_OK;
+    constexpr std::make_index_sequence<HZP_MAX_REPLICAS - kReduceEvenLeast + 1> all;
+    static const ReduceEvenOfR kernels[2][2] = {{reduce_even_kernels<false, false>(all), reduce_even_kernels<false, true>(all)},
+                                                {reduce_even_kernels<true, false>(all), reduce_even_kernels<true, true>(all)}};
+    const uint64_t distance = g[1] - g[0];
+    *done = true;
+    for (uint32_t r = 2; r < R; ++r) *done = *done && g[r] - g[r - 1] == distance;
+    if (!*done) return HZP_OK;
+    return start("hzp_reduce_shard", kernels[g32][accumulate][R - kReduceEvenLeast], grid, dim3(kWave), lds, stream, o, u64x2{g[0], distance});
 }
 
 hzp_status_t launch_reduce(bool g32, const void *const *slices, uint32_t R, uint64_t n, float scale,
@@ -1353,7 +1299,8 @@ hzp_status_t launch_reduce(bool g32, const void *const *slices, uint32_t R, uint
         const u64x2 o{a.out, nquad | (uint64_t)scale_bits << 32};
         hzp_status_t st = HZP_OK;
         bool done = false;
-        if (R >= kReduceApartLeast && (nquad + kGroupQuads - 1) / kGroupQuads <= apart_groups(g32) && !captured(stream)) st = start_reduce_apart(g32, R, accumulate != 0, g, o, grid, lds, stream, &done);
+        if (R >= kReduceEvenLeast && (nquad + kGroupQuads - 1) / kGroupQuads <= reduce_even_groups(g32) && !captured(stream))
+            st = start_reduce_even(g32, R, accumulate != 0, g, o, grid, lds, stream, &done);
         if (done) {
         } else if (reduce_from_block(g32, R, form, here, accumulate)) {
             st = start_any("hzp_reduce_shard", form == kReduceNarrow ? narrow_block[accumulate != 0][R - 1] : short_block[g32][R - 1], grid, block, lds, stream, &a);
@@ -1533,12 +1480,6 @@ static FusedOneKernel fused_one_kernel_of(bool g32, bool o32, uint32_t R)
 }
 
 template <bool G32, bool O32, size_t... I>
-static std::array<const void *, sizeof...(I)> fused_near_kernels(std::index_sequence<I...>)
-{
-    return {reinterpret_cast<const void *>(fused_near_kernel<I + kNearLeast, G32, O32, fused_chunk(G32, I + kNearLeast, kFew)>)...};
-}
-
-template <bool G32, bool O32, size_t... I>
 static std::array<const void *, sizeof...(I)> fused_even_kernels(std::index_sequence<I...>)
 {
     return {reinterpret_cast<const void *>(fused_even_kernel<I + 1, G32, O32, fused_chunk(G32, I + 1, kFew)>)...};
@@ -1552,14 +1493,15 @@ static hzp_status_t start_fused(bool g32, bool o32, uint32_t R, const FusedArgs 
     return start("hzp_adamw_shard", kernel, grid, dim3(kWave), fused_lds(g32, R, c, FORM, groups), stream, a);
 }
 
-// Longest launch that takes equally distant contributions by their distance.  Against the other forms, calls in a row on buffers of one call's size, streams 2, 4 .. 18 MiB apart,
-// median (worst) ratio: bf16 R = 1 / 2 of 0.2 to 0.52 M elements .95 / .97 (1.01), R = 5 to 8 .89 (1.00), R = 3 / 4 of 0.16 to 0.39 M .88 / .89 (.96), of 0.49 M 1.0 to 1.2 (1.6 to 1.9), R >= 9 of
-// 0.07 to 0.26 M .87 (1.02), of 0.33 M .90 (1.06); fp32 R <= 8 .90 (1.0), R >= 9 of 0.07 to 0.16 M .87 (1.00), of 0.23 / 0.26 M .91 / .93 (1.13 / 1.7).  R = 16 of 16 k elements 4.5 -> 3.7 us, fp32 R = 8 of
-// 0.26 M 5.1 -> 4.4.  (Longer ones take the device longer than the host, and what starts faster collides in the memory channels.  In graphs 1.00 (.95 to 1.03), so captured ones stay as they were.)
+// Longest launch that takes equally distant contributions by their distance.  Against pointers, buffers of one call's size, streams 2, 4 .. 18 MiB
+// apart, medians over the distances, bf16 and fp32, up to these lengths: calls in a row on an idle queue .89 and .92 (R = 16 of 16 k elements
+// 4.5 -> 3.7 us), behind a long kernel, with the host ahead, .975 and .997 (worst 1.01), in graphs 1.00 and 1.005 (worst 1.02), so captured ones take
+// pointers.  Beyond, what starts faster collides in the memory channels; behind a long kernel: bf16 R = 3 / 4 of 0.39 M elements 1.01 / 1.09, R = 9 / 12 /
+// 16 of 0.26 M 1.11 / 1.15 / 1.04, fp32 R = 3 of 0.33 / 0.39 M 1.09 / 1.07; fp32 R >= 9 of 0.23 / 0.26 M in a row, worst distance, 1.13 / 1.7.
+// (Others, each by its own distance from the first, gained 3 % in a row and lost 3 %, R = 5 14 %, behind a long kernel.)
 static uint32_t even_groups(bool g32, uint32_t R)
 {
-    if (R > 8) return g32 ? 640u : 1024u;
-    return !g32 && (R == 3 || R == 4) ? 1536u : kFewGroups;
+    return R > 8 ? 640u : R == 3 || (R == 4 && !g32) ? 1024u : kFewGroups;
 }
 
 // One segment with one multiplier: its record and pointers are a.word's first.
@@ -1582,31 +1524,6 @@ static hzp_status_t start_fused_one(bool g32, bool o32, uint32_t R, const FusedA
         const u64x2 far{R > 1 ? w[5] - w[4] : 0, reinterpret_cast<uint64_t>(a.scalars_dev)};
         const FusedEvenArgs rest{w[3], a.scalars};
         return start_any("hzp_adamw_shard", k, dim3(groups), dim3(kWave), 0, stream, &p, &far, &size, &rest);
-    }
-    // Others of up to 5.5 MB take two pointers and distances.  So / by pointers, us, bf16 of
-    // 16 k and 0.13 M elements, calls in a row: R = 4 3.8 / 4.3, 3.8 / 4.4, R = 8 3.8 / 4.35, 3.7 / 4.1 (a mean of -9 % over both types); on the
-    // device alone R = 4 2.46 / 2.42, 2.65 / 2.65, R = 8 2.60 / 2.55, 3.26 / 3.22 (the addresses are worked out before the first requests), so captured ones take pointers.  Beyond, the
-    // device's time shows: R = 8 of 0.15 / 0.2 M 3.39 / 3.27, 3.83 / 3.50, R = 4 of 0.46 M 4.6 / 4.3 in a row.
-    const uint64_t bytes = (uint64_t)groups * kGroupQuads * 4 * (R * (g32 ? 4u : 2u) + 24 + (o32 ? 4u : 2u));
-    if (bytes <= 5500000 && groups <= kFewGroups && R >= kNearLeast && R <= kNearR && !captured(stream)) {
-        bool fits = true;
-        auto distance = [&](uint64_t to, uint64_t from) {
-            const int64_t d = (int64_t)(to - from) / 16;        // (all are multiples of 16)
-            fits = fits && d == (int32_t)d;
-            return (int32_t)d;
-        };
-        const u64x2 base{w[0], w[4]};
-        const i32x4 d{distance(w[1], w[0]), distance(w[2], w[0]), w[3] ? distance(w[3], w[0]) : 0, distance(w[5], w[4])};
-        const i32x2 d2{distance(w[6], w[4]), R > 3 ? distance(w[7], w[4]) : 0};
-        const uint64_t out = w[3] ? kHasOut : 0, dev = reinterpret_cast<uint64_t>(a.scalars_dev), flagged = size | out;
-        FusedNearArgs<kNearR> near;
-        near.scalars = a.scalars;
-        for (uint32_t r = 4; r < R; ++r) near.g[r - 4] = distance(w[4 + r], w[4]);
-        if (fits) {
-            constexpr std::make_index_sequence<kNearR - kNearLeast + 1> some;
-            static const auto kernels16 = fused_near_kernels<false, false>(some), kernels32 = fused_near_kernels<true, true>(some);
-            return start_any("hzp_adamw_shard", (g32 ? kernels32 : kernels16)[R - kNearLeast], dim3(groups), dim3(kWave), 0, stream, &base, &d, &d2, &flagged, &dev, &near);
-        }
     }
     FusedOneArgs one;
     one.out = a.word[3];

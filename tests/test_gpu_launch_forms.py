@@ -753,8 +753,8 @@ def wide_room():
 @pytest.mark.parametrize("cls,R", [(0, R) for R in range(1, 10)] + [(1, R) for R in range(1, 10)] + [(0, 0)])
 @pytest.mark.parametrize("n", [8, 248, 256, 504, 10248])
 def test_short_updates_with_streams_near_and_far(cls, R, n, wide_room):
-    """Streams in any order, near each other (two pointers and distances) and with one of them 33 GiB away (pointers): the same bits, with
-    scalars from the call and from device memory, with an output and without."""
+    """Streams in any order, near each other and with one of them 33 GiB away (up to two contributions are always equally distant and go by their
+    distance, more by pointers): the same bits, with scalars from the call and from device memory, with an output and without."""
     print(cls, R, n, flush=True)
     rng = np.random.default_rng(R * 7 + n)
     k, wide = max(R, 1), cls == 1 or R == 0

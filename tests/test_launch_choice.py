@@ -134,3 +134,58 @@ def test_captured_unpacking_that_lists_serve_reads_nothing_of_the_plan(rec, nume
     assert names and all(k.startswith(("unpack_list_kernel", "copy_")) for k in names), names
     plan, call = unpacking(rec, [3000, 200] * 200, both, "placed")
     assert [k.split("<")[0] for k, _, _ in rec.launches(call, captured=True)] == ["unpack_placed_kernel"]
+
+
+def name_of(kernel):
+    return kernel.split("<")[0]
+
+
+def streams_at(k, distance, odd=None):
+    """k addresses at equal distances (contribution `odd` 16 bytes off)."""
+    return [0x7000000000 + r * distance + (16 if r == odd else 0) for r in range(k)]
+
+
+@pytest.mark.parametrize("captured", [False, True])
+@pytest.mark.parametrize("g32", [0, 1])
+@pytest.mark.parametrize("R", [1, 4, 8, 9, 12, 13, 16, 23, 24, 32])
+def test_form_of_a_reduction(rec, R, g32, captured):
+    """By size, type, number and distances of the contributions: from 13 equally distant ones their distance, up to 768 groups of 256 elements (fp32
+    384); all pointers where the call is captured."""
+    hzp, limit = rec.hzp, 384 if g32 else 768
+    for groups in (1, limit, limit + 1):
+        n = groups * 256 - 8
+        plan = hzp.hzp_plan([1], [n], align=8, z3=1, z1=1)
+        for odd in (None, 1, R - 1):
+            for distance in (n * 4, -n * 4, 1 << 40):
+                def call():
+                    hzp.hzp_reduce_shard(plan, 0, 0, 3, 0, streams_at(R, distance, odd), 0.5, 0, 0x6000000000, stream=0,
+                                         grad_dtype=hzp.HZP_GRAD_F32 if g32 else hzp.HZP_GRAD_BF16)
+                (kernel, grid, _), = rec.launches(call, captured)
+                even = R >= 13 and groups <= limit and odd is None and not captured
+                assert (name_of(kernel) == "reduce_even_kernel") == even, (kernel, groups, odd, distance)
+                assert even or name_of(kernel) in ("reduce_kernel", "reduce_block_kernel")
+                assert grid[1:] == (1, 1) and ("<%du, %s, false" % (R, "true" if g32 else "false")) in kernel
+
+
+@pytest.mark.parametrize("captured", [False, True])
+@pytest.mark.parametrize("cls", [0, 1])
+@pytest.mark.parametrize("R", [0, 1, 2, 3, 4, 5, 8, 9, 16, 32])
+def test_form_of_an_update_of_one_segment(rec, R, cls, captured):
+    """Equally distant contributions (up to two always are) by their distance: up to 2048 groups of 256 elements, 3 contributions and 4 bf16 ones up to
+    1024, more than 8 up to 640; all pointers where the call is captured; with the scalars from the call and from device memory, with an output and
+    without."""
+    hzp, k = rec.hzp, max(R, 1)
+    limit = 640 if R > 8 else 1024 if R == 3 or (R == 4 and not cls) else 2048
+    hy = hzp.adamw_hyper(1e-4, .9, .95, 1e-8, .1, 1.0, 1)
+    for groups in (1, limit, limit + 1):
+        n = groups * 256 - 8
+        plan = hzp.hzp_plan([1], [n], align=8, z3=1, z1=1, tensor_class=[cls])
+        for odd in (None, R - 1):
+            for distance in (n * 4, -n * 4, 1 << 40):
+                for call, scal in ((hzp.hzp_adamw_shard, hy), (hzp.hzp_adamw_shard_dev, 0x5000000000)):
+                    for out in ([0x6300000000], None):
+                        (kernel, grid, _), = rec.launches(lambda: call(plan, 0, 1, cls, 0, scal, streams_at(k, distance, odd), R, [0x6000000000], [0x6100000000],
+                                                                       [0x6200000000], out, stream=0), captured)
+                        even = groups <= limit and (odd is None or R < 3) and not captured
+                        assert name_of(kernel) == ("fused_even_kernel" if even else "fused_one_kernel"), (kernel, groups, odd, distance)
+                        assert grid == (groups, 1, 1) and kernel.split("<")[1].startswith("%du, " % k)
