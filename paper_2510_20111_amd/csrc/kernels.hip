@@ -2193,17 +2193,22 @@ static bool spans_reach(const BucketRec &b, uint32_t n_shards, uint32_t es)
 {
     return n_shards <= UnpackPlacedArgs::kShards && b.P * es < 1ull << 32;      // (kernels address with 32 bits)
 }
-// Most bytes of a bucket that are written by the bucket's lines of 128 bytes where those are not the tensors' own (a wavefront then writes parts of lines).  Lists / so,
-// us: tensors in the bucket's layout, 9 of 18 / 72 / 360 MB 9.0 / 8.6, 27.2 / 27.0, 127 / 128, of 720 MB 249 / 255; elsewhere, 9 of 7 / 18 / 72 / 360 MB 5.2 / 5.2, 8.6 / 8.6, 26.5 / 27.1,
-// 116 / 123, 64 of 13 / 128 MB 7.6 / 7.2, 45 / 47.
+// Most bytes of a bucket that are written by the bucket's lines of 128 bytes where those are not the tensors' own (a wavefront then writes parts
+// of lines).  Lists / so, us: tensors in the bucket's layout, 9 of 18 / 72 / 360 MB 9.0 / 8.6, 27.2 / 27.0, 127 / 128, of 720 MB 249 / 255;
+// elsewhere, 9 of 7 / 18 / 72 / 360 MB 5.2 / 5.2, 8.6 / 8.6, 26.5 / 27.1, 116 / 123, 64 of 13 / 128 MB 7.6 / 7.2, 45 / 47.
 constexpr uint64_t kOffLinesPlaced = 64u << 20, kOffLinesNear = 16u << 20;
-// Is the one launch of unpack_placed the better way to write the bucket's tensors?  Lists / placed, us, calls in a row (collisions of kFewBytes
-// included) and on the device alone (graph):
-//   up to 64 tensors: 6 / 9 / 64 of 0.04-0.1 MB in all 4.2 / 3.8, 4.3 / 3.9, 4.4 / 4.0 and 2.07 / 2.16, 2.08 / 2.12, 2.24 / 2.18, 9 of 1.8 / 18 / 360 MB
-//   4.35 / 3.8, 7.8 / 7.5, 107 / 106 and 3.02 / 2.80, 7.9 / 7.75, 108.7 / 107.8; even ones 2.01 / 2.05 and 3.59 / 3.57 on the device, from 20 MB the same.
-//   more, where lists are one launch: 100 uneven ones of 0.07 / 2 / 20 MB 2.28 / 2.46, 3.5 / 3.1, 9.4 / 9.7 on the device, even ones 2.1 / 2.4, 2.9 / 3.0, 8.3 / 9.3.
-//   more, where lists are several launches (or tables): 170 of 3.4 / 30 / 340 MB 4.4 / 3.7, 14.9 / 13.3, 110 / 111; 400 of 8 / 80 MB 6.6 / 5.9, 30 / 30; 1000 of
-//   0.7 / 20 / 200 MB 8.4 / 2.9, 17.9 / 11.4, 79 / 73.
+// Is the one launch of unpack_placed the better way to write the bucket's tensors?  Lists / placed, us, behind a long kernel (the host is ahead, so that the
+// device's time shows) and in a row on an idle queue, 8 shards but where others are named:
+//   up to 64 tensors: 6 / 9 / 30 / 64 uneven ones of 0.06-0.1 MB in all 1.78 / 1.80, 1.88 / 1.85, 1.83 / 1.92, 1.86 / 1.98 (in a row 4.4 / 4.0), of 0.16 MB 1.88 /
+//   1.86, 1.87 / 1.86, 2.14 / 1.93, 2.26 / 1.99, 9 of 0.5 / 3.6 MB 2.33 / 2.01, 3.34 / 3.09 (3.65 / 3.25), of 18 / 360 MB 7.8 / 7.5, 107 / 106; even parts (2 shards),
+//   placed by lists: 6 / 9 / 12 / 30 / 64 of 0.2 MB 1.06 / .99 / 1.01 / 1.06 / .98, of 0.5 MB 1.00 / 1.01 / 1.03 / 1.01 / 1.12, of 1.2 MB 1.00 / .91 / .91 / .86 / .84
+//   (in a row .89), from 20 MB the same.  (What the shortest lose on the device shows in a tail behind a long kernel alone: a launch costs the host longer.)
+//   more, where lists are one launch: 100 uneven ones of 0.07 / 0.6 / 2 / 20 MB 2.28 / 2.46 (in a graph), 2.48 / 2.32, 3.02 / 2.57, 9.4 / 9.7, even ones of 2 /
+//   20 MB 2.9 / 3.0, 8.3 / 9.3.
+//   more, where lists are several launches (or tables), 8 MiB for each: 170 uneven ones of 7 / 15 / 20 / 60 / 120 MB 5.45 / 4.93, 8.26 / 8.04, 10.0 / 9.7, 23.1 /
+//   22.6, 41.1 / 41.9; 400 of 8 / 24 / 32 / 80 / 200 MB 5.8 / 5.6, 11.3 / 11.4, 13.9 / 14.3, 29.6 / 29.6, 65.9 / 68.4, even ones 5.6 / 4.9, 10.9 / 10.6, 14.6 / 13.2,
+//   28.1 / 28.1, 62.8 / 65.0; 1000 uneven ones of 0.7 / 20 / 56 / 80 / 200 / 400 MB 11.6 / 5.2, 18.0 / 11.1, 28.8 / 24.0, 36.9 / 31.9, 79 / 72, 141 / 139.  (So
+//   the line is a cautious one for 1000.)
 static bool placed_pays(const BucketRec &b, const ListShape &lists, uint32_t es)
 {
     const uint64_t bytes = b.P * es;
@@ -2211,18 +2216,22 @@ static bool placed_pays(const BucketRec &b, const ListShape &lists, uint32_t es)
     if (lists.even) return false;
     return lists.launches == 1 ? bytes >= 512u << 10 && bytes <= 4u << 20 : bytes <= lists.launches * (8u << 20);
 }
-// And that of unpack_near?  Up to 12 tensors as above: 6 / 9 / 12 of 0.04-0.07 MB 4.6 / 3.7, 4.55 / 4.0, 4.4 / 4.1 and 2.07 / 2.23, 2.10 / 2.15, 2.10 / 2.16, 9 of 1.8 / 18 / 360 MB
-// 4.5 / 4.0, 8.0 / 7.5, 107 / 107.  More only where they are uneven and long enough: 64 of 0.05 / 0.76 / 12.8 / 128 MB 4.6 / 4.35, 4.5 / 4.3, 7.3 / 6.6, 41.6 / 39.0 and 2.26 / 2.32, 2.50 / 2.45, 7.3 / 6.4, 42.9 / 40.4.
-// On other than the bucket's 128-byte lines even ones of 0.36 MB take 2.02 / 2.28 on the device.
+// And that of unpack_near?  Up to 12 tensors from where the device loses little, near by lists behind a long kernel: uneven ones, 6 / 9 / 12 of 0.1 MB 1.11 / 1.12 /
+// 1.11, of 0.28 MB 1.11 / 1.00 / .91, of 0.4 MB 1.00 / .90 / .95, of 3.6 MB .94 (in a row .90); even parts (2 shards), of 0.2 MB 1.14 / 1.11 / 1.14, of 0.42 MB 1.14 /
+// 1.04 / 1.08, of 0.56 MB 1.05 / 1.09 / 1.07, of 1.2 MB 1.11 / 1.01 / .99, of 2 MB 1.02 / 1.02 / .96 (.91); off the bucket's 128-byte lines .97-1.03 of 0.4 MB, .91-.99 of 0.5 MB.
+// More, in a block of 320 bytes, only where they are uneven and long enough: 64 of 0.05 / 0.76 / 12.8 / 128 MB 4.6 / 4.35, 4.5 / 4.3, 7.3 / 6.6, 41.6 / 39.0 in a row
+// and 2.26 / 2.32, 2.50 / 2.45, 7.3 / 6.4, 42.9 / 40.4 in a graph: a cautious line.
 // (With the bucket beside them 0.2 us more on the device than lists: 9 of 0.06 MB 2.08 / 2.33.)
 static bool near_pays(const BucketRec &b, const ListShape &lists, uint32_t es)
 {
-    if (b.n_tensors <= UnpackNear12::kTensors) return placed_pays(b, lists, es);
-    return b.n_tensors <= UnpackNear64::kTensors && !lists.even && b.P * es >= 1u << 20;
+    const uint64_t bytes = b.P * es;
+    if (b.n_tensors <= UnpackNear12::kTensors) return bytes >= (lists.even ? 512u : 256u) << 10 && placed_pays(b, lists, es);
+    return b.n_tensors <= UnpackNear64::kTensors && !lists.even && bytes >= 1u << 20;
 }
-// The same with the bucket written too, where lists (`one_pass`) are one launch; else there are two passes: 100 tensors of 0.07 / 2 / 20 / 200 MB 3.8 / 2.5, 6.2 /
-// 3.2, 16.9 / 12.9, 124 / 97, 170 of 340 MB 209 / 162, 1000 of 0.7 / 200 MB 11 / 3.0, 139 / 106.  In one launch of lists: 6 / 30 of 0.04-0.07 MB 2.04 / 2.16, 2.07 / 2.19 on the
-// device and 4.35 / 3.8, 4.8 / 3.9 in a row, 9 of 1.8 / 18 / 360 MB 3.5 / 3.1, 11.2 / 10.7, 172 / 173; 100 even ones of 0.08 / 2 / 20 MB 2.1 / 2.4, 3.2 / 3.1, 11.6 / 12.4.
+// The same with the bucket written too, where lists (`one_pass`) are one launch: 9 uneven / 30 even / 64 even ones of 0.06-0.1 MB 1.81 / 1.88, 1.77 / 1.85, 1.80 / 1.95
+// (in a row 4.5 / 3.9, 4.8 / 3.9, 5.0 / 4.1), 9 / 30 / 64 even ones of 0.5 MB 2.06 / 1.84, 2.03 / 1.93, 1.89 / 1.86, 9 uneven ones of 4 MB 4.23 / 3.69, 9 of 18 / 360 MB
+// 11.2 / 10.7, 172 / 173; 100 even ones of 0.08 / 2 / 20 MB 2.1 / 2.4, 3.2 / 3.1, 11.6 / 12.4 in a graph.  Else there are two passes: 100 uneven ones of 0.6 / 2 / 10 /
+// 40 / 200 MB 4.19 / 2.37, 5.74 / 2.78, 11.1 / 7.9, 28.5 / 21.9, 123 / 95, 1000 of 0.7 / 200 MB 16.8 / 4.5, 139 / 105.
 static bool placed_pays_both(const BucketRec &b, uint32_t es, bool one_pass)
 {
     const uint64_t bytes = b.P * es;

@@ -189,3 +189,84 @@ def test_form_of_an_update_of_one_segment(rec, R, cls, captured):
                         even = groups <= limit and (odd is None or R < 3) and not captured
                         assert name_of(kernel) == ("fused_even_kernel" if even else "fused_one_kernel"), (kernel, groups, odd, distance)
                         assert grid == (groups, 1, 1) and kernel.split("<")[1].startswith("%du, " % k)
+
+
+def spread(n, total):
+    """n lengths of about `total` in all, every ninth 61 times the others."""
+    weights = [61 if t % 9 == 3 else 1 for t in range(n)]
+    return [max(1, total * w // sum(weights)) for w in weights]
+
+
+# tensors' lengths, how they lie, with the bucket, shards: the kernel of an eager call (bf16; sizes are the bucket's)
+UNPACKINGS = [
+    ([200] * 5, "placed", False, 1, "unpack_list_kernel"),                  # 5 parts: the smallest list
+    ([200] * 6, "placed", False, 1, "unpack_placed_kernel"),
+    (spread(9, 60000), "placed", False, 3, "unpack_placed_kernel"),
+    (spread(9, 120000), "near", False, 3, "unpack_list_kernel"),            # uneven parts: 0.24 MB,
+    (spread(9, 140000), "near", False, 3, "unpack_near_kernel"),            # 0.28 MB
+    (spread(9, 280000), "off", False, 3, "unpack_list_kernel"),
+    (spread(12, 140000), "near", False, 3, "unpack_near_kernel"),
+    (spread(13, 280000), "near", False, 3, "unpack_list_kernel"),           # (from 1 MiB)
+    (spread(13, 560000), "near", False, 3, "unpack_near_kernel"),
+    (spread(64, 560000), "near", False, 8, "unpack_near_kernel"),
+    (spread(65, 560000), "near", False, 8, "unpack_list_kernel"),
+    (spread(9, 280000), "near", False, 9, "unpack_list_kernel"),            # more shards than an argument block holds
+    (spread(9, 280000), "placed", False, 9, "unpack_list_kernel"),
+    ([170000] * 12, "placed", False, 1, "unpack_placed_kernel"),            # even parts: 4.1 MB,
+    ([180000] * 12, "placed", False, 1, "unpack_list_kernel"),              # 4.3 MB,
+    ([20000] * 12, "near", False, 1, "unpack_list_kernel"),                 # 0.48 MB,
+    ([24000] * 12, "near", False, 1, "unpack_near_kernel"),                 # 0.58 MB,
+    ([170000] * 12, "near", False, 1, "unpack_near_kernel"),
+    ([180000] * 12, "near", False, 1, "unpack_list_kernel"),
+    ([60000] * 13, "near", False, 1, "unpack_list_kernel"),
+    ([3000] * 100, "placed", False, 1, "unpack_list_kernel"),
+    (spread(100, 250000), "placed", False, 3, "unpack_list_kernel"),        # one launch of uneven parts: 0.5 MB,
+    (spread(100, 280000), "placed", False, 3, "unpack_placed_kernel"),
+    (spread(100, 2000000), "placed", False, 3, "unpack_placed_kernel"),     # 4 MB,
+    (spread(100, 2200000), "placed", False, 3, "unpack_list_kernel"),
+    (spread(400, 12000000), "placed", False, 3, "unpack_placed_kernel"),    # lists of three launches: 24 MB,
+    (spread(400, 14000000), "placed", False, 3, "unpack_kernel"),           # 28 MB, by the tables
+    ([200] * 2, "placed", True, 1, "unpack_placed_kernel"),                 # with the bucket, one pass of lists: any up to 4 MiB
+    (spread(9, 2000000), "placed", True, 3, "unpack_placed_kernel"),
+    (spread(9, 2200000), "placed", True, 3, "unpack_list_kernel"),
+    (spread(80, 250000), "placed", True, 3, "unpack_list_kernel"),          # more than 64 tensors: 0.5 MB,
+    (spread(80, 280000), "placed", True, 3, "unpack_placed_kernel"),
+    (spread(9, 280000), "near", True, 3, "unpack_list_kernel"),
+    ([100] * 200, "placed", True, 3, "unpack_placed_kernel"),               # (else two passes)
+]
+
+
+@pytest.mark.parametrize("numel,place,both,z3,kernel", UNPACKINGS)
+def test_form_of_an_unpacking(rec, numel, place, both, z3, kernel):
+    """Both sides of each line of the choice, eager and captured (lists where they serve); a grid is (tiles of a shard, shards) where the bucket
+    is passed over, and (tiles, parts) or flat where lists are."""
+    plan, call = unpacking(rec, numel, both, place, z3)
+    (got, grid, _), = rec.launches(call)
+    assert name_of(got) == kernel
+    if kernel in ("unpack_placed_kernel", "unpack_near_kernel"):
+        assert grid == (-(-plan.bucket(0).s3 // 512), z3, 1)
+        few = len(numel) <= 64
+        assert kernel == "unpack_near_kernel" or got == "unpack_placed_kernel<2, %s, %s>" % (str(both).lower(), str(few).lower())
+    captured = rec.launches(call, captured=True)
+    if kernel == "unpack_list_kernel":
+        assert captured == [(got, grid, 0)]
+
+
+def test_form_of_a_gather_of_equal_layers(rec):
+    """Layers at equal distances in every source and in the outputs go by the first one's pieces, captured or not; else by lists."""
+    hzp, layers, K, s1 = rec.hzp, 33, 4, 520
+    plan = hzp.hzp_plan([1] * layers, [s1 * K] * layers, align=8, z3=1, z1=K)
+    src = [0x7000000000 + k * 0x10000000 for k in range(K)]
+    for captured in (False, True):
+        for odd, stack in ((None, True), ("layer", False), ("source", False), ("piece", False), ("own", True)):
+            dsts = [0x7800000000 + l * 8192 + (4096 if odd == "layer" and l == 9 else 0) for l in range(layers)]
+            parts = [src[k] + l * (1072 if odd == "source" and k == 1 else 1056) for l in range(layers) for k in range(K)]
+            for l in range(layers):
+                if odd == "own" or (odd == "piece" and l == 9):
+                    parts[l * K + 2] = dsts[l] + 2 * s1 * 2
+            got = rec.launches(lambda: hzp.hzp_gather_layers(plan, 0, layers, 0, 1, parts, K, dsts, stream=0), captured)
+            names = {name_of(k) for k, _, _ in got}
+            if stack:
+                assert names == {"copy_stack_kernel"} and [g for _, g, _ in got] == [(-(-s1 // 512), K - (odd == "own"), layers)]
+            else:
+                assert names and "copy_stack_kernel" not in names
