@@ -21,9 +21,10 @@ class _KernelNode(ctypes.Structure):
                 ("params", ctypes.c_void_p), ("lds", ctypes.c_uint32)]
 
 
-def launches_of(call):
-    """The kernels that `call` enqueues on the current stream, in order, as (grid, dynamic LDS bytes, kernel): the call is captured into
-    a HIP graph, whose nodes are read; nothing runs.  Plans have to be prepared."""
+def launches_of(call, replay=False):
+    """The kernels that `call` enqueues where it is captured, in order, as (grid, dynamic LDS bytes, kernel): the call is captured into a HIP
+    graph, whose nodes are read; nothing runs, unless `replay` is set.  Plans have to be prepared.  Short updates and reductions and some
+    unpackings have other forms where they are not captured; which, test_launch_choice.py asserts without a GPU."""
     hip = hzp.binding._L            # symbols of the HIP runtime are found through the library that links it
     graph = torch.cuda.CUDAGraph(keep_graph=True)
     with torch.cuda.graph(graph):
@@ -37,6 +38,9 @@ def launches_of(call):
         info = _KernelNode()
         assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(info)) == 0
         out.append((tuple(info.grid), info.lds, info.func))
+    if replay:
+        graph.replay()
+        torch.cuda.synchronize()
     return out
 
 

@@ -561,11 +561,14 @@ def test_short_reductions_read_their_arguments_from_the_block(R, g32):
 
             def call():
                 hzp.hzp_reduce_shard(plan, 0, 0, 1, 0, [x[:n] for x in g], 0.3, acc, out[:n], grad_dtype=gd)
-            (_, _, kernel), = launches_of(call)
+            (_, _, kernel), = launches_of(call, replay=True)
             kernels.append(kernel)
-            call()
-            torch.cuda.synchronize()
-            assert torch.equal(out[:n], in_order_sum([x[:n] for x in g], acc)) and bool((out[n:] == 0.5).all())
+            for how in ("replayed", "eager"):           # (from 13 contributions on two forms)
+                if how == "eager":
+                    out.fill_(0.5)
+                    call()
+                    torch.cuda.synchronize()
+                assert torch.equal(out[:n], in_order_sum([x[:n] for x in g], acc)) and bool((out[n:] == 0.5).all()), how
     block, registers, accumulating = kernels[0], kernels[6], kernels[1]
     assert kernels == [block, accumulating] * 3 + [registers, accumulating] and len({block, registers, accumulating}) == 3
 
@@ -725,7 +728,8 @@ def test_tensors_that_lie_as_in_the_bucket(kind, n, z3, cls):
                                                  ([100, 9000] * 50, False, 1), ([100, 90000] * 50, False, 1), ([100, 9000] * 300, False, 1),
                                                  ([9000] * 200, True, 1), ([1000] * 9, True, 1), ([300000] * 9, True, 1)])
 def test_every_choice_between_lists_and_the_bucket_s_own_layout(numel, both, launches):
-    """Sizes on both sides of each line of the choice, from 3 shards, to the bit and in one launch."""
+    """Sizes on both sides of each line of the choice, from 3 shards, to the bit: the captured call, in one launch, and the eager one, whose form
+    may be another (test_launch_choice.py asserts both)."""
     n = len(numel)
     plan = hzp.hzp_plan([n], numel, align=64, z3=3, z1=3)
     plan.prepare()
@@ -735,19 +739,27 @@ def test_every_choice_between_lists_and_the_bucket_s_own_layout(numel, both, lau
     flat = torch.full((b.padded,), -1, dtype=torch.int16, device=DEV)
     views = [flat[plan.tensor(t).offset:plan.tensor(t).offset + numel[t]] for t in range(n)]
     bucket = torch.empty_like(whole) if both else None
-    got = launches_of(lambda: hzp.hzp_gather_layer(plan, 0, 0, 3, shards, bucket, views))
+    got = launches_of(lambda: hzp.hzp_gather_layer(plan, 0, 0, 3, shards, bucket, views), replay=True)
     assert len(got) == launches
-    hzp.hzp_gather_layer(plan, 0, 0, 3, shards, bucket, views)
-    torch.cuda.synchronize()
-    for t, v in enumerate(views):
-        assert torch.equal(v, whole[plan.tensor(t).offset:plan.tensor(t).offset + numel[t]]), t
-    assert not both or torch.equal(bucket, whole)
+    for how in ("replayed", "eager"):
+        if how == "eager":
+            flat.fill_(-1)
+            if both:
+                bucket.fill_(-1)
+            hzp.hzp_gather_layer(plan, 0, 0, 3, shards, bucket, views)
+            torch.cuda.synchronize()
+        for t, v in enumerate(views):
+            assert torch.equal(v, whole[plan.tensor(t).offset:plan.tensor(t).offset + numel[t]]), (how, t)
+        assert not both or torch.equal(bucket, whole), how
 
 
 @pytest.fixture(scope="module")
 def wide_room():
     """An allocation whose ends lie further apart than 32 bits of 16-byte units reach."""
-    yield torch.empty((33 << 30) + (16 << 20), dtype=torch.uint8, device=DEV)
+    room = torch.empty((33 << 30) + (16 << 20), dtype=torch.uint8, device=DEV)
+    yield room
+    room.untyped_storage().resize_(0)                       # given back with the module
+    torch.cuda.empty_cache()
 
 
 @pytest.mark.parametrize("cls,R", [(0, R) for R in range(1, 10)] + [(1, R) for R in range(1, 10)] + [(0, 0)])
@@ -782,6 +794,10 @@ def test_short_updates_with_streams_near_and_far(cls, R, n, wide_room):
                 assert all(torch.equal(a, b) for a, b in zip(got, first)), (far, call, given)
                 want = got[0].to(types[-1]) if given else torch.full_like(streams[-1], 7)
                 assert torch.equal(streams[-1], want), (far, call, given)
+    for t, s in zip(streams, start):                        # the form of a captured call
+        t.copy_(s)
+    launches_of(lambda: hzp.hzp_adamw_shard(plan, 0, 1, cls, 0, hy, streams[:k], R, *[[t] for t in streams[k:]]), replay=True)
+    assert all(torch.equal(a, b) for a, b in zip(streams[k:], first + [first[0].to(types[-1])]))
 
 
 @pytest.mark.parametrize("accumulate", [0, 1])
@@ -815,6 +831,9 @@ def test_short_reductions_by_distance(n, R, g32, accumulate, wide_room):
         hzp.hzp_reduce_shard(plan, 0, 0, 3, 0, g, 0.5, accumulate, out, grad_dtype=hzp.HZP_GRAD_F32 if g32 else hzp.HZP_GRAD_BF16)
         torch.cuda.synchronize()
         assert torch.equal(out, want), (placed[:3], far)
+    out = before.clone()                                    # the form of a captured call
+    launches_of(lambda: hzp.hzp_reduce_shard(plan, 0, 0, 3, 0, g, 0.5, accumulate, out, grad_dtype=hzp.HZP_GRAD_F32 if g32 else hzp.HZP_GRAD_BF16), replay=True)
+    assert torch.equal(out, want)
 
 
 @pytest.mark.parametrize("cls,R", [(c, R) for c in (0, 1) for R in (2, 3, 4, 5, 8, 9, 16, 17, 31, 32)])
