@@ -2202,7 +2202,7 @@ constexpr uint64_t kOffLinesPlaced = 64u << 20, kOffLinesNear = 16u << 20;
 //   up to 64 tensors: 6 / 9 / 30 / 64 uneven ones of 0.06-0.1 MB in all 1.78 / 1.80, 1.88 / 1.85, 1.83 / 1.92, 1.86 / 1.98 (in a row 4.4 / 4.0), of 0.16 MB 1.88 /
 //   1.86, 1.87 / 1.86, 2.14 / 1.93, 2.26 / 1.99, 9 of 0.5 / 3.6 MB 2.33 / 2.01, 3.34 / 3.09 (3.65 / 3.25), of 18 / 360 MB 7.8 / 7.5, 107 / 106; even parts (2 shards),
 //   placed by lists: 6 / 9 / 12 / 30 / 64 of 0.2 MB 1.06 / .99 / 1.01 / 1.06 / .98, of 0.5 MB 1.00 / 1.01 / 1.03 / 1.01 / 1.12, of 1.2 MB 1.00 / .91 / .91 / .86 / .84
-//   (in a row .89), from 20 MB the same.  (What the shortest lose on the device shows in a tail behind a long kernel alone: a launch costs the host longer.)
+//   (in a row .89), from 20 MB the same.  (What the shortest lose on the device shows behind a long kernel alone: a launch costs the host longer.)
 //   more, where lists are one launch: 100 uneven ones of 0.07 / 0.6 / 2 / 20 MB 2.28 / 2.46 (in a graph), 2.48 / 2.32, 3.02 / 2.57, 9.4 / 9.7, even ones of 2 /
 //   20 MB 2.9 / 3.0, 8.3 / 9.3.
 //   more, where lists are several launches (or tables), 8 MiB for each: 170 uneven ones of 7 / 15 / 20 / 60 / 120 MB 5.45 / 4.93, 8.26 / 8.04, 10.0 / 9.7, 23.1 /
@@ -2216,17 +2216,17 @@ static bool placed_pays(const BucketRec &b, const ListShape &lists, uint32_t es)
     if (lists.even) return false;
     return lists.launches == 1 ? bytes >= 512u << 10 && bytes <= 4u << 20 : bytes <= lists.launches * (8u << 20);
 }
-// And that of unpack_near?  Up to 12 tensors from where the device loses little, near by lists behind a long kernel: uneven ones, 6 / 9 / 12 of 0.1 MB 1.11 / 1.12 /
-// 1.11, of 0.28 MB 1.11 / 1.00 / .91, of 0.4 MB 1.00 / .90 / .95, of 3.6 MB .94 (in a row .90); even parts (2 shards), of 0.2 MB 1.14 / 1.11 / 1.14, of 0.42 MB 1.14 /
-// 1.04 / 1.08, of 0.56 MB 1.05 / 1.09 / 1.07, of 1.2 MB 1.11 / 1.01 / .99, of 2 MB 1.02 / 1.02 / .96 (.91); off the bucket's 128-byte lines .97-1.03 of 0.4 MB, .91-.99 of 0.5 MB.
+// And that of unpack_near?  Up to 12 tensors as above, near by lists: uneven ones, behind a long kernel 6 / 9 / 12 of 0.1 MB 1.11 / 1.12 / 1.11, of 0.28 MB 1.11 /
+// 1.00 / .91, of 0.4 MB 1.00 / .90 / .95, of 3.6 MB .94; even parts (2 shards), of 0.2 MB 1.14 / 1.11 / 1.14, of 0.56 MB 1.05 / 1.09 / 1.07, of 1.2 MB 1.11 / 1.01 /
+// .99, of 2 MB 1.02 / 1.02 / .96; off the bucket's 128-byte lines .97-1.03 of 0.4 MB, .91-.99 of 0.5 MB.  In a row .88-.93 throughout.  So the shortest cost the
+// device 0.1 to 0.3 us and save the host 0.4, and the host takes longer than the device for a launch: a program that makes many such calls sees the latter.
 // More, in a block of 320 bytes, only where they are uneven and long enough: 64 of 0.05 / 0.76 / 12.8 / 128 MB 4.6 / 4.35, 4.5 / 4.3, 7.3 / 6.6, 41.6 / 39.0 in a row
 // and 2.26 / 2.32, 2.50 / 2.45, 7.3 / 6.4, 42.9 / 40.4 in a graph: a cautious line.
 // (With the bucket beside them 0.2 us more on the device than lists: 9 of 0.06 MB 2.08 / 2.33.)
 static bool near_pays(const BucketRec &b, const ListShape &lists, uint32_t es)
 {
-    const uint64_t bytes = b.P * es;
-    if (b.n_tensors <= UnpackNear12::kTensors) return bytes >= (lists.even ? 512u : 256u) << 10 && placed_pays(b, lists, es);
-    return b.n_tensors <= UnpackNear64::kTensors && !lists.even && bytes >= 1u << 20;
+    if (b.n_tensors <= UnpackNear12::kTensors) return placed_pays(b, lists, es);
+    return b.n_tensors <= UnpackNear64::kTensors && !lists.even && b.P * es >= 1u << 20;
 }
 // The same with the bucket written too, where lists (`one_pass`) are one launch: 9 uneven / 30 even / 64 even ones of 0.06-0.1 MB 1.81 / 1.88, 1.77 / 1.85, 1.80 / 1.95
 // (in a row 4.5 / 3.9, 4.8 / 3.9, 5.0 / 4.1), 9 / 30 / 64 even ones of 0.5 MB 2.06 / 1.84, 2.03 / 1.93, 1.89 / 1.86, 9 uneven ones of 4 MB 4.23 / 3.69, 9 of 18 / 360 MB

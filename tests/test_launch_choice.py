@@ -202,8 +202,8 @@ UNPACKINGS = [
     ([200] * 5, "placed", False, 1, "unpack_list_kernel"),                  # 5 parts: the smallest list
     ([200] * 6, "placed", False, 1, "unpack_placed_kernel"),
     (spread(9, 60000), "placed", False, 3, "unpack_placed_kernel"),
-    (spread(9, 120000), "near", False, 3, "unpack_list_kernel"),            # uneven parts: 0.24 MB,
-    (spread(9, 140000), "near", False, 3, "unpack_near_kernel"),            # 0.28 MB
+    (spread(6, 4000), "near", False, 3, "unpack_near_kernel"),
+    (spread(9, 140000), "near", False, 3, "unpack_near_kernel"),
     (spread(9, 280000), "off", False, 3, "unpack_list_kernel"),
     (spread(12, 140000), "near", False, 3, "unpack_near_kernel"),
     (spread(13, 280000), "near", False, 3, "unpack_list_kernel"),           # (from 1 MiB)
@@ -214,8 +214,7 @@ UNPACKINGS = [
     (spread(9, 280000), "placed", False, 9, "unpack_list_kernel"),
     ([170000] * 12, "placed", False, 1, "unpack_placed_kernel"),            # even parts: 4.1 MB,
     ([180000] * 12, "placed", False, 1, "unpack_list_kernel"),              # 4.3 MB,
-    ([20000] * 12, "near", False, 1, "unpack_list_kernel"),                 # 0.48 MB,
-    ([24000] * 12, "near", False, 1, "unpack_near_kernel"),                 # 0.58 MB,
+    ([2000] * 12, "near", False, 1, "unpack_near_kernel"),
     ([170000] * 12, "near", False, 1, "unpack_near_kernel"),
     ([180000] * 12, "near", False, 1, "unpack_list_kernel"),
     ([60000] * 13, "near", False, 1, "unpack_list_kernel"),
