@@ -112,8 +112,9 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
 // ---------------------------------------------------------------------------------------
 constexpr int kWave = 64;
 // The runtime copies a launch's arguments into memory that another of its threads gives back, a thousand launches at a time.  Where copies
-// are longer than this the two threads wait for each other: calls in a row, in a process that has PyTorch loaded, blocks of 96 / 104 / 112 / 120 / 128 / 256 /
-// 816 bytes, us a launch: 2.80 / 2.81 / 2.78 / 3.25-3.6 / 3.55 / 3.65 / 3.9.
+// are longer than this the two threads wait for each other.  Calls in a row, blocks of 24 / 96 / 104 / 112 / 120 / 128 / 256 / 816 / 3616
+// bytes, us a launch: in a C++ program of nothing else 2.7 / 2.8 / 2.85 / 2.85 / 3.45 / 3.5 / 3.6 / 3.7 / 3.9, with PyTorch loaded - / 2.80
+// / 2.81 / 2.78 / 3.25-3.6 / 3.55 / 3.65 / 3.9 / -.  (Of this runtime with this C library; longer blocks work as well.)
 constexpr size_t kFewBytes = 112;
 constexpr uint32_t kGroupQuads = 64;        // quads per group (256 elements)
 
@@ -351,7 +352,8 @@ __global__ __launch_bounds__(kWave) void reduce_even_kernel(const u64x2 o, const
     uint64_t at[CHUNK];
 #pragma unroll
     for (uint32_t c = 0; c < CHUNK; ++c) at[c] = c < R ? g[0] + c * g[1] : 0;
-    reduce<R, G32, ACC, kReduceFew>(o[0], (uint32_t)o[1], __uint_as_float((uint32_t)(o[1] >> 32)), at, [&](uint32_t r) { return g[0] + r * g[1]; });
+    reduce<R, G32, ACC, kReduceFew>(o[0], (uint32_t)o[1], __uint_as_float((uint32_t)(o[1] >> 32)), at,
+                                    [&](uint32_t r) { return g[0] + r * g[1]; });
 }
 
 // ---------------------------------------------------------------------------------------
@@ -381,8 +383,8 @@ struct FusedArgs {
 };
 static_assert(sizeof(FusedArgs) <= 4096, "kernel arguments");
 // The same for one segment with pointers of its own and one multiplier, whose leading arguments (FusedLead) are in scalar registers when a
-// wavefront starts: all that its first requests need, up to two contributions.  The block is a tenth of the other, and
-// launching costs 2.3 us with the smallest blocks and 2.6 with the largest (the host writes it to device memory).
+// wavefront starts: all that its first requests need, up to two contributions.  The block is a tenth of the other,
+// which the host has to write to device memory (kFewBytes).
 struct FusedOneArgs {
     uint64_t out;
     AdamScalars scalars;
@@ -399,7 +401,8 @@ struct FusedLead {
 };
 constexpr uint32_t kLeadBytes = 56;         // of the argument block; the struct follows
 static_assert(sizeof(u64x4) + sizeof(u64x2) + sizeof(uint64_t) == kLeadBytes && alignof(FusedOneArgs) == 8, "argument block");
-// The same for short launches where contributions lie at equal distances, as in the planner's arena or one receive buffer: any number of them, within kFewBytes.
+// The same for short launches where contributions lie at equal distances, as in the planner's arena or one receive buffer: any number of
+// them, within kFewBytes.
 struct FusedEvenArgs {
     uint64_t out;
     AdamScalars scalars;
@@ -595,7 +598,8 @@ __device__ __forceinline__ void fused_adamw(const FusedLead lead, const Args &a)
         else
             return slice[r];
     };
-    sum_contributions<R, CHUNK, G32, 1, false, (FORM == kOne && G32 && CHUNK > 8 ? 8u : 0u)>(at, contribution, shift * (G32 ? 16 : 8), quads, g, [&] {
+    constexpr uint32_t GAP = FORM == kOne && G32 && CHUNK > 8 ? 8 : 0;
+    sum_contributions<R, CHUNK, G32, 1, false, GAP>(at, contribution, shift * (G32 ? 16 : 8), quads, g, [&] {
         if (FORM == kOne)       // needed last, but read by now
             pin(OUT, h.lr, h.beta1, h.beta2, h.one_minus_beta1, h.one_minus_beta2, h.eps, h.weight_decay, h.grad_scale, h.inv_bc1, h.inv_bc2);
     });
@@ -713,8 +717,9 @@ __global__ __launch_bounds__(kWave) void copy_bucket_kernel(const CopyBucketArgs
 }
 
 // Layers of one length, at equal distances in every source and in the output (the blocks of a transformer in an arena, or in one buffer per
-// source): up to 8 pieces of the first layer and the two distances, in place of a list of pieces or of layers (1.5 to 4 KB).  Lists / so, us, calls in a row: 8 layers
-// of 4 pieces of 2 KB 3.5 / 3.25, 16 of 8 3.8 / 3.4, 60 of 2 5.2 / 4.6, 120 of 8 7.7 / 6.25, 300 of 2 12.4 / 8.2 (two launches), 32 of 4 of 128 KB 6.0 / 5.6, of 2 MB 78.9 / 78.7; on the device alone .98.
+// source): up to 8 pieces of the first layer and the two distances, in place of a list of pieces or of layers (1.5 to 4 KB).  Lists / so,
+// us, calls in a row: 8 layers of 4 pieces of 2 KB 3.5 / 3.25, 16 of 8 3.8 / 3.4, 60 of 2 5.2 / 4.6, 120 of 8 7.7 / 6.25, 300 of 2 12.4 /
+// 8.2 (two launches), 32 of 4 of 128 KB 6.0 / 5.6, of 2 MB 78.9 / 78.7; on the device alone .98.
 // grid = (tiles of a piece, pieces, layers).
 struct CopyStackArgs {
     CopyBucketArgs first;                   // (its output the first layer's)
@@ -907,7 +912,7 @@ __global__ __launch_bounds__(kWave) void unpack_list_kernel(const Args a)
 // Tensors that lie in one buffer as they do in the bucket (its parameters are views of a flat buffer of the same alignment): every
 // vector's place is known without its tensor, and which of its elements belong to one is looked up while the data arrive, in the plan's
 // device table of the tensors' begins and ends.  Up to 8 shards.  grid = (tiles of a shard, shards).
-// One round of memory instead of a list's two (three in a flat grid), and a block of 96 bytes whatever the number of tensors.
+// One round of memory instead of a list's two (three in a flat grid), and a block of 104 bytes whatever the number of tensors.
 struct UnpackPlacedArgs {
     static constexpr uint32_t kShards = 8;
     uint64_t src[kShards];
@@ -920,8 +925,8 @@ struct UnpackPlacedArgs {
 };
 static_assert(sizeof(UnpackPlacedArgs) <= kFewBytes, "kernel arguments");
 
-// The same for up to 64 tensors that lie anywhere on 16 bytes, but no further apart than 32 bits of such units reach (nor the shards): a lane finds
-// its tensor's distance with its end.  For 12 tensors the block stays within kFewBytes.
+// The same for up to 64 tensors that lie anywhere on 16 bytes, but no further apart than 32 bits of such units reach (nor the shards): a
+// lane finds its tensor's distance with its end.  For 12 tensors the block stays within kFewBytes.
 template <uint32_t N>
 struct UnpackNearArgs {
     static constexpr uint32_t kTensors = N;
@@ -937,10 +942,12 @@ static_assert(sizeof(UnpackNear12) <= kFewBytes, "kernel arguments");
 
 constexpr int32_t kNoDistance = INT32_MIN;
 
-// FEW: at most 64 tensors, whose spans are asked for together with the data; else 64 pivots a round lead to the first that a tile meets (asking
-// for up to 256 spans at once, four a lane, took as long: 100 tensors of 0.07 MB 2.61 us, with pivots 2.46).  NEAR: lane t's `distance` is tensor t's.
+// FEW: at most 64 tensors, whose spans are asked for together with the data; else 64 pivots a round lead to the first that a tile meets
+// (asking for up to 256 spans at once, four a lane, took as long: 100 tensors of 0.07 MB 2.61 us, with pivots 2.46).  NEAR: lane t's
+// `distance` is tensor t's.
 template <int ES, bool BOTH, bool FEW, bool NEAR>
-__device__ __forceinline__ void unpack_spans(uint64_t src, uint64_t dst, uint64_t bucket, uint64_t table, uint32_t nvec, uint32_t n, uint32_t end, const int32_t *distances)
+__device__ __forceinline__ void unpack_spans(uint64_t src, uint64_t dst, uint64_t bucket, uint64_t table, uint32_t nvec, uint32_t n, uint32_t end,
+                                             const int32_t *distances)
 {
     constexpr uint32_t VE = 16 / ES, TILE = kWave * VE;         // elements of a vector, of a tile
     typedef typename std::conditional<ES == 2, uint16_t, uint32_t>::type elem_t;
@@ -950,7 +957,8 @@ __device__ __forceinline__ void unpack_spans(uint64_t src, uint64_t dst, uint64_
     const uint32_t first = (blockIdx.y * nvec + blockIdx.x * kWave) * VE, mine = first + lane * VE;     // bucket positions
     if (!BOTH && first >= end) return;  // padding behind the last tensor
     const u32x4 val = ld_stream<u32x4>(src, vec < nvec ? vec : nvec - 1);
-    // (the bucket's store needs the data alone, so there they are asked for first, 30 tensors of 1.8 MB 3.4 -> 3.2 us; else the spans, 64 of 12.8 MB 6.7 -> 6.3)
+    // (the bucket's store needs the data alone, so there they are asked for first, 30 tensors of 1.8 MB 3.4 -> 3.2 us; else the spans, 64
+    // of 12.8 MB 6.7 -> 6.3)
     if (BOTH) __builtin_amdgcn_sched_barrier(0);
     int32_t distance = 0, away = 0;     // tensor `lane`'s, the one's that the lane's vector belongs to
     if (NEAR) distance = distances[lane < n ? lane : n - 1];
@@ -985,7 +993,8 @@ __device__ __forceinline__ void unpack_spans(uint64_t src, uint64_t dst, uint64_
         at += kWave;
     }
     if (vec >= nvec) return;
-    if (BOTH && src != bucket + (uint64_t)(blockIdx.y * nvec) * 16) st_writethrough(bucket, mine * ES, __builtin_bit_cast(f32x4, val));        // (else it lies in place)
+    if (BOTH && src != bucket + (uint64_t)(blockIdx.y * nvec) * 16)         // (else it lies in place)
+        st_writethrough(bucket, mine * ES, __builtin_bit_cast(f32x4, val));
     if (mine >= until) return;
     const uint64_t to = NEAR ? dst + (int64_t)away * 16 + (uint64_t)(mine - from) * ES : dst + (uint64_t)mine * ES;
     if (until - mine >= VE) {
@@ -1095,7 +1104,8 @@ struct AsIs {
 };
 // Launches a kernel whose arguments lie at `args`; it reads as many bytes there as its own parameters have.
 template <class... P>
-static hzp_status_t start_any(const char *who, const void *kernel, dim3 grid, dim3 block, unsigned lds, hipStream_t stream, const P *...args)
+static hzp_status_t start_any(const char *who, const void *kernel, dim3 grid, dim3 block, unsigned lds, hipStream_t stream,
+                              const P *...args)
 {
     void *ptrs[] = {const_cast<void *>(static_cast<const void *>(args))...};
     (void)hipLaunchKernel(kernel, grid, block, ptrs, lds, stream);
@@ -1111,7 +1121,8 @@ static hzp_status_t start(const char *who, void (*kernel)(P...), dim3 grid, dim3
     return start_any(who, reinterpret_cast<const void *>(kernel), grid, block, lds, stream, &args...);
 }
 
-// Is the call being captured?  A replay costs the host nothing for each launch, so there the shortest time on the device is all that counts.
+// Is the call being captured?  A replay costs the host nothing for each launch, so there the shortest time on the device is all that
+// counts.
 static bool captured(hipStream_t stream)
 {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
@@ -1242,16 +1253,18 @@ static bool reduce_from_block(bool g32, uint32_t R, ReduceForm form, uint64_t n,
 // 6.84 / 6.85, bf16 R = 8 (5.7 GB) 6.89 / 6.88 / 6.82 / 6.70, R = 4 (3.4 GB) 6.84 / 6.82 / 6.80 / 6.68.
 constexpr uint64_t most_reduce_bytes(uint32_t R) { return R > 8 ? 3000000000ull : 6000000000ull; }
 
-// Longest launch of equally distant contributions by their distance, in groups.  Against pointers (120 to 272 bytes of arguments), R = 13 to 32,
-// up to 0.2 M elements, accumulating or not, streams 2, 4 .. 18 MiB apart, medians over the distances: calls in a row on an idle queue bf16 .86,
-// fp32 .90 (R = 16 of 16 k elements 4.2 -> 3.6 us); behind a long kernel, with the host ahead, .974 and .982 (worst: bf16 R = 16 accumulating
-// 0.1 M elements 1.04, fp32 R = 13 of 4 k 1.07); in graphs 1.008 and 1.003 (worst 1.06), so captured ones take pointers.  Beyond, what starts faster collides in the memory channels (in a
-// row, worst distance: bf16 of 0.46 / 0.52 M elements 1.12, fp32 of 0.26 M 1.13).  Contributions at any distances, 13 to 23 of them each by its
-// own from the first, would take .86 in a row too, but 1.05 on average and up to 1.19 behind a long kernel: these take pointers.
+// Longest launch of equally distant contributions by their distance, in groups.  Against pointers (120 to 272 bytes of arguments), R = 13
+// to 32, up to 0.2 M elements, accumulating or not, streams 2, 4 .. 18 MiB apart, medians over the distances: calls in a row on an idle
+// queue bf16 .86, fp32 .90 (R = 16 of 16 k elements 4.2 -> 3.6 us); behind a long kernel, with the host ahead, .974 and .982 (worst: bf16 R
+// = 16 accumulating 0.1 M elements 1.04, fp32 R = 13 of 4 k 1.07); in graphs 1.008 and 1.003 (worst 1.06), so captured ones take pointers.
+// Beyond, what starts faster collides in the memory channels (in a row, worst distance: bf16 of 0.46 / 0.52 M elements 1.12, fp32 of 0.26 M
+// 1.13).  Contributions at any distances, 13 to 23 of them each by its own from the first, would take .86 in a row too, but 1.05 on average
+// and up to 1.19 behind a long kernel: these take pointers.
 static uint32_t reduce_even_groups(bool g32) { return g32 ? 384u : 768u; }
 
 // Such a launch; *done is false (and nothing launched) where the distances differ.
-static hzp_status_t start_reduce_even(bool g32, uint32_t R, bool accumulate, const uint64_t *g, u64x2 o, dim3 grid, unsigned lds, hipStream_t stream, bool *done)
+static hzp_status_t start_reduce_even(bool g32, uint32_t R, bool accumulate, const uint64_t *g, u64x2 o, dim3 grid, unsigned lds,
+                                      hipStream_t stream, bool *done)
 {
     constexpr std::make_index_sequence<HZP_MAX_REPLICAS - kReduceEvenLeast + 1> all;
     static const ReduceEvenOfR kernels[2][2] = {{reduce_even_kernels<false, false>(all), reduce_even_kernels<false, true>(all)},
@@ -1260,7 +1273,8 @@ static hzp_status_t start_reduce_even(bool g32, uint32_t R, bool accumulate, con
     *done = true;
     for (uint32_t r = 2; r < R; ++r) *done = *done && g[r] - g[r - 1] == distance;
     if (!*done) return HZP_OK;
-    return start("hzp_reduce_shard", kernels[g32][accumulate][R - kReduceEvenLeast], grid, dim3(kWave), lds, stream, o, u64x2{g[0], distance});
+    const ReduceEvenKernel kernel = kernels[g32][accumulate][R - kReduceEvenLeast];
+    return start("hzp_reduce_shard", kernel, grid, dim3(kWave), lds, stream, o, u64x2{g[0], distance});
 }
 
 hzp_status_t launch_reduce(bool g32, const void *const *slices, uint32_t R, uint64_t n, float scale,
@@ -1274,8 +1288,10 @@ hzp_status_t launch_reduce(bool g32, const void *const *slices, uint32_t R, uint
          {reduce_kernels<false, true, kReducePlain>(all), reduce_kernels<false, true, kReduceFew>(all), {}}},
         {{reduce_kernels<true, false, kReducePlain>(all), reduce_kernels<true, false, kReduceFew>(all), reduce_kernels<true, false, kReduceNarrow>(all)},
          {reduce_kernels<true, true, kReducePlain>(all), reduce_kernels<true, true, kReduceFew>(all), reduce_kernels<true, true, kReduceNarrow>(all)}}};
-    static const KernelOfR narrow_block[2] = {reduce_block_kernels<false, false, kReduceNarrow>(all), reduce_block_kernels<false, true, kReduceNarrow>(all)};
-    static const KernelOfR short_block[2] = {reduce_block_kernels<false, false, kReduceFew>(all), reduce_block_kernels<true, false, kReduceFew>(all)};
+    static const KernelOfR narrow_block[2] = {reduce_block_kernels<false, false, kReduceNarrow>(all),
+                                              reduce_block_kernels<false, true, kReduceNarrow>(all)};
+    static const KernelOfR short_block[2] = {reduce_block_kernels<false, false, kReduceFew>(all),
+                                             reduce_block_kernels<true, false, kReduceFew>(all)};
     // Launches of about equal length; over a longer one the XCDs drift apart, as in the update below.
     const uint64_t launches = (n * (R * es + (accumulate ? 8u : 4u)) + most_reduce_bytes(R) - 1) / most_reduce_bytes(R);
     constexpr uint64_t kTwoGroups = 8 * kGroupQuads;        // what a wavefront with two quads per lane takes
@@ -1303,7 +1319,8 @@ hzp_status_t launch_reduce(bool g32, const void *const *slices, uint32_t R, uint
             st = start_reduce_even(g32, R, accumulate != 0, g, o, grid, lds, stream, &done);
         if (done) {
         } else if (reduce_from_block(g32, R, form, here, accumulate)) {
-            st = start_any("hzp_reduce_shard", form == kReduceNarrow ? narrow_block[accumulate != 0][R - 1] : short_block[g32][R - 1], grid, block, lds, stream, &a);
+            const void *const kernel = form == kReduceNarrow ? narrow_block[accumulate != 0][R - 1] : short_block[g32][R - 1];
+            st = start_any("hzp_reduce_shard", kernel, grid, block, lds, stream, &a);
         } else {
             const u64x4 lead{g[0], g[1], g[2], g[3]};
             st = start_any("hzp_reduce_shard", kernels[g32][accumulate != 0][form][R - 1], grid, block, lds, stream, &lead, &o, g + 4);
@@ -1493,12 +1510,13 @@ static hzp_status_t start_fused(bool g32, bool o32, uint32_t R, const FusedArgs 
     return start("hzp_adamw_shard", kernel, grid, dim3(kWave), fused_lds(g32, R, c, FORM, groups), stream, a);
 }
 
-// Longest launch that takes equally distant contributions by their distance.  Against pointers, buffers of one call's size, streams 2, 4 .. 18 MiB
-// apart, medians over the distances, bf16 and fp32, up to these lengths: calls in a row on an idle queue .89 and .92 (R = 16 of 16 k elements
-// 4.5 -> 3.7 us), behind a long kernel, with the host ahead, .975 and .997 (worst 1.01), in graphs 1.00 and 1.005 (worst 1.02), so captured ones take
-// pointers.  Beyond, what starts faster collides in the memory channels; behind a long kernel: bf16 R = 3 / 4 of 0.39 M elements 1.01 / 1.09, R = 9 / 12 /
-// 16 of 0.26 M 1.11 / 1.15 / 1.04, fp32 R = 3 of 0.33 / 0.39 M 1.09 / 1.07; fp32 R >= 9 of 0.23 / 0.26 M in a row, worst distance, 1.13 / 1.7.
-// (Others, each by its own distance from the first, gained 3 % in a row and lost 3 %, R = 5 14 %, behind a long kernel.)
+// Longest launch that takes equally distant contributions by their distance.  Against pointers, buffers of one call's size, streams 2, 4 ..
+// 18 MiB apart, medians over the distances, bf16 and fp32, up to these lengths: calls in a row on an idle queue .89 and .92 (R = 16 of 16 k
+// elements 4.5 -> 3.7 us), behind a long kernel, with the host ahead, .975 and .997 (worst 1.01), in graphs 1.00 and 1.005 (worst 1.02), so
+// captured ones take pointers.  Beyond, what starts faster collides in the memory channels; behind a long kernel: bf16 R = 3 / 4 of 0.39 M
+// elements 1.01 / 1.09, R = 9 / 12 / 16 of 0.26 M 1.11 / 1.15 / 1.04, fp32 R = 3 of 0.33 / 0.39 M 1.09 / 1.07; fp32 R >= 9 of 0.23 / 0.26 M
+// in a row, worst distance, 1.13 / 1.7. (Others, each by its own distance from the first, gained 3 % in a row and lost 3 %, R = 5 14 %,
+// behind a long kernel.)
 static uint32_t even_groups(bool g32, uint32_t R)
 {
     return R > 8 ? 640u : R == 3 || (R == 4 && !g32) ? 1024u : kFewGroups;
@@ -1519,7 +1537,9 @@ static hzp_status_t start_fused_one(bool g32, bool o32, uint32_t R, const FusedA
     if (even) {
         constexpr std::make_index_sequence<HZP_MAX_REPLICAS> all;
         static const auto kernels16 = fused_even_kernels<false, false>(all), kernels32 = fused_even_kernels<true, true>(all);
-        const void *const k = !g32 ? kernels16[R - 1] : o32 ? kernels32[R - 1] : reinterpret_cast<const void *>(fused_even_kernel<1, true, false, fused_chunk(true, 1, kFew)>);
+        const void *const k = !g32 ? kernels16[R - 1]
+                              : o32 ? kernels32[R - 1]
+                                    : reinterpret_cast<const void *>(fused_even_kernel<1, true, false, fused_chunk(true, 1, kFew)>);
         const u64x4 p{w[0], w[1], w[2], w[4]};
         const u64x2 far{R > 1 ? w[5] - w[4] : 0, reinterpret_cast<uint64_t>(a.scalars_dev)};
         const FusedEvenArgs rest{w[3], a.scalars};
@@ -1711,8 +1731,8 @@ static size_t units_of_launch(size_t left, size_t most, uint64_t rows, TilesAt t
     return all ? all : take_units(left, most, rows, kSurplusEven, kSurplusEven, tiles_at);
 }
 
-// One launch, with the smallest block that holds the pieces (up to 5 stay within kFewBytes; buckets of 64 KiB to 1 MiB from 9 to 64 shards, call after call: 4.75 us
-// with the block of 192, 4.55 with the block of 64; up to 8 shards 4.4 with the block of 8).
+// One launch, with the smallest block that holds the pieces: up to 5 stay within kFewBytes (as a bucket of up to 8 shards does, which is no
+// list); buckets of 64 KiB to 1 MiB from 9 to 64 shards, call after call, 4.75 us with the block of 192, 4.55 with the block of 64.
 static hzp_status_t copy_one(const Move *moves, size_t n, hipStream_t stream, const char *who)
 {
     if (n <= (size_t)CopyLeastArgs::kPieces) return copy_list<CopyLeastArgs>(moves, n, stream, who);
@@ -1807,9 +1827,10 @@ static hzp_status_t copy_shared(const void *const *srcs, uint32_t per_layer, con
     return HZP_OK;
 }
 
-// Layers of one length at equal distances, in one launch; *done is false (and nothing launched) where they are not, would exceed a launch or have more than 8 pieces
-// that move, and where some of a source's pieces lie in place.
-static hzp_status_t copy_stack(const void *const *srcs, uint32_t per_layer, const uint64_t *bytes_per_piece, void *const *dsts, const std::vector<uint32_t> &layers, hipStream_t stream, bool *done)
+// Layers of one length at equal distances, in one launch; *done is false (and nothing launched) where they are not, would exceed a launch
+// or have more than 8 pieces that move, and where some of a source's pieces lie in place.
+static hzp_status_t copy_stack(const void *const *srcs, uint32_t per_layer, const uint64_t *bytes_per_piece, void *const *dsts,
+                               const std::vector<uint32_t> &layers, hipStream_t stream, bool *done)
 {
     *done = false;
     const size_t n = layers.size();
@@ -1841,7 +1862,8 @@ static hzp_status_t copy_stack(const void *const *srcs, uint32_t per_layer, cons
         a.first.slots |= (uint64_t)k << (8 * moving++);
     }
     *done = true;
-    return moving ? start("hzp_gather_layers", copy_stack_kernel, dim3((uint32_t)tiles_of(nvec), moving, (uint32_t)n), dim3(kWave), 0, stream, a) : HZP_OK;
+    if (moving == 0) return HZP_OK;
+    return start("hzp_gather_layers", copy_stack_kernel, dim3((uint32_t)tiles_of(nvec), moving, (uint32_t)n), dim3(kWave), 0, stream, a);
 }
 
 // Sorts layers by the length of their pieces, longest first, equal ones in order.  Mostly they are nearly so (equal layers beside a few
@@ -2040,8 +2062,9 @@ static hzp_status_t unpack_list(const Parts &parts, size_t n, uint64_t cut, hipS
     return start(who, unpack_list_kernel<ES, Args>, grid, dim3(kWave), 0, stream, a);
 }
 
-// Launches over a list of parts: each takes parts while they fit its table and hold no more than kMaxTilesPerLaunch tiles.
-// The smaller blocks save the host what they leave out (5 parts stay within kFewBytes; 4 MB in 24 / 48 / 72 even parts, block of 72 / of 200, us: 4.9 / 5.1, 5.1 / 5.4, 5.3 / 5.5).
+// Launches over a list of parts: each takes parts while they fit its table and hold no more than kMaxTilesPerLaunch tiles. The smaller
+// blocks save the host what they leave out (5 parts stay within kFewBytes; 4 MB in 24 / 48 / 72 even parts, block of 72 / of 200, us: 4.9 /
+// 5.1, 5.1 / 5.4, 5.3 / 5.5).
 template <int ES, bool BOTH, class Parts>
 static hzp_status_t unpack_parts(const Parts &parts, size_t n, hipStream_t stream, const char *who)
 {
@@ -2097,7 +2120,8 @@ static hzp_status_t unpack_parts(const Parts &parts, size_t n, hipStream_t strea
 
 // One tensor of below 2^32 elements in up to 8 parts of about equal length.
 template <int ES>
-static hzp_status_t unpack_tensor(const Piece *pieces, size_t n, const void *const *shards, void *tensor, uint64_t longest, hipStream_t stream)
+static hzp_status_t unpack_tensor(const Piece *pieces, size_t n, const void *const *shards, void *tensor, uint64_t longest,
+                                  hipStream_t stream)
 {
     UnpackTensorArgs a;
     a.dst = reinterpret_cast<uint64_t>(tensor);
@@ -2193,22 +2217,23 @@ static bool spans_reach(const BucketRec &b, uint32_t n_shards, uint32_t es)
 {
     return n_shards <= UnpackPlacedArgs::kShards && b.P * es < 1ull << 32;      // (kernels address with 32 bits)
 }
-// Most bytes of a bucket that are written by the bucket's lines of 128 bytes where those are not the tensors' own (a wavefront then writes parts
-// of lines).  Lists / so, us: tensors in the bucket's layout, 9 of 18 / 72 / 360 MB 9.0 / 8.6, 27.2 / 27.0, 127 / 128, of 720 MB 249 / 255;
-// elsewhere, 9 of 7 / 18 / 72 / 360 MB 5.2 / 5.2, 8.6 / 8.6, 26.5 / 27.1, 116 / 123, 64 of 13 / 128 MB 7.6 / 7.2, 45 / 47.
+// Most bytes of a bucket that are written by the bucket's lines of 128 bytes where those are not the tensors' own (a wavefront then writes
+// parts of lines).  Lists / so, us: tensors in the bucket's layout, 9 of 18 / 72 / 360 MB 9.0 / 8.6, 27.2 / 27.0, 127 / 128, of 720 MB 249
+// / 255; elsewhere, 9 of 7 / 18 / 72 / 360 MB 5.2 / 5.2, 8.6 / 8.6, 26.5 / 27.1, 116 / 123, 64 of 13 / 128 MB 7.6 / 7.2, 45 / 47.
 constexpr uint64_t kOffLinesPlaced = 64u << 20, kOffLinesNear = 16u << 20;
-// Is the one launch of unpack_placed the better way to write the bucket's tensors?  Lists / placed, us, behind a long kernel (the host is ahead, so that the
-// device's time shows) and in a row on an idle queue, 8 shards but where others are named:
-//   up to 64 tensors: 6 / 9 / 30 / 64 uneven ones of 0.06-0.1 MB in all 1.78 / 1.80, 1.88 / 1.85, 1.83 / 1.92, 1.86 / 1.98 (in a row 4.4 / 4.0), of 0.16 MB 1.88 /
-//   1.86, 1.87 / 1.86, 2.14 / 1.93, 2.26 / 1.99, 9 of 0.5 / 3.6 MB 2.33 / 2.01, 3.34 / 3.09 (3.65 / 3.25), of 18 / 360 MB 7.8 / 7.5, 107 / 106; even parts (2 shards),
-//   placed by lists: 6 / 9 / 12 / 30 / 64 of 0.2 MB 1.06 / .99 / 1.01 / 1.06 / .98, of 0.5 MB 1.00 / 1.01 / 1.03 / 1.01 / 1.12, of 1.2 MB 1.00 / .91 / .91 / .86 / .84
-//   (in a row .89), from 20 MB the same.  (What the shortest lose on the device shows behind a long kernel alone: a launch costs the host longer.)
-//   more, where lists are one launch: 100 uneven ones of 0.07 / 0.6 / 2 / 20 MB 2.28 / 2.46 (in a graph), 2.48 / 2.32, 3.02 / 2.57, 9.4 / 9.7, even ones of 2 /
-//   20 MB 2.9 / 3.0, 8.3 / 9.3.
-//   more, where lists are several launches (or tables), 8 MiB for each: 170 uneven ones of 7 / 15 / 20 / 60 / 120 MB 5.45 / 4.93, 8.26 / 8.04, 10.0 / 9.7, 23.1 /
-//   22.6, 41.1 / 41.9; 400 of 8 / 24 / 32 / 80 / 200 MB 5.8 / 5.6, 11.3 / 11.4, 13.9 / 14.3, 29.6 / 29.6, 65.9 / 68.4, even ones 5.6 / 4.9, 10.9 / 10.6, 14.6 / 13.2,
-//   28.1 / 28.1, 62.8 / 65.0; 1000 uneven ones of 0.7 / 20 / 56 / 80 / 200 / 400 MB 11.6 / 5.2, 18.0 / 11.1, 28.8 / 24.0, 36.9 / 31.9, 79 / 72, 141 / 139.  (So
-//   the line is a cautious one for 1000.)
+// Is the one launch of unpack_placed the better way to write the bucket's tensors?  Lists / placed, us, behind a long kernel (the host is
+// ahead, so that the device's time shows) and in a row on an idle queue, 8 shards but where others are named:
+//   up to 64 tensors: 6 / 9 / 30 / 64 uneven ones of 0.06-0.1 MB in all 1.78 / 1.80, 1.88 / 1.85, 1.83 / 1.92, 1.86 / 1.98 (in a row 4.4 /
+//   4.0), of 0.16 MB 1.88 / 1.86, 1.87 / 1.86, 2.14 / 1.93, 2.26 / 1.99, 9 of 0.5 / 3.6 MB 2.33 / 2.01, 3.34 / 3.09 (3.65 / 3.25), of 18 /
+//   360 MB 7.8 / 7.5, 107 / 106; even parts (2 shards), placed by lists: 6 / 9 / 12 / 30 / 64 of 0.2 MB 1.06 / .99 / 1.01 / 1.06 / .98, of
+//   0.5 MB 1.00 / 1.01 / 1.03 / 1.01 / 1.12, of 1.2 MB 1.00 / .91 / .91 / .86 / .84 (in a row .89), from 20 MB the same.  (What the
+//   shortest lose on the device shows behind a long kernel alone: a launch costs the host longer.)
+//   more, where lists are one launch: 100 uneven ones of 0.07 / 0.6 / 2 / 20 MB 2.28 / 2.46 (in a graph), 2.48 / 2.32, 3.02 / 2.57, 9.4 /
+//   9.7, even ones of 2 / 20 MB 2.9 / 3.0, 8.3 / 9.3.
+//   more, where lists are several launches (or tables), 8 MiB for each: 170 uneven ones of 7 / 15 / 20 / 60 / 120 MB 5.45 / 4.93, 8.26 /
+//   8.04, 10.0 / 9.7, 23.1 / 22.6, 41.1 / 41.9; 400 of 8 / 24 / 32 / 80 / 200 MB 5.8 / 5.6, 11.3 / 11.4, 13.9 / 14.3, 29.6 / 29.6, 65.9 /
+//   68.4, even ones 5.6 / 4.9, 10.9 / 10.6, 14.6 / 13.2, 28.1 / 28.1, 62.8 / 65.0; 1000 uneven ones of 0.7 / 20 / 56 / 80 / 200 / 400 MB
+//   11.6 / 5.2, 18.0 / 11.1, 28.8 / 24.0, 36.9 / 31.9, 79 / 72, 141 / 139.  (So the line is a cautious one for 1000.)
 static bool placed_pays(const BucketRec &b, const ListShape &lists, uint32_t es)
 {
     const uint64_t bytes = b.P * es;
@@ -2216,22 +2241,24 @@ static bool placed_pays(const BucketRec &b, const ListShape &lists, uint32_t es)
     if (lists.even) return false;
     return lists.launches == 1 ? bytes >= 512u << 10 && bytes <= 4u << 20 : bytes <= lists.launches * (8u << 20);
 }
-// And that of unpack_near?  Up to 12 tensors as above, near by lists: uneven ones, behind a long kernel 6 / 9 / 12 of 0.1 MB 1.11 / 1.12 / 1.11, of 0.28 MB 1.11 /
-// 1.00 / .91, of 0.4 MB 1.00 / .90 / .95, of 3.6 MB .94; even parts (2 shards), of 0.2 MB 1.14 / 1.11 / 1.14, of 0.56 MB 1.05 / 1.09 / 1.07, of 1.2 MB 1.11 / 1.01 /
-// .99, of 2 MB 1.02 / 1.02 / .96; off the bucket's 128-byte lines .97-1.03 of 0.4 MB, .91-.99 of 0.5 MB.  In a row .88-.93 throughout.  So the shortest cost the
-// device 0.1 to 0.3 us and save the host 0.4, and the host takes longer than the device for a launch: a program that makes many such calls sees the latter.
-// More, in a block of 320 bytes, only where they are uneven and long enough: 64 of 0.05 / 0.76 / 12.8 / 128 MB 4.6 / 4.35, 4.5 / 4.3, 7.3 / 6.6, 41.6 / 39.0 in a row
-// and 2.26 / 2.32, 2.50 / 2.45, 7.3 / 6.4, 42.9 / 40.4 in a graph: a cautious line.
+// And that of unpack_near?  Up to 12 tensors as above, near by lists: uneven ones, behind a long kernel 6 / 9 / 12 of 0.1 MB 1.11 / 1.12 /
+// 1.11, of 0.28 MB 1.11 / 1.00 / .91, of 0.4 MB 1.00 / .90 / .95, of 3.6 MB .94; even parts (2 shards), of 0.2 MB 1.14 / 1.11 / 1.14, of
+// 0.56 MB 1.05 / 1.09 / 1.07, of 1.2 MB 1.11 / 1.01 / .99, of 2 MB 1.02 / 1.02 / .96; off the bucket's 128-byte lines .97-1.03 of 0.4 MB,
+// .91-.99 of 0.5 MB.  In a row .88-.93 throughout.  So the shortest cost the device 0.1 to 0.3 us and save the host 0.4, and the host takes
+// longer than the device for a launch: a program that makes many such calls sees the latter. More, in a block of 320 bytes, only where they
+// are uneven and long enough: 64 of 0.05 / 0.76 / 12.8 / 128 MB 4.6 / 4.35, 4.5 / 4.3, 7.3 / 6.6, 41.6 / 39.0 in a row and 2.26 / 2.32,
+// 2.50 / 2.45, 7.3 / 6.4, 42.9 / 40.4 in a graph: a cautious line.
 // (With the bucket beside them 0.2 us more on the device than lists: 9 of 0.06 MB 2.08 / 2.33.)
 static bool near_pays(const BucketRec &b, const ListShape &lists, uint32_t es)
 {
     if (b.n_tensors <= UnpackNear12::kTensors) return placed_pays(b, lists, es);
     return b.n_tensors <= UnpackNear64::kTensors && !lists.even && b.P * es >= 1u << 20;
 }
-// The same with the bucket written too, where lists (`one_pass`) are one launch: 9 uneven / 30 even / 64 even ones of 0.06-0.1 MB 1.81 / 1.88, 1.77 / 1.85, 1.80 / 1.95
-// (in a row 4.5 / 3.9, 4.8 / 3.9, 5.0 / 4.1), 9 / 30 / 64 even ones of 0.5 MB 2.06 / 1.84, 2.03 / 1.93, 1.89 / 1.86, 9 uneven ones of 4 MB 4.23 / 3.69, 9 of 18 / 360 MB
-// 11.2 / 10.7, 172 / 173; 100 even ones of 0.08 / 2 / 20 MB 2.1 / 2.4, 3.2 / 3.1, 11.6 / 12.4 in a graph.  Else there are two passes: 100 uneven ones of 0.6 / 2 / 10 /
-// 40 / 200 MB 4.19 / 2.37, 5.74 / 2.78, 11.1 / 7.9, 28.5 / 21.9, 123 / 95, 1000 of 0.7 / 200 MB 16.8 / 4.5, 139 / 105.
+// The same with the bucket written too, where lists (`one_pass`) are one launch: 9 uneven / 30 even / 64 even ones of 0.06-0.1 MB 1.81 /
+// 1.88, 1.77 / 1.85, 1.80 / 1.95 (in a row 4.5 / 3.9, 4.8 / 3.9, 5.0 / 4.1), 9 / 30 / 64 even ones of 0.5 MB 2.06 / 1.84, 2.03 / 1.93, 1.89
+// / 1.86, 9 uneven ones of 4 MB 4.23 / 3.69, 9 of 18 / 360 MB 11.2 / 10.7, 172 / 173; 100 even ones of 0.08 / 2 / 20 MB 2.1 / 2.4, 3.2 /
+// 3.1, 11.6 / 12.4 in a graph.  Else there are two passes: 100 uneven ones of 0.6 / 2 / 10 / 40 / 200 MB 4.19 / 2.37, 5.74 / 2.78, 11.1 /
+// 7.9, 28.5 / 21.9, 123 / 95, 1000 of 0.7 / 200 MB 16.8 / 4.5, 139 / 105.
 static bool placed_pays_both(const BucketRec &b, uint32_t es, bool one_pass)
 {
     const uint64_t bytes = b.P * es;
@@ -2239,7 +2266,8 @@ static bool placed_pays_both(const BucketRec &b, uint32_t es, bool one_pass)
 }
 
 template <int ES, bool BOTH>
-static hzp_status_t unpack_placed(const DeviceTables &tab, const BucketRec &b, const void *const *shards, uint32_t n_shards, uint64_t origin, void *bucket, hipStream_t stream)
+static hzp_status_t unpack_placed(const DeviceTables &tab, const BucketRec &b, const void *const *shards, uint32_t n_shards, uint64_t origin,
+                                  void *bucket, hipStream_t stream)
 {
     UnpackPlacedArgs a;
     for (uint32_t j = 0; j < n_shards; ++j) a.src[j] = reinterpret_cast<uint64_t>(shards[j]);
@@ -2253,9 +2281,11 @@ static hzp_status_t unpack_placed(const DeviceTables &tab, const BucketRec &b, c
     return start("hzp_gather_layer", kernel, dim3((uint32_t)tiles_of(a.nvec), n_shards), dim3(kWave), 0, stream, a);
 }
 
-// The same for tensors that lie elsewhere; *done is false (and nothing launched) where they or the shards lie too far apart, or off 16 bytes.
+// The same for tensors that lie elsewhere; *done is false (and nothing launched) where they or the shards lie too far apart, or off 16
+// bytes.
 template <int ES, class Args>
-static hzp_status_t unpack_near(const hzp_plan_t *plan, const DeviceTables &tab, const BucketRec &b, const void *const *shards, uint32_t n_shards, void *const *tensors, hipStream_t stream, bool *done)
+static hzp_status_t unpack_near(const hzp_plan_t *plan, const DeviceTables &tab, const BucketRec &b, const void *const *shards,
+                                uint32_t n_shards, void *const *tensors, hipStream_t stream, bool *done)
 {
     Args a;
     a.src = reinterpret_cast<uint64_t>(shards[0]);
@@ -2272,17 +2302,19 @@ static hzp_status_t unpack_near(const hzp_plan_t *plan, const DeviceTables &tab,
     }
     if (off % 128 && b.P * ES > kOffLinesNear) fits = false;
     *done = fits;
-    return fits ? start("hzp_gather_layer", unpack_near_kernel<ES, Args>, dim3((uint32_t)tiles_of(a.nvec), n_shards), dim3(kWave), 0, stream, a) : HZP_OK;
+    if (!fits) return HZP_OK;
+    return start("hzp_gather_layer", unpack_near_kernel<ES, Args>, dim3((uint32_t)tiles_of(a.nvec), n_shards), dim3(kWave), 0, stream, a);
 }
 template <int ES>
-static hzp_status_t unpack_near(const hzp_plan_t *plan, const DeviceTables &tab, const BucketRec &b, const void *const *shards, uint32_t n_shards, void *const *tensors, hipStream_t stream, bool *done)
+static hzp_status_t unpack_near(const hzp_plan_t *plan, const DeviceTables &tab, const BucketRec &b, const void *const *shards,
+                                uint32_t n_shards, void *const *tensors, hipStream_t stream, bool *done)
 {
     return b.n_tensors <= UnpackNear12::kTensors ? unpack_near<ES, UnpackNear12>(plan, tab, b, shards, n_shards, tensors, stream, done)
                                                  : unpack_near<ES, UnpackNear64>(plan, tab, b, shards, n_shards, tensors, stream, done);
 }
 
-// Do lists serve the unpacking of pieces [p0, p1), or the plan's tables?  A graph may be replayed after its plan has been freed where nothing of the plan's
-// is read, so captured calls that lists serve take lists and not the spans, which are a table too.
+// Do lists serve the unpacking of pieces [p0, p1), or the plan's tables?  A graph may be replayed after its plan has been freed where
+// nothing of the plan's is read, so captured calls that lists serve take lists and not the spans, which are a table too.
 static bool lists_serve(const BucketRec &b, size_t p0, size_t p1, void *const *tensors, uint32_t t_begin, uint32_t es)
 {
     const size_t n = p1 - p0;
@@ -2311,7 +2343,8 @@ hzp_status_t launch_unpack(const hzp_plan_t *plan, const BucketRec &b, const voi
         const ListShape lists = list_shape(b, es);
         auto outlived = [&] { return captured(stream) && lists_serve(b, p0, p1, tensors, t_begin, es); };
         uint64_t origin = 0;
-        if (placed_pays(b, lists, es) && placed_as_in_bucket(plan, b, tensors, es, &origin) && (origin % 128 == 0 || b.P * es <= kOffLinesPlaced) && !outlived())
+        if (placed_pays(b, lists, es) && placed_as_in_bucket(plan, b, tensors, es, &origin) &&
+            (origin % 128 == 0 || b.P * es <= kOffLinesPlaced) && !outlived())
             return es == 4 ? unpack_placed<4, false>(*tab, b, shards, n_shards, origin, nullptr, stream)
                            : unpack_placed<2, false>(*tab, b, shards, n_shards, origin, nullptr, stream);
         if (near_pays(b, lists, es) && !outlived()) {
@@ -2333,8 +2366,10 @@ hzp_status_t launch_unpack(const hzp_plan_t *plan, const BucketRec &b, const voi
             longest = std::max(longest, piece[i].len);
         }
         const uint64_t tile = kWave * 16 / es;
-        if (total / tile <= kMaxTilesPerLaunch && even_parts(n, total, longest, tile))      // (what unpack_parts puts into one uncut launch)
-            return es == 4 ? unpack_tensor<4>(piece, n, shards, tensors[0], longest, stream) : unpack_tensor<2>(piece, n, shards, tensors[0], longest, stream);
+        // (what unpack_parts puts into one uncut launch)
+        if (total / tile <= kMaxTilesPerLaunch && even_parts(n, total, longest, tile))
+            return es == 4 ? unpack_tensor<4>(piece, n, shards, tensors[0], longest, stream)
+                           : unpack_tensor<2>(piece, n, shards, tensors[0], longest, stream);
     }
     return es == 4 ? unpack_parts<4, false>(PieceParts<4>{piece, shards, tensors, t_begin}, n, stream, "hzp_gather_layer")
                    : unpack_parts<2, false>(PieceParts<2>{piece, shards, tensors, t_begin}, n, stream, "hzp_gather_layer");
@@ -2358,7 +2393,8 @@ hzp_status_t launch_unpack_both(const hzp_plan_t *plan, const BucketRec &b, cons
     uint64_t origin = 0;
     if (spans_reach(b, n_shards, es) && placed_pays_both(b, es, one_pass) && placed_as_in_bucket(plan, b, tensors, es, &origin) &&
         !(captured(stream) && (one_pass || lists_serve(b, 0, b.pieces.size(), tensors, 0, es))))
-        return es == 4 ? unpack_placed<4, true>(*tab, b, shards, n_shards, origin, bucket, stream) : unpack_placed<2, true>(*tab, b, shards, n_shards, origin, bucket, stream);
+        return es == 4 ? unpack_placed<4, true>(*tab, b, shards, n_shards, origin, bucket, stream)
+                       : unpack_placed<2, true>(*tab, b, shards, n_shards, origin, bucket, stream);
     if (!one_pass) {
         st = launch_concat(shards, n_shards, b.S3 * es, bucket, stream);
         if (st != HZP_OK) return st;

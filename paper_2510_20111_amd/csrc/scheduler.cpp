@@ -231,7 +231,8 @@ void worker_main(hzp_sched *s)
             else
                 s->stats.reduces_issued++;
         } else if (cmd.kind == Cmd::FENCE) {
-            // A stream without new work keeps its event: once that has happened, waiting for it costs the host 0.1 us, for a new one 7 to 11.
+            // A stream without new work keeps its event: once that has happened, waiting for it costs the host 0.1 us, for a new one
+            // 7 to 11.
             hipError_t e = s->gathered ? hipEventRecord(s->fence_gather, s->gather_stream) : hipSuccess;
             if (e == hipSuccess) s->gathered = false;
             if (e == hipSuccess && s->reduced) e = hipEventRecord(s->fence_reduce, s->reduce_stream);
