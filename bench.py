@@ -755,17 +755,12 @@ def fused_launch_count(w):
 
 
 def fused_kernel_name(w):
-    """The kernel of a call over all buckets: one segment where the slices follow each other in every stream (a short one with the
-    arena's equally distant contributions by their distance), else the general one."""
-    if w.layout == "separate":
-        return "fused_adamw_kernel"
-    groups = -(-w.s1_total // 256)
-    return "fused_even_kernel" if groups <= (1024 if w.R > 8 else 1536 if w.R in (3, 4) else 2048) else "fused_one_kernel"
+    """The kernels that a call over all buckets may have: one segment where the slices follow each other in every stream, else the general one.
+    (Which of one segment's two, the library decides by lengths and distances.)"""
+    return "fused_adamw_kernel" if w.layout == "separate" else "fused_one_kernel (short: fused_even_kernel)"
 
 
-def bucket_copy_name(n_pieces):
-    """The kernel that gathers `n_pieces` equal pieces into one bucket."""
-    return "copy_bucket_kernel" if n_pieces <= 8 else "copy_list_kernel"
+BUCKET_COPY = "copy_bucket_kernel (many shards: copy_list_kernel)"
 
 
 COPY_MAX_TILES = 600000         # 1 KiB tiles one launch of the layer-range gather covers at most
@@ -799,7 +794,7 @@ def gather1_launches(w):
     launches = 0
     while left:
         left, launches = left[take(left, most, float("inf"), 24576) or take(left, most, 8192, 8192):], launches + 1
-    return "copy_shared_kernel" if shared else "copy_list_kernel", launches
+    return "copy_shared_kernel" if shared else "copy_list_kernel (short equal layers: copy_stack_kernel)", launches
 
 
 def roofline_entry(np, kernel, algo_bytes, ms, launches, key, step_kernel_ms=None, per_step=None):
@@ -862,7 +857,7 @@ def time_workload(idx, args, torch, np, hzp, hzp_inputs, steps, warmup, keep=Fal
     fused_launches = fused_launch_count(w)
     rooflines = {}
     if "fused" in phases:
-        rooflines["fused_adamw"] = roof("%s<R=%d,bf16>" % (fused_kernel_name(w), R), fused_bytes, fused_ms,
+        rooflines["fused_adamw"] = roof("%s, R=%d, bf16" % (fused_kernel_name(w), R), fused_bytes, fused_ms,
                                         fused_launches, "fused_adamw_%s" % cfg["name"], ph[:, 0])
         # context, outside the timed steps: the update alone, call after call (inside the step it starts behind
         # the level-3 gather's trailing writes)
@@ -882,14 +877,14 @@ def time_workload(idx, args, torch, np, hzp, hzp_inputs, steps, warmup, keep=Fal
             "avg_launch_us": round(alone_ms / fused_launches * 1e3, 2), "calls": alone}
     if "gather1" in phases:
         if w.l1_per_layer:
-            rooflines["gather_level1"] = roof("%s (K=%d x S1 -> S3)" % (bucket_copy_name(w.K), w.K), g1_bytes, g1_ms,
+            rooflines["gather_level1"] = roof("%s (K=%d x S1 -> S3)" % (BUCKET_COPY, w.K), g1_bytes, g1_ms,
                                               w.n_layers, "gather_l1_per_layer_%s" % cfg["name"], ph[:, 1])
         else:
             kernel, launches = gather1_launches(w)
             rooflines["gather_level1"] = roof("%s (all layers, K=%d x S1 -> S3)" % (kernel, w.K), g1_bytes, g1_ms, launches,
                                               "gather_l1_%s" % cfg["name"], ph[:, 1])
     if "gather3" in phases:
-        rooflines["gather_level3"] = roof("%s (Z3=%d x S3 -> P)" % (bucket_copy_name(w.z3), w.z3), g3_bytes, g3_ms,
+        rooflines["gather_level3"] = roof("%s (Z3=%d x S3 -> P)" % (BUCKET_COPY, w.z3), g3_bytes, g3_ms,
                                           w.n_layers, "gather_l3_%s" % cfg["name"], ph[:, 2])
     # the launch-bound workloads also as one captured step replayed (context; the timed steps are issued call by call)
     graph = None
@@ -1014,13 +1009,13 @@ def main():
                       "f32class": lambda: (28 + 4 * R) * w.s1_total,
                       "perlayer": lambda: fused_bytes, "freegroups": lambda: 4 * w.free_s3_total,
                       "prereduced": lambda: 30 * w.s1_total}[phase]()
-            kname = {"unpack": "unpack_list_kernel<2> (up to 12 uneven tensors to a bucket: unpack_near_kernel<2>)", "reduce": "reduce_kernel<bf16,R=%d>" % R,
+            kname = {"unpack": "unpack_list_kernel<2> (few tensors: unpack_near_kernel<2>)", "reduce": "reduce_kernel<bf16,R=%d>" % R,
                      "accumulate": "reduce_kernel<f32,R=%d,accumulate>" % R,
                      "inplace": "fused update writing into the ZeRO-3 shard + level-1 gather of the other %d pieces" % (w.K - 1),
                      "notinplace": "fused update + level-1 gather of all %d pieces" % w.K,
                      "f32class": "fused_one_kernel<R=%d, fp32 gradients, fp32 output> (class F32 on the same shapes)" % R,
                      "perlayer": "fused_one_kernel<R=%d,bf16>, one call per layer" % R,
-                     "prereduced": "%s<R=1,f32 gradient> (update from a reduced fp32 shard)" % fused_kernel_name(w),
+                     "prereduced": "%s, R=1, f32 gradient (update from a reduced fp32 shard)" % fused_kernel_name(w),
                      "freegroups": "copy_ranges_kernel (Z1=%d over Z3=%d: ZeRO-3 shard from partial owners)"
                                    % (getattr(w, "free_z1", 0), w.z3)}[phase]
             launches = fused_launches if phase in ("prereduced", "f32class") else 1 if phase in ("inplace", "notinplace") else w.n_layers
