@@ -248,3 +248,13 @@ def test_a_captured_unpacking_outlives_its_plan(numel, both):
         assert torch.equal(flat, want) and (bucket is None or torch.equal(bucket, whole))
     for p in taken:
         assert hip.hipFree(p) == 0
+
+
+def test_the_null_stream_cannot_be_captured():
+    """The launchers do not ask whether it is being captured."""
+    hip = hzp.binding._L
+    for mode in range(3):           # global, thread-local, relaxed
+        assert hip.hipStreamBeginCapture(None, mode) != 0
+        hip.hipGetLastError()
+    status = ctypes.c_int(-1)
+    assert hip.hipStreamIsCapturing(None, ctypes.byref(status)) == 0 and status.value == 0

@@ -7,6 +7,7 @@ import os
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+STREAM = 0x1000         # (any but the null stream, which cannot be captured)
 
 
 def load(name, *path):
@@ -63,14 +64,14 @@ def test_tables_whose_copies_were_not_waited_for_are_not_used(rec):
     shard, tensors = 0x7000000000, [0x7100000000 + 4096 * t for t in range(9)]
     rec.lib.set_wait_status(719)
     try:
-        for call in (lambda: plan.prepare(stream=0), lambda: hzp.hzp_gather_layer(plan, 0, 0, 3, [shard], None, tensors, stream=0)):
+        for call in (lambda: plan.prepare(stream=STREAM), lambda: hzp.hzp_gather_layer(plan, 0, 0, 3, [shard], None, tensors, stream=STREAM)):
             with pytest.raises(hzp.HzpError) as caught:
                 rec.launches(call)
             assert caught.value.status == hzp.HZP_ERR_HIP
             assert rec.lib.recorded() == 0 and rec.lib.live_allocations() == 0
     finally:
         rec.lib.set_wait_status(0)
-    assert len(rec.launches(lambda: hzp.hzp_gather_layer(plan, 0, 0, 3, [shard], None, tensors, stream=0))) == 1
+    assert len(rec.launches(lambda: hzp.hzp_gather_layer(plan, 0, 0, 3, [shard], None, tensors, stream=STREAM))) == 1
     assert rec.lib.live_allocations() == 4
     del plan
     assert rec.lib.live_allocations() == 0
@@ -85,12 +86,12 @@ def test_calls_that_run_out_of_host_memory_end_with_a_status(rec):
     hy = hzp.adamw_hyper(1e-4, .9, .95, 1e-8, .1, 1.0, 1)
     at = lambda k: 0x7000000000 + k * 0x10000000
     tensors = [at(8) + 4096 * t + 2 for t in range(n)]
-    calls = [lambda: plan.prepare(stream=0),
-             lambda: hzp.hzp_gather_layer(plan, 0, 0, 3, [at(0), at(1)], None, tensors, stream=0),
-             lambda: hzp.hzp_gather_layer(plan, 0, 0, 3, [at(0), at(1)], at(2), [t - 2 for t in tensors], stream=0),
-             lambda: hzp.hzp_gather_layers(plan, 0, 2, 0, 1, [at(0), at(1), at(2), at(3)], 2, [at(4), at(5)], stream=0),
-             lambda: hzp.hzp_adamw_shard(plan, 0, 2, 0, 0, hy, [at(0), at(1)], 1, *[[at(2 * i), at(2 * i + 1)] for i in range(1, 5)], stream=0),
-             lambda: hzp.hzp_reduce_shard(plan, 0, 0, 1, 0, [at(0), at(1)], 1.0, 0, at(2), stream=0)]
+    calls = [lambda: plan.prepare(stream=STREAM),
+             lambda: hzp.hzp_gather_layer(plan, 0, 0, 3, [at(0), at(1)], None, tensors, stream=STREAM),
+             lambda: hzp.hzp_gather_layer(plan, 0, 0, 3, [at(0), at(1)], at(2), [t - 2 for t in tensors], stream=STREAM),
+             lambda: hzp.hzp_gather_layers(plan, 0, 2, 0, 1, [at(0), at(1), at(2), at(3)], 2, [at(4), at(5)], stream=STREAM),
+             lambda: hzp.hzp_adamw_shard(plan, 0, 2, 0, 0, hy, [at(0), at(1)], 1, *[[at(2 * i), at(2 * i + 1)] for i in range(1, 5)], stream=STREAM),
+             lambda: hzp.hzp_reduce_shard(plan, 0, 0, 1, 0, [at(0), at(1)], 1.0, 0, at(2), stream=STREAM)]
     for call in calls:
         for which in range(1000):
             held = rec.lib.live_allocations()
@@ -112,7 +113,7 @@ def unpacking(rec, numel, both, place, z3=3, align=64, cls=0):
     off 16 bytes ("off")."""
     hzp, n, es = rec.hzp, len(numel), 4 if cls else 2
     plan = hzp.hzp_plan([n], numel, align=align, z3=z3, z1=z3, tensor_class=[cls] * n)
-    plan.prepare(stream=0)
+    plan.prepare(stream=STREAM)
     shards = [0x7000000000 + j * 0x40000000 for j in range(z3)]
     at = [plan.tensor(t).offset * es for t in range(n)]
     if place != "placed":
@@ -120,7 +121,7 @@ def unpacking(rec, numel, both, place, z3=3, align=64, cls=0):
     if place == "off":
         at[n // 2] += es
     tensors = [0x7800000000 + a for a in at]
-    return plan, lambda: hzp.hzp_gather_layer(plan, 0, cls, 3, shards, 0x7900000000 if both else None, tensors, stream=0)
+    return plan, lambda: hzp.hzp_gather_layer(plan, 0, cls, 3, shards, 0x7900000000 if both else None, tensors, stream=STREAM)
 
 
 @pytest.mark.parametrize("place", ["placed", "near"])
@@ -158,7 +159,7 @@ def test_form_of_a_reduction(rec, R, g32, captured):
         for odd in (None, 1, R - 1):
             for distance in (n * 4, -n * 4, 1 << 40):
                 def call():
-                    hzp.hzp_reduce_shard(plan, 0, 0, 3, 0, streams_at(R, distance, odd), 0.5, 0, 0x6000000000, stream=0,
+                    hzp.hzp_reduce_shard(plan, 0, 0, 3, 0, streams_at(R, distance, odd), 0.5, 0, 0x6000000000, stream=STREAM,
                                          grad_dtype=hzp.HZP_GRAD_F32 if g32 else hzp.HZP_GRAD_BF16)
                 (kernel, grid, _), = rec.launches(call, captured)
                 even = R >= 13 and groups <= limit and odd is None and not captured
@@ -185,7 +186,7 @@ def test_form_of_an_update_of_one_segment(rec, R, cls, captured):
                 for call, scal in ((hzp.hzp_adamw_shard, hy), (hzp.hzp_adamw_shard_dev, 0x5000000000)):
                     for out in ([0x6300000000], None):
                         (kernel, grid, _), = rec.launches(lambda: call(plan, 0, 1, cls, 0, scal, streams_at(k, distance, odd), R, [0x6000000000], [0x6100000000],
-                                                                       [0x6200000000], out, stream=0), captured)
+                                                                       [0x6200000000], out, stream=STREAM), captured)
                         even = groups <= limit and (odd is None or R < 3) and not captured
                         assert name_of(kernel) == ("fused_even_kernel" if even else "fused_one_kernel"), (kernel, groups, odd, distance)
                         assert grid == (groups, 1, 1) and kernel.split("<")[1].startswith("%du, " % k)
@@ -263,7 +264,7 @@ def test_form_of_a_gather_of_equal_layers(rec):
             for l in range(layers):
                 if odd == "own" or (odd == "piece" and l == 9):
                     parts[l * K + 2] = dsts[l] + 2 * s1 * 2
-            got = rec.launches(lambda: hzp.hzp_gather_layers(plan, 0, layers, 0, 1, parts, K, dsts, stream=0), captured)
+            got = rec.launches(lambda: hzp.hzp_gather_layers(plan, 0, layers, 0, 1, parts, K, dsts, stream=STREAM), captured)
             names = {name_of(k) for k, _, _ in got}
             if stack:
                 assert names == {"copy_stack_kernel"} and [g for _, g, _ in got] == [(-(-s1 // 512), K - (odd == "own"), layers)]
